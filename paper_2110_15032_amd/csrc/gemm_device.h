@@ -91,6 +91,33 @@ struct Tile {
             return ((uint32_t)krow * (uint32_t)ld + (uint32_t)col) * 2u;
         }
     }
+    // The 16 bytes of LDS chunk position p of a stage that starts at reduction index k0 and reaches past the end kk
+    // of the reduction: zeros there (in both operands, so that no stored NaN or Inf can leak in), element by element
+    // where a chunk of a KC tile straddles the end, rows and columns clamped as in src_offset.
+    __device__ static u32x4 tail_chunk(const uint16_t* src, int ld, int first, int limit, int kk, int k0, int p) {
+        const u32x4 zero = {0u, 0u, 0u, 0u};
+        if constexpr (KC) {
+            const int row = p / CPK;
+            int g = first + row;
+            g = g < limit ? g : limit - 1;
+            const int k = k0 + ((p % CPK) ^ ksw(row)) * 8;
+            const uint16_t* at = src + (int64_t)g * ld + k;
+            if (k + 8 <= kk) return *reinterpret_cast<const u32x4*>(at);
+            u32x4 v = zero;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (k + e < kk) v[e >> 1] |= (uint32_t)at[e] << (16 * (e & 1));
+            return v;
+        } else {
+            const int krow = p / CPR;
+            int col = first + (((p % CPR) ^ nswz(krow)) * 8);
+            col = col < limit ? col : limit - 8;
+            if (k0 + krow >= kk) return zero;
+            u32x4 v;
+            __builtin_memcpy(&v, src + (int64_t)(k0 + krow) * ld + col, 16);   // limit - 8 need not be a multiple of 8
+            return v;
+        }
+    }
     // bytes to advance the source by for one BKT step
     __device__ static uint32_t step_bytes(int ld) { return KC ? BKT * 2u : (uint32_t)ld * BKT * 2u; }
 

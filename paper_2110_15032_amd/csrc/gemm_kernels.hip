@@ -717,7 +717,10 @@ __global__ __launch_bounds__(WM * WN * 64, (BM * BN <= 256 * 128 && WM * WN == 4
 }
 
 // The pipelined kernel on v_mfma_f32_16x16x32_bf16 (four stages; fragments, step and epilogue as in
-// gemm_mfma_persist16_kernel): shapes whose reduction length is a multiple of 32 but not of 128.
+// gemm_mfma_persist16_kernel): shapes whose reduction length is not a multiple of 128.  Any length will do: what is
+// left behind the last whole stage goes through registers once per tile (Tile::tail_chunk).  Measured on
+// [1024, 125000] x [125000, 512] per device, 8 devices: 661 ms with the generic kernel, 2.0 ms with the 128 x 128 tile
+// here; [777, 1000] x [1000, 1000], 3 devices: 1170 us against 15.
 template <int BM, int BN, int WM, int WN, bool A_KC, bool B_KC, int NST, int EPI, typename OutT>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_pipe16_kernel(GemmPlan p, int tm, int tn, int order) {
     constexpr int BKT = 32;
@@ -834,18 +837,37 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_pipe16_kernel(GemmPlan
         pace<HM * FN, NDS_A + NDS_B, 0>();
     };
 
-    static_for<NST - 1>([&](auto i) { issue(stA(i), stB(i)); });
-    __builtin_amdgcn_s_waitcnt(WAIT_IMM);
-    __builtin_amdgcn_s_barrier();
-    read_a(sA0, 0);
-    read_b(sB0, 0);
-    int t = 0;
-    for (; t + NST <= steps; t += NST) static_for<NST>([&](auto i) { step(i); });
-    const int rem = steps - t;   // 0 .. NST - 1 steps left, stage numbering continues from 0
-    static_for<NST - 1>([&](auto i) {
-        if (decltype(i)::value < rem) step(i);
-    });
-    __builtin_amdgcn_s_waitcnt(0x0070);   // drain the (unread) trailing loads before LDS is released
+    if (steps > 0) {
+        static_for<NST - 1>([&](auto i) { issue(stA(i), stB(i)); });
+        __builtin_amdgcn_s_waitcnt(WAIT_IMM);
+        __builtin_amdgcn_s_barrier();
+        read_a(sA0, 0);
+        read_b(sB0, 0);
+        int t = 0;
+        for (; t + NST <= steps; t += NST) static_for<NST>([&](auto i) { step(i); });
+        const int rem = steps - t;   // 0 .. NST - 1 steps left, stage numbering continues from 0
+        static_for<NST - 1>([&](auto i) {
+            if (decltype(i)::value < rem) step(i);
+        });
+        __builtin_amdgcn_s_waitcnt(0x0070);   // drain the (unread) trailing loads before their stages are reused or released
+    }
+    if (const int k0 = steps * BKT; k0 < s.kk) {
+        // The last 1 .. 31 reduction elements: through registers into stage 0, zeros behind the end.  Every wave has
+        // waited for its own loads; the barrier makes that true of all of them.
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < TA::PER_THREAD; ++it)
+            *reinterpret_cast<u32x4*>(sA0 + (it * NT + tid) * 16) = TA::tail_chunk(static_cast<const uint16_t*>(s.a), s.lda, m0, s.m, s.kk, k0, it * NT + tid);
+#pragma unroll
+        for (int it = 0; it < TB::PER_THREAD; ++it)
+            *reinterpret_cast<u32x4*>(sB0 + (it * NT + tid) * 16) = TB::tail_chunk(static_cast<const uint16_t*>(s.b), s.ldb, n0, s.n, s.kk, k0, it * NT + tid);
+        __syncthreads();
+        read_a(sA0, 0);
+        read_a(sA0, 1);
+        read_b(sB0, 0);
+        mfmas(0, 0);
+        mfmas(1, 0);
+    }
 
     store_tile16<BM, BN, TM, TN, EPI, OutT>(acc, s, m0, n0, wm, wn, lane, sOut);
 }
@@ -1491,13 +1513,14 @@ void launch_generic_epi(const GemmPlan& plan, dim3 grid, hipStream_t st) {
         hipLaunchKernelGGL((gemm_generic_kernel<A_BF16, B_BF16, OutT, SBP_EPI_NONE>), grid, dim3(16, 16), 0, st, plan);
 }
 
-// Shapes the MFMA kernel takes: whole 64-element reduction steps, 16-byte aligned rows.
+// Shapes the direct-to-LDS MFMA kernels take: 16-byte aligned rows; any reduction length (gemm_mfma_pipe16_kernel), the
+// other kernels whole 64-element steps (k64) or 128-element rounds.
 bool mfma_ok(const GemmPlan& plan) {
     if (plan.in_dtype != SBP_BF16) return false;
     for (int g = 0; g < plan.groups; ++g) {
         const GemmShard& s = plan.s[g];
         if (s.m == 0 || s.n == 0) continue;
-        if (s.kk == 0 || s.kk % BK) return false;
+        if (s.kk == 0) continue;
         if (s.lda % 8 || s.ldb % 8) return false;
         if (!plan.a_kc && s.m < 8) return false;
         if (!plan.b_kc && s.n < 8) return false;
@@ -1536,6 +1559,16 @@ bool pingpong_pays(const GemmPlan& plan, int max_m, int max_n) {
         if (plan.s[g].m && plan.s[g].n && plan.s[g].kk > max_k) max_k = plan.s[g].kk;
     const int64_t tiles = (int64_t)((max_m + 255) / 256) * ((max_n + 255) / 256) * plan.groups;
     return max_k <= 1024 && tiles >= 4 * (int64_t)compute_units();
+}
+
+// Tile of gemm_mfma_pipe16_kernel for a reduction length that is not a multiple of 64: 256 x 256 (variant 9, one
+// workgroup per compute unit) or 128 x 128 (variant 8, two).  A large tile does the work of four small ones in the
+// time of about three; compared are the rounds that the compute units need for all tiles.
+int ragged_tile(const GemmPlan& plan, int max_m, int max_n) {
+    const int64_t cu = compute_units();
+    const int64_t big = (int64_t)((max_m + 255) / 256) * ((max_n + 255) / 256) * plan.groups;
+    const int64_t small = (int64_t)((max_m + 127) / 128) * ((max_n + 127) / 128) * plan.groups;
+    return 3 * ((big + cu - 1) / cu) <= (small + cu - 1) / cu ? 9 : 8;
 }
 
 }  // namespace
@@ -1596,9 +1629,12 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
         }
         return launch_status(__func__);
     }
-    bool k128 = true;   // every local reduction a whole number of four-stage rounds
-    for (int g = 0; g < plan.groups; ++g)
-        if (plan.s[g].m && plan.s[g].n && plan.s[g].kk % 128) k128 = false;
+    bool k64 = true, k128 = true;   // every local reduction a whole number of 64-element steps / of four-stage rounds
+    for (int g = 0; g < plan.groups; ++g) {
+        if (!plan.s[g].m || !plan.s[g].n) continue;
+        if (plan.s[g].kk == 0 || plan.s[g].kk % BK) k64 = false;
+        if (plan.s[g].kk == 0 || plan.s[g].kk % 128) k128 = false;
+    }
     if (plan.epilogue == EPI_ROWMAX) {
         // fused row maximum: persistent bf16 kernel only; anything else is done in two passes by the caller
         if (!(k128 && max_m > 128 && max_n > 128 && plan.out_dtype == SBP_BF16 && (variant == 0 || variant == 12 || variant == 16 || variant == 21))) return SBP_ERR_UNSUPPORTED;
@@ -1617,13 +1653,17 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
         // workgroup per compute unit when the reduction length allows it; shapes that would leave most
         // of such a tile empty take the 128 x 128 tile.  The persistent kernel runs on the 16x16x32
         // matrix instruction.
-        variant = (max_m > 128 && max_n > 128) ? (k128 ? (pingpong_pays(plan, max_m, max_n) ? 21 : 16) : 7) : 4;
+        if (!k64) variant = ragged_tile(plan, max_m, max_n);
+        else variant = (max_m > 128 && max_n > 128) ? (k128 ? (pingpong_pays(plan, max_m, max_n) ? 21 : 16) : 7) : 4;
     }
+    if (!k64 && variant != 8 && variant != 9) return SBP_ERR_UNSUPPORTED;
     switch (variant) {
         case 3: return launch_mfma_out<256, 256, 2, 4, 0>(plan, max_m, max_n, stream);
         case 4: return launch_mfma_out<128, 128, 2, 2, 0>(plan, max_m, max_n, stream);
         case 6: return launch_mfma_out<256, 256, 2, 4, 4>(plan, max_m, max_n, stream);
-        case 7: return launch_mfma_out<256, 256, 2, 4, 54>(plan, max_m, max_n, stream);
+        case 7:
+        case 9: return launch_mfma_out<256, 256, 2, 4, 54>(plan, max_m, max_n, stream);
+        case 8: return launch_mfma_out<128, 128, 2, 2, 54>(plan, max_m, max_n, stream);
         case 12: return k128 ? launch_mfma_out<256, 256, 2, 4, 104>(plan, max_m, max_n, stream) : SBP_ERR_UNSUPPORTED;
         case 16: return k128 ? launch_mfma_out<256, 256, 2, 4, 204>(plan, max_m, max_n, stream) : SBP_ERR_UNSUPPORTED;
         case 21: {
