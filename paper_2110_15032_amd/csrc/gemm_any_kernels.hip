@@ -1,0 +1,443 @@
+// Grouped bf16 GEMMs (sbp_matmul, paper Sec. 3.1, Table 1: device g computes C_g = A_g B_g) for what the 256 x 256 kernels
+// are not made for: few output tiles, and rows that do not start 16-byte aligned.
+//
+// gemm_wavek_kernel: the waves of a workgroup split the REDUCTION instead of the output tile.  Every wave multiplies the
+// whole BM x BN tile, on every NW-th 32-deep stage, and the NW partial tiles are added through LDS at the end.
+//
+// What that buys (us, 8 devices, [32, 4096] x [4096, 2048] each: 45.8 with the 128 x 128 tile of gemm_mfma_kernel, 35.6
+// with that of gemm_mfma_pipe16_kernel, 24.7 here, 5.4 TB/s of weights; feature gradient of a classifier, 4 devices,
+// [300, 30000] x [30000, 256]: 340 against 108):
+//   * A wave fills a private pair of LDS stages and waits for its own loads only; the reduction loop has no barrier.
+//   * Small tiles keep many loads in flight: eight waves bring eight consecutive stages at a time, so a product with
+//     few output tiles (a batch of single tokens, the feature gradient of a narrow classifier) streams its operands
+//     instead of waiting for one stage after the other.
+//   * The fragment reads per matrix instruction are those of the whole tile, not of a wave's quarter of it: 64 x 64
+//     per wave reads 8 fragments for 16 instructions, where 32 x 32 reads 4 for 4.
+// The price is the final addition (BM BN NW floats through LDS, one or two microseconds).  A 128 x 128 tile per wave does
+// not fit the registers (256 accumulators and two sets of 64 fragment registers spill).
+//
+// gemm_reg_kernel: the waves split the output tile as usual; operands of any pitch through registers.  Bound by the
+// unaligned loads and the LDS writes: 540 TFLOP/s on [1500, 1501] x [1501, 2501], 2 devices, where the one-element-per-lane
+// kernel reached 4.
+//
+// Matrix instruction: v_mfma_f32_16x16x32_bf16 fed (B fragment, A fragment), so that a lane's four accumulators are
+// four consecutive columns of one row.  DIRECT: rows of both operands start 16-byte aligned, operands go global -> LDS
+// directly, fragments are read one stage ahead.  Otherwise (any pitch) the 16-byte chunks pass through registers, two
+// stages ahead, with unaligned loads: one cache line more per load instruction at worst, against eight loads of single
+// elements.
+#include "gemm_device.h"
+
+namespace sbp {
+namespace {
+
+constexpr int LGKM0_ONLY = 0xC07F;   // s_waitcnt lgkmcnt(0), vmcnt untouched
+
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+
+// EPV consecutive columns of row m from column n on, at whatever alignment the row pitch gives
+template <typename OutT, int EPV>
+__device__ inline void store_columns(const GemmShard& s, int m, int n, const float (&v)[EPV]) {
+    if (m >= s.m) return;
+    OutT* dst = static_cast<OutT*>(s.c) + (int64_t)m * s.ldc + n;
+    if (n + EPV <= s.n) {
+        if constexpr (sizeof(OutT) == 4) *reinterpret_cast<f32x4_any*>(dst) = f32x4{v[0], v[1], v[2], v[3]};
+        else *reinterpret_cast<u32x4_any*>(dst) = u32x4{f32_to_bf16x2(v[0], v[1]), f32_to_bf16x2(v[2], v[3]), f32_to_bf16x2(v[4], v[5]), f32_to_bf16x2(v[6], v[7])};
+    } else {
+#pragma unroll
+        for (int e = 0; e < EPV; ++e)
+            if (n + e < s.n) {
+                if constexpr (sizeof(OutT) == 4) dst[e] = v[e];
+                else dst[e] = f32_to_bf16(v[e]);
+            }
+    }
+}
+
+// Whole 32-deep stages whose 16-byte chunks may be read without a look at the ends, rows of any pitch: a chunk of a
+// not-KC operand may run past the end of its row into the next one, so the stage with the last row is left to the
+// careful path, and rows shorter than a chunk leave it everything.
+template <bool A_KC, bool B_KC>
+__device__ inline int plain_stages(const GemmShard& s) {
+    if constexpr (A_KC && B_KC) return s.kk / 32;
+    if ((!A_KC && s.lda < 8) || (!B_KC && s.ldb < 8)) return 0;
+    return (s.kk - 1) / 32;
+}
+
+template <int BM, int BN, int NW, bool A_KC, bool B_KC, bool DIRECT, int EPI, typename OutT>
+__global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(GemmPlan p, int tm, int tn, int order) {
+    constexpr int BKT = 32, FM = BM / 16, FN = BN / 16, BLOCKS = FM * FN;
+    using TA = Tile<BM, A_KC, 64, BKT, true>;
+    using TB = Tile<BN, B_KC, 64, BKT, true>;
+    constexpr int NLA = TA::PER_THREAD, NLB = TB::PER_THREAD, NVM = NLA + NLB;   // 16-byte loads per stage
+    constexpr int STAGE = TA::BYTES + TB::BYTES;
+    // blocks of the partial tiles that go through LDS at a time (1 KB per block and wave)
+    constexpr int NB = BLOCKS * NW <= 128 ? BLOCKS : 128 / NW, ROUNDS = BLOCKS / NB;
+    constexpr int SMEM = NW * (2 * STAGE > NB * 1024 ? 2 * STAGE : NB * 1024);
+    static_assert(BLOCKS % NB == 0 && NB % 4 == 0 && FN % 4 == 0 && SMEM <= 160 * 1024 && NVM < 64, "tile does not fit the scheme");
+    __shared__ __attribute__((aligned(1024))) char smem[SMEM];
+
+    const TileCoord tc = map_tile(blockIdx.x, gridDim.x, tm, tn, p.groups, order);
+    if (!tc.valid) return;
+    const GemmShard s = p.s[tc.g];
+    const int m0 = tc.tile_m * BM, n0 = tc.tile_n * BN;
+    if (m0 >= s.m || n0 >= s.n) return;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    char* const st0 = smem + wave * (2 * STAGE);   // this wave's two stages: A tile, then B tile
+
+    f32x4 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int loa = TA::lane_offset16(0, lane), lob = TB::lane_offset16(0, lane);
+
+    const int steps = DIRECT ? s.kk / BKT : plain_stages<A_KC, B_KC>(s);
+    const int mine = steps > wave ? (steps - wave + NW - 1) / NW : 0;   // stages wave, wave + NW, ...
+    gbl_char* A = (gbl_char*)s.a + (uint64_t)TA::step_bytes(s.lda) * (uint32_t)wave;
+    gbl_char* B = (gbl_char*)s.b + (uint64_t)TB::step_bytes(s.ldb) * (uint32_t)wave;
+    const uint64_t stepa = (uint64_t)TA::step_bytes(s.lda) * NW, stepb = (uint64_t)TB::step_bytes(s.ldb) * NW;
+    uint32_t offa[NLA], offb[NLB];
+#pragma unroll
+    for (int it = 0; it < NLA; ++it) offa[it] = TA::src_offset(s.lda, m0, s.m, it * 64 + lane);
+#pragma unroll
+    for (int it = 0; it < NLB; ++it) offb[it] = TB::src_offset(s.ldb, n0, s.n, it * 64 + lane);
+    int loaded = 0;
+    auto advance = [&]() {   // past the last stage the source stays: the reload is in bounds and unread
+        ++loaded;
+        const bool adv = loaded < mine;
+        A += adv ? stepa : 0u;
+        B += adv ? stepb : 0u;
+    };
+
+    if constexpr (DIRECT) {
+        bf16x8 fa[2][FM], fb[2][FN];
+        auto issue = [&](char* st) {
+            TA::load_direct_untracked(st, A, offa, 0);
+            TB::load_direct_untracked(st + TA::BYTES, B, offb, 0);
+            advance();
+        };
+        auto read = [&](const char* st, int set) {
+#pragma unroll
+            for (int j = 0; j < FN; ++j) fb[set][j] = TB::frag16(st + TA::BYTES, lob, j);
+#pragma unroll
+            for (int i = 0; i < FM; ++i) fa[set][i] = TA::frag16(st, loa, i);
+        };
+        // One stage: its fragments are in registers (set CUR), so its LDS stage takes the loads of the stage after the
+        // next.  The upper row blocks are multiplied first, which gives the next stage's loads half a step more.
+        auto step = [&](auto cur) {
+            constexpr int CUR = decltype(cur)::value;
+            __builtin_amdgcn_s_waitcnt(LGKM0_ONLY);
+            issue(st0 + CUR * STAGE);
+#pragma unroll
+            for (int i = 0; i < FM / 2; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[CUR][j], fa[CUR][i], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(vmcnt_only(NVM));
+            __builtin_amdgcn_sched_barrier(0);
+            read(st0 + (1 - CUR) * STAGE, 1 - CUR);
+#pragma unroll
+            for (int i = FM / 2; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[CUR][j], fa[CUR][i], acc[i][j], 0, 0, 0);
+            constexpr int NM = (FM - FM / 2) * FN, NDS = (A_KC ? FM : 2 * FM) + (B_KC ? FN : 2 * FN);
+            static_for<NM>([&](auto i) {   // fragment reads spread over the matrix instructions
+                constexpr int I = decltype(i)::value, nds = NDS * (I + 1) / NM - NDS * I / NM;
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if constexpr (nds > 0) __builtin_amdgcn_sched_group_barrier(0x100, nds, 0);
+            });
+        };
+        if (mine > 0) {
+            issue(st0);
+            issue(st0 + STAGE);
+            __builtin_amdgcn_s_waitcnt(vmcnt_only(NVM));
+            __builtin_amdgcn_sched_barrier(0);
+            read(st0, 0);
+            int t = 0;
+            for (; t + 2 <= mine; t += 2) {
+                step(std::integral_constant<int, 0>{});
+                step(std::integral_constant<int, 1>{});
+            }
+            if (mine & 1) step(std::integral_constant<int, 0>{});
+            __builtin_amdgcn_s_waitcnt(0x0070);   // the unread trailing loads have landed before their stages are reused
+        }
+    } else {
+        u32x4 ra[2][NLA], rb[2][NLB];
+        auto fetch = [&](int set) {
+#pragma unroll
+            for (int it = 0; it < NLA; ++it) ra[set][it] = *(const __attribute__((address_space(1))) u32x4_any*)(A + offa[it]);
+#pragma unroll
+            for (int it = 0; it < NLB; ++it) rb[set][it] = *(const __attribute__((address_space(1))) u32x4_any*)(B + offb[it]);
+            advance();
+        };
+        auto stash = [&](char* st, int set) {
+#pragma unroll
+            for (int it = 0; it < NLA; ++it) *reinterpret_cast<u32x4*>(st + (it * 64 + lane) * 16) = ra[set][it];
+#pragma unroll
+            for (int it = 0; it < NLB; ++it) *reinterpret_cast<u32x4*>(st + TA::BYTES + (it * 64 + lane) * 16) = rb[set][it];
+        };
+        auto multiply = [&](const char* st) {
+            bf16x8 fb[FN];
+#pragma unroll
+            for (int j = 0; j < FN; ++j) fb[j] = TB::frag16(st + TA::BYTES, lob, j);
+#pragma unroll
+            for (int i = 0; i < FM; ++i) {
+                const bf16x8 fa = TA::frag16(st, loa, i);
+#pragma unroll
+                for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa, acc[i][j], 0, 0, 0);
+            }
+        };
+        auto step = [&](auto cur) {   // stage t is in LDS (CUR), t + 1 and t + 2 are on their way in registers
+            constexpr int CUR = decltype(cur)::value;
+            stash(st0 + (1 - CUR) * STAGE, 1 - CUR);
+            fetch(1 - CUR);
+            multiply(st0 + CUR * STAGE);
+            __builtin_amdgcn_wave_barrier();
+        };
+        if (mine > 0) {
+            fetch(0);
+            fetch(1);
+            stash(st0, 0);
+            fetch(0);
+            int t = 0;
+            for (; t + 2 <= mine; t += 2) {
+                step(std::integral_constant<int, 0>{});
+                step(std::integral_constant<int, 1>{});
+            }
+            if (mine & 1) step(std::integral_constant<int, 0>{});
+        }
+    }
+    // what is left behind the whole stages: the next waves in turn, with every chunk checked against the ends
+    for (int t = steps + (wave - steps % NW + NW) % NW; t * BKT < s.kk; t += NW) {
+#pragma unroll
+        for (int it = 0; it < NLA; ++it)
+            *reinterpret_cast<u32x4*>(st0 + (it * 64 + lane) * 16) = TA::tail_chunk(static_cast<const uint16_t*>(s.a), s.lda, m0, s.m, s.kk, t * BKT, it * 64 + lane);
+#pragma unroll
+        for (int it = 0; it < NLB; ++it)
+            *reinterpret_cast<u32x4*>(st0 + TA::BYTES + (it * 64 + lane) * 16) = TB::tail_chunk(static_cast<const uint16_t*>(s.b), s.ldb, n0, s.n, s.kk, t * BKT, it * 64 + lane);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        bf16x8 fb[FN];
+#pragma unroll
+        for (int j = 0; j < FN; ++j) fb[j] = TB::frag16(st0 + TA::BYTES, lob, j);
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            const bf16x8 fa = TA::frag16(st0, loa, i);
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa, acc[i][j], 0, 0, 0);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+
+    // Addition of the NW partial tiles, wave order, NB blocks at a time.  A block is kept as it lies in the registers:
+    // row r = lane % 16, four columns from 4 q on, q = lane / 16, at (16 q + (r ^ 4 q)) * 16 (the exclusive-or spreads
+    // the reads below over the banks).  Reading, eight consecutive lanes own the 128 (bf16: 64-column) bytes of a row.
+    constexpr int EPV = 16 / (int)sizeof(OutT);           // columns per lane
+    constexpr int UNIT = sizeof(OutT) == 4 ? 2 : 4;       // blocks side by side that eight lanes cover
+    constexpr int UNITS = NB / UNIT * 2;                  // ... by eight rows: half the rows of a block
+    const int q = lane >> 4, r = lane & 15;
+    char* const dump = smem + wave * (NB * 1024) + (16 * q + (r ^ (4 * q))) * 16;
+    static_for<ROUNDS>([&](auto rix) {
+        constexpr int B0 = decltype(rix)::value * NB;
+        __syncthreads();
+        static_for<NB>([&](auto bix) {
+            constexpr int b = B0 + decltype(bix)::value;
+            *reinterpret_cast<f32x4*>(dump + decltype(bix)::value * 1024) = acc[b / FN][b % FN];
+        });
+        __syncthreads();
+        for (int u = wave; u < UNITS; u += NW) {
+            const int blk = u / 2 * UNIT, row = 8 * (u & 1) + (lane >> 3);
+            const int m = m0 + (B0 + blk) / FN * 16 + row, n = n0 + (B0 + blk) % FN * 16 + (lane & 7) * EPV;
+            float v[EPV];
+#pragma unroll
+            for (int h = 0; h < EPV / 4; ++h) {
+                const int cg = (lane & 7) * (EPV / 4) + h;   // group of four columns: block cg / 4, q = cg % 4
+                const char* at = smem + (blk + cg / 4) * 1024 + (16 * (cg & 3) + (row ^ (4 * (cg & 3)))) * 16;
+                f32x4 sum = *reinterpret_cast<const f32x4*>(at);
+#pragma unroll
+                for (int w = 1; w < NW; ++w) sum += *reinterpret_cast<const f32x4*>(at + w * (NB * 1024));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * h + e] = mfma_epilogue<EPI>(sum[e]);
+            }
+            store_columns<OutT>(s, m, n, v);
+        }
+    });
+}
+
+// 4 waves of BM/2 x BN/2, two 32-deep LDS stages filled from registers that run two stages ahead, one barrier a
+// stage.  Two or three workgroups share a compute unit and cover each other's waits; a register ring of four stages was
+// no faster (odd sizes 1500 x 1501 x 2501, 2 devices: 42.0 us with two stages, 43.2 with four).
+template <int BM, int BN, bool A_KC, bool B_KC, int EPI, typename OutT>
+__global__ __launch_bounds__(256, 2) void gemm_reg_kernel(GemmPlan p, int tm, int tn, int order) {
+    constexpr int BKT = 32, NT = 256, TM = BM / 2, TN = BN / 2, FM = TM / 16, FN = TN / 16, BLOCKS = FM * FN;
+    using TA = Tile<BM, A_KC, NT, BKT, true>;
+    using TB = Tile<BN, B_KC, NT, BKT, true>;
+    constexpr int NLA = TA::PER_THREAD, NLB = TB::PER_THREAD, STAGE = TA::BYTES + TB::BYTES;
+    constexpr int DEPTH = 2;   // the register ring and the two LDS stages turn together
+    __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
+
+    const TileCoord tc = map_tile(blockIdx.x, gridDim.x, tm, tn, p.groups, order);
+    if (!tc.valid) return;
+    const GemmShard s = p.s[tc.g];
+    const int m0 = tc.tile_m * BM, n0 = tc.tile_n * BN;
+    if (m0 >= s.m || n0 >= s.n) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+
+    f32x4 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int loa = TA::lane_offset16(wm * TM, lane), lob = TB::lane_offset16(wn * TN, lane);
+    const int steps = plain_stages<A_KC, B_KC>(s);
+    gbl_char* A = (gbl_char*)s.a;
+    gbl_char* B = (gbl_char*)s.b;
+    const uint32_t stepa = TA::step_bytes(s.lda), stepb = TB::step_bytes(s.ldb);
+    uint32_t offa[NLA], offb[NLB];
+#pragma unroll
+    for (int it = 0; it < NLA; ++it) offa[it] = TA::src_offset(s.lda, m0, s.m, it * NT + tid);
+#pragma unroll
+    for (int it = 0; it < NLB; ++it) offb[it] = TB::src_offset(s.ldb, n0, s.n, it * NT + tid);
+    int loaded = 0;
+    u32x4 ra[DEPTH][NLA], rb[DEPTH][NLB];
+    auto fetch = [&](int set) {   // past the last stage the source stays: the reload is in bounds and unread
+#pragma unroll
+        for (int it = 0; it < NLA; ++it) ra[set][it] = *(const __attribute__((address_space(1))) u32x4_any*)(A + offa[it]);
+#pragma unroll
+        for (int it = 0; it < NLB; ++it) rb[set][it] = *(const __attribute__((address_space(1))) u32x4_any*)(B + offb[it]);
+        ++loaded;
+        const bool adv = loaded < steps;
+        A += adv ? stepa : 0u;
+        B += adv ? stepb : 0u;
+    };
+    auto stash = [&](char* st, int set) {
+#pragma unroll
+        for (int it = 0; it < NLA; ++it) *reinterpret_cast<u32x4*>(st + (it * NT + tid) * 16) = ra[set][it];
+#pragma unroll
+        for (int it = 0; it < NLB; ++it) *reinterpret_cast<u32x4*>(st + TA::BYTES + (it * NT + tid) * 16) = rb[set][it];
+    };
+    auto multiply = [&](const char* st) {
+        bf16x8 fb[FN];
+#pragma unroll
+        for (int j = 0; j < FN; ++j) fb[j] = TB::frag16(st + TA::BYTES, lob, j);
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            const bf16x8 fa = TA::frag16(st, loa, i);
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa, acc[i][j], 0, 0, 0);
+        }
+    };
+    // LDS traffic of this wave done, then all waves: the loads into registers stay in flight
+    auto barrier = []() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    auto step = [&](auto tix) {   // stage t (= T mod DEPTH) is in LDS stage t & 1, the next DEPTH ones on their way
+        constexpr int T = decltype(tix)::value, N = (T + 1) % DEPTH;
+        stash(smem + (N & 1) * STAGE, N);
+        fetch(N);
+        multiply(smem + (T & 1) * STAGE);
+        barrier();
+    };
+    if (steps > 0) {
+        static_for<DEPTH>([&](auto d) { fetch(decltype(d)::value); });
+        stash(smem, 0);
+        fetch(0);
+        barrier();
+        int t = 0;
+        for (; t + DEPTH <= steps; t += DEPTH) static_for<DEPTH>(step);
+        static_for<DEPTH - 1>([&](auto d) {
+            if (t + decltype(d)::value < steps) step(d);
+        });
+    }
+    for (int t = steps; t * BKT < s.kk; ++t) {   // the rest, every chunk checked against the ends
+#pragma unroll
+        for (int it = 0; it < NLA; ++it)
+            *reinterpret_cast<u32x4*>(smem + (it * NT + tid) * 16) = TA::tail_chunk(static_cast<const uint16_t*>(s.a), s.lda, m0, s.m, s.kk, t * BKT, it * NT + tid);
+#pragma unroll
+        for (int it = 0; it < NLB; ++it)
+            *reinterpret_cast<u32x4*>(smem + TA::BYTES + (it * NT + tid) * 16) = TB::tail_chunk(static_cast<const uint16_t*>(s.b), s.ldb, n0, s.n, s.kk, t * BKT, it * NT + tid);
+        __syncthreads();
+        multiply(smem);
+        __syncthreads();
+    }
+
+    // Results through a private part of LDS, layout as in gemm_wavek_kernel: LPR consecutive lanes own a row of UNIT blocks.
+    constexpr int NB = 2 * STAGE / 4096 < BLOCKS ? 2 * STAGE / 4096 : BLOCKS;   // blocks at a time
+    constexpr int EPV = 16 / (int)sizeof(OutT), UNIT = sizeof(OutT) == 4 || FN < 4 ? 2 : 4;
+    constexpr int LPR = UNIT * 16 / EPV, ROWS = 64 / LPR;
+    static_assert(BLOCKS % NB == 0 && NB % FN == 0 && FN % UNIT == 0, "whole rows of blocks");
+    char* const win = smem + wave * (NB * 1024);
+    const int q = lane >> 4, r = lane & 15;
+    static_for<BLOCKS / NB>([&](auto rix) {
+        constexpr int B0 = decltype(rix)::value * NB;
+        static_for<NB>([&](auto bix) {
+            constexpr int b = B0 + decltype(bix)::value;
+            *reinterpret_cast<f32x4*>(win + decltype(bix)::value * 1024 + (16 * q + (r ^ (4 * q))) * 16) = acc[b / FN][b % FN];
+        });
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int u = 0; u < NB / UNIT * (16 / ROWS); ++u) {
+            const int blk = u / (16 / ROWS) * UNIT, row = u % (16 / ROWS) * ROWS + lane / LPR;
+            float v[EPV];
+#pragma unroll
+            for (int h = 0; h < EPV / 4; ++h) {
+                const int cg = (lane % LPR) * (EPV / 4) + h;
+                const f32x4 x = *reinterpret_cast<const f32x4*>(win + (blk + cg / 4) * 1024 + (16 * (cg & 3) + (row ^ (4 * (cg & 3)))) * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * h + e] = mfma_epilogue<EPI>(x[e]);
+            }
+            store_columns<OutT>(s, m0 + wm * TM + (B0 + blk) / FN * 16 + row, n0 + wn * TN + (B0 + blk) % FN * 16 + (lane % LPR) * EPV, v);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    });
+}
+
+template <int BM, int BN, int NW, bool DIRECT, bool A_KC, bool B_KC, int EPI, typename OutT>
+constexpr auto pick_kernel() {   // NW = 0: gemm_reg_kernel
+    if constexpr (NW == 0) return gemm_reg_kernel<BM, BN, A_KC, B_KC, EPI, OutT>;
+    else return gemm_wavek_kernel<BM, BN, NW, A_KC, B_KC, DIRECT, EPI, OutT>;
+}
+
+template <int BM, int BN, int NW, bool DIRECT, int EPI, typename OutT>
+int32_t launch_layout(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t st) {
+    const int tm = (max_m + BM - 1) / BM, tn = (max_n + BN - 1) / BN;
+    const int64_t nblk = ((int64_t)tm * tn * plan.groups + 7) / 8 * 8;
+    if (nblk > 0x7FFFFFFF) return SBP_ERR_UNSUPPORTED;
+    void (*kern)(GemmPlan, int, int, int) = nullptr;
+    if (plan.a_kc) {
+        if (plan.b_kc) kern = pick_kernel<BM, BN, NW, DIRECT, true, true, EPI, OutT>();
+        else kern = pick_kernel<BM, BN, NW, DIRECT, true, false, EPI, OutT>();
+    } else if constexpr (BM >= 64) {
+        if (plan.b_kc) kern = pick_kernel<BM, BN, NW, DIRECT, false, true, EPI, OutT>();
+        else kern = pick_kernel<BM, BN, NW, DIRECT, false, false, EPI, OutT>();
+    }
+    if (!kern) return SBP_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)nblk), dim3(NW > 0 ? NW * 64 : 256), 0, st, plan, tm, tn, order);
+    return launch_status(__func__);
+}
+
+template <int BM, int BN, int NW, bool DIRECT>
+int32_t launch_out(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t st) {
+    if (plan.out_dtype == SBP_F32) {
+        if (plan.epilogue != SBP_EPI_NONE) return SBP_ERR_UNSUPPORTED;
+        return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_NONE, float>(plan, max_m, max_n, order, st);
+    }
+    if (plan.epilogue == SBP_EPI_GELU) return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_GELU, uint16_t>(plan, max_m, max_n, order, st);
+    return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_NONE, uint16_t>(plan, max_m, max_n, order, st);
+}
+
+}  // namespace
+
+int32_t launch_gemm_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool direct, int order, hipStream_t stream) {
+    switch (tile) {
+        case WAVEK_128: return direct ? launch_out<128, 64, 4, true>(plan, max_m, max_n, order, stream) : SBP_ERR_UNSUPPORTED;
+        case WAVEK_64: return direct ? launch_out<64, 64, 8, true>(plan, max_m, max_n, order, stream) : launch_out<64, 64, 8, false>(plan, max_m, max_n, order, stream);
+        case WAVEK_32: return direct ? launch_out<32, 64, 8, true>(plan, max_m, max_n, order, stream) : launch_out<32, 64, 8, false>(plan, max_m, max_n, order, stream);
+        case REG_128: return launch_out<128, 128, 0, false>(plan, max_m, max_n, order, stream);
+        case REG_64: return launch_out<64, 64, 0, false>(plan, max_m, max_n, order, stream);
+        default: return SBP_ERR_UNSUPPORTED;
+    }
+}
+
+}  // namespace sbp

@@ -60,7 +60,13 @@ __device__ inline int kswz16(int row) { return (0 - (row >> 2)) & 3; }
 // moving row q by (q % 4) * 64 B spreads them over all 64 banks.  The 16x16x32 fragments read kk-rows
 // q and q + 8 in one pass, 32 bytes each: rows with bit 3 set move by another 32 B (a constant inside
 // every pass of the 32x32x16 fragments, so those are not affected).
-__device__ inline int nswz(int krow) { return ((krow & 3) << 2) ^ (((krow >> 3) & 1) << 1); }
+// R = 64 (128-byte rows, tiles of gemm_wavek_kernel): kk-rows of equal parity share banks; rows 0, 2, 8, 10 of a pass
+// of the 16x16x32 fragments move by 0, 32, 64, 96 bytes.
+template <int R = 128>
+__device__ inline int nswz(int krow) {
+    if constexpr (R == 64) return (((krow >> 1) & 1) << 1) | (((krow >> 3) & 1) << 2);
+    else return ((krow & 3) << 2) ^ (((krow >> 3) & 1) << 1);
+}
 
 // F16: the tile feeds v_mfma_f32_16x16x32_bf16 (frag16) and its KC image is permuted by kswz16.
 template <int R, bool KC, int NT, int BKT = BK, bool F16 = false>
@@ -73,7 +79,7 @@ struct Tile {
     static constexpr int ROWB = BKT * 2;     // bytes per row of a KC tile
     __device__ static int ksw(int row) { return F16 ? kswz16(row) : kswz<BKT>(row); }
     static_assert(CHUNKS % NT == 0, "tile must divide over the workgroup");
-    static_assert(KC || CPR >= 16, "not-KC swizzle needs at least 16 chunks per row");
+    static_assert(KC || CPR >= 16 || (CPR == 8 && F16), "not-KC swizzles: 8 chunks per row, or at least 16");
 
     // Byte offset (from the operand's base, at reduction offset 0) of the 16 bytes that belong in
     // LDS chunk position p.  first = first tile row (m or n), limit = extent of that index; rows or
@@ -86,37 +92,39 @@ struct Tile {
             return ((uint32_t)g * (uint32_t)ld + (uint32_t)(((p % CPK) ^ ksw(row)) * 8)) * 2u;
         } else {
             const int krow = p / CPR;
-            int col = first + (((p % CPR) ^ nswz(krow)) * 8);
-            col = col < limit ? col : limit - 8;
+            int col = first + (((p % CPR) ^ nswz<R>(krow)) * 8);
+            col = col < limit ? col : 0;
             return ((uint32_t)krow * (uint32_t)ld + (uint32_t)col) * 2u;
         }
     }
-    // The 16 bytes of LDS chunk position p of a stage that starts at reduction index k0 and reaches past the end kk
-    // of the reduction: zeros there (in both operands, so that no stored NaN or Inf can leak in), element by element
-    // where a chunk of a KC tile straddles the end, rows and columns clamped as in src_offset.
+    // The 16 bytes of LDS chunk position p of a stage that starts at reduction index k0 and may reach past the end kk
+    // of the reduction: zeros there (in both operands, so that no stored NaN or Inf can leak in) and behind the end of
+    // a row, element by element where a chunk straddles either.  Any pitch and alignment; nothing outside is read.
     __device__ static u32x4 tail_chunk(const uint16_t* src, int ld, int first, int limit, int kk, int k0, int p) {
-        const u32x4 zero = {0u, 0u, 0u, 0u};
+        u32x4 v = {0u, 0u, 0u, 0u};
+        const uint16_t* at;
+        int valid;   // elements of this chunk that exist
         if constexpr (KC) {
             const int row = p / CPK;
             int g = first + row;
             g = g < limit ? g : limit - 1;
             const int k = k0 + ((p % CPK) ^ ksw(row)) * 8;
-            const uint16_t* at = src + (int64_t)g * ld + k;
-            if (k + 8 <= kk) return *reinterpret_cast<const u32x4*>(at);
-            u32x4 v = zero;
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (k + e < kk) v[e >> 1] |= (uint32_t)at[e] << (16 * (e & 1));
-            return v;
+            at = src + (int64_t)g * ld + k;
+            valid = kk - k;
         } else {
             const int krow = p / CPR;
-            int col = first + (((p % CPR) ^ nswz(krow)) * 8);
-            col = col < limit ? col : limit - 8;
-            if (k0 + krow >= kk) return zero;
-            u32x4 v;
-            __builtin_memcpy(&v, src + (int64_t)(k0 + krow) * ld + col, 16);   // limit - 8 need not be a multiple of 8
-            return v;
+            const int col = first + (((p % CPR) ^ nswz<R>(krow)) * 8);
+            at = src + (int64_t)(k0 + krow) * ld + col;
+            valid = k0 + krow < kk ? limit - col : 0;
         }
+        if (valid >= 8) {
+            __builtin_memcpy(&v, at, 16);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 7; ++e)
+                if (e < valid) v[e >> 1] |= (uint32_t)at[e] << (16 * (e & 1));
+        }
+        return v;
     }
     // bytes to advance the source by for one BKT step
     __device__ static uint32_t step_bytes(int ld) { return KC ? BKT * 2u : (uint32_t)ld * BKT * 2u; }
@@ -164,7 +172,7 @@ struct Tile {
             const int s = lane & 15, nh = (lane >> 4) & 1, kh = lane >> 5;
             const int krow = 8 * kh + (s >> 2);
             const int chunk = ((wave_base + 32 * idx) >> 3) + 2 * nh + ((s & 3) >> 1);
-            off = krow * (R * 2) + ((chunk ^ nswz(krow)) << 4) + (s & 1) * 8;
+            off = krow * (R * 2) + ((chunk ^ nswz<R>(krow)) << 4) + (s & 1) * 8;
         }
         asm("" : "+v"(off));   // opaque: keep it one addend
         return off;
@@ -210,7 +218,7 @@ struct Tile {
             const int s = lane & 15, g = lane >> 4;
             const int krow = 8 * g + (s >> 2);
             const int chunk = (wave_base >> 3) + ((s & 3) >> 1);
-            off = krow * (R * 2) + ((chunk ^ nswz(krow)) << 4) + (s & 1) * 8;
+            off = krow * (R * 2) + ((chunk ^ nswz<R>(krow)) << 4) + (s & 1) * 8;
         }
         asm("" : "+v"(off));
         return off;

@@ -1513,21 +1513,23 @@ void launch_generic_epi(const GemmPlan& plan, dim3 grid, hipStream_t st) {
         hipLaunchKernelGGL((gemm_generic_kernel<A_BF16, B_BF16, OutT, SBP_EPI_NONE>), grid, dim3(16, 16), 0, st, plan);
 }
 
-// Shapes the direct-to-LDS MFMA kernels take: 16-byte aligned rows; any reduction length (gemm_mfma_pipe16_kernel), the
-// other kernels whole 64-element steps (k64) or 128-element rounds.
+// What the MFMA kernels take.  Their source offsets are 32-bit byte offsets from the shard base.
 bool mfma_ok(const GemmPlan& plan) {
     if (plan.in_dtype != SBP_BF16) return false;
     for (int g = 0; g < plan.groups; ++g) {
         const GemmShard& s = plan.s[g];
-        if (s.m == 0 || s.n == 0) continue;
-        if (s.kk == 0) continue;
-        if (s.lda % 8 || s.ldb % 8) return false;
-        if (!plan.a_kc && s.m < 8) return false;
-        if (!plan.b_kc && s.n < 8) return false;
-        // source offsets are 32-bit byte offsets from the shard base
+        if (s.m == 0 || s.n == 0 || s.kk == 0) continue;
         const int64_t ea = plan.a_kc ? (int64_t)s.m * s.lda : (int64_t)s.kk * s.lda;
         const int64_t eb = plan.b_kc ? (int64_t)s.n * s.ldb : (int64_t)s.kk * s.ldb;
         if (ea * 2 >= ((int64_t)1 << 32) || eb * 2 >= ((int64_t)1 << 32)) return false;
+    }
+    return true;
+}
+// Rows of both operands start 16-byte aligned: direct-to-LDS loads are possible.
+bool rows_aligned(const GemmPlan& plan) {
+    for (int g = 0; g < plan.groups; ++g) {
+        const GemmShard& s = plan.s[g];
+        if (s.m && s.n && s.kk && (s.lda % 8 || s.ldb % 8)) return false;
     }
     return true;
 }
@@ -1550,25 +1552,59 @@ bool split_ok(const GemmPlan& plan) {
     return true;
 }
 
+int64_t tiles_of(const GemmPlan& plan, int max_m, int max_n, int bm, int bn) {
+    return (int64_t)((max_m + bm - 1) / bm) * ((max_n + bn - 1) / bn) * plan.groups;
+}
+int longest_reduction(const GemmPlan& plan) {
+    int k = 0;
+    for (int g = 0; g < plan.groups; ++g)
+        if (plan.s[g].m && plan.s[g].n && plan.s[g].kk > k) k = plan.s[g].kk;
+    return k;
+}
+
 // Which persistent kernel for a shape both take.  Measured (ms, lockstep / ping-pong): reduction length 512 with
 // 61 tiles per compute unit 1.42 / 1.35; 2048 with 16 tiles 1.00 / 1.00, with 2 tiles 0.121 / 0.135; 4096 with 8
 // tiles 0.93 / 0.93.  Short reductions gain (the tile change is cheaper), few tiles per unit lose.
 bool pingpong_pays(const GemmPlan& plan, int max_m, int max_n) {
-    int max_k = 0;
-    for (int g = 0; g < plan.groups; ++g)
-        if (plan.s[g].m && plan.s[g].n && plan.s[g].kk > max_k) max_k = plan.s[g].kk;
-    const int64_t tiles = (int64_t)((max_m + 255) / 256) * ((max_n + 255) / 256) * plan.groups;
-    return max_k <= 1024 && tiles >= 4 * (int64_t)compute_units();
+    return longest_reduction(plan) <= 1024 && tiles_of(plan, max_m, max_n, 256, 256) >= 4 * (int64_t)compute_units();
 }
 
-// Tile of gemm_mfma_pipe16_kernel for a reduction length that is not a multiple of 64: 256 x 256 (variant 9, one
-// workgroup per compute unit) or 128 x 128 (variant 8, two).  A large tile does the work of four small ones in the
-// time of about three; compared are the rounds that the compute units need for all tiles.
-int ragged_tile(const GemmPlan& plan, int max_m, int max_n) {
+// 256 x 256 tiles (one workgroup per compute unit) or 128 x 128 ones (gemm_mfma_pipe16_kernel, two)?  A round of large
+// tiles takes about 1.35 times a full round of small ones, a round of small tiles that leaves half the places free about
+// 0.55 of a full one.  us, large / small tiles: 512 large ones 34.9 / 41.1, 320: 54.0 / 44.9, 200: 50.0 / 66.6, 192: 27.5 /
+// 30.0, 160: 42.7 / 51.5, 128: 42.0 / 37.5 and 72.1 / 59.6, 96: 24.2 / 18.9, 32: 14.8 / 8.6.
+bool large_tiles_pay(const GemmPlan& plan, int max_m, int max_n) {
     const int64_t cu = compute_units();
-    const int64_t big = (int64_t)((max_m + 255) / 256) * ((max_n + 255) / 256) * plan.groups;
-    const int64_t small = (int64_t)((max_m + 127) / 128) * ((max_n + 127) / 128) * plan.groups;
-    return 3 * ((big + cu - 1) / cu) <= (small + cu - 1) / cu ? 9 : 8;
+    const int64_t large = (tiles_of(plan, max_m, max_n, 256, 256) + cu - 1) / cu;
+    const int64_t small = tiles_of(plan, max_m, max_n, 128, 128), rest = small % (2 * cu);
+    return 27 * large <= 20 * (small / (2 * cu)) + (rest == 0 ? 0 : rest <= cu ? 11 : 20);
+}
+
+// Too few 128 x 128 tiles for half the chip and a reduction long enough to be shared out: the waves of a workgroup split
+// the reduction.  us, 128 x 128 tile / waves splitting: 128 tiles of length 4096 35.6 / 24.7, 96 of 1024 11.9 / 10.1, 64 of
+// 125000 2333 / 985, 48 of 2048 18.5 / 9.1, 16 of 2048 18.7 / 8.5, 16 of 512 8.6 / 8.1; 168 of 1000 15.2 / 25.7, 256 of
+// 2048 23.0 / 27.8.  The largest tile that still occupies most of the chip: 128 x 64 (192 of them 10.1 against 12.0 with
+// 64 x 64), 64 x 64 (160: 9.1, against 15.0 with 32 x 64), else 32 x 64 (80 of 64 x 64: 166, 160 of 32 x 64: 108).
+bool wavek_pays(const GemmPlan& plan, int max_m, int max_n) {
+    return 2 * tiles_of(plan, max_m, max_n, 128, 128) <= compute_units() && longest_reduction(plan) >= 512;
+}
+AnyTile wavek_tile(const GemmPlan& plan, int max_m, int max_n) {
+    const int64_t cu = compute_units();
+    if (plan.a_kc && max_m <= 32) return WAVEK_32;
+    if (max_m > 64 && 4 * tiles_of(plan, max_m, max_n, 128, 64) >= 3 * cu) return WAVEK_128;
+    return !plan.a_kc || 2 * tiles_of(plan, max_m, max_n, 64, 64) >= cu ? WAVEK_64 : WAVEK_32;
+}
+// Rows at any alignment.  us, register kernel 128 x 128 / 64 x 64 / waves splitting, 32 x 64: 472 large tiles 14.7 / 16.7 /
+// 59.8; 288: 62.3 / 77.0 / 137; 84: 13.9 / 10.9 / -; 10 rows, 1501 long 23.7 / 12.6 / 14.6; 64 tiles of 64 x 64, 7503 long
+// 115 / 52 / 40; 128 of them, 50001 long 1090 / 452 / 275; 64 x 50001 results 28.3 / 23.1 / -.
+AnyTile any_tile(const GemmPlan& plan, int max_m, int max_n) {
+    const int64_t cu = compute_units();
+    if (2 * tiles_of(plan, max_m, max_n, 64, 64) <= cu && longest_reduction(plan) >= 4096) return plan.a_kc ? WAVEK_32 : WAVEK_64;
+    return max_m > 64 && max_n > 64 && 2 * tiles_of(plan, max_m, max_n, 128, 128) >= cu ? REG_128 : REG_64;
+}
+int32_t launch_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool direct, hipStream_t stream) {
+    const int bm = tile == WAVEK_32 ? 32 : tile == WAVEK_64 || tile == REG_64 ? 64 : 128, bn = tile == REG_128 ? 128 : 64;
+    return launch_gemm_any(plan, max_m, max_n, tile, direct, tile_order_for((max_m + bm - 1) / bm, (max_n + bn - 1) / bn), stream);
 }
 
 }  // namespace
@@ -1595,7 +1631,7 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
         max_n = plan.s[g].n > max_n ? plan.s[g].n : max_n;
     }
     // the fused row maximum exists in the persistent bf16 kernel only; the caller does anything else in two passes
-    if (plan.epilogue == EPI_ROWMAX && (max_m == 0 || max_n == 0 || plan.f32_operand || variant == 1 || !mfma_ok(plan)))
+    if (plan.epilogue == EPI_ROWMAX && (max_m == 0 || max_n == 0 || plan.f32_operand || variant == 1 || !mfma_ok(plan) || !rows_aligned(plan)))
         return SBP_ERR_UNSUPPORTED;
     if (max_m == 0 || max_n == 0) return SBP_OK;   // every local product is empty
     // variants 31 / 32 choose the tile of the split kernel only; every other product takes the default path
@@ -1629,6 +1665,12 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
         }
         return launch_status(__func__);
     }
+    const bool direct = rows_aligned(plan);
+    if (variant >= 40 && variant <= 44) return launch_any(plan, max_m, max_n, variant - 40, direct, stream);
+    if (!direct) {
+        if (variant > 1) return SBP_ERR_UNSUPPORTED;
+        return launch_any(plan, max_m, max_n, any_tile(plan, max_m, max_n), false, stream);
+    }
     bool k64 = true, k128 = true;   // every local reduction a whole number of 64-element steps / of four-stage rounds
     for (int g = 0; g < plan.groups; ++g) {
         if (!plan.s[g].m || !plan.s[g].n) continue;
@@ -1649,12 +1691,11 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
         return launch_mfma_layout<256, 256, 2, 4, 204, EPI_ROWMAX, uint16_t>(plan, max_m, max_n, stream);
     }
     if (variant == 0) {
-        // Default: the 256 x 256 tile over 8 waves with four 32-deep LDS stages, as one persistent
-        // workgroup per compute unit when the reduction length allows it; shapes that would leave most
-        // of such a tile empty take the 128 x 128 tile.  The persistent kernel runs on the 16x16x32
-        // matrix instruction.
-        if (!k64) variant = ragged_tile(plan, max_m, max_n);
-        else variant = (max_m > 128 && max_n > 128) ? (k128 ? (pingpong_pays(plan, max_m, max_n) ? 21 : 16) : 7) : 4;
+        // Default: the 256 x 256 tile over 8 waves with four 32-deep LDS stages, as one persistent workgroup per compute
+        // unit when the reduction length allows it, on the 16x16x32 matrix instruction; 128 x 128 tiles where those
+        // finish sooner; waves splitting the reduction where neither fills the chip.
+        if (wavek_pays(plan, max_m, max_n)) return launch_any(plan, max_m, max_n, wavek_tile(plan, max_m, max_n), true, stream);
+        variant = !large_tiles_pay(plan, max_m, max_n) ? 8 : !k128 ? 9 : pingpong_pays(plan, max_m, max_n) ? 21 : 16;
     }
     if (!k64 && variant != 8 && variant != 9) return SBP_ERR_UNSUPPORTED;
     switch (variant) {

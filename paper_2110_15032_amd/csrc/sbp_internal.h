@@ -85,6 +85,16 @@ void set_tile_order(int32_t order);
 // The ping-pong persistent kernel (gemm_pingpong_kernel.hip).  The caller has checked: bf16 operands, every
 // local reduction length a multiple of 128, operand row pitches of 16 bytes.  order: tile walk (see map_tile).
 int32_t launch_gemm_pingpong(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t stream);
+// gemm_any_kernels.hip: bf16 operands, any reduction length, local operands below 4 GiB.  direct: rows of both operands
+// 16-byte aligned, else any pitch (REG tiles always).
+enum AnyTile : int32_t {
+    WAVEK_32 = 0,   // 32 x 64, reduction-contiguous A only
+    WAVEK_64,       // 64 x 64
+    WAVEK_128,      // 128 x 64, direct only
+    REG_128,        // 128 x 128
+    REG_64          // 64 x 64
+};
+int32_t launch_gemm_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool direct, int order, hipStream_t stream);
 // Compute units of the current device, asked of the runtime once per device and kept.
 int compute_units();
 // Diagnostic matrix-pipe loop (probe_kernels.hip); scratch: 1 MiB of device memory.

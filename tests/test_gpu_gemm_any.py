@@ -53,3 +53,37 @@ def test_bf16_any_reduction_length(kk, tx, tw, variant):
     got, _ = run(Xs, orc.S1, Ws, orc.S0, M, k * kk, N, k, tx, tw, pitch(Xs, tx, 8), pitch(Ws, tw, 8), variant=variant)
     for i in range(k):
         assert_matmul_close(got[i], ref[i], 1e-5, f"kk={kk} trans=({tx},{tw}) v{variant} shard {i}")
+
+
+@pytest.mark.parametrize("variant", [0, 40, 41, 42, 43, 44])
+@pytest.mark.parametrize("aligned", [False, True])
+@pytest.mark.parametrize("tx,tw", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("M,kk,N", [(1, 1, 1), (3, 5, 2), (31, 7, 9), (33, 65, 65), (64, 289, 64), (129, 544, 67), (140, 1000, 130)])
+def test_bf16_any_shape_and_pitch(M, kk, N, tx, tw, aligned, variant):
+    """no whole stage, one, fewer than waves, several per wave; rows shorter than a 16-byte chunk; odd pitches (register
+    path) and 16-byte aligned ones (direct path)"""
+    k = 2
+    if variant == 40 and tx:
+        pytest.skip("the 32-row tile takes a reduction-contiguous left operand")
+    if variant == 42 and not aligned:
+        pytest.skip("the 128 x 64 tile takes aligned rows")
+    X, W = bf16(3, (M, k * kk)), bf16(4, (k * kk, N), 0.5)
+    Xs, Ws = orc.scatter(X, orc.S1, k), orc.scatter(W, orc.S0, k)
+    ref, _ = orc.matmul_sbp([values(x) for x in Xs], orc.S1, [values(w) for w in Ws], orc.S0)
+    to, extra = (8, 0) if aligned else (2, 1)
+    got, _ = run(Xs, orc.S1, Ws, orc.S0, M, k * kk, N, k, tx, tw, pitch(Xs, tx, to, extra), pitch(Ws, tw, to, extra), pitch(ref, 0, 2, 1), variant=variant)
+    for i in range(k):
+        assert_matmul_close(got[i], ref[i], 1e-5, f"{M}x{kk}x{N} trans=({tx},{tw}) v{variant} shard {i}")
+
+
+@pytest.mark.parametrize("epilogue", [sbp.EPI_NONE, sbp.EPI_GELU])
+@pytest.mark.parametrize("M,K,N", [(5, 33, 7), (70, 100, 203)])
+def test_bf16_odd_rows_rounded_results(M, K, N, epilogue):
+    k = 3
+    X, W = bf16(5, (M, K)), bf16(6, (K, N), 0.2)
+    Xs, Ws = orc.scatter(X, orc.B, k), orc.scatter(W, orc.S1, k)
+    ref, _ = orc.matmul_sbp([values(x) for x in Xs], orc.B, [values(w) for w in Ws], orc.S1)
+    got, _ = run(Xs, orc.B, Ws, orc.S1, M, K, N, k, 0, 0, 0, 0, epilogue=epilogue)
+    for i in range(k):
+        r = orc.gelu(ref[i]) if epilogue == sbp.EPI_GELU else ref[i]
+        assert_matmul_close(got[i], r, 2.0 ** -7, f"epilogue {epilogue} shard {i}")
