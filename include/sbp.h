@@ -260,7 +260,9 @@ enum {
                                    12 on the 16x16x32 matrix instruction, 21 = 16 with the two waves of
                                    every SIMD taking turns at the matrix pipe (ping-pong), 40-42 = the
                                    waves of a workgroup split the reduction (tile 32x64, 64x64, 128x64),
-                                   43, 44 = operands through registers (tile 128x128, 64x64); a forced
+                                   43, 44 = operands through registers (tile 128x128, 64x64); fp32 operands:
+                                   45-47 = tile 128x128, 64x64, 32x32 with the waves splitting the
+                                   reduction; a forced
                                    kernel that cannot take the shapes gives SBP_ERR_UNSUPPORTED        */
     SBP_KNOB_TILE_ORDER = 1,    /* order in which workgroups walk output tiles: low byte = tile-rows per
                                    band (0, the default: chosen from the shape), bit 8 set = no per-XCD

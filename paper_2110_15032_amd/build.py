@@ -16,7 +16,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsbp_mi355x.so")
 
-SOURCES = ["sbp_api.hip", "boxing_kernels.hip", "gemm_kernels.hip", "gemm_pingpong_kernel.hip", "gemm_any_kernels.hip", "softmax_kernels.hip", "probe_kernels.hip"]
+SOURCES = ["sbp_api.hip", "boxing_kernels.hip", "gemm_kernels.hip", "gemm_pingpong_kernel.hip", "gemm_any_kernels.hip", "gemm_f32_kernels.hip", "softmax_kernels.hip", "probe_kernels.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -2,7 +2,7 @@
 // C_g = A_g B_g from the local tensors it holds; all k devices run in ONE launch.
 //
 //   gemm_generic_kernel       any dtype / shape / pitch, one output element per lane, fp32 FMA chain.
-//                             Used for fp32 operands and for shapes the MFMA kernels do not take.
+//                             Used for bf16 operands of 4 GiB and more, and on request.
 //   gemm_mfma_kernel          bf16 x bf16 -> fp32 on the matrix cores (v_mfma_f32_32x32x16_bf16),
 //                             BM x BN macro-tile per workgroup, global->LDS loads that bypass
 //                             registers, two LDS stages of 64 reduction elements.
@@ -1602,6 +1602,22 @@ AnyTile any_tile(const GemmPlan& plan, int max_m, int max_n) {
     if (2 * tiles_of(plan, max_m, max_n, 64, 64) <= cu && longest_reduction(plan) >= 4096) return plan.a_kc ? WAVEK_32 : WAVEK_64;
     return max_m > 64 && max_n > 64 && 2 * tiles_of(plan, max_m, max_n, 128, 128) >= cu ? REG_128 : REG_64;
 }
+// fp32 operands on the matrix cores: the largest tile that gives the chip enough workgroups and is not mostly padding.  us,
+// 128 x 128 / 64 x 64 / 32 x 32 with the waves splitting the reduction (rows x reduction x columns, devices):
+// 2000 x 750 x 1500, 4: 177 / 194 / 233; 1024 x 12500 x 512, 4 (128 large tiles): 906 / 472 / 578; 600 x 1000 x 500, 3 (240 of
+// 64 x 64): 79 / 29 / 30; 300 x 1000 x 300, 2 (50): 77 / 27 / 12; 8 x 256 x 12500, 4: 41 / 24 / 16; 256 x 8 x 12500, 4: 17 / 20 / 47.
+F32Tile f32_tile(const GemmPlan& plan, int max_m, int max_n) {
+    const int64_t cu = compute_units();
+    const bool deep = longest_reduction(plan) >= 64;   // the 32 x 32 tile's stage
+    if (max_m > 64 && max_n > 64 && tiles_of(plan, max_m, max_n, 128, 128) >= cu) return F32_128;
+    if (deep && (max_m <= 32 || max_n <= 32)) return F32_32;
+    return !deep || 4 * tiles_of(plan, max_m, max_n, 64, 64) >= 3 * cu ? F32_64 : F32_32;
+}
+int32_t launch_f32(const GemmPlan& plan, int max_m, int max_n, int32_t variant, hipStream_t stream) {
+    const int tile = variant >= 45 ? variant - 45 : f32_tile(plan, max_m, max_n);
+    const int b = tile == F32_128 ? 128 : tile == F32_64 ? 64 : 32;
+    return launch_gemm_f32(plan, max_m, max_n, tile, tile_order_for((max_m + b - 1) / b, (max_n + b - 1) / b), stream);
+}
 int32_t launch_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool direct, hipStream_t stream) {
     const int bm = tile == WAVEK_32 ? 32 : tile == WAVEK_64 || tile == REG_64 ? 64 : 128, bn = tile == REG_128 ? 128 : 64;
     return launch_gemm_any(plan, max_m, max_n, tile, direct, tile_order_for((max_m + bm - 1) / bm, (max_n + bn - 1) / bn), stream);
@@ -1638,19 +1654,23 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
     if ((variant == 31 || variant == 32) && !(plan.f32_operand && split_ok(plan))) variant = 0;
 
     if (plan.f32_operand) {
-        // Table 1 rows 4 / 5 with a bf16 partner: split kernel, else the generic kernel with mixed element types
+        // Table 1 rows 4 / 5 with a bf16 partner: split kernel, else the fp32 matrix instruction with mixed element types
+        if (plan.out_dtype != SBP_F32 || plan.epilogue != SBP_EPI_NONE) return SBP_ERR_DTYPE;
+        if (variant >= 45 && variant <= 47) return launch_f32(plan, max_m, max_n, variant, stream);
         if (variant != 1 && split_ok(plan)) {
             if (variant > 1 && variant != 31 && variant != 32) return SBP_ERR_UNSUPPORTED;
             return plan.f32_operand == 2 ? launch_split<true>(plan, max_m, max_n, variant, stream) : launch_split<false>(plan, max_m, max_n, variant, stream);
         }
         if (variant > 1) return SBP_ERR_UNSUPPORTED;
+        if (variant == 0) return launch_f32(plan, max_m, max_n, variant, stream);
         const dim3 grid((max_n + 15) / 16, (max_m + 15) / 16, plan.groups);
         if (grid.y > 65535 || grid.z > 65535) return SBP_ERR_UNSUPPORTED;
-        if (plan.out_dtype != SBP_F32 || plan.epilogue != SBP_EPI_NONE) return SBP_ERR_DTYPE;
         if (plan.f32_operand == 2) launch_generic_epi<true, false, float>(plan, grid, stream);
         else launch_generic_epi<false, true, float>(plan, grid, stream);
         return launch_status(__func__);
     }
+    if (plan.in_dtype == SBP_F32 && (variant == 0 || (variant >= 45 && variant <= 47)))
+        return plan.out_dtype == SBP_F32 ? launch_f32(plan, max_m, max_n, variant, stream) : SBP_ERR_DTYPE;
     const bool fast = mfma_ok(plan);
     if (variant == 1 || !fast) {
         if (variant > 1) return SBP_ERR_UNSUPPORTED;   // a forced MFMA variant cannot take this shape

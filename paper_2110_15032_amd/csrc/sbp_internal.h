@@ -95,6 +95,13 @@ enum AnyTile : int32_t {
     REG_64          // 64 x 64
 };
 int32_t launch_gemm_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool direct, int order, hipStream_t stream);
+// gemm_f32_kernels.hip: fp32 x fp32 (fp32 results, GeLU or no epilogue) and fp32 next to bf16 (f32_operand), any pitch and extent.
+enum F32Tile : int32_t {
+    F32_128 = 0,   // 128 x 128
+    F32_64,        // 64 x 64
+    F32_32         // 32 x 32, waves splitting the reduction
+};
+int32_t launch_gemm_f32(const GemmPlan& plan, int max_m, int max_n, int tile, int order, hipStream_t stream);
 // Compute units of the current device, asked of the runtime once per device and kept.
 int compute_units();
 // Diagnostic matrix-pipe loop (probe_kernels.hip); scratch: 1 MiB of device memory.

@@ -87,3 +87,42 @@ def test_bf16_odd_rows_rounded_results(M, K, N, epilogue):
     for i in range(k):
         r = orc.gelu(ref[i]) if epilogue == sbp.EPI_GELU else ref[i]
         assert_matmul_close(got[i], r, 2.0 ** -7, f"epilogue {epilogue} shard {i}")
+
+
+def f32(tid, shape):
+    return wl.uniform(SEED, tid, shape).astype(np.float32)
+
+
+@pytest.mark.parametrize("variant", [0, 45, 46, 47])
+@pytest.mark.parametrize("tx,tw", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("types", ["f32,f32", "f32,bf16", "bf16,f32"])
+@pytest.mark.parametrize("M,kk,N", [(1, 1, 1), (3, 5, 2), (31, 15, 9), (33, 65, 66), (64, 128, 64), (129, 131, 67), (140, 321, 257)])
+def test_f32_operands_any_shape_and_pitch(M, kk, N, types, tx, tw, variant):
+    """the fp32 matrix instruction: no whole stage, one, several and a remainder, rows shorter than a chunk, one tile and
+    a ragged second one of every tile size, fp32 x fp32 and either operand bf16.  Bar: summation order (see above)."""
+    k = 2
+    if types == "f32,f32":
+        X, W, sx, sw = f32(7, (M, k * kk)), f32(8, (k * kk, N)), orc.S1, orc.S0
+        Xs, Ws = orc.scatter(X, sx, k), orc.scatter(W, sw, k)
+    elif types == "f32,bf16":
+        X, W, sx, sw, kk = None, bf16(8, (kk, N), 0.5), orc.P_SUM, orc.B, kk
+        Xs, Ws = [f32(10 + i, (M, kk)) for i in range(k)], orc.scatter(W, sw, k)
+    else:
+        X, W, sx, sw = bf16(7, (M, kk)), None, orc.B, orc.P_SUM
+        Xs, Ws = orc.scatter(X, sx, k), [f32(10 + i, (kk, N)) for i in range(k)]
+    wide = lambda v: values(v) if v.dtype == np.uint16 else v
+    ref, _ = orc.matmul_sbp([wide(x) for x in Xs], sx, [wide(w) for w in Ws], sw)
+    got, _ = run(Xs, sx, Ws, sw, M, k * kk if sx == orc.S1 else kk, N, k, tx, tw, pitch(Xs, tx, 2, 1), pitch(Ws, tw, 2, 1), pitch(ref, 0, 2, 1), variant=variant)
+    for i in range(k):
+        assert_matmul_close(got[i], ref[i], 1e-5, f"{M}x{kk}x{N} {types} trans=({tx},{tw}) v{variant} shard {i}")
+
+
+@pytest.mark.parametrize("M,K,N", [(5, 33, 7), (70, 300, 203)])
+def test_f32_gelu(M, K, N):
+    k = 3
+    X, W = f32(5, (M, K)), f32(6, (K, N))
+    Xs, Ws = orc.scatter(X, orc.B, k), orc.scatter(W, orc.S1, k)
+    ref, _ = orc.matmul_sbp(Xs, orc.B, Ws, orc.S1)
+    got, _ = run(Xs, orc.B, Ws, orc.S1, M, K, N, k, 0, 0, 0, 0, epilogue=sbp.EPI_GELU)
+    for i in range(k):
+        assert_matmul_close(got[i], orc.gelu(ref[i]), 1e-5, f"gelu shard {i}")
