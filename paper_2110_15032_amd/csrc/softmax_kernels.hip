@@ -2,6 +2,8 @@
 // columns of the logits it holds, first to a row max (P(max)), then -- once the max has been boxed
 // to B -- to a row sum of exp(l - max) (P(sum)).  One workgroup per (row, shard); 16-byte loads
 // where the row pitch allows, wavefront shuffles then one LDS hop across the four waves.
+#include <type_traits>
+
 #include "sbp_internal.h"
 
 namespace sbp {
@@ -118,11 +120,19 @@ __device__ inline uint32_t pack_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
-// VE elements per lane: 8 bf16 / 4 fp32 (16 bytes) when the row pitch allows, else 1
-template <bool BF16, int VE>
+// 16 bytes (8 bf16 / 4 fp32 elements) per lane whatever the row pitch: rows that do not start 16-byte aligned are read and
+// written with unaligned vectors, which cost a second cache line per wave and instruction; the last group of a row goes
+// element by element where the row does not fill it.  ALIGNED: every row of both tensors starts 16-byte aligned; the
+// result is then stored past the caches.  Otherwise neighbouring waves share a line, which L2 has to keep for both.
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;
+template <bool BF16, bool ALIGNED>
 __global__ __launch_bounds__(RS_THREADS) void xent_grad_kernel(XentPlan p) {
+    constexpr int VE = BF16 ? 8 : 4;
+    using Elem = std::conditional_t<BF16, uint16_t, float>;
+    using Vec = std::conditional_t<BF16, std::conditional_t<ALIGNED, u32x4, u32x4_any>, std::conditional_t<ALIGNED, f32x4, f32x4_any>>;
     const int i = blockIdx.y;
-    const uint32_t cols_v = (uint32_t)p.cols[i] / VE;
+    const uint32_t cols = (uint32_t)p.cols[i], cols_v = (cols + VE - 1) / VE;
     if (cols_v == 0) return;
     // (row, vector) of this lane's first item by one division, then advanced by the grid stride with adds only:
     // a 64-bit division per item costs more vector instructions than the item's arithmetic and made the kernel
@@ -144,36 +154,30 @@ __global__ __launch_bounds__(RS_THREADS) void xent_grad_kernel(XentPlan p) {
         const float g = live ? p.grad[i][r] : 0.0f;
         const float m = p.gmax[i][r], inv = 1.0f / p.denom[i][r];
         const int32_t yc = y - p.begin[i] - (int32_t)c;   // position of the label inside this group, if any
-        const int64_t pos = (int64_t)r * p.ld[i] + c, opos = (int64_t)r * p.ld_out[i] + c;
-        float v[VE];
-        if constexpr (BF16 && VE == 8) {
+        const Elem* src = static_cast<const Elem*>(p.logits[i]) + (int64_t)r * p.ld[i] + c;
+        Elem* dst = static_cast<Elem*>(p.out[i]) + (int64_t)r * p.ld_out[i] + c;
+        auto value = [&](float v, int e) { return (__expf(v - m) * inv - (e == yc ? 1.0f : 0.0f)) * g; };
+        if (c + VE <= cols) {
             // streaming load: the gradient pass is the last reader of the logits (measured 2 % faster than a cached load;
             // two items per lane and round, both loaded before either is worked on, 1 % slower than this)
-            const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(p.logits[i]) + pos));
+            const Vec w = __builtin_nontemporal_load(reinterpret_cast<const Vec*>(src));
+            Vec o;
+            if constexpr (BF16) {
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                v[2 * d] = bf16_lo(w[d]);
-                v[2 * d + 1] = bf16_hi(w[d]);
+                for (int d = 0; d < 4; ++d) o[d] = pack_bf16(value(bf16_lo(w[d]), 2 * d), value(bf16_hi(w[d]), 2 * d + 1));
+            } else {
+#pragma unroll
+                for (int e = 0; e < VE; ++e) o[e] = value(w[e], e);
             }
-        } else if constexpr (!BF16 && VE == 4) {
-            const f32x4 w = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(static_cast<const float*>(p.logits[i]) + pos));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = w[e];
+            if constexpr (ALIGNED) __builtin_nontemporal_store(o, reinterpret_cast<Vec*>(dst));
+            else *reinterpret_cast<Vec*>(dst) = o;
         } else {
-            if constexpr (BF16) v[0] = __uint_as_float((uint32_t) static_cast<const uint16_t*>(p.logits[i])[pos] << 16);
-            else v[0] = static_cast<const float*>(p.logits[i])[pos];
-        }
 #pragma unroll
-        for (int e = 0; e < VE; ++e) v[e] = (__expf(v[e] - m) * inv - (e == yc ? 1.0f : 0.0f)) * g;
-        if constexpr (BF16 && VE == 8) {
-            const u32x4 o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
-            __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(static_cast<uint16_t*>(p.out[i]) + opos));
-        } else if constexpr (!BF16 && VE == 4) {
-            const f32x4 o = {v[0], v[1], v[2], v[3]};
-            __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(static_cast<float*>(p.out[i]) + opos));
-        } else {
-            if constexpr (BF16) static_cast<uint16_t*>(p.out[i])[opos] = (uint16_t)(pack_bf16(v[0], 0.0f) & 0xFFFFu);
-            else static_cast<float*>(p.out[i])[opos] = v[0];
+            for (int e = 0; e < VE - 1; ++e)
+                if (c + e < cols) {
+                    if constexpr (BF16) dst[e] = (uint16_t)(pack_bf16(value(__uint_as_float((uint32_t)src[e] << 16), e), 0.0f) & 0xFFFFu);
+                    else dst[e] = value(src[e], e);
+                }
         }
     }
 }
@@ -194,13 +198,14 @@ int32_t launch_xent_grad(const XentPlan& plan, hipStream_t stream) {
     if (plan.rows == 0 || plan.total_cols == 0) return SBP_OK;
     const bool bf = plan.dtype == SBP_BF16;
     const int epv = bf ? 8 : 4;
-    bool vec = true;
+    bool aligned = true;
     int64_t max_units = 0;
     for (int i = 0; i < plan.k; ++i) {
-        if (plan.cols[i] % epv || plan.ld[i] % epv || plan.ld_out[i] % epv) vec = false;
-        max_units = plan.cols[i] > max_units ? plan.cols[i] : max_units;
+        if (plan.ld[i] % epv || plan.ld_out[i] % epv) aligned = false;
+        const int64_t units = ((int64_t)plan.cols[i] + epv - 1) / epv;
+        max_units = units > max_units ? units : max_units;
     }
-    max_units = max_units * plan.rows / (vec ? epv : 1);
+    max_units *= plan.rows;
     int64_t bx = (max_units + RS_THREADS - 1) / RS_THREADS;
     // at most 65536 workgroups, grid-stride beyond (2 GB of bf16 logits: 0.68 ms; with one vector per lane and
     // half a million short-lived workgroups 0.74 ms, with 16384 workgroups 0.73 ms)
@@ -208,10 +213,10 @@ int32_t launch_xent_grad(const XentPlan& plan, hipStream_t stream) {
     if (bx > cap) bx = cap;
     if (bx < 1) bx = 1;
     const dim3 grid((uint32_t)bx, (uint32_t)plan.k);
-    if (bf && vec) hipLaunchKernelGGL((xent_grad_kernel<true, 8>), grid, dim3(RS_THREADS), 0, stream, plan);
-    else if (bf) hipLaunchKernelGGL((xent_grad_kernel<true, 1>), grid, dim3(RS_THREADS), 0, stream, plan);
-    else if (vec) hipLaunchKernelGGL((xent_grad_kernel<false, 4>), grid, dim3(RS_THREADS), 0, stream, plan);
-    else hipLaunchKernelGGL((xent_grad_kernel<false, 1>), grid, dim3(RS_THREADS), 0, stream, plan);
+    if (bf && aligned) hipLaunchKernelGGL((xent_grad_kernel<true, true>), grid, dim3(RS_THREADS), 0, stream, plan);
+    else if (bf) hipLaunchKernelGGL((xent_grad_kernel<true, false>), grid, dim3(RS_THREADS), 0, stream, plan);
+    else if (aligned) hipLaunchKernelGGL((xent_grad_kernel<false, true>), grid, dim3(RS_THREADS), 0, stream, plan);
+    else hipLaunchKernelGGL((xent_grad_kernel<false, false>), grid, dim3(RS_THREADS), 0, stream, plan);
     return launch_status(__func__);
 }
 
