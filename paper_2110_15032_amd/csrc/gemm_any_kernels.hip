@@ -393,6 +393,145 @@ __global__ __launch_bounds__(256, 2) void gemm_reg_kernel(GemmPlan p, int tm, in
     });
 }
 
+// gemm_deep_kernel: 128 x 128 tile, rows 16-byte aligned, for products with about one such tile per compute unit.  Two groups
+// of four waves (64 x 64 each) take the two 32-deep halves of every 64-deep stage; four stages, one barrier a stage, the
+// two partial tiles added through LDS.
+//   * Two waves per SIMD cover each other's waits, which one workgroup of gemm_mfma_pipe16_kernel per compute unit does not.
+//   * A stage reads 128 consecutive bytes of a reduction-contiguous row, not 64: by the time the next 32-deep stage asks for the
+//     other half of a 128-byte line it has left the L1, so that every line came from L2 twice.
+// Bound by a compute unit's load path: 32 KB a stage take 0.56 us at 4096 x 512 results (8 devices, 1 PFLOP/s), 0.60 where rows
+// lie 250112 bytes apart and 0.95 where they lie 250000 apart and every piece straddles two lines.  Neither more stages in
+// flight (eight of 32) nor LDS reads spread over the whole stage changed these.  Feature gradient of a classifier, 8 devices,
+// [1024, 125000] x [125000, 512], us: 1523 -> 1177 and, with 250000-byte rows, 2428 -> 1885.
+template <bool A_KC, bool B_KC, int EPI, typename OutT>
+__global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int tn, int order) {
+    constexpr int BM = 128, BN = 128, BKT = 64, NT = 512, NST = 4, FM = 4, FN = 4;
+    using TA = Tile<BM, A_KC, NT, BKT, true>;
+    using TB = Tile<BN, B_KC, NT, BKT, true>;
+    constexpr int NVM = TA::PER_THREAD + TB::PER_THREAD, STAGE = TA::BYTES + TB::BYTES;
+    static_assert(NST * STAGE == 8 * FM * FN * 1024, "the partial tiles fill the stages");
+    __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE];
+
+    const TileCoord tc = map_tile(blockIdx.x, gridDim.x, tm, tn, p.groups, order);
+    if (!tc.valid) return;
+    const GemmShard s = p.s[tc.g];
+    const int m0 = tc.tile_m * BM, n0 = tc.tile_n * BN;
+    if (m0 >= s.m || n0 >= s.n) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int sub = wave & 3, half = wave >> 2, wm = sub >> 1, wn = sub & 1;
+
+    f32x4 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int loa = TA::lane_offset16(wm * 64, lane, half), lob = TB::lane_offset16(wn * 64, lane, half);
+
+    const int steps = s.kk / BKT;
+    gbl_char* A = (gbl_char*)s.a;
+    gbl_char* B = (gbl_char*)s.b;
+    uint32_t offa[TA::PER_THREAD], offb[TB::PER_THREAD];
+#pragma unroll
+    for (int it = 0; it < TA::PER_THREAD; ++it) offa[it] = TA::src_offset(s.lda, m0, s.m, it * NT + tid);
+#pragma unroll
+    for (int it = 0; it < TB::PER_THREAD; ++it) offb[it] = TB::src_offset(s.ldb, n0, s.n, it * NT + tid);
+    const uint32_t stepa = TA::step_bytes(s.lda), stepb = TB::step_bytes(s.ldb);
+    int loaded = 0;
+    auto issue = [&](char* st) {   // past the last stage the source stays: the reload is in bounds and unread
+        TA::load_direct_untracked(st, A, offa, wave);
+        TB::load_direct_untracked(st + TA::BYTES, B, offb, wave);
+        ++loaded;
+        const bool adv = loaded < steps;
+        A += adv ? stepa : 0u;
+        B += adv ? stepb : 0u;
+    };
+    bf16x8 fa[2][FM], fb[2][FN];
+    auto read = [&](const char* st, int set) {
+#pragma unroll
+        for (int j = 0; j < FN; ++j) fb[set][j] = TB::frag16(st + TA::BYTES, lob, j);
+#pragma unroll
+        for (int i = 0; i < FM; ++i) fa[set][i] = TA::frag16(st, loa, i);
+    };
+    auto mfmas = [&](int set) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
+    };
+    // Stage t's fragments were read in the step before.  Its successor has landed for this wave, and this wave's reads have
+    // returned, before the barrier; behind it that holds for all waves: stage t is free for t + NST, and t + 1 may be read,
+    // all through the multiplication.
+    auto wait_keep = [](auto n) { __builtin_amdgcn_s_waitcnt((vmcnt_only(decltype(n)::value) & ~0x0F00)); };   // vmcnt(n) lgkmcnt(0)
+    auto step = [&](auto cur) {
+        constexpr int CUR = decltype(cur)::value;
+        wait_keep(std::integral_constant<int, (NST - 2) * NVM>{});
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        issue(smem + CUR * STAGE);
+        read(smem + (CUR + 1) % NST * STAGE, (CUR + 1) & 1);
+        mfmas(CUR & 1);
+        constexpr int NDS = (A_KC ? FM : 2 * FM) + (B_KC ? FN : 2 * FN), NM = FM * FN - 4;
+        static_for<NM>([&](auto i) {   // fragment reads spread over all but the last matrix instructions
+            constexpr int I = decltype(i)::value, nds = NDS * (I + 1) / NM - NDS * I / NM;
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            if constexpr (nds > 0) __builtin_amdgcn_sched_group_barrier(0x100, nds, 0);
+        });
+        __builtin_amdgcn_sched_group_barrier(0x008, FM * FN - NM, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (steps > 0) {
+        static_for<NST>([&](auto i) { issue(smem + decltype(i)::value * STAGE); });
+        wait_keep(std::integral_constant<int, (NST - 1) * NVM>{});
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        read(smem, 0);
+        int t = 0;
+        for (; t + NST <= steps; t += NST) static_for<NST>(step);
+        const int rem = steps - t;
+        static_for<NST - 1>([&](auto i) {
+            if (decltype(i)::value < rem) step(i);
+        });
+        __builtin_amdgcn_s_waitcnt(0x0070);   // the unread trailing loads have landed before their stages are reused
+    }
+    __syncthreads();
+    if (const int k0 = steps * BKT; k0 < s.kk) {   // the last 1 .. 63 elements, zeros behind them
+#pragma unroll
+        for (int it = 0; it < TA::PER_THREAD; ++it)
+            *reinterpret_cast<u32x4*>(smem + (it * NT + tid) * 16) = TA::tail_chunk(static_cast<const uint16_t*>(s.a), s.lda, m0, s.m, s.kk, k0, it * NT + tid);
+#pragma unroll
+        for (int it = 0; it < TB::PER_THREAD; ++it)
+            *reinterpret_cast<u32x4*>(smem + TA::BYTES + (it * NT + tid) * 16) = TB::tail_chunk(static_cast<const uint16_t*>(s.b), s.ldb, n0, s.n, s.kk, k0, it * NT + tid);
+        __syncthreads();
+        read(smem, 0);
+        mfmas(0);
+        __syncthreads();
+    }
+
+    // the partial tiles, blocks as in gemm_wavek_kernel; the two waves of a 64 x 64 part share its sum
+    constexpr int EPV = 16 / (int)sizeof(OutT), UNIT = sizeof(OutT) == 4 ? 2 : 4, PART = FM * FN * 1024;
+    const int q = lane >> 4, r = lane & 15;
+    static_for<FM * FN>([&](auto bix) {
+        constexpr int b = decltype(bix)::value;
+        *reinterpret_cast<f32x4*>(smem + wave * PART + b * 1024 + (16 * q + (r ^ (4 * q))) * 16) = acc[b / FN][b % FN];
+    });
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < FM * FN / UNIT; ++u) {   // this wave: eight of every 16 rows
+        const int blk = u * UNIT, row = 8 * half + (lane >> 3);
+        float v[EPV];
+#pragma unroll
+        for (int h = 0; h < EPV / 4; ++h) {
+            const int cg = (lane & 7) * (EPV / 4) + h;
+            const char* at = smem + sub * PART + (blk + cg / 4) * 1024 + (16 * (cg & 3) + (row ^ (4 * (cg & 3)))) * 16;
+            const f32x4 sum = *reinterpret_cast<const f32x4*>(at) + *reinterpret_cast<const f32x4*>(at + 4 * PART);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * h + e] = mfma_epilogue<EPI>(sum[e]);
+        }
+        store_columns<OutT>(s, m0 + wm * 64 + blk / FN * 16 + row, n0 + wn * 64 + blk % FN * 16 + (lane & 7) * EPV, v);
+    }
+}
+
 template <int BM, int BN, int NW, bool DIRECT, bool A_KC, bool B_KC, int EPI, typename OutT>
 constexpr auto pick_kernel() {   // NW = 0: gemm_reg_kernel
     if constexpr (NW == 0) return gemm_reg_kernel<BM, BN, A_KC, B_KC, EPI, OutT>;
@@ -427,7 +566,25 @@ int32_t launch_out(const GemmPlan& plan, int max_m, int max_n, int order, hipStr
     return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_NONE, uint16_t>(plan, max_m, max_n, order, st);
 }
 
+template <int EPI, typename OutT>
+int32_t launch_deep_layout(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t st) {
+    const int tm = (max_m + 127) / 128, tn = (max_n + 127) / 128;
+    const int64_t nblk = ((int64_t)tm * tn * plan.groups + 7) / 8 * 8;
+    if (nblk > 0x7FFFFFFF) return SBP_ERR_UNSUPPORTED;
+    void (*kern)(GemmPlan, int, int, int);
+    if (plan.a_kc) kern = plan.b_kc ? gemm_deep_kernel<true, true, EPI, OutT> : gemm_deep_kernel<true, false, EPI, OutT>;
+    else kern = plan.b_kc ? gemm_deep_kernel<false, true, EPI, OutT> : gemm_deep_kernel<false, false, EPI, OutT>;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)nblk), dim3(512), 0, st, plan, tm, tn, order);
+    return launch_status(__func__);
+}
+
 }  // namespace
+
+int32_t launch_gemm_deep(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t stream) {
+    if (plan.out_dtype == SBP_F32) return plan.epilogue == SBP_EPI_NONE ? launch_deep_layout<SBP_EPI_NONE, float>(plan, max_m, max_n, order, stream) : SBP_ERR_UNSUPPORTED;
+    if (plan.epilogue == SBP_EPI_GELU) return launch_deep_layout<SBP_EPI_GELU, uint16_t>(plan, max_m, max_n, order, stream);
+    return launch_deep_layout<SBP_EPI_NONE, uint16_t>(plan, max_m, max_n, order, stream);
+}
 
 int32_t launch_gemm_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool direct, int order, hipStream_t stream) {
     switch (tile) {

@@ -53,7 +53,13 @@ __device__ inline int kswz(int row) {
 // {4-7, 8-11, 16-19, 28-31}, then the same plus 32: a pass mixes rows 0-3 and 12-15 of one chunk column
 // with rows 4-11 of its neighbour.  With q = row / 4, XOR values (0, 3, 2, 1)[q] keep the four rows of
 // equal row % 4 in such a pass on four different chunks (and do so for 16 consecutive lanes as well).
-__device__ inline int kswz16(int row) { return (0 - (row >> 2)) & 3; }
+// BKT = 64 (128-byte rows, two on all banks): XOR with row / 2 puts the eight rows of equal parity of such a pass, and of 16
+// consecutive lanes, on eight different chunks.
+template <int BKT>
+__device__ inline int kswz16(int row) {
+    if constexpr (BKT == 64) return (row >> 1) & 7;
+    else return (0 - (row >> 2)) & 3;
+}
 // LDS image of a not-KC tile: [BKT][R] with the 16-byte chunks of kk-row q permuted by XOR with
 // nswz(q).  A ds_read_b64_tr_b16 serves 32 lanes per pass: 4 consecutive kk-rows x 64 contiguous
 // bytes.  Row pitch is a multiple of 256 B, so without the permutation the 4 rows share banks;
@@ -77,7 +83,7 @@ struct Tile {
     static constexpr int CPR = R / 8;        // 16-byte chunks per kk-row of a not-KC tile
     static constexpr int CPK = BKT / 8;      // 16-byte chunks per row of a KC tile
     static constexpr int ROWB = BKT * 2;     // bytes per row of a KC tile
-    __device__ static int ksw(int row) { return F16 ? kswz16(row) : kswz<BKT>(row); }
+    __device__ static int ksw(int row) { return F16 ? kswz16<BKT>(row) : kswz<BKT>(row); }
     static_assert(CHUNKS % NT == 0, "tile must divide over the workgroup");
     static_assert(KC || CPR >= 16 || (CPR == 8 && F16), "not-KC swizzles: 8 chunks per row, or at least 16");
 
@@ -204,19 +210,20 @@ struct Tile {
 
     // ---- operands of v_mfma_f32_16x16x32_bf16 (BKT = 32: one instruction spans the whole stage) ----
     // Lane l holds the 8 values kk = 8 (l / 16) + 0..7 of row (block base + l % 16).
-    // One lane offset serves every block.  KC: a 16-row block adds 16 * ROWB (kswz16 repeats every 16 rows).
+    // One lane offset serves every block.  KC: a 16-row block adds 16 * ROWB (the swizzle repeats every 16 rows).
     // Not KC: block b adds 2 b to the chunk index; the wave's base chunk is a multiple of 16 and b < 8, so
     // that sum is an OR, and the swizzle being an XOR, block b's offset is block 0's with (b << 5) flipped.
-    __device__ static int lane_offset16(int wave_base, int lane) {
-        static_assert(BKT == 32, "one 16x16x32 instruction per 32-deep stage");
+    // BKT = 64: `half` says which 32 of the stage (32 kk-rows on: the not-KC swizzle repeats).
+    __device__ static int lane_offset16(int wave_base, int lane, int half = 0) {
+        static_assert(BKT == 32 || BKT == 64, "one 16x16x32 instruction per 32-deep stage");
         int off;
         static_assert(F16, "frag16 reads tiles laid out for it");
         if constexpr (KC) {
             const int row = wave_base + (lane & 15);
-            off = row * ROWB + (((lane >> 4) ^ kswz16(row)) << 4);
+            off = row * ROWB + (((4 * half + (lane >> 4)) ^ ksw(row)) << 4);
         } else {              // the second read adds 4 kk-rows
             const int s = lane & 15, g = lane >> 4;
-            const int krow = 8 * g + (s >> 2);
+            const int krow = 32 * half + 8 * g + (s >> 2);
             const int chunk = (wave_base >> 3) + ((s & 3) >> 1);
             off = krow * (R * 2) + ((chunk ^ nswz<R>(krow)) << 4) + (s & 1) * 8;
         }

@@ -1623,6 +1623,25 @@ int32_t launch_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool di
     return launch_gemm_any(plan, max_m, max_n, tile, direct, tile_order_for((max_m + bm - 1) / bm, (max_n + bn - 1) / bn), stream);
 }
 
+// 128 x 128 tiles with one workgroup of eight waves per compute unit (gemm_deep_kernel): where the tiles of that size fill at
+// most one round, or two if both operands are reduction-contiguous, and enough of them are not padding.  us, this / 128 x 128
+// with four waves / the choice without it (rows x reduction x columns, devices): 1024 x 125000 x 512, 8 (256 tiles), A and B
+// reduction-contiguous 1885 / 2428 / 2428, A alone 1451 / 2026 / 2033, neither 1264 / 1303 / 1326; 1024 x 4096 x 512, 8: 34-36 /
+// 39-45 / 39-44; 777 x 1000 x 1000, 3 (147): 13.3-14.2 / 15.1-16.4 / 15.1-16.6; 1024 x 512 x 512, 8: 10.6 / 10.0 / 10.6; 512
+// tiles of length 2048, A and B 39.6 / 44.0 / 44.7 (128 large tiles), A alone 40.1 / 39.4 / 38.9.  Below half a round only
+// against the waves' splitting of short reductions: 108 tiles of 1000 12.2 / 13.8 / 15.0, 96 of 600 9.3-9.8 / 10.9-11.8 /
+// 11.2-12.1; but 72 of 2000 15.7-17.9 / 19-24 / 15.6-16.4, 128 of 40000 344-358 / 383-471 / 245-329.
+bool deep_pays(const GemmPlan& plan, int max_m, int max_n) {
+    const int64_t cu = compute_units(), tiles = tiles_of(plan, max_m, max_n, 128, 128);
+    const int k = longest_reduction(plan);
+    if (max_m <= 64 || max_n <= 64 || k < 576) return false;
+    if (2 * tiles <= cu) return 8 * tiles >= 3 * cu && k <= 1536;
+    return tiles <= (plan.a_kc && plan.b_kc ? 2 : 1) * cu;
+}
+int32_t launch_deep(const GemmPlan& plan, int max_m, int max_n, hipStream_t stream) {
+    return launch_gemm_deep(plan, max_m, max_n, tile_order_for((max_m + 127) / 128, (max_n + 127) / 128), stream);
+}
+
 }  // namespace
 
 void set_tile_order(int32_t order) { g_tile_order.store(order, std::memory_order_relaxed); }
@@ -1687,6 +1706,7 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
     }
     const bool direct = rows_aligned(plan);
     if (variant >= 40 && variant <= 44) return launch_any(plan, max_m, max_n, variant - 40, direct, stream);
+    if (variant == 48) return direct ? launch_deep(plan, max_m, max_n, stream) : SBP_ERR_UNSUPPORTED;
     if (!direct) {
         if (variant > 1) return SBP_ERR_UNSUPPORTED;
         return launch_any(plan, max_m, max_n, any_tile(plan, max_m, max_n), false, stream);
@@ -1713,7 +1733,9 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
     if (variant == 0) {
         // Default: the 256 x 256 tile over 8 waves with four 32-deep LDS stages, as one persistent workgroup per compute
         // unit when the reduction length allows it, on the 16x16x32 matrix instruction; 128 x 128 tiles where those
-        // finish sooner; waves splitting the reduction where neither fills the chip.
+        // finish sooner, with eight waves where one such tile per compute unit is all there is; waves splitting the
+        // reduction where no tile of these sizes fills the chip.
+        if (deep_pays(plan, max_m, max_n)) return launch_deep(plan, max_m, max_n, stream);
         if (wavek_pays(plan, max_m, max_n)) return launch_any(plan, max_m, max_n, wavek_tile(plan, max_m, max_n), true, stream);
         variant = !large_tiles_pay(plan, max_m, max_n) ? 8 : !k128 ? 9 : pingpong_pays(plan, max_m, max_n) ? 21 : 16;
     }

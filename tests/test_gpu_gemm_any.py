@@ -76,6 +76,25 @@ def test_bf16_any_shape_and_pitch(M, kk, N, tx, tw, aligned, variant):
         assert_matmul_close(got[i], ref[i], 1e-5, f"{M}x{kk}x{N} trans=({tx},{tw}) v{variant} shard {i}")
 
 
+@pytest.mark.parametrize("out", ["f32", "bf16", "gelu"])
+@pytest.mark.parametrize("tx,tw", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("M,kk,N", [(1, 8, 1), (128, 64, 128), (130, 63, 129), (200, 128, 300), (129, 200, 136), (260, 1000, 140), (64, 449, 200)])
+def test_bf16_two_wave_groups_over_the_reduction(M, kk, N, tx, tw, out):
+    """variant 48: no whole 64-deep stage, one, two, fewer and more than the pipeline holds, with and without a remainder;
+    one tile and ragged further ones"""
+    k = 2
+    if out == "f32":
+        X, W, sx, sw, K, C = bf16(3, (M, k * kk)), bf16(4, (k * kk, N), 0.5), orc.S1, orc.S0, k * kk, N
+    else:
+        X, W, sx, sw, K, C = bf16(3, (M, kk)), bf16(4, (kk, k * N), 0.1), orc.B, orc.S1, kk, k * N
+    Xs, Ws = orc.scatter(X, sx, k), orc.scatter(W, sw, k)
+    ref, _ = orc.matmul_sbp([values(x) for x in Xs], sx, [values(w) for w in Ws], sw)
+    epi = sbp.EPI_GELU if out == "gelu" else sbp.EPI_NONE
+    got, _ = run(Xs, sx, Ws, sw, M, K, C, k, tx, tw, pitch(Xs, tx, 8), pitch(Ws, tw, 8), pitch(ref, 0, 2, 1), variant=48, epilogue=epi)
+    for i in range(k):
+        assert_matmul_close(got[i], orc.gelu(ref[i]) if out == "gelu" else ref[i], 1e-5 if out == "f32" else 2.0 ** -7, f"{M}x{kk}x{N} trans=({tx},{tw}) {out} shard {i}")
+
+
 @pytest.mark.parametrize("epilogue", [sbp.EPI_NONE, sbp.EPI_GELU])
 @pytest.mark.parametrize("M,K,N", [(5, 33, 7), (70, 100, 203)])
 def test_bf16_odd_rows_rounded_results(M, K, N, epilogue):
