@@ -25,6 +25,7 @@
 // vector (up to 16 B per lane) that all offsets and pitches of the conversion allow.
 #include <atomic>
 #include <cstdlib>
+#include <type_traits>
 
 #include "sbp_internal.h"
 
@@ -182,10 +183,13 @@ __global__ __launch_bounds__(BOX_THREADS) void box_reduce_kernel(BoxParams p) {
                     if constexpr (OP == BOX_SUM) a = V(0.0f);
                     else a = V(-__builtin_inff());
                     if (ns > 0) a = __builtin_nontemporal_load(static_cast<const V*>(p.src[sb + T.s0]) + spos);
-                    for (int i = 1; i < ns; ++i) {
-                        const V b = __builtin_nontemporal_load(static_cast<const V*>(p.src[sb + T.s0 + i * T.sstep]) + spos);
-                        a = combine<OP>(a, b);
+                    auto load = [&](int i) { return __builtin_nontemporal_load(static_cast<const V*>(p.src[sb + T.s0 + i * T.sstep]) + spos); };
+                    int i = 1;
+                    for (; i + 2 < ns; i += 3) {   // three loads in flight
+                        const V b0 = load(i), b1 = load(i + 1), b2 = load(i + 2);
+                        a = combine<OP>(combine<OP>(combine<OP>(a, b0), b1), b2);
                     }
+                    for (; i < ns; ++i) a = combine<OP>(a, load(i));
                 }
                 acc[u] = a;
             }
@@ -278,6 +282,91 @@ __global__ __launch_bounds__(BOX_THREADS) void box_copy_kernel(BoxParams p) {
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// Rectangles whose offsets, pitches or widths are no multiple of 16 bytes.  Every row is cut into 16-byte vectors all the
+// same, read and written unaligned, and its last one goes element by element where the row does not fill it.  An unaligned
+// wave access touches one 128-byte line more than an aligned one; one element per lane, which is what the widest vector that
+// divides every offset comes to on odd sizes, needs 4 to 8 times the instructions and left the kernels bound by them.
+// Stores are cached: neighbouring waves complete each other's lines in L2.
+// us before / now, 20000 x 4095, 3 devices: bf16 S(0) -> S(1) 192 / 92, S(0) -> B 268 / 135, fp32 P -> S(0) 364 / 234, cast S(0) -> B
+// 593 / 170, cast P -> S(0) 441 / 166 (4.9 TB/s; the aligned kernels reach 5.6-5.9); 3001 x 1001, 8 devices: P -> B 40 / 32.
+// ------------------------------------------------------------------------------------------------
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+
+template <typename E, int UNROLL>
+__global__ __launch_bounds__(BOX_THREADS) void box_copy_any_kernel(BoxParams p) {
+    constexpr uint32_t EPV = 16 / sizeof(E);
+    const Task T = make_task(p, blockIdx.y);
+    const uint32_t cols_v = (uint32_t)((T.cols + EPV - 1) / EPV), total = (uint32_t)T.rows * cols_v;
+    const E* __restrict__ src = static_cast<const E*>(p.src[T.s0]) + T.src_off;
+    const uint32_t stride = gridDim.x * BOX_THREADS;
+    for (uint32_t base = blockIdx.x * BOX_THREADS + threadIdx.x; base < total; base += stride * UNROLL) {
+        u32x4 val[UNROLL];
+        const E* from[UNROLL];
+        int64_t dpos[UNROLL];
+        uint32_t n[UNROLL];   // elements of the vector that exist
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            const uint32_t idx = base + u * stride;
+            n[u] = 0;
+            if (idx < total) {
+                const uint32_t r = T.rows == 1 ? 0 : idx / cols_v;
+                const int64_t c = (int64_t)(idx - r * cols_v) * EPV;
+                n[u] = T.cols - c < EPV ? (uint32_t)(T.cols - c) : EPV;
+                from[u] = src + (int64_t)r * T.src_ld + c;
+                dpos[u] = T.dst_off + (int64_t)r * T.dst_ld + c;
+                if (n[u] == EPV) val[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(from[u]));
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            for (int j = 0; n[u] && j < T.nd; ++j) {
+                E* dst = static_cast<E*>(p.dst[T.d0 + j]) + dpos[u];
+                if (n[u] == EPV) *reinterpret_cast<u32x4_any*>(dst) = val[u];
+                else
+                    for (uint32_t e = 0; e < n[u]; ++e) dst[e] = from[u][e];
+            }
+        }
+    }
+}
+
+// Reductions of KS sources (0: p.ki of them), shard order, as box_reduce_kernel.
+template <int OP, int KS>
+__global__ __launch_bounds__(BOX_THREADS) void box_reduce_any_kernel(BoxParams p) {
+    const Task T = make_task(p, blockIdx.y);
+    const int32_t ns = KS > 0 ? KS : p.ki;
+    const int32_t sb = (int32_t)blockIdx.z * p.ki, db = (int32_t)blockIdx.z * p.ko;
+    const uint32_t cols_v = (uint32_t)((T.cols + 3) / 4), total = (uint32_t)T.rows * cols_v;
+    const uint32_t stride = gridDim.x * BOX_THREADS;
+    for (uint32_t idx = blockIdx.x * BOX_THREADS + threadIdx.x; idx < total; idx += stride) {
+        const uint32_t r = T.rows == 1 ? 0 : idx / cols_v;
+        const int64_t c = (int64_t)(idx - r * cols_v) * 4;
+        const int64_t spos = T.src_off + (int64_t)r * T.src_ld + c, dpos = T.dst_off + (int64_t)r * T.dst_ld + c;
+        auto source = [&](int i) { return static_cast<const float*>(p.src[sb + i]) + spos; };
+        if (T.cols - c >= 4) {
+            auto load = [&](int i) { return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(source(i))); };
+            f32x4 a = load(0);
+            if constexpr (KS > 0) {
+                f32x4 part[KS];
+#pragma unroll
+                for (int i = 1; i < KS; ++i) part[i] = load(i);
+#pragma unroll
+                for (int i = 1; i < KS; ++i) a = combine<OP>(a, part[i]);
+            } else {
+                for (int i = 1; i < ns; ++i) a = combine<OP>(a, (f32x4)load(i));
+            }
+            for (int j = 0; j < T.nd; ++j) *reinterpret_cast<f32x4_any*>(static_cast<float*>(p.dst[db + T.d0 + j]) + dpos) = a;
+        } else {
+            for (int e = 0; e < (int)(T.cols - c); ++e) {
+                float a = source(0)[e];
+                for (int i = 1; i < ns; ++i) a = combine<OP>(a, source(i)[e]);
+                for (int j = 0; j < T.nd; ++j) static_cast<float*>(p.dst[db + T.d0 + j])[dpos + e] = a;
+            }
+        }
+    }
+}
+
 // S(a) -> B (all-gather) at scale.  Writing every vector to all k destinations at once keeps k write
 // streams open across the chip, and HBM takes that badly (measured on 16 x 1 GiB: 5.1 TB/s, against
 // 6.9 TB/s for one stream).  So the logical tensor is cut into chunks of `pieces` x 4 KB and each chunk
@@ -365,8 +454,8 @@ __global__ __launch_bounds__(BOX_THREADS) void box_gather_bcast_kernel(BoxParams
 // ------------------------------------------------------------------------------------------------
 // Cast fused into boxing (Sec. 6.4: sharded optimizer state with mixed precision).
 // Forward, fp32 S(a) -> bf16 B: the walk of box_gather_bcast_kernel (chunked passes, one destination at
-// a time, re-reads from L2) with VE elements per lane: 32 bytes in, one hardware conversion per pair
-// (round to nearest even), 16 bytes out.  VE = 1 is the fallback for shapes without 8-element alignment.
+// a time, re-reads from L2) with 8 elements per lane: 32 bytes in, one hardware conversion per pair
+// (round to nearest even), 16 bytes out.
 // ------------------------------------------------------------------------------------------------
 __device__ inline uint32_t cvt2_bf16(float lo, float hi) {
     typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -374,12 +463,12 @@ __device__ inline uint32_t cvt2_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
-template <int VE>
 __global__ __launch_bounds__(BOX_THREADS) void box_cast_gather_kernel(BoxParams p, uint32_t log2_pieces, uint32_t total,
                                                                        uint32_t q, uint32_t rem) {
     __shared__ const float* sp[SBP_MAX_K];
     if ((int)threadIdx.x < p.ki) sp[threadIdx.x] = static_cast<const float*>(p.src[threadIdx.x]);
     __syncthreads();
+    constexpr int VE = 8;
     const uint32_t k = (uint32_t)p.ko;
     const uint32_t piece = blockIdx.x & ((1u << log2_pieces) - 1);
     const uint32_t cj = blockIdx.x >> log2_pieces;
@@ -404,36 +493,59 @@ __global__ __launch_bounds__(BOX_THREADS) void box_cast_gather_kernel(BoxParams 
     }
     const int64_t spos = by_rows ? ((int64_t)(r - begin) * p.cols + (int64_t)c * VE) : ((int64_t)r * len + (x - begin));   // elements
     const float* src = sp[i] + spos;
-    if constexpr (VE == 8) {
-        const f32x4 a = *reinterpret_cast<const f32x4*>(src), b = *reinterpret_cast<const f32x4*>(src + 4);
-        const u32x4 o = {cvt2_bf16(a[0], a[1]), cvt2_bf16(a[2], a[3]), cvt2_bf16(b[0], b[1]), cvt2_bf16(b[2], b[3])};
-        __builtin_nontemporal_store(o, static_cast<u32x4*>(p.dst[j]) + idx);
-    } else {
-        static_cast<uint16_t*>(p.dst[j])[idx] = (uint16_t)(cvt2_bf16(*src, 0.0f) & 0xFFFFu);
+    const f32x4 a = *reinterpret_cast<const f32x4*>(src), b = *reinterpret_cast<const f32x4*>(src + 4);
+    const u32x4 o = {cvt2_bf16(a[0], a[1]), cvt2_bf16(a[2], a[3]), cvt2_bf16(b[0], b[1]), cvt2_bf16(b[2], b[3])};
+    __builtin_nontemporal_store(o, static_cast<u32x4*>(p.dst[j]) + idx);
+}
+
+// The same where rows or shard boundaries are no multiple of 8 elements: tasks and vectors as in box_copy_any_kernel.
+__global__ __launch_bounds__(BOX_THREADS) void box_cast_gather_any_kernel(BoxParams p) {
+    const Task T = make_task(p, blockIdx.y);
+    const uint32_t cols_v = (uint32_t)((T.cols + 7) / 8), total = (uint32_t)T.rows * cols_v;
+    const float* __restrict__ src = static_cast<const float*>(p.src[T.s0]) + T.src_off;
+    const uint32_t stride = gridDim.x * BOX_THREADS;
+    for (uint32_t idx = blockIdx.x * BOX_THREADS + threadIdx.x; idx < total; idx += stride) {
+        const uint32_t r = T.rows == 1 ? 0 : idx / cols_v;
+        const int64_t c = (int64_t)(idx - r * cols_v) * 8;
+        const float* from = src + (int64_t)r * T.src_ld + c;
+        const int64_t dpos = T.dst_off + (int64_t)r * T.dst_ld + c;
+        if (T.cols - c >= 8) {
+            const f32x4 a = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(from)), b = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(from + 4));
+            const u32x4 o = {cvt2_bf16(a[0], a[1]), cvt2_bf16(a[2], a[3]), cvt2_bf16(b[0], b[1]), cvt2_bf16(b[2], b[3])};
+            for (int j = 0; j < T.nd; ++j) *reinterpret_cast<u32x4_any*>(static_cast<uint16_t*>(p.dst[T.d0 + j]) + dpos) = o;
+        } else {
+            for (int e = 0; e < (int)(T.cols - c); ++e) {
+                const uint16_t o = (uint16_t)(cvt2_bf16(from[e], 0.0f) & 0xFFFFu);
+                for (int j = 0; j < T.nd; ++j) static_cast<uint16_t*>(p.dst[T.d0 + j])[dpos + e] = o;
+            }
+        }
     }
 }
 
 // Backward, bf16 P(sum) -> fp32 S(a): out_j = sum over the k partials of slice j, widened to fp32 and
 // added in shard order.  Tasks as for P -> S (one per destination).
-template <int VE, int KS>
+// ALIGNED: every vector starts 16-byte aligned and fills its row; otherwise as in box_copy_any_kernel.
+template <bool ALIGNED, int KS>
 __global__ __launch_bounds__(BOX_THREADS) void box_cast_reduce_kernel(BoxParams p) {
+    using VI = std::conditional_t<ALIGNED, u32x4, u32x4_any>;
+    using VO = std::conditional_t<ALIGNED, f32x4, f32x4_any>;
     const Task T = make_task(p, blockIdx.y);
     const int32_t ns = KS > 0 ? KS : T.ns;
-    const uint32_t cols_v = (uint32_t)(T.cols / VE);
+    const uint32_t cols_v = (uint32_t)((T.cols + 7) / 8);
     const uint32_t total = (uint32_t)T.rows * cols_v;
     const uint32_t stride = gridDim.x * BOX_THREADS;
     float* __restrict__ dst = static_cast<float*>(p.dst[T.d0]);
     for (uint32_t idx = blockIdx.x * BOX_THREADS + threadIdx.x; idx < total; idx += stride) {
         const uint32_t r = T.rows == 1 ? 0 : idx / cols_v;
-        const uint32_t c = idx - r * cols_v;
-        const int64_t spos = T.src_off + (int64_t)r * T.src_ld + (int64_t)c * VE;
-        const int64_t dpos = T.dst_off + (int64_t)r * T.dst_ld + (int64_t)c * VE;
-        if constexpr (VE == 8) {
+        const int64_t c = (int64_t)(idx - r * cols_v) * 8;
+        const int64_t spos = T.src_off + (int64_t)r * T.src_ld + c;
+        const int64_t dpos = T.dst_off + (int64_t)r * T.dst_ld + c;
+        if (ALIGNED || T.cols - c >= 8) {
             float acc[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
-            auto add = [&](int i) {
-                const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(p.src[i]) + spos));
+            auto load = [&](int i) -> u32x4 { return __builtin_nontemporal_load(reinterpret_cast<const VI*>(static_cast<const uint16_t*>(p.src[i]) + spos)); };
+            auto add = [&](const u32x4 w) {
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
                     acc[2 * d] += __uint_as_float(w[d] << 16);
@@ -442,17 +554,24 @@ __global__ __launch_bounds__(BOX_THREADS) void box_cast_reduce_kernel(BoxParams 
             };
             if constexpr (KS > 0) {
 #pragma unroll
-                for (int i = 0; i < KS; ++i) add(i);
+                for (int i = 0; i < KS; ++i) add(load(i));
             } else {
-                for (int i = 0; i < ns; ++i) add(i);
+                for (int i = 0; i < ns; ++i) add(load(i));
             }
             const f32x4 o0 = {acc[0], acc[1], acc[2], acc[3]}, o1 = {acc[4], acc[5], acc[6], acc[7]};
-            __builtin_nontemporal_store(o0, reinterpret_cast<f32x4*>(dst + dpos));
-            __builtin_nontemporal_store(o1, reinterpret_cast<f32x4*>(dst + dpos + 4));
+            if constexpr (ALIGNED) {
+                __builtin_nontemporal_store(o0, reinterpret_cast<VO*>(dst + dpos));
+                __builtin_nontemporal_store(o1, reinterpret_cast<VO*>(dst + dpos + 4));
+            } else {
+                *reinterpret_cast<VO*>(dst + dpos) = o0;
+                *reinterpret_cast<VO*>(dst + dpos + 4) = o1;
+            }
         } else {
-            float acc = 0.0f;
-            for (int i = 0; i < ns; ++i) acc += __uint_as_float((uint32_t)static_cast<const uint16_t*>(p.src[i])[spos] << 16);
-            dst[dpos] = acc;
+            for (int e = 0; e < (int)(T.cols - c); ++e) {
+                float acc = 0.0f;
+                for (int i = 0; i < ns; ++i) acc += __uint_as_float((uint32_t)static_cast<const uint16_t*>(p.src[i])[spos + e] << 16);
+                dst[dpos + e] = acc;
+            }
         }
     }
 }
@@ -553,6 +672,7 @@ template <typename V, int OP, int UNROLL>
 void launch_reduce_k(const BoxParams& p, dim3 grid, hipStream_t st) {
     switch (p.mode == M_P2P ? 0 : p.ki) {   // P -> P walks a strided source list: run-time count
         case 2: hipLaunchKernelGGL((box_reduce_kernel<V, OP, 2, UNROLL>), grid, dim3(BOX_THREADS), 0, st, p); break;
+        case 3: hipLaunchKernelGGL((box_reduce_kernel<V, OP, 3, UNROLL>), grid, dim3(BOX_THREADS), 0, st, p); break;
         case 4: hipLaunchKernelGGL((box_reduce_kernel<V, OP, 4, UNROLL>), grid, dim3(BOX_THREADS), 0, st, p); break;
         case 8: hipLaunchKernelGGL((box_reduce_kernel<V, OP, 8, UNROLL>), grid, dim3(BOX_THREADS), 0, st, p); break;
         case 16: hipLaunchKernelGGL((box_reduce_kernel<V, OP, 16, UNROLL>), grid, dim3(BOX_THREADS), 0, st, p); break;
@@ -576,6 +696,28 @@ void launch_reduce(const BoxParams& p, dim3 grid, int unroll, hipStream_t st) {
         else launch_reduce_k<f32x4, OP, 1>(p, grid, st);
     } else if (p.vec_elems == 2) launch_reduce_k<f32x2, OP, 1>(p, grid, st);
     else launch_reduce_k<float, OP, 1>(p, grid, st);
+}
+
+template <int OP>
+void launch_reduce_any(const BoxParams& p, dim3 grid, hipStream_t st) {
+    switch (p.ki) {
+        case 2: hipLaunchKernelGGL((box_reduce_any_kernel<OP, 2>), grid, dim3(BOX_THREADS), 0, st, p); break;
+        case 3: hipLaunchKernelGGL((box_reduce_any_kernel<OP, 3>), grid, dim3(BOX_THREADS), 0, st, p); break;
+        case 4: hipLaunchKernelGGL((box_reduce_any_kernel<OP, 4>), grid, dim3(BOX_THREADS), 0, st, p); break;
+        case 8: hipLaunchKernelGGL((box_reduce_any_kernel<OP, 8>), grid, dim3(BOX_THREADS), 0, st, p); break;
+        default: hipLaunchKernelGGL((box_reduce_any_kernel<OP, 0>), grid, dim3(BOX_THREADS), 0, st, p); break;
+    }
+}
+
+template <bool ALIGNED>
+void launch_cast_reduce(const BoxParams& p, dim3 grid, hipStream_t st) {
+    switch (p.ki) {
+        case 2: hipLaunchKernelGGL((box_cast_reduce_kernel<ALIGNED, 2>), grid, dim3(BOX_THREADS), 0, st, p); break;
+        case 3: hipLaunchKernelGGL((box_cast_reduce_kernel<ALIGNED, 3>), grid, dim3(BOX_THREADS), 0, st, p); break;
+        case 4: hipLaunchKernelGGL((box_cast_reduce_kernel<ALIGNED, 4>), grid, dim3(BOX_THREADS), 0, st, p); break;
+        case 8: hipLaunchKernelGGL((box_cast_reduce_kernel<ALIGNED, 8>), grid, dim3(BOX_THREADS), 0, st, p); break;
+        default: hipLaunchKernelGGL((box_cast_reduce_kernel<ALIGNED, 0>), grid, dim3(BOX_THREADS), 0, st, p); break;
+    }
 }
 
 template <typename V>
@@ -688,7 +830,8 @@ int32_t launch_boxing(const BoxPlan& plan, hipStream_t stream) {
     // widest vector every task allows: all offsets, pitches and widths must be multiples of it
     int64_t g = 16 / plan.elem_bytes;  // elements in 16 bytes
     p.vec_elems = 1;                   // make_task does not depend on it
-    int64_t max_units = 0;
+    const int64_t epv = g;
+    int64_t max_units = 0, any_units = 0, widest = 0;
     for (int32_t t = 0; t < tasks; ++t) {
         const Task T = make_task(p, t);
         if (T.rows * T.cols == 0) continue;
@@ -700,6 +843,9 @@ int32_t launch_boxing(const BoxPlan& plan, hipStream_t stream) {
             g = gcd64(g, T.dst_ld);
         }
         max_units = T.rows * T.cols > max_units ? T.rows * T.cols : max_units;
+        const int64_t units = T.rows * ((T.cols + epv - 1) / epv);
+        any_units = units > any_units ? units : any_units;
+        widest = T.cols > widest ? T.cols : widest;
     }
     if (max_units == 0) return SBP_OK;  // nothing to move
     p.vec_elems = (int32_t)g;
@@ -708,6 +854,22 @@ int32_t launch_boxing(const BoxPlan& plan, hipStream_t stream) {
 
     const bool reduce = p_in && p.mode != M_IDENT;
     const int vbytes = p.vec_elems * plan.elem_bytes;
+    // No 16-byte vector divides everything: unaligned vectors, unless rows are so short that their ends are most of the work.  us,
+    // widest exact vector / unaligned, 65536 rows: 13 fp32 columns S(0) -> S(1) 29.9 / 13.4, 13 columns P -> S(1) 28.4 / 22.0; with
+    // 8-byte vectors 10 columns P -> S(1) 28.2 / 38.5.
+    if (vbytes < 16 && widest >= (vbytes == 8 ? 4 : 2) * epv && p.mode != M_P2P) {
+        constexpr int UNROLL = 2;
+        const int per_lane = reduce ? 1 : UNROLL;
+        int64_t bx = (any_units + (int64_t)BOX_THREADS * per_lane - 1) / ((int64_t)BOX_THREADS * per_lane);
+        const int64_t cap = ((reduce ? 65536 : 32768) + (int64_t)tasks * nb - 1) / ((int64_t)tasks * nb);
+        if (bx > cap) bx = cap;
+        const dim3 grid((uint32_t)bx, (uint32_t)tasks, (uint32_t)nb);
+        if (reduce && plan.sbp_in == SBP_P_SUM) launch_reduce_any<BOX_SUM>(p, grid, stream);
+        else if (reduce) launch_reduce_any<BOX_MAX>(p, grid, stream);
+        else if (plan.elem_bytes == 2) hipLaunchKernelGGL((box_copy_any_kernel<uint16_t, UNROLL>), grid, dim3(BOX_THREADS), 0, stream, p);
+        else hipLaunchKernelGGL((box_copy_any_kernel<uint32_t, UNROLL>), grid, dim3(BOX_THREADS), 0, stream, p);
+        return launch_status(__func__);
+    }
     const int64_t total_v = plan.rows * plan.cols / g;
     if (p.mode == M_S2B && ko > 1 && vbytes == 16 && plan.cols % g == 0 && total_v < ((int64_t)1 << 31) &&
         plan.rows < ((int64_t)1 << 31) && plan.cols < ((int64_t)1 << 31)) {
@@ -802,17 +964,27 @@ int32_t launch_boxing_cast(const BoxPlan& plan, hipStream_t stream) {
         if (blocks >= ((int64_t)1 << 31)) return SBP_ERR_UNSUPPORTED;
         const int64_t n = p.axis_in == 0 ? plan.rows : plan.cols;
         const uint32_t q = (uint32_t)(n / plan.k), rem = (uint32_t)(n % plan.k);
-        if (ve == 8)
-            hipLaunchKernelGGL(box_cast_gather_kernel<8>, dim3((uint32_t)blocks), dim3(BOX_THREADS), 0, stream, p, lp, (uint32_t)total, q, rem);
-        else
-            hipLaunchKernelGGL(box_cast_gather_kernel<1>, dim3((uint32_t)blocks), dim3(BOX_THREADS), 0, stream, p, lp, (uint32_t)total, q, rem);
+        if (ve == 8) {
+            hipLaunchKernelGGL(box_cast_gather_kernel, dim3((uint32_t)blocks), dim3(BOX_THREADS), 0, stream, p, lp, (uint32_t)total, q, rem);
+        } else {
+            p.mode = M_S2B;
+            int64_t units = 0;
+            for (int32_t t = 0; t < plan.k; ++t) {
+                const Task T = make_task(p, t);
+                units = T.rows * ((T.cols + 7) / 8) > units ? T.rows * ((T.cols + 7) / 8) : units;
+            }
+            int64_t bx = (units + BOX_THREADS - 1) / BOX_THREADS;
+            const int64_t cap = (32768 + plan.k - 1) / plan.k;
+            if (bx > cap) bx = cap;
+            hipLaunchKernelGGL(box_cast_gather_any_kernel, dim3((uint32_t)bx, (uint32_t)plan.k), dim3(BOX_THREADS), 0, stream, p);
+        }
         return launch_status(__func__);
     }
     if (plan.sbp_in == SBP_P_SUM && p.axis_out >= 0) {
         // backward: bf16 P(sum) -> fp32 S(a)
         p.mode = M_P2S;
         p.vec_elems = 1;
-        int64_t g = 8, max_units = 0;
+        int64_t g = 8, max_units = 0, elems = 0;
         for (int32_t t = 0; t < plan.k; ++t) {
             const Task T = make_task(p, t);
             if (T.rows * T.cols == 0) continue;
@@ -823,19 +995,19 @@ int32_t launch_boxing_cast(const BoxPlan& plan, hipStream_t stream) {
                 g = gcd64(g, T.src_ld);
                 g = gcd64(g, T.dst_ld);
             }
-            max_units = T.rows * T.cols > max_units ? T.rows * T.cols : max_units;
+            const int64_t units = T.rows * ((T.cols + 7) / 8);
+            max_units = units > max_units ? units : max_units;
+            elems = T.rows * T.cols > elems ? T.rows * T.cols : elems;
         }
         if (max_units == 0) return SBP_OK;
-        const int ve = g == 8 ? 8 : 1;
-        max_units /= ve;
-        if (max_units >= ((int64_t)1 << 31)) return SBP_ERR_UNSUPPORTED;
+        const bool aligned = g == 8;
+        if ((aligned ? max_units : elems) >= ((int64_t)1 << 31)) return SBP_ERR_UNSUPPORTED;
         int64_t bx = (max_units + BOX_THREADS - 1) / BOX_THREADS;
         const int64_t cap = (65536 + plan.k - 1) / plan.k;
         if (bx > cap) bx = cap;
         const dim3 grid((uint32_t)bx, (uint32_t)plan.k);
-        if (ve == 8 && plan.k == 8) hipLaunchKernelGGL((box_cast_reduce_kernel<8, 8>), grid, dim3(BOX_THREADS), 0, stream, p);
-        else if (ve == 8) hipLaunchKernelGGL((box_cast_reduce_kernel<8, 0>), grid, dim3(BOX_THREADS), 0, stream, p);
-        else hipLaunchKernelGGL((box_cast_reduce_kernel<1, 0>), grid, dim3(BOX_THREADS), 0, stream, p);
+        if (aligned) launch_cast_reduce<true>(p, grid, stream);
+        else launch_cast_reduce<false>(p, grid, stream);
         return launch_status(__func__);
     }
     return SBP_ERR_UNSUPPORTED;
