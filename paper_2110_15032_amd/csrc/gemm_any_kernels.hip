@@ -563,6 +563,7 @@ int32_t launch_out(const GemmPlan& plan, int max_m, int max_n, int order, hipStr
         return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_NONE, float>(plan, max_m, max_n, order, st);
     }
     if (plan.epilogue == SBP_EPI_GELU) return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_GELU, uint16_t>(plan, max_m, max_n, order, st);
+    if (plan.epilogue != SBP_EPI_NONE) return SBP_ERR_UNSUPPORTED;
     return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_NONE, uint16_t>(plan, max_m, max_n, order, st);
 }
 
@@ -583,6 +584,7 @@ int32_t launch_deep_layout(const GemmPlan& plan, int max_m, int max_n, int order
 int32_t launch_gemm_deep(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t stream) {
     if (plan.out_dtype == SBP_F32) return plan.epilogue == SBP_EPI_NONE ? launch_deep_layout<SBP_EPI_NONE, float>(plan, max_m, max_n, order, stream) : SBP_ERR_UNSUPPORTED;
     if (plan.epilogue == SBP_EPI_GELU) return launch_deep_layout<SBP_EPI_GELU, uint16_t>(plan, max_m, max_n, order, stream);
+    if (plan.epilogue != SBP_EPI_NONE) return SBP_ERR_UNSUPPORTED;
     return launch_deep_layout<SBP_EPI_NONE, uint16_t>(plan, max_m, max_n, order, stream);
 }
 

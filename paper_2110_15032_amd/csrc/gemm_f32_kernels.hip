@@ -258,6 +258,7 @@ int32_t launch_types(const GemmPlan& plan, int max_m, int max_n, int order, hipS
     if (plan.f32_operand == 1) return launch_layout<BM, BN, BK, WM, WN, WK, float, uint16_t, SBP_EPI_NONE>(plan, max_m, max_n, order, st);
     if (plan.f32_operand == 2) return launch_layout<BM, BN, BK, WM, WN, WK, uint16_t, float, SBP_EPI_NONE>(plan, max_m, max_n, order, st);
     if (plan.epilogue == SBP_EPI_GELU) return launch_layout<BM, BN, BK, WM, WN, WK, float, float, SBP_EPI_GELU>(plan, max_m, max_n, order, st);
+    if (plan.epilogue != SBP_EPI_NONE) return SBP_ERR_UNSUPPORTED;
     return launch_layout<BM, BN, BK, WM, WN, WK, float, float, SBP_EPI_NONE>(plan, max_m, max_n, order, st);
 }
 

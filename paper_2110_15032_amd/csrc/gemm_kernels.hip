@@ -1502,6 +1502,7 @@ int32_t launch_mfma_out(const GemmPlan& plan, int max_m, int max_n, hipStream_t 
         return launch_mfma_layout<BM, BN, WM, WN, ODD, SBP_EPI_NONE, float>(plan, max_m, max_n, st);
     }
     if (plan.epilogue == SBP_EPI_GELU) return launch_mfma_layout<BM, BN, WM, WN, ODD, SBP_EPI_GELU, uint16_t>(plan, max_m, max_n, st);
+    if (plan.epilogue != SBP_EPI_NONE) return SBP_ERR_UNSUPPORTED;
     return launch_mfma_layout<BM, BN, WM, WN, ODD, SBP_EPI_NONE, uint16_t>(plan, max_m, max_n, st);
 }
 
@@ -1705,12 +1706,6 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
         return launch_status(__func__);
     }
     const bool direct = rows_aligned(plan);
-    if (variant >= 40 && variant <= 44) return launch_any(plan, max_m, max_n, variant - 40, direct, stream);
-    if (variant == 48) return direct ? launch_deep(plan, max_m, max_n, stream) : SBP_ERR_UNSUPPORTED;
-    if (!direct) {
-        if (variant > 1) return SBP_ERR_UNSUPPORTED;
-        return launch_any(plan, max_m, max_n, any_tile(plan, max_m, max_n), false, stream);
-    }
     bool k64 = true, k128 = true;   // every local reduction a whole number of 64-element steps / of four-stage rounds
     for (int g = 0; g < plan.groups; ++g) {
         if (!plan.s[g].m || !plan.s[g].n) continue;
@@ -1718,7 +1713,7 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
         if (plan.s[g].kk == 0 || plan.s[g].kk % 128) k128 = false;
     }
     if (plan.epilogue == EPI_ROWMAX) {
-        // fused row maximum: persistent bf16 kernel only; anything else is done in two passes by the caller
+        // ahead of every other choice, forced or not: no other kernel below writes row maxima
         if (!(k128 && max_m > 128 && max_n > 128 && plan.out_dtype == SBP_BF16 && (variant == 0 || variant == 12 || variant == 16 || variant == 21))) return SBP_ERR_UNSUPPORTED;
         hipLaunchKernelGGL(fill_rowmax_kernel, dim3((uint32_t)((max_m + 255) / 256), (uint32_t)plan.groups), dim3(256), 0, stream, plan);
         const int32_t st = launch_status(__func__);
@@ -1729,6 +1724,12 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
             return launch_gemm_pingpong(plan, max_m, max_n, tile_order_for(tm, tn) & 0xFFFF, stream);
         }
         return launch_mfma_layout<256, 256, 2, 4, 204, EPI_ROWMAX, uint16_t>(plan, max_m, max_n, stream);
+    }
+    if (variant >= 40 && variant <= 44) return launch_any(plan, max_m, max_n, variant - 40, direct, stream);
+    if (variant == 48) return direct ? launch_deep(plan, max_m, max_n, stream) : SBP_ERR_UNSUPPORTED;
+    if (!direct) {
+        if (variant > 1) return SBP_ERR_UNSUPPORTED;
+        return launch_any(plan, max_m, max_n, any_tile(plan, max_m, max_n), false, stream);
     }
     if (variant == 0) {
         // Default: the 256 x 256 tile over 8 waves with four 32-deep LDS stages, as one persistent workgroup per compute

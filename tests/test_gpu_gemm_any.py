@@ -145,3 +145,32 @@ def test_f32_gelu(M, K, N):
     got, _ = run(Xs, orc.B, Ws, orc.S1, M, K, N, k, 0, 0, 0, 0, epilogue=sbp.EPI_GELU)
     for i in range(k):
         assert_matmul_close(got[i], orc.gelu(ref[i]), 1e-5, f"gelu shard {i}")
+
+
+@pytest.mark.parametrize("tx", [0, 1])
+@pytest.mark.parametrize("K", [256, 200])
+def test_row_maxima_under_every_forced_kernel(K, tx):
+    """sbp_matmul_rowmax under every knob value: a forced kernel that cannot write row maxima is followed by the row
+    reduction, one that cannot take the shape refuses.  The maxima are those of the stored values, exactly."""
+    k, M, N = 2, 264, 2 * 200
+    X, W = bf16(20, (M, K)), bf16(21, (K, N), 0.2)
+    Xs, Ws = orc.scatter(X, orc.B, k), orc.scatter(W, orc.S1, k)
+    ref, _ = orc.matmul_sbp([values(x) for x in Xs], orc.B, [values(w) for w in Ws], orc.S1)
+    dx, dw = DevTensor.from_host(Xs, M, K, orc.B, trans=tx), DevTensor.from_host(Ws, K, N, orc.S1)
+    ran = set()
+    for variant in range(64):
+        dy, dm = DevTensor.empty(M, N, np.uint16, orc.S1, k), DevTensor.empty(M, 1, np.float32, orc.P_MAX, k)
+        sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, variant)
+        try:
+            sbp.sbp_matmul_rowmax(dx.desc, sbp.B, dw.desc, sbp.S(1), dy.desc, sbp.AUTO, dm.desc, k)
+        except sbp.SbpError as e:
+            assert e.status == -9, f"variant {variant}: {e}"
+            continue
+        finally:
+            sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, 0)
+        sync()
+        ran.add(variant)
+        for i, (y, m) in enumerate(zip(dy.host(), dm.host())):
+            assert_matmul_close(values(y), ref[i], 2.0 ** -7, f"K={K} v{variant} shard {i}")
+            assert np.array_equal(m[:, 0].astype(np.float64), values(y).max(axis=1)), f"K={K} v{variant}: row maxima of shard {i}"
+    assert {0, 1, 8, 9, 41, 42, 43, 44, 48} <= ran
