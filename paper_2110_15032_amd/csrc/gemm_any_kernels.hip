@@ -376,7 +376,7 @@ __global__ __launch_bounds__(256, 2) void gemm_reg_kernel(GemmPlan p, int tm, in
             *reinterpret_cast<f32x4*>(win + decltype(bix)::value * 1024 + (16 * q + (r ^ (4 * q))) * 16) = acc[b / FN][b % FN];
         });
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
+#pragma unroll EPI == EPI_GELU_ERF ? 1 : 64   // erfcf is long
         for (int u = 0; u < NB / UNIT * (16 / ROWS); ++u) {
             const int blk = u / (16 / ROWS) * UNIT, row = u % (16 / ROWS) * ROWS + lane / LPR;
             float v[EPV];
@@ -516,7 +516,7 @@ __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int 
         *reinterpret_cast<f32x4*>(smem + wave * PART + b * 1024 + (16 * q + (r ^ (4 * q))) * 16) = acc[b / FN][b % FN];
     });
     __syncthreads();
-#pragma unroll
+#pragma unroll EPI == EPI_GELU_ERF ? 1 : 64
     for (int u = 0; u < FM * FN / UNIT; ++u) {   // this wave: eight of every 16 rows
         const int blk = u * UNIT, row = 8 * half + (lane >> 3);
         float v[EPV];
@@ -562,7 +562,9 @@ int32_t launch_out(const GemmPlan& plan, int max_m, int max_n, int order, hipStr
         if (plan.epilogue != SBP_EPI_NONE) return SBP_ERR_UNSUPPORTED;
         return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_NONE, float>(plan, max_m, max_n, order, st);
     }
-    if (plan.epilogue == SBP_EPI_GELU) return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_GELU, uint16_t>(plan, max_m, max_n, order, st);
+    if constexpr (DIRECT)
+        if (plan.epilogue == SBP_EPI_GELU) return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_GELU, uint16_t>(plan, max_m, max_n, order, st);
+    if (plan.epilogue == EPI_GELU_ERF) return launch_layout<BM, BN, NW, DIRECT, EPI_GELU_ERF, uint16_t>(plan, max_m, max_n, order, st);
     if (plan.epilogue != SBP_EPI_NONE) return SBP_ERR_UNSUPPORTED;
     return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_NONE, uint16_t>(plan, max_m, max_n, order, st);
 }
@@ -584,6 +586,7 @@ int32_t launch_deep_layout(const GemmPlan& plan, int max_m, int max_n, int order
 int32_t launch_gemm_deep(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t stream) {
     if (plan.out_dtype == SBP_F32) return plan.epilogue == SBP_EPI_NONE ? launch_deep_layout<SBP_EPI_NONE, float>(plan, max_m, max_n, order, stream) : SBP_ERR_UNSUPPORTED;
     if (plan.epilogue == SBP_EPI_GELU) return launch_deep_layout<SBP_EPI_GELU, uint16_t>(plan, max_m, max_n, order, stream);
+    if (plan.epilogue == EPI_GELU_ERF) return launch_deep_layout<EPI_GELU_ERF, uint16_t>(plan, max_m, max_n, order, stream);
     if (plan.epilogue != SBP_EPI_NONE) return SBP_ERR_UNSUPPORTED;
     return launch_deep_layout<SBP_EPI_NONE, uint16_t>(plan, max_m, max_n, order, stream);
 }

@@ -317,9 +317,13 @@ __device__ inline float gelu_fast(float x) {
     return fmaf(-fabsf(xc), e, max3f(x, 0.0f, 0.0f));
 }
 
+// 0.5 x (1 + erf(x / sqrt 2)) written with erfc so that the negative tail keeps its relative accuracy; NaN stays NaN
+__device__ inline float gelu_erf(float x) { return 0.5f * x * erfcf(x * -0.70710678118654752f); }
+
 template <int EPI>
 __device__ inline float mfma_epilogue(float v) {
     if constexpr (EPI == SBP_EPI_GELU) return gelu_fast(v);
+    else if constexpr (EPI == EPI_GELU_ERF) return gelu_erf(v);
     else return v;
 }
 

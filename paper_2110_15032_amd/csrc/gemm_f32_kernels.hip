@@ -29,9 +29,6 @@ typedef f32x4 __attribute__((aligned(4))) f32x4_any;
 typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 typedef u16x4 __attribute__((aligned(2))) u16x4_any;
 
-// 0.5 x (1 + erf(x / sqrt 2)) written with erfc so that the negative tail keeps its relative accuracy
-__device__ inline float gelu_erf32(float x) { return 0.5f * x * erfcf(x * -0.70710678118654752f); }
-
 template <typename T>
 __device__ inline f32x4 load4(const T* at) {
     if constexpr (sizeof(T) == 4) return *reinterpret_cast<const f32x4_any*>(at);
@@ -203,7 +200,7 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmPlan p,
     }
 
     auto finish = [](float v) {
-        if constexpr (EPI == SBP_EPI_GELU) return gelu_erf32(v);
+        if constexpr (EPI == SBP_EPI_GELU) return gelu_erf(v);
         else return v;
     };
     float* const C = static_cast<float*>(s.c);
