@@ -25,7 +25,6 @@
 // vector (up to 16 B per lane) that all offsets and pitches of the conversion allow.
 #include <atomic>
 #include <cstdlib>
-#include <type_traits>
 
 #include "sbp_internal.h"
 
@@ -291,8 +290,11 @@ __global__ __launch_bounds__(BOX_THREADS) void box_copy_kernel(BoxParams p) {
 // us before / now, 20000 x 4095, 3 devices: bf16 S(0) -> S(1) 192 / 92, S(0) -> B 268 / 135, fp32 P -> S(0) 364 / 234, cast S(0) -> B
 // 593 / 170, cast P -> S(0) 441 / 166 (4.9 TB/s; the aligned kernels reach 5.6-5.9); 3001 x 1001, 8 devices: P -> B 40 / 32.
 // ------------------------------------------------------------------------------------------------
+// Named directly wherever they are used: a template argument (std::conditional_t) drops the attribute, and with it the promise
+// of no alignment that the load and store instructions are chosen by.
 typedef f32x4 __attribute__((aligned(4))) f32x4_any;
 typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+static_assert(alignof(f32x4_any) == 4 && alignof(u32x4_any) == 2, "unaligned vectors");
 
 template <typename E, int UNROLL>
 __global__ __launch_bounds__(BOX_THREADS) void box_copy_any_kernel(BoxParams p) {
@@ -527,8 +529,6 @@ __global__ __launch_bounds__(BOX_THREADS) void box_cast_gather_any_kernel(BoxPar
 // ALIGNED: every vector starts 16-byte aligned and fills its row; otherwise as in box_copy_any_kernel.
 template <bool ALIGNED, int KS>
 __global__ __launch_bounds__(BOX_THREADS) void box_cast_reduce_kernel(BoxParams p) {
-    using VI = std::conditional_t<ALIGNED, u32x4, u32x4_any>;
-    using VO = std::conditional_t<ALIGNED, f32x4, f32x4_any>;
     const Task T = make_task(p, blockIdx.y);
     const int32_t ns = KS > 0 ? KS : T.ns;
     const uint32_t cols_v = (uint32_t)((T.cols + 7) / 8);
@@ -544,7 +544,11 @@ __global__ __launch_bounds__(BOX_THREADS) void box_cast_reduce_kernel(BoxParams 
             float acc[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
-            auto load = [&](int i) -> u32x4 { return __builtin_nontemporal_load(reinterpret_cast<const VI*>(static_cast<const uint16_t*>(p.src[i]) + spos)); };
+            auto load = [&](int i) -> u32x4 {
+                const uint16_t* at = static_cast<const uint16_t*>(p.src[i]) + spos;
+                if constexpr (ALIGNED) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(at));
+                else return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(at));
+            };
             auto add = [&](const u32x4 w) {
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
@@ -560,11 +564,11 @@ __global__ __launch_bounds__(BOX_THREADS) void box_cast_reduce_kernel(BoxParams 
             }
             const f32x4 o0 = {acc[0], acc[1], acc[2], acc[3]}, o1 = {acc[4], acc[5], acc[6], acc[7]};
             if constexpr (ALIGNED) {
-                __builtin_nontemporal_store(o0, reinterpret_cast<VO*>(dst + dpos));
-                __builtin_nontemporal_store(o1, reinterpret_cast<VO*>(dst + dpos + 4));
+                __builtin_nontemporal_store(o0, reinterpret_cast<f32x4*>(dst + dpos));
+                __builtin_nontemporal_store(o1, reinterpret_cast<f32x4*>(dst + dpos + 4));
             } else {
-                *reinterpret_cast<VO*>(dst + dpos) = o0;
-                *reinterpret_cast<VO*>(dst + dpos + 4) = o1;
+                *reinterpret_cast<f32x4_any*>(dst + dpos) = o0;
+                *reinterpret_cast<f32x4_any*>(dst + dpos + 4) = o1;
             }
         } else {
             for (int e = 0; e < (int)(T.cols - c); ++e) {

@@ -128,11 +128,31 @@ __device__ inline uint32_t pack_bf16(float lo, float hi) {
 // devices, 685 against 742 us; 512 x 40000 fp32 on 4, 30 against 35); broken groups, 200 x 30008 on 4: 10 us, 19 by elements.
 typedef u32x4 __attribute__((aligned(2))) u32x4_any;
 typedef f32x4 __attribute__((aligned(4))) f32x4_any;
+// streaming load and the store of 16 bytes; the unaligned types are named here, since a template argument drops the attribute
+template <bool ALIGNED>
+__device__ inline u32x4 load16(const uint16_t* at) {
+    if constexpr (ALIGNED) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(at));
+    else return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(at));
+}
+template <bool ALIGNED>
+__device__ inline f32x4 load16(const float* at) {
+    if constexpr (ALIGNED) return __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(at));
+    else return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(at));
+}
+template <bool ALIGNED>
+__device__ inline void store16(uint16_t* at, u32x4 v) {
+    if constexpr (ALIGNED) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(at));
+    else *reinterpret_cast<u32x4_any*>(at) = v;
+}
+template <bool ALIGNED>
+__device__ inline void store16(float* at, f32x4 v) {
+    if constexpr (ALIGNED) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(at));
+    else *reinterpret_cast<f32x4_any*>(at) = v;
+}
 template <bool BF16, bool ALIGNED, bool WHOLE>
 __global__ __launch_bounds__(RS_THREADS) void xent_grad_kernel(XentPlan p) {
     constexpr int VE = BF16 ? 8 : 4;
     using Elem = std::conditional_t<BF16, uint16_t, float>;
-    using Vec = std::conditional_t<BF16, std::conditional_t<ALIGNED, u32x4, u32x4_any>, std::conditional_t<ALIGNED, f32x4, f32x4_any>>;
     const int i = blockIdx.y;
     const uint32_t cols = (uint32_t)p.cols[i], cols_v = (cols + VE - 1) / VE;
     if (cols_v == 0) return;
@@ -162,8 +182,8 @@ __global__ __launch_bounds__(RS_THREADS) void xent_grad_kernel(XentPlan p) {
         if (WHOLE || c + VE <= cols) {
             // streaming load: the gradient pass is the last reader of the logits (measured 2 % faster than a cached load;
             // two items per lane and round, both loaded before either is worked on, 1 % slower than this)
-            const Vec w = __builtin_nontemporal_load(reinterpret_cast<const Vec*>(src));
-            Vec o;
+            const auto w = load16<ALIGNED>(src);
+            std::conditional_t<BF16, u32x4, f32x4> o;
             if constexpr (BF16) {
 #pragma unroll
                 for (int d = 0; d < 4; ++d) o[d] = pack_bf16(value(bf16_lo(w[d]), 2 * d), value(bf16_hi(w[d]), 2 * d + 1));
@@ -171,8 +191,7 @@ __global__ __launch_bounds__(RS_THREADS) void xent_grad_kernel(XentPlan p) {
 #pragma unroll
                 for (int e = 0; e < VE; ++e) o[e] = value(w[e], e);
             }
-            if constexpr (ALIGNED) __builtin_nontemporal_store(o, reinterpret_cast<Vec*>(dst));
-            else *reinterpret_cast<Vec*>(dst) = o;
+            store16<ALIGNED>(dst, o);
         } else {
 #pragma unroll
             for (int e = 0; e < VE - 1; ++e)
