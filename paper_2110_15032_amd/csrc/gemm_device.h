@@ -44,7 +44,7 @@ typedef __attribute__((address_space(1))) const char gbl_char;
 // Both measured conflict-free on gfx950 (SQ_LDS_BANK_CONFLICT = 0), whichever 16 lanes make a pass
 // (see kswz16 for the lane sets that the measurements point to).
 template <int BKT>
-__device__ inline int kswz(int row) {
+__host__ __device__ inline int kswz(int row) {
     if constexpr (BKT == 64) return (row ^ (row >> 3)) & 7;
     else return (row >> 2) & 3;
 }
@@ -56,7 +56,7 @@ __device__ inline int kswz(int row) {
 // BKT = 64 (128-byte rows, two on all banks): XOR with row / 2 puts the eight rows of equal parity of such a pass, and of 16
 // consecutive lanes, on eight different chunks.
 template <int BKT>
-__device__ inline int kswz16(int row) {
+__host__ __device__ inline int kswz16(int row) {
     if constexpr (BKT == 64) return (row >> 1) & 7;
     else return (0 - (row >> 2)) & 3;
 }
@@ -69,7 +69,7 @@ __device__ inline int kswz16(int row) {
 // R = 64 (128-byte rows, tiles of gemm_wavek_kernel): kk-rows of equal parity share banks; rows 0, 2, 8, 10 of a pass
 // of the 16x16x32 fragments move by 0, 32, 64, 96 bytes.
 template <int R = 128>
-__device__ inline int nswz(int krow) {
+__host__ __device__ inline int nswz(int krow) {
     if constexpr (R == 64) return (((krow >> 1) & 1) << 1) | (((krow >> 3) & 1) << 2);
     else return ((krow & 3) << 2) ^ (((krow >> 3) & 1) << 1);
 }
@@ -83,14 +83,14 @@ struct Tile {
     static constexpr int CPR = R / 8;        // 16-byte chunks per kk-row of a not-KC tile
     static constexpr int CPK = BKT / 8;      // 16-byte chunks per row of a KC tile
     static constexpr int ROWB = BKT * 2;     // bytes per row of a KC tile
-    __device__ static int ksw(int row) { return F16 ? kswz16<BKT>(row) : kswz<BKT>(row); }
+    __host__ __device__ static int ksw(int row) { return F16 ? kswz16<BKT>(row) : kswz<BKT>(row); }
     static_assert(CHUNKS % NT == 0, "tile must divide over the workgroup");
     static_assert(KC || CPR >= 16 || (CPR == 8 && F16), "not-KC swizzles: 8 chunks per row, or at least 16");
 
     // Byte offset (from the operand's base, at reduction offset 0) of the 16 bytes that belong in
     // LDS chunk position p.  first = first tile row (m or n), limit = extent of that index; rows or
     // columns past the limit are clamped to valid memory and never reach an output.
-    __device__ static uint32_t src_offset(int ld, int first, int limit, int p) {
+    __host__ __device__ static uint32_t src_offset(int ld, int first, int limit, int p) {
         if constexpr (KC) {
             const int row = p / CPK;
             int g = first + row;
@@ -101,6 +101,16 @@ struct Tile {
             int col = first + (((p % CPR) ^ nswz<R>(krow)) * 8);
             col = col < limit ? col : 0;
             return ((uint32_t)krow * (uint32_t)ld + (uint32_t)col) * 2u;
+        }
+    }
+    // An fp32 operand has 32 bytes per chunk, twice src_offset on.  How far behind the first 16 the second 16 are read: 0,
+    // the first ones again, where a row of a not-KC tile ends between them (the values belong to no result; read on, the
+    // reduction's last row would lead 16 bytes past the end of the buffer).  Rows are whole 16-byte pieces long.
+    __host__ __device__ static uint32_t second_half(int first, int limit, int p) {
+        if constexpr (KC) return 16u;
+        else {
+            const int col = first + (((p % CPR) ^ nswz<R>(p / CPR)) * 8);
+            return col < limit && col + 8 > limit ? 0u : 16u;
         }
     }
     // The 16 bytes of LDS chunk position p of a stage that starts at reduction index k0 and may reach past the end kk

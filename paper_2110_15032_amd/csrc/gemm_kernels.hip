@@ -1326,6 +1326,10 @@ __global__ __launch_bounds__(HW * 2, HW == 256 ? 4 : 2) void gemm_split_kernel(G
         offf[it] = (uint64_t)2 * TF::src_offset(ldf, F32_B ? n0 : m0, F32_B ? s.n : s.m, it * NT + tid);
 #pragma unroll
     for (int it = 0; it < TH::PER_THREAD; ++it) offh[it] = TH::src_offset(ldh, F32_B ? m0 : n0, F32_B ? s.m : s.n, it * NT + tid);
+    // One for all of a thread's chunks: they lie a multiple of 16 reduction rows apart, after which nswz repeats.  The wide tile,
+    // which has no register to spare for it (676 us become 733), is given whole chunks only (see launch_split).
+    static_assert(HW == 256 || NT / TF::CPR % 16 == 0, "chunks of a thread share their column");
+    const uint32_t second = HW == 256 ? 16u : TF::second_half(F32_B ? n0 : m0, F32_B ? s.n : s.m, tid);
     const uint64_t stepf = (uint64_t)2 * TF::step_bytes(ldf);
     const uint32_t steph = TH::step_bytes(ldh);
 
@@ -1342,9 +1346,8 @@ __global__ __launch_bounds__(HW * 2, HW == 256 ? 4 : 2) void gemm_split_kernel(G
     auto fetch = [&]() {   // global -> registers (fp32 operand), global -> LDS (bf16 operand)
 #pragma unroll
         for (int it = 0; it < TF::PER_THREAD; ++it) {
-            const f32x4* g = reinterpret_cast<const f32x4*>(F + offf[it]);
-            raw[it][0] = g[0];
-            raw[it][1] = g[1];
+            raw[it][0] = *reinterpret_cast<const f32x4*>(F + offf[it]);
+            raw[it][1] = *reinterpret_cast<const f32x4*>(F + offf[it] + second);
         }
     };
     auto stash = [&](char (*dst)[TF::BYTES]) {   // registers -> three term tiles
@@ -1446,13 +1449,23 @@ int32_t launch_split_cfg(const GemmPlan& plan, int max_m, int max_n, hipStream_t
     return launch_status(__func__);
 }
 
+// Rows of an fp32 operand stored along the reduction are whole 32-byte chunks (or it is stored the other way).
+bool whole_f32_chunks(const GemmPlan& plan) {
+    const bool fb = plan.f32_operand == 2;
+    if (fb ? plan.b_kc : plan.a_kc) return true;
+    for (int g = 0; g < plan.groups; ++g)
+        if (plan.s[g].m && plan.s[g].n && (fb ? plan.s[g].n : plan.s[g].m) % 8) return false;
+    return true;
+}
+
 // The wide tile when the bf16 operand's side has at least 256 rows or columns and the narrow tiling would
-// still leave every compute unit several workgroups; `variant` 31 / 32 force the narrow / the wide tile.
+// still leave every compute unit several workgroups; `variant` 31 / 32 force the narrow / the wide tile.  The narrow one
+// in any case where rows of the fp32 operand end inside a chunk.
 template <bool F32_B>
 int32_t launch_split(const GemmPlan& plan, int max_m, int max_n, int variant, hipStream_t st) {
     const int hside = F32_B ? max_m : max_n;
     const int64_t wide_tiles = (int64_t)((max_m + (F32_B ? 255 : 127)) / (F32_B ? 256 : 128)) * ((max_n + (F32_B ? 127 : 255)) / (F32_B ? 128 : 256)) * plan.groups;
-    const bool wide = variant == 32 || (variant != 31 && hside >= 256 && wide_tiles >= 2 * (int64_t)compute_units());
+    const bool wide = whole_f32_chunks(plan) && (variant == 32 || (variant != 31 && hside >= 256 && wide_tiles >= 2 * (int64_t)compute_units()));
     return wide ? launch_split_cfg<F32_B, 256>(plan, max_m, max_n, st) : launch_split_cfg<F32_B, 128>(plan, max_m, max_n, st);
 }
 

@@ -200,3 +200,25 @@ def test_gelu_keeps_fp32_accuracy_where_the_reduction_fits_no_step(K, to, extra,
         step = 2.0 ** (np.floor(np.log2(np.abs(ref))) - 7)
         bad = np.abs(got[i][ok] - ref) > 0.5 * step + 2.0 ** -18 * np.abs(ref)
         assert not bad.any(), f"K={K} v{variant} shard {i}: {bad.sum()} of {bad.size} further off than rounding explains"
+
+
+@pytest.mark.parametrize("variant", [0, 31, 32])
+@pytest.mark.parametrize("extra", [0, 4])
+@pytest.mark.parametrize("f32_side", ["x", "w"])
+@pytest.mark.parametrize("n,kk", [(12, 32), (268, 96), (300, 256)])
+def test_split_kernel_on_rows_that_end_inside_a_chunk(n, kk, f32_side, extra, variant):
+    """an fp32 P(sum) operand stored along the reduction, its rows 8 i + 4 floats long, dense and with 4 floats of padding
+    (NaN); the last chunk of a row is half of it.  Bar: summation order."""
+    k, other = 2, 264
+    if f32_side == "w":
+        X, sx, sw, M, N, tx, tw = bf16(30, (other, kk)), orc.B, orc.P_SUM, other, n, 0, 0
+        Xs, Ws = orc.scatter(X, sx, k), [f32(31 + i, (kk, n)) for i in range(k)]
+    else:
+        W, sx, sw, M, N, tx, tw = bf16(30, (kk, other), 0.5), orc.P_SUM, orc.B, n, other, 1, 0
+        Xs, Ws = [f32(31 + i, (n, kk)) for i in range(k)], orc.scatter(W, sw, k)
+    wide = lambda v: values(v) if v.dtype == np.uint16 else v
+    ref, _ = orc.matmul_sbp([wide(x) for x in Xs], sx, [wide(w) for w in Ws], sw)
+    ld = n + extra
+    got, _ = run(Xs, sx, Ws, sw, M, kk, N, k, tx, tw, ld if f32_side == "x" else 0, ld if f32_side == "w" else 0, variant=variant)
+    for i in range(k):
+        assert_matmul_close(got[i], ref[i], 1e-5, f"{f32_side} {n}x{kk}+{extra} v{variant} shard {i}")
