@@ -540,9 +540,9 @@ constexpr auto pick_kernel() {   // NW = 0: gemm_reg_kernel
 
 template <int BM, int BN, int NW, bool DIRECT, int EPI, typename OutT>
 int32_t launch_layout(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t st) {
-    const int tm = (max_m + BM - 1) / BM, tn = (max_n + BN - 1) / BN;
+    const int tm = tiles_along(max_m, BM), tn = tiles_along(max_n, BN);
     const int64_t nblk = ((int64_t)tm * tn * plan.groups + 7) / 8 * 8;
-    if (nblk > 0x7FFFFFFF) return SBP_ERR_UNSUPPORTED;
+    if (!grid_fits(nblk, NW > 0 ? NW * 64 : 256)) return SBP_ERR_UNSUPPORTED;
     void (*kern)(GemmPlan, int, int, int) = nullptr;
     if (plan.a_kc) {
         if (plan.b_kc) kern = pick_kernel<BM, BN, NW, DIRECT, true, true, EPI, OutT>();
@@ -571,9 +571,9 @@ int32_t launch_out(const GemmPlan& plan, int max_m, int max_n, int order, hipStr
 
 template <int EPI, typename OutT>
 int32_t launch_deep_layout(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t st) {
-    const int tm = (max_m + 127) / 128, tn = (max_n + 127) / 128;
+    const int tm = tiles_along(max_m, 128), tn = tiles_along(max_n, 128);
     const int64_t nblk = ((int64_t)tm * tn * plan.groups + 7) / 8 * 8;
-    if (nblk > 0x7FFFFFFF) return SBP_ERR_UNSUPPORTED;
+    if (!grid_fits(nblk, 512)) return SBP_ERR_UNSUPPORTED;
     void (*kern)(GemmPlan, int, int, int);
     if (plan.a_kc) kern = plan.b_kc ? gemm_deep_kernel<true, true, EPI, OutT> : gemm_deep_kernel<true, false, EPI, OutT>;
     else kern = plan.b_kc ? gemm_deep_kernel<false, true, EPI, OutT> : gemm_deep_kernel<false, false, EPI, OutT>;

@@ -240,9 +240,9 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmPlan p,
 
 template <int BM, int BN, int BK, int WM, int WN, int WK, typename TA, typename TB, int EPI>
 int32_t launch_layout(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t st) {
-    const int tm = (max_m + BM - 1) / BM, tn = (max_n + BN - 1) / BN;
+    const int tm = tiles_along(max_m, BM), tn = tiles_along(max_n, BN);
     const int64_t nblk = ((int64_t)tm * tn * plan.groups + 7) / 8 * 8;
-    if (nblk > 0x7FFFFFFF) return SBP_ERR_UNSUPPORTED;
+    if (!grid_fits(nblk, WM * WN * WK * 64)) return SBP_ERR_UNSUPPORTED;
     void (*kern)(GemmPlan, int, int, int);
     if (plan.a_kc) kern = plan.b_kc ? gemm_f32_kernel<BM, BN, BK, WM, WN, WK, TA, TB, true, true, EPI> : gemm_f32_kernel<BM, BN, BK, WM, WN, WK, TA, TB, true, false, EPI>;
     else kern = plan.b_kc ? gemm_f32_kernel<BM, BN, BK, WM, WN, WK, TA, TB, false, true, EPI> : gemm_f32_kernel<BM, BN, BK, WM, WN, WK, TA, TB, false, false, EPI>;

@@ -1437,9 +1437,9 @@ __global__ __launch_bounds__(HW * 2, HW == 256 ? 4 : 2) void gemm_split_kernel(G
 template <bool F32_B, int HW>
 int32_t launch_split_cfg(const GemmPlan& plan, int max_m, int max_n, hipStream_t st) {
     constexpr int BM = F32_B ? HW : 128, BN = F32_B ? 128 : HW;
-    const int tm = (max_m + BM - 1) / BM, tn = (max_n + BN - 1) / BN;
+    const int tm = tiles_along(max_m, BM), tn = tiles_along(max_n, BN);
     const int64_t nblk = ((int64_t)tm * tn * plan.groups + 7) / 8 * 8;
-    if (nblk > 0x7FFFFFFF) return SBP_ERR_UNSUPPORTED;
+    if (!grid_fits(nblk, HW * 2)) return SBP_ERR_UNSUPPORTED;
     void (*kern)(GemmPlan, int, int, int);
     if (plan.a_kc && plan.b_kc) kern = gemm_split_kernel<true, true, F32_B, HW>;
     else if (plan.a_kc) kern = gemm_split_kernel<true, false, F32_B, HW>;
@@ -1464,17 +1464,17 @@ bool whole_f32_chunks(const GemmPlan& plan) {
 template <bool F32_B>
 int32_t launch_split(const GemmPlan& plan, int max_m, int max_n, int variant, hipStream_t st) {
     const int hside = F32_B ? max_m : max_n;
-    const int64_t wide_tiles = (int64_t)((max_m + (F32_B ? 255 : 127)) / (F32_B ? 256 : 128)) * ((max_n + (F32_B ? 127 : 255)) / (F32_B ? 128 : 256)) * plan.groups;
+    const int64_t wide_tiles = (int64_t)tiles_along(max_m, F32_B ? 256 : 128) * tiles_along(max_n, F32_B ? 128 : 256) * plan.groups;
     const bool wide = whole_f32_chunks(plan) && (variant == 32 || (variant != 31 && hside >= 256 && wide_tiles >= 2 * (int64_t)compute_units()));
     return wide ? launch_split_cfg<F32_B, 256>(plan, max_m, max_n, st) : launch_split_cfg<F32_B, 128>(plan, max_m, max_n, st);
 }
 
 template <int BM, int BN, int WM, int WN, bool A_KC, bool B_KC, int ODD, int EPI, typename OutT>
 int32_t launch_mfma_cfg(const GemmPlan& plan, int max_m, int max_n, hipStream_t st) {
-    const int tm = (max_m + BM - 1) / BM, tn = (max_n + BN - 1) / BN;
+    const int tm = tiles_along(max_m, BM), tn = tiles_along(max_n, BN);
     const int64_t tiles = (int64_t)tm * tn * plan.groups;
     const int64_t nblk = (tiles + 7) / 8 * 8;
-    if (nblk > 0x7FFFFFFF) return SBP_ERR_UNSUPPORTED;
+    if (ODD >= 100 ? nblk > 0x7FFFFFFF : !grid_fits(nblk, WM * WN * 64)) return SBP_ERR_UNSUPPORTED;
     if constexpr (ODD >= 100) {   // persistent kernel, ODD - 100 stages
         int grid = compute_units() / 8 * 8;
         if (grid > nblk) grid = (int)nblk;
@@ -1526,6 +1526,21 @@ void launch_generic_epi(const GemmPlan& plan, dim3 grid, hipStream_t st) {
         hipLaunchKernelGGL((gemm_generic_kernel<A_BF16, B_BF16, OutT, SBP_EPI_NONE>), grid, dim3(16, 16), 0, st, plan);
 }
 
+int32_t launch_generic(const GemmPlan& plan, int max_m, int max_n, hipStream_t stream) {
+    const dim3 grid((uint32_t)tiles_along(max_n, 16), (uint32_t)tiles_along(max_m, 16), (uint32_t)plan.groups);
+    if (grid.y > 65535 || grid.z > 65535) return SBP_ERR_UNSUPPORTED;
+    if (plan.f32_operand == 2) launch_generic_epi<true, false, float>(plan, grid, stream);
+    else if (plan.f32_operand) launch_generic_epi<false, true, float>(plan, grid, stream);
+    else if (plan.in_dtype == SBP_BF16) {
+        if (plan.out_dtype == SBP_F32) launch_generic_epi<true, true, float>(plan, grid, stream);
+        else launch_generic_epi<true, true, uint16_t>(plan, grid, stream);
+    } else {
+        if (plan.out_dtype != SBP_F32) return SBP_ERR_DTYPE;
+        launch_generic_epi<false, false, float>(plan, grid, stream);
+    }
+    return launch_status(__func__);
+}
+
 // What the MFMA kernels take.  Their source offsets are 32-bit byte offsets from the shard base.
 bool mfma_ok(const GemmPlan& plan) {
     if (plan.in_dtype != SBP_BF16) return false;
@@ -1574,7 +1589,7 @@ bool split_ok(const GemmPlan& plan) {
 }
 
 int64_t tiles_of(const GemmPlan& plan, int max_m, int max_n, int bm, int bn) {
-    return (int64_t)((max_m + bm - 1) / bm) * ((max_n + bn - 1) / bn) * plan.groups;
+    return (int64_t)tiles_along(max_m, bm) * tiles_along(max_n, bn) * plan.groups;
 }
 int longest_reduction(const GemmPlan& plan) {
     int k = 0;
@@ -1637,11 +1652,11 @@ F32Tile f32_tile(const GemmPlan& plan, int max_m, int max_n) {
 int32_t launch_f32(const GemmPlan& plan, int max_m, int max_n, int32_t variant, hipStream_t stream) {
     const int tile = variant >= 45 ? variant - 45 : f32_tile(plan, max_m, max_n);
     const int b = tile == F32_128 ? 128 : tile == F32_64 ? 64 : 32;
-    return launch_gemm_f32(plan, max_m, max_n, tile, tile_order_for((max_m + b - 1) / b, (max_n + b - 1) / b), stream);
+    return launch_gemm_f32(plan, max_m, max_n, tile, tile_order_for(tiles_along(max_m, b), tiles_along(max_n, b)), stream);
 }
 int32_t launch_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool direct, hipStream_t stream) {
     const int bm = tile == WAVEK_32 ? 32 : tile == WAVEK_64 || tile == REG_64 ? 64 : 128, bn = tile == REG_128 ? 128 : 64;
-    return launch_gemm_any(plan, max_m, max_n, tile, direct, tile_order_for((max_m + bm - 1) / bm, (max_n + bn - 1) / bn), stream);
+    return launch_gemm_any(plan, max_m, max_n, tile, direct, tile_order_for(tiles_along(max_m, bm), tiles_along(max_n, bn)), stream);
 }
 
 // 128 x 128 tiles with one workgroup of eight waves per compute unit (gemm_deep_kernel): where the tiles of that size fill at
@@ -1660,32 +1675,11 @@ bool deep_pays(const GemmPlan& plan, int max_m, int max_n) {
     return tiles <= (plan.a_kc && plan.b_kc ? 2 : 1) * cu;
 }
 int32_t launch_deep(const GemmPlan& plan, int max_m, int max_n, hipStream_t stream) {
-    return launch_gemm_deep(plan, max_m, max_n, tile_order_for((max_m + 127) / 128, (max_n + 127) / 128), stream);
+    return launch_gemm_deep(plan, max_m, max_n, tile_order_for(tiles_along(max_m, 128), tiles_along(max_n, 128)), stream);
 }
 
-}  // namespace
-
-void set_tile_order(int32_t order) { g_tile_order.store(order, std::memory_order_relaxed); }
-
-int compute_units() {
-    constexpr int MAX_DEV = 64;
-    static std::atomic<int> cached[MAX_DEV];   // 0 = not asked yet
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEV) return 256;
-    int n = cached[dev].load(std::memory_order_relaxed);
-    if (n > 0) return n;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
-    cached[dev].store(n, std::memory_order_relaxed);
-    return n;
-}
-
-int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
-    int max_m = 0, max_n = 0;
-    for (int g = 0; g < plan.groups; ++g) {
-        if (plan.s[g].m == 0 || plan.s[g].n == 0) continue;
-        max_m = plan.s[g].m > max_m ? plan.s[g].m : max_m;
-        max_n = plan.s[g].n > max_n ? plan.s[g].n : max_n;
-    }
+// The kernel of `variant` (0: the default for the shape).  max_m, max_n: largest extents of a product that is not empty.
+int32_t launch_chosen(const GemmPlan& plan, int max_m, int max_n, int32_t variant, hipStream_t stream) {
     // the fused row maximum exists in the persistent bf16 kernel only; the caller does anything else in two passes
     if (plan.epilogue == EPI_ROWMAX && (max_m == 0 || max_n == 0 || plan.f32_operand || variant == 1 || !mfma_ok(plan) || !rows_aligned(plan)))
         return SBP_ERR_UNSUPPORTED;
@@ -1702,28 +1696,14 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
             return plan.f32_operand == 2 ? launch_split<true>(plan, max_m, max_n, variant, stream) : launch_split<false>(plan, max_m, max_n, variant, stream);
         }
         if (variant > 1) return SBP_ERR_UNSUPPORTED;
-        if (variant == 0) return launch_f32(plan, max_m, max_n, variant, stream);
-        const dim3 grid((max_n + 15) / 16, (max_m + 15) / 16, plan.groups);
-        if (grid.y > 65535 || grid.z > 65535) return SBP_ERR_UNSUPPORTED;
-        if (plan.f32_operand == 2) launch_generic_epi<true, false, float>(plan, grid, stream);
-        else launch_generic_epi<false, true, float>(plan, grid, stream);
-        return launch_status(__func__);
+        return variant == 0 ? launch_f32(plan, max_m, max_n, variant, stream) : launch_generic(plan, max_m, max_n, stream);
     }
     if (plan.in_dtype == SBP_F32 && (variant == 0 || (variant >= 45 && variant <= 47)))
         return plan.out_dtype == SBP_F32 ? launch_f32(plan, max_m, max_n, variant, stream) : SBP_ERR_DTYPE;
     const bool fast = mfma_ok(plan);
     if (variant == 1 || !fast) {
         if (variant > 1) return SBP_ERR_UNSUPPORTED;   // a forced MFMA variant cannot take this shape
-        const dim3 grid((max_n + 15) / 16, (max_m + 15) / 16, plan.groups);
-        if (grid.y > 65535 || grid.z > 65535) return SBP_ERR_UNSUPPORTED;
-        if (plan.in_dtype == SBP_BF16) {
-            if (plan.out_dtype == SBP_F32) launch_generic_epi<true, true, float>(plan, grid, stream);
-            else launch_generic_epi<true, true, uint16_t>(plan, grid, stream);
-        } else {
-            if (plan.out_dtype != SBP_F32) return SBP_ERR_DTYPE;
-            launch_generic_epi<false, false, float>(plan, grid, stream);
-        }
-        return launch_status(__func__);
+        return launch_generic(plan, max_m, max_n, stream);
     }
     const bool direct = rows_aligned(plan);
     bool k64 = true, k128 = true;   // every local reduction a whole number of 64-element steps / of four-stage rounds
@@ -1735,12 +1715,12 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
     if (plan.epilogue == EPI_ROWMAX) {
         // ahead of every other choice, forced or not: no other kernel below writes row maxima
         if (!(k128 && max_m > 128 && max_n > 128 && plan.out_dtype == SBP_BF16 && (variant == 0 || variant == 12 || variant == 16 || variant == 21))) return SBP_ERR_UNSUPPORTED;
-        hipLaunchKernelGGL(fill_rowmax_kernel, dim3((uint32_t)((max_m + 255) / 256), (uint32_t)plan.groups), dim3(256), 0, stream, plan);
+        hipLaunchKernelGGL(fill_rowmax_kernel, dim3((uint32_t)tiles_along(max_m, 256), (uint32_t)plan.groups), dim3(256), 0, stream, plan);
         const int32_t st = launch_status(__func__);
         if (st != SBP_OK) return st;
         if (variant == 12) return launch_mfma_layout<256, 256, 2, 4, 104, EPI_ROWMAX, uint16_t>(plan, max_m, max_n, stream);
         if (variant == 21 || (variant == 0 && pingpong_pays(plan, max_m, max_n))) {
-            const int tm = (max_m + 255) / 256, tn = (max_n + 255) / 256;
+            const int tm = tiles_along(max_m, 256), tn = tiles_along(max_n, 256);
             return launch_gemm_pingpong(plan, max_m, max_n, tile_order_for(tm, tn) & 0xFFFF, stream);
         }
         return launch_mfma_layout<256, 256, 2, 4, 204, EPI_ROWMAX, uint16_t>(plan, max_m, max_n, stream);
@@ -1752,7 +1732,7 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
     if (plan.epilogue == SBP_EPI_GELU && !(direct && k64 && rows_of_8(plan))) {
         GemmPlan erf = plan;
         erf.epilogue = EPI_GELU_ERF;
-        return launch_gemm(erf, variant, stream);
+        return launch_chosen(erf, max_m, max_n, variant, stream);
     }
     if (variant >= 40 && variant <= 44) return launch_any(plan, max_m, max_n, variant - 40, direct, stream);
     if (variant == 48) return direct ? launch_deep(plan, max_m, max_n, stream) : SBP_ERR_UNSUPPORTED;
@@ -1781,11 +1761,41 @@ int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
         case 16: return k128 ? launch_mfma_out<256, 256, 2, 4, 204>(plan, max_m, max_n, stream) : SBP_ERR_UNSUPPORTED;
         case 21: {
             if (!k128) return SBP_ERR_UNSUPPORTED;
-            const int tm = (max_m + 255) / 256, tn = (max_n + 255) / 256;
+            const int tm = tiles_along(max_m, 256), tn = tiles_along(max_n, 256);
             return launch_gemm_pingpong(plan, max_m, max_n, tile_order_for(tm, tn) & 0xFFFF, stream);
         }
         default: return SBP_ERR_UNSUPPORTED;
     }
+}
+
+}  // namespace
+
+void set_tile_order(int32_t order) { g_tile_order.store(order, std::memory_order_relaxed); }
+
+int compute_units() {
+    constexpr int MAX_DEV = 64;
+    static std::atomic<int> cached[MAX_DEV];   // 0 = not asked yet
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEV) return 256;
+    int n = cached[dev].load(std::memory_order_relaxed);
+    if (n > 0) return n;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
+    cached[dev].store(n, std::memory_order_relaxed);
+    return n;
+}
+
+int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream) {
+    int max_m = 0, max_n = 0;
+    for (int g = 0; g < plan.groups; ++g) {
+        if (plan.s[g].m == 0 || plan.s[g].n == 0) continue;
+        max_m = plan.s[g].m > max_m ? plan.s[g].m : max_m;
+        max_n = plan.s[g].n > max_n ? plan.s[g].n : max_n;
+    }
+    const int32_t st = launch_chosen(plan, max_m, max_n, variant, stream);
+    // A tile with few useful elements (64 x 64 for a single row) can need more work items than one launch holds, at 2^24
+    // tiles and up; the one-element-per-lane kernel spreads its grid over three dimensions.
+    if (st == SBP_ERR_UNSUPPORTED && variant == 0 && plan.epilogue != EPI_ROWMAX) return launch_generic(plan, max_m, max_n, stream);
+    return st;
 }
 
 }  // namespace sbp

@@ -465,7 +465,7 @@ int32_t launch_pp_cfg(const GemmPlan& plan, int tm, int tn, int order, int nblk,
 
 // bf16 operands, every local reduction length a multiple of 128, row pitches of 16 bytes: checked by the caller
 int32_t launch_gemm_pingpong(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t st) {
-    const int tm = (max_m + 255) / 256, tn = (max_n + 255) / 256;
+    const int tm = tiles_along(max_m, 256), tn = tiles_along(max_n, 256);
     const int64_t tiles = (int64_t)tm * tn * plan.groups;
     const int64_t nblk = (tiles + 7) / 8 * 8;
     if (nblk > 0x7FFFFFFF) return SBP_ERR_UNSUPPORTED;

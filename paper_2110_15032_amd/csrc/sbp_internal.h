@@ -27,6 +27,11 @@ inline int32_t launch_status(const char* where) {
     return SBP_ERR_LAUNCH;
 }
 
+// Tiles along an extent, which may be as large as 2^31 - 1.
+inline int tiles_along(int extent, int tile) { return (int)(((int64_t)extent + tile - 1) / tile); }
+// Can a grid of `blocks` workgroups of `threads` be launched?  HIP counts the work items of a grid dimension in 32 bits.
+inline bool grid_fits(int64_t blocks, int threads) { return blocks <= 0xFFFFFFFFll / threads; }
+
 // ---------------------------------------------------------------------------------------------
 // Boxing: every conversion is a set of rectangle tasks.  Task t reads a rows x cols rectangle
 // from n_src source shards (all at the same offset / leading dimension), combines them
@@ -82,6 +87,8 @@ struct GemmPlan {
     int32_t epilogue;   // SBP_EPI_*
 };
 
+// variant: SBP_KNOB_GEMM_VARIANT.  The launch_gemm_* functions below return SBP_ERR_UNSUPPORTED, with nothing enqueued, for a
+// grid that cannot be launched (grid_fits).
 int32_t launch_gemm(const GemmPlan& plan, int32_t variant, hipStream_t stream);
 void set_tile_order(int32_t order);
 // The ping-pong persistent kernel (gemm_pingpong_kernel.hip).  The caller has checked: bf16 operands, every

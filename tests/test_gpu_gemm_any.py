@@ -222,3 +222,31 @@ def test_split_kernel_on_rows_that_end_inside_a_chunk(n, kk, f32_side, extra, va
     got, _ = run(Xs, sx, Ws, sw, M, kk, N, k, tx, tw, ld if f32_side == "x" else 0, ld if f32_side == "w" else 0, variant=variant)
     for i in range(k):
         assert_matmul_close(got[i], ref[i], 1e-5, f"{f32_side} {n}x{kk}+{extra} v{variant} shard {i}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_more_tiles_than_a_launch_holds(dtype):
+    """one row per device, 2^24 columns, 64 devices: 2^24 tiles of 64 x 64, 2^32 work items.  Single products: exact in fp32
+    for bf16 operands, correctly rounded otherwise."""
+    torch = __import__("torch")
+    k, n, td = 64, 1 << 24, torch.float32 if dtype == "f32" else torch.bfloat16
+    code = sbp.F32 if dtype == "f32" else sbp.BF16
+    x = [torch.full((1, 1), 0.5 + i, dtype=td, device="cuda") for i in range(k)]
+    w = torch.randn(1, n, device="cuda", dtype=td)
+    y = [torch.full((1, n), float("nan"), dtype=td, device="cuda") for _ in range(k)]
+    sbp.sbp_matmul(sbp.SbpTensor(x, k, 1, code), sbp.S(0), sbp.SbpTensor([w] * k, 1, n, code), sbp.B, sbp.SbpTensor(y, k, n, code), sbp.S(0), k)
+    sync()
+    for i in range(k):
+        assert torch.equal(y[i], (x[i].float() * w.float()).to(td)), f"shard {i}"
+
+
+@pytest.mark.parametrize("rows", [2 ** 31 - 1, 2 ** 31 - 64])
+def test_extents_near_the_largest_are_refused(rows):
+    """rounding such an extent up to tiles leaves 32 bits; the product is one that no kernel here takes"""
+    torch = __import__("torch")
+    x, y = (torch.empty(rows, 1, device="cuda") for _ in range(2))
+    w = torch.ones(1, 1, device="cuda")
+    with pytest.raises(sbp.SbpError) as e:
+        sbp.sbp_matmul(sbp.SbpTensor([x], rows, 1, sbp.F32), sbp.B, sbp.SbpTensor([w], 1, 1, sbp.F32), sbp.B, sbp.SbpTensor([y], rows, 1, sbp.F32), sbp.B, 1)
+    assert e.value.status == -9
+    sync()
