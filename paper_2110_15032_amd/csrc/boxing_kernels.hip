@@ -147,6 +147,13 @@ __device__ inline V combine(V a, V b) {
 
 constexpr int BOX_THREADS = 256;
 
+// Reductions of 3 and of other uncommon numbers of sources keep several loads in flight where rows are whole 128-byte lines (or
+// nearly so, being long).  Short pieces of lines lose by it: the chip then asks k source arrays for the same lines again before
+// they have served their neighbours.  us, one load after another / three at once (fp32 P -> S(1)): 7 devices, 12 columns each,
+// 65536 rows 58 / 72, 36 columns 150 / 163; 32 columns, 18700 rows 38 / 27; 1024 columns, 580 rows 36 / 27; 5 devices, P -> B of
+// 16 MiB 36 / 30.  3 devices, 36 columns, 65536 rows 27.7 / 29.4; P -> B of 16 MiB 21.1 / 17.1.
+__host__ __device__ inline bool whole_lines(const Task& T) { return T.rows <= 1 || T.cols % 32 == 0 || T.cols >= 512; }
+
 // Reduction tasks: NS sources (compile-time when KS > 0), fp32 math in shard order.
 template <typename V, int OP, int KS, int UNROLL>
 __global__ __launch_bounds__(BOX_THREADS) void box_reduce_kernel(BoxParams p) {
@@ -184,10 +191,11 @@ __global__ __launch_bounds__(BOX_THREADS) void box_reduce_kernel(BoxParams p) {
                     if (ns > 0) a = __builtin_nontemporal_load(static_cast<const V*>(p.src[sb + T.s0]) + spos);
                     auto load = [&](int i) { return __builtin_nontemporal_load(static_cast<const V*>(p.src[sb + T.s0 + i * T.sstep]) + spos); };
                     int i = 1;
-                    for (; i + 2 < ns; i += 3) {   // three loads in flight
-                        const V b0 = load(i), b1 = load(i + 1), b2 = load(i + 2);
-                        a = combine<OP>(combine<OP>(combine<OP>(a, b0), b1), b2);
-                    }
+                    if (whole_lines(T))
+                        for (; i + 2 < ns; i += 3) {   // three loads in flight
+                            const V b0 = load(i), b1 = load(i + 1), b2 = load(i + 2);
+                            a = combine<OP>(combine<OP>(combine<OP>(a, b0), b1), b2);
+                        }
                     for (; i < ns; ++i) a = combine<OP>(a, load(i));
                 }
                 acc[u] = a;
@@ -282,19 +290,27 @@ __global__ __launch_bounds__(BOX_THREADS) void box_copy_kernel(BoxParams p) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Rectangles whose offsets, pitches or widths are no multiple of 16 bytes.  Every row is cut into 16-byte vectors all the
-// same, read and written unaligned, and its last one goes element by element where the row does not fill it.  An unaligned
+// Rectangles whose offsets, pitches or widths are no multiple of 16 bytes, rows of at least 16 bytes.  Every row is cut into
+// 16-byte vectors all the same, read and written unaligned.  The last one ends with the row, so that two lanes may store the
+// same values: element by element, in one lane's turns, those ends cost more than the rest of a short row (cast P -> S(1) of
+// [65536, 248], 8 devices, us: 221 with one element per lane, 449 with ends by elements, 151 so).  An unaligned
 // wave access touches one 128-byte line more than an aligned one; one element per lane, which is what the widest vector that
 // divides every offset comes to on odd sizes, needs 4 to 8 times the instructions and left the kernels bound by them.
 // Stores are cached: neighbouring waves complete each other's lines in L2.
-// us before / now, 20000 x 4095, 3 devices: bf16 S(0) -> S(1) 192 / 92, S(0) -> B 268 / 135, fp32 P -> S(0) 364 / 234, cast S(0) -> B
-// 593 / 170, cast P -> S(0) 441 / 166 (4.9 TB/s; the aligned kernels reach 5.6-5.9); 3001 x 1001, 8 devices: P -> B 40 / 32.
+// us before / now, 20000 x 4095, 3 devices: bf16 S(0) -> S(1) 192 / 72, S(0) -> B 268 / 135, fp32 P -> S(0) 364 / 234, cast S(0) -> B
+// 593 / 173, cast P -> S(0) 441 / 167 (4.9 TB/s; the aligned kernels reach 5.6-5.9); 3001 x 1001, 8 devices: P -> B 40 / 32.
 // ------------------------------------------------------------------------------------------------
 // Named directly wherever they are used: a template argument (std::conditional_t) drops the attribute, and with it the promise
 // of no alignment that the load and store instructions are chosen by.
 typedef f32x4 __attribute__((aligned(4))) f32x4_any;
 typedef u32x4 __attribute__((aligned(2))) u32x4_any;
 static_assert(alignof(f32x4_any) == 4 && alignof(u32x4_any) == 2, "unaligned vectors");
+
+// first column of vector v of a row of at least `elems` columns, the elements of a vector
+__device__ inline int64_t vector_start(const Task& T, uint32_t v, int elems) {
+    const int64_t c = (int64_t)v * elems;
+    return c + elems <= T.cols ? c : T.cols - elems;
+}
 
 template <typename E, int UNROLL>
 __global__ __launch_bounds__(BOX_THREADS) void box_copy_any_kernel(BoxParams p) {
@@ -305,30 +321,21 @@ __global__ __launch_bounds__(BOX_THREADS) void box_copy_any_kernel(BoxParams p) 
     const uint32_t stride = gridDim.x * BOX_THREADS;
     for (uint32_t base = blockIdx.x * BOX_THREADS + threadIdx.x; base < total; base += stride * UNROLL) {
         u32x4 val[UNROLL];
-        const E* from[UNROLL];
         int64_t dpos[UNROLL];
-        uint32_t n[UNROLL];   // elements of the vector that exist
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
             const uint32_t idx = base + u * stride;
-            n[u] = 0;
             if (idx < total) {
                 const uint32_t r = T.rows == 1 ? 0 : idx / cols_v;
-                const int64_t c = (int64_t)(idx - r * cols_v) * EPV;
-                n[u] = T.cols - c < EPV ? (uint32_t)(T.cols - c) : EPV;
-                from[u] = src + (int64_t)r * T.src_ld + c;
+                const int64_t c = vector_start(T, idx - r * cols_v, EPV);
+                val[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(src + (int64_t)r * T.src_ld + c));
                 dpos[u] = T.dst_off + (int64_t)r * T.dst_ld + c;
-                if (n[u] == EPV) val[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(from[u]));
             }
         }
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
-            for (int j = 0; n[u] && j < T.nd; ++j) {
-                E* dst = static_cast<E*>(p.dst[T.d0 + j]) + dpos[u];
-                if (n[u] == EPV) *reinterpret_cast<u32x4_any*>(dst) = val[u];
-                else
-                    for (uint32_t e = 0; e < n[u]; ++e) dst[e] = from[u][e];
-            }
+            if (base + u * stride < total)
+                for (int j = 0; j < T.nd; ++j) *reinterpret_cast<u32x4_any*>(static_cast<E*>(p.dst[T.d0 + j]) + dpos[u]) = val[u];
         }
     }
 }
@@ -343,29 +350,20 @@ __global__ __launch_bounds__(BOX_THREADS) void box_reduce_any_kernel(BoxParams p
     const uint32_t stride = gridDim.x * BOX_THREADS;
     for (uint32_t idx = blockIdx.x * BOX_THREADS + threadIdx.x; idx < total; idx += stride) {
         const uint32_t r = T.rows == 1 ? 0 : idx / cols_v;
-        const int64_t c = (int64_t)(idx - r * cols_v) * 4;
+        const int64_t c = vector_start(T, idx - r * cols_v, 4);
         const int64_t spos = T.src_off + (int64_t)r * T.src_ld + c, dpos = T.dst_off + (int64_t)r * T.dst_ld + c;
-        auto source = [&](int i) { return static_cast<const float*>(p.src[sb + i]) + spos; };
-        if (T.cols - c >= 4) {
-            auto load = [&](int i) { return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(source(i))); };
-            f32x4 a = load(0);
-            if constexpr (KS > 0) {
-                f32x4 part[KS];
+        auto load = [&](int i) -> f32x4 { return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(static_cast<const float*>(p.src[sb + i]) + spos)); };
+        f32x4 a = load(0);
+        if constexpr (KS > 0) {
+            f32x4 part[KS];
 #pragma unroll
-                for (int i = 1; i < KS; ++i) part[i] = load(i);
+            for (int i = 1; i < KS; ++i) part[i] = load(i);
 #pragma unroll
-                for (int i = 1; i < KS; ++i) a = combine<OP>(a, part[i]);
-            } else {
-                for (int i = 1; i < ns; ++i) a = combine<OP>(a, (f32x4)load(i));
-            }
-            for (int j = 0; j < T.nd; ++j) *reinterpret_cast<f32x4_any*>(static_cast<float*>(p.dst[db + T.d0 + j]) + dpos) = a;
+            for (int i = 1; i < KS; ++i) a = combine<OP>(a, part[i]);
         } else {
-            for (int e = 0; e < (int)(T.cols - c); ++e) {
-                float a = source(0)[e];
-                for (int i = 1; i < ns; ++i) a = combine<OP>(a, source(i)[e]);
-                for (int j = 0; j < T.nd; ++j) static_cast<float*>(p.dst[db + T.d0 + j])[dpos + e] = a;
-            }
+            for (int i = 1; i < ns; ++i) a = combine<OP>(a, load(i));
         }
+        for (int j = 0; j < T.nd; ++j) *reinterpret_cast<f32x4_any*>(static_cast<float*>(p.dst[db + T.d0 + j]) + dpos) = a;
     }
 }
 
@@ -456,8 +454,8 @@ __global__ __launch_bounds__(BOX_THREADS) void box_gather_bcast_kernel(BoxParams
 // ------------------------------------------------------------------------------------------------
 // Cast fused into boxing (Sec. 6.4: sharded optimizer state with mixed precision).
 // Forward, fp32 S(a) -> bf16 B: the walk of box_gather_bcast_kernel (chunked passes, one destination at
-// a time, re-reads from L2) with 8 elements per lane: 32 bytes in, one hardware conversion per pair
-// (round to nearest even), 16 bytes out.
+// a time, re-reads from L2) with VE elements per lane: 32 bytes in, one hardware conversion per pair
+// (round to nearest even), 16 bytes out; or one element (see launch_boxing_cast).
 // ------------------------------------------------------------------------------------------------
 __device__ inline uint32_t cvt2_bf16(float lo, float hi) {
     typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -465,12 +463,12 @@ __device__ inline uint32_t cvt2_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
+template <int VE>
 __global__ __launch_bounds__(BOX_THREADS) void box_cast_gather_kernel(BoxParams p, uint32_t log2_pieces, uint32_t total,
                                                                        uint32_t q, uint32_t rem) {
     __shared__ const float* sp[SBP_MAX_K];
     if ((int)threadIdx.x < p.ki) sp[threadIdx.x] = static_cast<const float*>(p.src[threadIdx.x]);
     __syncthreads();
-    constexpr int VE = 8;
     const uint32_t k = (uint32_t)p.ko;
     const uint32_t piece = blockIdx.x & ((1u << log2_pieces) - 1);
     const uint32_t cj = blockIdx.x >> log2_pieces;
@@ -495,9 +493,13 @@ __global__ __launch_bounds__(BOX_THREADS) void box_cast_gather_kernel(BoxParams 
     }
     const int64_t spos = by_rows ? ((int64_t)(r - begin) * p.cols + (int64_t)c * VE) : ((int64_t)r * len + (x - begin));   // elements
     const float* src = sp[i] + spos;
-    const f32x4 a = *reinterpret_cast<const f32x4*>(src), b = *reinterpret_cast<const f32x4*>(src + 4);
-    const u32x4 o = {cvt2_bf16(a[0], a[1]), cvt2_bf16(a[2], a[3]), cvt2_bf16(b[0], b[1]), cvt2_bf16(b[2], b[3])};
-    __builtin_nontemporal_store(o, static_cast<u32x4*>(p.dst[j]) + idx);
+    if constexpr (VE == 8) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(src), b = *reinterpret_cast<const f32x4*>(src + 4);
+        const u32x4 o = {cvt2_bf16(a[0], a[1]), cvt2_bf16(a[2], a[3]), cvt2_bf16(b[0], b[1]), cvt2_bf16(b[2], b[3])};
+        __builtin_nontemporal_store(o, static_cast<u32x4*>(p.dst[j]) + idx);
+    } else {
+        static_cast<uint16_t*>(p.dst[j])[idx] = (uint16_t)(cvt2_bf16(*src, 0.0f) & 0xFFFFu);
+    }
 }
 
 // The same where rows or shard boundaries are no multiple of 8 elements: tasks and vectors as in box_copy_any_kernel.
@@ -508,39 +510,33 @@ __global__ __launch_bounds__(BOX_THREADS) void box_cast_gather_any_kernel(BoxPar
     const uint32_t stride = gridDim.x * BOX_THREADS;
     for (uint32_t idx = blockIdx.x * BOX_THREADS + threadIdx.x; idx < total; idx += stride) {
         const uint32_t r = T.rows == 1 ? 0 : idx / cols_v;
-        const int64_t c = (int64_t)(idx - r * cols_v) * 8;
+        const int64_t c = vector_start(T, idx - r * cols_v, 8);
         const float* from = src + (int64_t)r * T.src_ld + c;
         const int64_t dpos = T.dst_off + (int64_t)r * T.dst_ld + c;
-        if (T.cols - c >= 8) {
-            const f32x4 a = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(from)), b = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(from + 4));
-            const u32x4 o = {cvt2_bf16(a[0], a[1]), cvt2_bf16(a[2], a[3]), cvt2_bf16(b[0], b[1]), cvt2_bf16(b[2], b[3])};
-            for (int j = 0; j < T.nd; ++j) *reinterpret_cast<u32x4_any*>(static_cast<uint16_t*>(p.dst[T.d0 + j]) + dpos) = o;
-        } else {
-            for (int e = 0; e < (int)(T.cols - c); ++e) {
-                const uint16_t o = (uint16_t)(cvt2_bf16(from[e], 0.0f) & 0xFFFFu);
-                for (int j = 0; j < T.nd; ++j) static_cast<uint16_t*>(p.dst[T.d0 + j])[dpos + e] = o;
-            }
-        }
+        const f32x4 a = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(from)), b = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(from + 4));
+        const u32x4 o = {cvt2_bf16(a[0], a[1]), cvt2_bf16(a[2], a[3]), cvt2_bf16(b[0], b[1]), cvt2_bf16(b[2], b[3])};
+        for (int j = 0; j < T.nd; ++j) *reinterpret_cast<u32x4_any*>(static_cast<uint16_t*>(p.dst[T.d0 + j]) + dpos) = o;
     }
 }
 
 // Backward, bf16 P(sum) -> fp32 S(a): out_j = sum over the k partials of slice j, widened to fp32 and
 // added in shard order.  Tasks as for P -> S (one per destination).
-// ALIGNED: every vector starts 16-byte aligned and fills its row; otherwise as in box_copy_any_kernel.
-template <bool ALIGNED, int KS>
+// VE = 8, ALIGNED: every vector starts 16-byte aligned and fills its row; VE = 8 otherwise: as in box_copy_any_kernel; VE = 1: one
+// element per lane (see launch_boxing_cast).
+template <int VE, bool ALIGNED, int KS>
 __global__ __launch_bounds__(BOX_THREADS) void box_cast_reduce_kernel(BoxParams p) {
     const Task T = make_task(p, blockIdx.y);
     const int32_t ns = KS > 0 ? KS : T.ns;
-    const uint32_t cols_v = (uint32_t)((T.cols + 7) / 8);
+    const uint32_t cols_v = (uint32_t)((T.cols + VE - 1) / VE);
     const uint32_t total = (uint32_t)T.rows * cols_v;
     const uint32_t stride = gridDim.x * BOX_THREADS;
     float* __restrict__ dst = static_cast<float*>(p.dst[T.d0]);
     for (uint32_t idx = blockIdx.x * BOX_THREADS + threadIdx.x; idx < total; idx += stride) {
         const uint32_t r = T.rows == 1 ? 0 : idx / cols_v;
-        const int64_t c = (int64_t)(idx - r * cols_v) * 8;
+        const int64_t c = VE == 8 && !ALIGNED ? vector_start(T, idx - r * cols_v, 8) : (int64_t)(idx - r * cols_v) * VE;
         const int64_t spos = T.src_off + (int64_t)r * T.src_ld + c;
         const int64_t dpos = T.dst_off + (int64_t)r * T.dst_ld + c;
-        if (ALIGNED || T.cols - c >= 8) {
+        if constexpr (VE == 8) {
             float acc[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
@@ -571,11 +567,9 @@ __global__ __launch_bounds__(BOX_THREADS) void box_cast_reduce_kernel(BoxParams 
                 *reinterpret_cast<f32x4_any*>(dst + dpos + 4) = o1;
             }
         } else {
-            for (int e = 0; e < (int)(T.cols - c); ++e) {
-                float acc = 0.0f;
-                for (int i = 0; i < ns; ++i) acc += __uint_as_float((uint32_t)static_cast<const uint16_t*>(p.src[i])[spos + e] << 16);
-                dst[dpos + e] = acc;
-            }
+            float acc = 0.0f;
+            for (int i = 0; i < ns; ++i) acc += __uint_as_float((uint32_t)static_cast<const uint16_t*>(p.src[i])[spos] << 16);
+            dst[dpos] = acc;
         }
     }
 }
@@ -674,7 +668,8 @@ inline int64_t gcd64(int64_t a, int64_t b) {
 
 template <typename V, int OP, int UNROLL>
 void launch_reduce_k(const BoxParams& p, dim3 grid, hipStream_t st) {
-    switch (p.mode == M_P2P ? 0 : p.ki) {   // P -> P walks a strided source list: run-time count
+    // P -> P walks a strided source list: run-time count; so does a reduction of 3 in pieces of lines (task 0 is a longest one)
+    switch (p.mode == M_P2P || (p.ki == 3 && !whole_lines(make_task(p, 0))) ? 0 : p.ki) {
         case 2: hipLaunchKernelGGL((box_reduce_kernel<V, OP, 2, UNROLL>), grid, dim3(BOX_THREADS), 0, st, p); break;
         case 3: hipLaunchKernelGGL((box_reduce_kernel<V, OP, 3, UNROLL>), grid, dim3(BOX_THREADS), 0, st, p); break;
         case 4: hipLaunchKernelGGL((box_reduce_kernel<V, OP, 4, UNROLL>), grid, dim3(BOX_THREADS), 0, st, p); break;
@@ -713,14 +708,16 @@ void launch_reduce_any(const BoxParams& p, dim3 grid, hipStream_t st) {
     }
 }
 
+// The source count is compiled in for 8 devices, and for fewer where the partials are not so large that HBM alone bounds them
+// (us, compiled in / run-time count, [4096, 1024]: 3 devices 11.3 / 11.8, 4 devices 12.2 / 12.7; [16384, 4096]: 126 / 123 and 145 / 141).
 template <bool ALIGNED>
 void launch_cast_reduce(const BoxParams& p, dim3 grid, hipStream_t st) {
-    switch (p.ki) {
-        case 2: hipLaunchKernelGGL((box_cast_reduce_kernel<ALIGNED, 2>), grid, dim3(BOX_THREADS), 0, st, p); break;
-        case 3: hipLaunchKernelGGL((box_cast_reduce_kernel<ALIGNED, 3>), grid, dim3(BOX_THREADS), 0, st, p); break;
-        case 4: hipLaunchKernelGGL((box_cast_reduce_kernel<ALIGNED, 4>), grid, dim3(BOX_THREADS), 0, st, p); break;
-        case 8: hipLaunchKernelGGL((box_cast_reduce_kernel<ALIGNED, 8>), grid, dim3(BOX_THREADS), 0, st, p); break;
-        default: hipLaunchKernelGGL((box_cast_reduce_kernel<ALIGNED, 0>), grid, dim3(BOX_THREADS), 0, st, p); break;
+    switch (ALIGNED && p.ki != 8 && p.rows * p.cols >= (1 << 24) ? 0 : p.ki) {
+        case 2: hipLaunchKernelGGL((box_cast_reduce_kernel<8, ALIGNED, 2>), grid, dim3(BOX_THREADS), 0, st, p); break;
+        case 3: hipLaunchKernelGGL((box_cast_reduce_kernel<8, ALIGNED, 3>), grid, dim3(BOX_THREADS), 0, st, p); break;
+        case 4: hipLaunchKernelGGL((box_cast_reduce_kernel<8, ALIGNED, 4>), grid, dim3(BOX_THREADS), 0, st, p); break;
+        case 8: hipLaunchKernelGGL((box_cast_reduce_kernel<8, ALIGNED, 8>), grid, dim3(BOX_THREADS), 0, st, p); break;
+        default: hipLaunchKernelGGL((box_cast_reduce_kernel<8, ALIGNED, 0>), grid, dim3(BOX_THREADS), 0, st, p); break;
     }
 }
 
@@ -835,7 +832,7 @@ int32_t launch_boxing(const BoxPlan& plan, hipStream_t stream) {
     int64_t g = 16 / plan.elem_bytes;  // elements in 16 bytes
     p.vec_elems = 1;                   // make_task does not depend on it
     const int64_t epv = g;
-    int64_t max_units = 0, any_units = 0, widest = 0;
+    int64_t max_units = 0, any_units = 0, narrowest = INT64_MAX;
     for (int32_t t = 0; t < tasks; ++t) {
         const Task T = make_task(p, t);
         if (T.rows * T.cols == 0) continue;
@@ -849,7 +846,7 @@ int32_t launch_boxing(const BoxPlan& plan, hipStream_t stream) {
         max_units = T.rows * T.cols > max_units ? T.rows * T.cols : max_units;
         const int64_t units = T.rows * ((T.cols + epv - 1) / epv);
         any_units = units > any_units ? units : any_units;
-        widest = T.cols > widest ? T.cols : widest;
+        narrowest = T.cols < narrowest ? T.cols : narrowest;
     }
     if (max_units == 0) return SBP_OK;  // nothing to move
     p.vec_elems = (int32_t)g;
@@ -858,10 +855,14 @@ int32_t launch_boxing(const BoxPlan& plan, hipStream_t stream) {
 
     const bool reduce = p_in && p.mode != M_IDENT;
     const int vbytes = p.vec_elems * plan.elem_bytes;
-    // No 16-byte vector divides everything: unaligned vectors, unless rows are so short that their ends are most of the work.  us,
-    // widest exact vector / unaligned, 65536 rows: 13 fp32 columns S(0) -> S(1) 29.9 / 13.4, 13 columns P -> S(1) 28.4 / 22.0; with
-    // 8-byte vectors 10 columns P -> S(1) 28.2 / 38.5.
-    if (vbytes < 16 && widest >= (vbytes == 8 ? 4 : 2) * epv && p.mode != M_P2P) {
+    // No 16-byte vector divides everything: unaligned ones, in rows that hold one.  us, widest exact vector / unaligned, 65536
+    // rows, 3 devices, columns a device: bf16 S(0) -> S(1) 9 columns 20.8 / 6.7, bf16 S(1) -> B 9 columns 17.0 / 7.9, fp32
+    // S(0) -> S(1) 5 columns 14.7 / 6.5, fp32 P -> S(1) 13 columns 26.5 / 18.8; but bf16 S(1) -> B 7 columns 14.1 / 18.0.  A
+    // reduction of three sources and more with exact 8-byte vectors from 32 columns on: 4 devices 10 columns 28.5 / 31, 18
+    // columns 39 / 43, 34 and more 0.8 of the time.  An all-gather of a few thousand vectors to many devices with the smaller ones,
+    // of which there are more (us, bf16 [512, 120], 8 devices, 5.9 / 7.3; [512, 504] 7.5 / 5.6).
+    const bool few = p.mode == M_S2B && ko > 4 && plan.rows * plan.cols < (1 << 17);
+    if (vbytes < 16 && !few && narrowest >= (reduce && vbytes == 8 && ki > 2 ? 32 : epv) && p.mode != M_P2P) {
         constexpr int UNROLL = 2;
         const int per_lane = reduce ? 1 : UNROLL;
         int64_t bx = (any_units + (int64_t)BOX_THREADS * per_lane - 1) / ((int64_t)BOX_THREADS * per_lane);
@@ -969,13 +970,21 @@ int32_t launch_boxing_cast(const BoxPlan& plan, hipStream_t stream) {
         const int64_t n = p.axis_in == 0 ? plan.rows : plan.cols;
         const uint32_t q = (uint32_t)(n / plan.k), rem = (uint32_t)(n % plan.k);
         if (ve == 8) {
-            hipLaunchKernelGGL(box_cast_gather_kernel, dim3((uint32_t)blocks), dim3(BOX_THREADS), 0, stream, p, lp, (uint32_t)total, q, rem);
+            hipLaunchKernelGGL(box_cast_gather_kernel<8>, dim3((uint32_t)blocks), dim3(BOX_THREADS), 0, stream, p, lp, (uint32_t)total, q, rem);
         } else {
             p.mode = M_S2B;
-            int64_t units = 0;
+            int64_t units = 0, narrowest = INT64_MAX;
             for (int32_t t = 0; t < plan.k; ++t) {
                 const Task T = make_task(p, t);
+                if (T.rows * T.cols == 0) continue;
                 units = T.rows * ((T.cols + 7) / 8) > units ? T.rows * ((T.cols + 7) / 8) : units;
+                narrowest = T.cols < narrowest ? T.cols : narrowest;
+            }
+            // One element per lane for rows that hold no vector and for so few elements that vectors leave the chip idle.  us,
+            // element / vectors: 3 devices of [512, 31] 3.4 / 3.9, [65536, 7] 12.6 / 17.1, [65536, 9] 16 / 11, [65536, 31] 43 / 27.6.
+            if (narrowest < 8 || plan.rows * plan.cols * plan.k < (1 << 19)) {
+                hipLaunchKernelGGL(box_cast_gather_kernel<1>, dim3((uint32_t)blocks), dim3(BOX_THREADS), 0, stream, p, lp, (uint32_t)total, q, rem);
+                return launch_status(__func__);
             }
             int64_t bx = (units + BOX_THREADS - 1) / BOX_THREADS;
             const int64_t cap = (32768 + plan.k - 1) / plan.k;
@@ -988,7 +997,7 @@ int32_t launch_boxing_cast(const BoxPlan& plan, hipStream_t stream) {
         // backward: bf16 P(sum) -> fp32 S(a)
         p.mode = M_P2S;
         p.vec_elems = 1;
-        int64_t g = 8, max_units = 0, elems = 0;
+        int64_t g = 8, max_units = 0, elems = 0, narrowest = INT64_MAX;
         for (int32_t t = 0; t < plan.k; ++t) {
             const Task T = make_task(p, t);
             if (T.rows * T.cols == 0) continue;
@@ -1002,15 +1011,20 @@ int32_t launch_boxing_cast(const BoxPlan& plan, hipStream_t stream) {
             const int64_t units = T.rows * ((T.cols + 7) / 8);
             max_units = units > max_units ? units : max_units;
             elems = T.rows * T.cols > elems ? T.rows * T.cols : elems;
+            narrowest = T.cols < narrowest ? T.cols : narrowest;
         }
         if (max_units == 0) return SBP_OK;
         const bool aligned = g == 8;
         if ((aligned ? max_units : elems) >= ((int64_t)1 << 31)) return SBP_ERR_UNSUPPORTED;
-        int64_t bx = (max_units + BOX_THREADS - 1) / BOX_THREADS;
+        // One element per lane as above; with many sources up to 23 columns a device.  us, element / vectors: 8 devices of
+        // [512, 47] 5.0 / 6.5, [65536, 13] 110 / 116, [65536, 19] 129 / 133, [65536, 25] 153 / 141; 4 of [65536, 13] 29 / 20.
+        const bool elements = !aligned && (narrowest < (plan.k > 4 ? 24 : 8) || plan.rows * plan.cols < (1 << 18));
+        int64_t bx = ((elements ? elems : max_units) + BOX_THREADS - 1) / BOX_THREADS;
         const int64_t cap = (65536 + plan.k - 1) / plan.k;
         if (bx > cap) bx = cap;
         const dim3 grid((uint32_t)bx, (uint32_t)plan.k);
-        if (aligned) launch_cast_reduce<true>(p, grid, stream);
+        if (elements) hipLaunchKernelGGL((box_cast_reduce_kernel<1, false, 0>), grid, dim3(BOX_THREADS), 0, stream, p);
+        else if (aligned) launch_cast_reduce<true>(p, grid, stream);
         else launch_cast_reduce<false>(p, grid, stream);
         return launch_status(__func__);
     }

@@ -120,38 +120,44 @@ __device__ inline uint32_t pack_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
-// 16 bytes (8 bf16 / 4 fp32 elements) per lane whatever the row pitch: rows that do not start 16-byte aligned are read and
-// written with unaligned vectors, which cost a second cache line per wave and instruction; the last group of a row goes
-// element by element where the row does not fill it.  ALIGNED: every row of both tensors starts 16-byte aligned; the
-// result is then stored past the caches.  Otherwise neighbouring waves share a line, which L2 has to keep for both.
-// WHOLE: no row has a broken last group.  Asking for every vector costs 7 % where all are whole (1024 x 1000000 bf16 on 8
-// devices, 685 against 742 us; 512 x 40000 fp32 on 4, 30 against 35); broken groups, 200 x 30008 on 4: 10 us, 19 by elements.
 typedef u32x4 __attribute__((aligned(2))) u32x4_any;
 typedef f32x4 __attribute__((aligned(4))) f32x4_any;
-// streaming load and the store of 16 bytes; the unaligned types are named here, since a template argument drops the attribute
-template <bool ALIGNED>
+// how the rows of the logits and of their gradient lie
+enum RowLayout {
+    ROWS_WHOLE,     // every row starts 16-byte aligned and is whole vectors
+    ROWS_ALIGNED,   // every row starts 16-byte aligned
+    ROWS_ANY
+};
+// Streaming load and the store of 16 bytes: past the caches where rows are aligned.  (The unaligned types are named here, since a
+// template argument drops the attribute.)
+template <RowLayout L>
 __device__ inline u32x4 load16(const uint16_t* at) {
-    if constexpr (ALIGNED) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(at));
+    if constexpr (L == ROWS_WHOLE) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(at));
     else return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(at));
 }
-template <bool ALIGNED>
+template <RowLayout L>
 __device__ inline f32x4 load16(const float* at) {
-    if constexpr (ALIGNED) return __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(at));
+    if constexpr (L == ROWS_WHOLE) return __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(at));
     else return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(at));
 }
-template <bool ALIGNED>
+template <RowLayout L>
 __device__ inline void store16(uint16_t* at, u32x4 v) {
-    if constexpr (ALIGNED) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(at));
+    if constexpr (L == ROWS_WHOLE) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(at));
+    else if constexpr (L == ROWS_ALIGNED) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_any*>(at));
     else *reinterpret_cast<u32x4_any*>(at) = v;
 }
-template <bool ALIGNED>
+template <RowLayout L>
 __device__ inline void store16(float* at, f32x4 v) {
-    if constexpr (ALIGNED) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(at));
+    if constexpr (L == ROWS_WHOLE) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(at));
+    else if constexpr (L == ROWS_ALIGNED) __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any*>(at));
     else *reinterpret_cast<f32x4_any*>(at) = v;
 }
-template <bool BF16, bool ALIGNED, bool WHOLE>
+// VE elements per lane, 16 bytes or one (see launch_xent_grad).  Vectors of rows that are not whole ones are read and written
+// unaligned, which costs a second cache line per wave and instruction; the last vector of a row ends with it, and two lanes may
+// store the same values; no row is shorter than a vector.  Where rows are not aligned neighbouring waves share a line, which L2
+// has to keep for both: the result is stored past the caches otherwise.
+template <bool BF16, int VE, RowLayout L>
 __global__ __launch_bounds__(RS_THREADS) void xent_grad_kernel(XentPlan p) {
-    constexpr int VE = BF16 ? 8 : 4;
     using Elem = std::conditional_t<BF16, uint16_t, float>;
     const int i = blockIdx.y;
     const uint32_t cols = (uint32_t)p.cols[i], cols_v = (cols + VE - 1) / VE;
@@ -170,7 +176,8 @@ __global__ __launch_bounds__(RS_THREADS) void xent_grad_kernel(XentPlan p) {
             if (++r64 >= (uint64_t)p.rows) break;
         }
         const uint32_t r = (uint32_t)r64;
-        const uint32_t c = cv * VE;
+        uint32_t c = cv * VE;
+        if constexpr (L != ROWS_WHOLE && VE > 1) c = c + VE <= cols ? c : cols - VE;
         const int32_t y = p.labels[i][r];
         const bool live = y >= 0 && y < p.total_cols;
         const float g = live ? p.grad[i][r] : 0.0f;
@@ -179,10 +186,10 @@ __global__ __launch_bounds__(RS_THREADS) void xent_grad_kernel(XentPlan p) {
         const Elem* src = static_cast<const Elem*>(p.logits[i]) + (int64_t)r * p.ld[i] + c;
         Elem* dst = static_cast<Elem*>(p.out[i]) + (int64_t)r * p.ld_out[i] + c;
         auto value = [&](float v, int e) { return (__expf(v - m) * inv - (e == yc ? 1.0f : 0.0f)) * g; };
-        if (WHOLE || c + VE <= cols) {
+        if constexpr (VE > 1) {
             // streaming load: the gradient pass is the last reader of the logits (measured 2 % faster than a cached load;
             // two items per lane and round, both loaded before either is worked on, 1 % slower than this)
-            const auto w = load16<ALIGNED>(src);
+            const auto w = load16<L>(src);
             std::conditional_t<BF16, u32x4, f32x4> o;
             if constexpr (BF16) {
 #pragma unroll
@@ -191,14 +198,11 @@ __global__ __launch_bounds__(RS_THREADS) void xent_grad_kernel(XentPlan p) {
 #pragma unroll
                 for (int e = 0; e < VE; ++e) o[e] = value(w[e], e);
             }
-            store16<ALIGNED>(dst, o);
+            store16<L>(dst, o);
+        } else if constexpr (BF16) {
+            *dst = (uint16_t)(pack_bf16(value(__uint_as_float((uint32_t)*src << 16), 0), 0.0f) & 0xFFFFu);
         } else {
-#pragma unroll
-            for (int e = 0; e < VE - 1; ++e)
-                if (c + e < cols) {
-                    if constexpr (BF16) dst[e] = (uint16_t)(pack_bf16(value(__uint_as_float((uint32_t)src[e] << 16), e), 0.0f) & 0xFFFFu);
-                    else dst[e] = value(src[e], e);
-                }
+            *dst = value(*src, 0);
         }
     }
 }
@@ -220,14 +224,21 @@ int32_t launch_xent_grad(const XentPlan& plan, hipStream_t stream) {
     const bool bf = plan.dtype == SBP_BF16;
     const int epv = bf ? 8 : 4;
     bool aligned = true, whole = true;
-    int64_t max_units = 0;
+    int32_t narrowest = INT32_MAX;
+    int64_t widest = 0;
     for (int i = 0; i < plan.k; ++i) {
+        if (plan.cols[i] == 0) continue;
         if (plan.ld[i] % epv || plan.ld_out[i] % epv) aligned = false;
         if (plan.cols[i] % epv) whole = false;
-        const int64_t units = ((int64_t)plan.cols[i] + epv - 1) / epv;
-        max_units = units > max_units ? units : max_units;
+        narrowest = plan.cols[i] < narrowest ? plan.cols[i] : narrowest;
+        widest = plan.cols[i] > widest ? plan.cols[i] : widest;
     }
-    max_units *= plan.rows;
+    // Vectors where rows hold one and there is enough to do, else one element per lane.  us, element / vectors, columns a device:
+    // bf16, 3 devices: 65536 rows of 9 7.6 / 5.1, of 31 20.1 / 10.6; 512 rows of 31 3.6 / 4.0; fp32: 65536 rows of 5 6.0 / 5.3.
+    // Vectors known to be whole and aligned: 1024 x 1000000 bf16, 8 devices, 685 against 742.
+    whole = whole && aligned;
+    const bool vec = whole || (narrowest >= epv && plan.rows * plan.total_cols >= (1 << 19));
+    const int64_t max_units = (vec ? (widest + epv - 1) / epv : widest) * plan.rows;
     int64_t bx = (max_units + RS_THREADS - 1) / RS_THREADS;
     // at most 65536 workgroups, grid-stride beyond (2 GB of bf16 logits: 0.68 ms; with one vector per lane and
     // half a million short-lived workgroups 0.74 ms, with 16384 workgroups 0.73 ms)
@@ -235,12 +246,10 @@ int32_t launch_xent_grad(const XentPlan& plan, hipStream_t stream) {
     if (bx > cap) bx = cap;
     if (bx < 1) bx = 1;
     const dim3 grid((uint32_t)bx, (uint32_t)plan.k);
-    if (bf && aligned && whole) hipLaunchKernelGGL((xent_grad_kernel<true, true, true>), grid, dim3(RS_THREADS), 0, stream, plan);
-    else if (bf && aligned) hipLaunchKernelGGL((xent_grad_kernel<true, true, false>), grid, dim3(RS_THREADS), 0, stream, plan);
-    else if (bf) hipLaunchKernelGGL((xent_grad_kernel<true, false, false>), grid, dim3(RS_THREADS), 0, stream, plan);
-    else if (aligned && whole) hipLaunchKernelGGL((xent_grad_kernel<false, true, true>), grid, dim3(RS_THREADS), 0, stream, plan);
-    else if (aligned) hipLaunchKernelGGL((xent_grad_kernel<false, true, false>), grid, dim3(RS_THREADS), 0, stream, plan);
-    else hipLaunchKernelGGL((xent_grad_kernel<false, false, false>), grid, dim3(RS_THREADS), 0, stream, plan);
+    void (*kern)(XentPlan);
+    if (bf) kern = whole ? xent_grad_kernel<true, 8, ROWS_WHOLE> : !vec ? xent_grad_kernel<true, 1, ROWS_ANY> : aligned ? xent_grad_kernel<true, 8, ROWS_ALIGNED> : xent_grad_kernel<true, 8, ROWS_ANY>;
+    else kern = whole ? xent_grad_kernel<false, 4, ROWS_WHOLE> : !vec ? xent_grad_kernel<false, 1, ROWS_ANY> : aligned ? xent_grad_kernel<false, 4, ROWS_ALIGNED> : xent_grad_kernel<false, 4, ROWS_ANY>;
+    hipLaunchKernelGGL(kern, grid, dim3(RS_THREADS), 0, stream, plan);
     return launch_status(__func__);
 }
 

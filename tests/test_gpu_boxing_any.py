@@ -10,8 +10,9 @@ from sbp_harness import DevTensor, TO_ABI, assert_bits_equal, sync
 
 pytestmark = pytest.mark.gpu
 SEED = wl.SEED_BASE + 1900
-# widths: one vector and a rest on some shards, an empty rest on others, less than a vector per shard, many rows of few vectors
-SHAPES = [(5, 17), (37, 259), (130, 1031), (7, 24), (1, 8191), (600, 33), (2, 8200)]
+# widths: one vector and a rest on some shards, an empty rest on others, less than a vector per shard, many rows of few vectors;
+# 34 columns on each of 8 and of 3 devices and 10 on each of 3: exact 8-byte vectors
+SHAPES = [(5, 17), (37, 259), (130, 1031), (7, 24), (1, 8191), (600, 33), (2, 8200), (50, 272), (9, 102), (50, 30)]
 
 
 def f32(tid, shape):
@@ -95,3 +96,60 @@ def test_cross_entropy_gradient_does_not_depend_on_the_pitch(cols, dtype):
         outs.append(d_d.host())
     for i in range(k):
         assert_bits_equal(outs[0][i], outs[1][i], f"{cols} {dtype} shard {i}")
+
+
+# enough elements for the vector kernels of the casts and of the gradient: rows of exactly one vector and one more, a last
+# vector that shares one, three and seven elements with its neighbour, one long row
+LARGE = [(40000, 9), (9000, 66), (700, 1031), (1, 600011)]
+
+
+@pytest.mark.parametrize("k", [2, 3, 8])
+@pytest.mark.parametrize("axis", [0, 1])
+def test_casts_of_many_elements(k, axis):
+    sig = orc.S0 if axis == 0 else orc.S1
+    for n, shape in enumerate(LARGE):
+        if axis == 1:
+            shape = (shape[0], shape[1] * k) if shape[0] > 1 else shape
+        T = f32(500 + n, shape)
+        d_in, d_out = DevTensor.from_host(orc.scatter(T, sig, k), *shape, sig), DevTensor.empty(*shape, np.uint16, orc.B, k)
+        sbp.sbp_boxing_cast(d_in.desc, TO_ABI[sig], d_out.desc, sbp.B, k)
+        parts = [wl.to_bf16_bits(f32(600 + 10 * n + i, shape)) for i in range(k)]
+        d_p, d_s = DevTensor.from_host(parts, *shape, orc.P_SUM), DevTensor.empty(*shape, np.float32, sig, k)
+        sbp.sbp_boxing_cast(d_p.desc, sbp.P_SUM, d_s.desc, TO_ABI[sig], k)
+        sync()
+        want = orc.bf16_round(T.astype(np.float64))
+        for j, got in enumerate(d_out.host()):
+            assert_bits_equal(got, want, f"gather {shape} k={k} copy {j}")
+        ref = np.zeros(shape, np.float32)
+        for p in parts:
+            ref = ref + orc.bf16_to_f64(p).astype(np.float32)
+        for j, (got, want) in enumerate(zip(d_s.host(), orc.scatter(ref, sig, k))):
+            assert_bits_equal(got, want, f"reduce {shape} k={k} shard {j}")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows,cols,pad", [(70000, 16, 0), (60000, 18, 3), (9000, 67, 0), (9000, 67, 7), (600, 2050, 0), (300, 8191, 1)])
+def test_cross_entropy_gradient_of_many_rows(rows, cols, pad, dtype):
+    """against the same call on a few of the rows, which takes one element per lane: the same bits; padding untouched"""
+    torch = __import__("torch")
+    k, few = 2, 20
+    L = f32(700, (rows, cols)) * np.float32(3.0)
+    if dtype == "bf16":
+        L = wl.to_bf16_bits(L)
+    y = (np.arange(rows, dtype=np.int32) * 7 % (cols + 1) - 1).reshape(rows, 1).astype(np.int32)
+    m, s, g = np.full((rows, 1), 2.0, np.float32), np.full((rows, 1), 9.0, np.float32), f32(702, (rows, 1))
+    ld = -(-cols // k) + pad if pad else 0
+
+    def grad(a, b):
+        n = b - a
+        one = lambda v: DevTensor.from_host([v[a:b]] * k, n, 1, orc.B).desc      # noqa: E731
+        labels = sbp.SbpTensor([torch.from_numpy(y[a:b].copy()).cuda() for _ in range(k)], n, 1, sbp.I32)
+        d_l, d_d = DevTensor.from_host(orc.scatter(L[a:b], orc.S1, k), n, cols, orc.S1, ld=ld), DevTensor.empty(n, cols, L.dtype, orc.S1, k, ld=ld)
+        sbp.sbp_xent_grad(d_l.desc, sbp.S(1), labels, one(m), one(s), one(g), d_d.desc, k)
+        sync()
+        return d_d.host()
+
+    whole = grad(0, rows)
+    for a in (0, rows // 2, rows - few):
+        for i, (got, want) in enumerate(zip(whole, grad(a, a + few))):
+            assert_bits_equal(np.ascontiguousarray(got[a:a + few]), want, f"{rows}x{cols}+{pad} {dtype} rows from {a}, shard {i}")

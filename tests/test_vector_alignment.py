@@ -11,8 +11,8 @@ from paper_2110_15032_amd import build
 
 # kernels whose template arguments say "any pitch", by mangled name, and the largest alignment that their elements give
 KERNELS = {
-    "softmax_kernels.hip": [("xent_grad_kernelILb1ELb0E", 2), ("xent_grad_kernelILb0ELb0E", 4)],
-    "boxing_kernels.hip": [("box_cast_reduce_kernelILb0E", 4), ("box_cast_gather_any_kernel", 4), ("box_reduce_any_kernel", 4), ("box_copy_any_kernelIt", 2), ("box_copy_any_kernelIj", 4)],
+    "softmax_kernels.hip": [("xent_grad_kernelILb1ELi8ELNS0_9RowLayoutE%d" % i, 2) for i in (1, 2)] + [("xent_grad_kernelILb0ELi4ELNS0_9RowLayoutE%d" % i, 4) for i in (1, 2)],
+    "boxing_kernels.hip": [("box_cast_reduce_kernelILi8ELb0E", 4), ("box_cast_gather_any_kernel", 4), ("box_reduce_any_kernel", 4), ("box_copy_any_kernelIt", 2), ("box_copy_any_kernelIj", 4)],
 }
 
 
