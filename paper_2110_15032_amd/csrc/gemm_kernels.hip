@@ -1608,26 +1608,36 @@ bool pingpong_pays(const GemmPlan& plan, int max_m, int max_n) {
 // 256 x 256 tiles (one workgroup per compute unit) or 128 x 128 ones (gemm_mfma_pipe16_kernel, two)?  A round of large
 // tiles takes about 1.35 times a full round of small ones, a round of small tiles that leaves half the places free about
 // 0.55 of a full one.  us, large / small tiles: 512 large ones 34.9 / 41.1, 320: 54.0 / 44.9, 200: 50.0 / 66.6, 192: 27.5 /
-// 30.0, 160: 42.7 / 51.5, 128: 42.0 / 37.5 and 72.1 / 59.6, 96: 24.2 / 18.9, 32: 14.8 / 8.6.
+// 30.0, 160: 42.7 / 51.5, 128: 42.0 / 37.5 and 72.1 / 59.6, 96: 24.2 / 18.9, 32: 14.8 / 8.6.  In long reductions the operand
+// traffic of small tiles tells.  From two full rounds of small ones on, a last round of large ones that is well filled wins: 368
+// large, 3072 long 147 / 175, 546 of 2624 192 / 230, 320 of 5952 284 / 324; but 304 of 1856 113 / 92, 276 of 1472 93 / 77.  So does one row of large
+// tiles where it replaces two: 92 large (200 rows), 16128 long 309 / 359, 84 (248 columns) of 15360 310 / 354; but 98 of 14400,
+// 1552 columns 303 / 217.
 bool large_tiles_pay(const GemmPlan& plan, int max_m, int max_n) {
-    const int64_t cu = compute_units();
-    const int64_t large = (tiles_of(plan, max_m, max_n, 256, 256) + cu - 1) / cu;
+    const int64_t cu = compute_units(), tiles = tiles_of(plan, max_m, max_n, 256, 256);
+    const int64_t large = (tiles + cu - 1) / cu;
     const int64_t small = tiles_of(plan, max_m, max_n, 128, 128), rest = small % (2 * cu);
+    const int k = longest_reduction(plan);
+    if (max_m > 128 && max_n > 128) {
+        if (k > 12000 && (max_m <= 256 || max_n <= 256)) return true;
+        if (k > 1024 && small >= 4 * cu && 10 * tiles >= (k > 2500 ? 6 : 7) * large * cu) return true;
+    }
     return 27 * large <= 20 * (small / (2 * cu)) + (rest == 0 ? 0 : rest <= cu ? 11 : 20);
 }
 
 // Too few 128 x 128 tiles for half the chip and a reduction long enough to be shared out: the waves of a workgroup split
 // the reduction.  us, 128 x 128 tile / waves splitting: 128 tiles of length 4096 35.6 / 24.7, 96 of 1024 11.9 / 10.1, 64 of
 // 125000 2333 / 985, 48 of 2048 18.5 / 9.1, 16 of 2048 18.7 / 8.5, 16 of 512 8.6 / 8.1; 168 of 1000 15.2 / 25.7, 256 of
-// 2048 23.0 / 27.8.  The largest tile that still occupies most of the chip: 128 x 64 (192 of them 10.1 against 12.0 with
+// 2048 23.0 / 27.8.  At any length under a GeLU by erfcf, whose code this kernel holds once and not unrolled over a tile of
+// registers (length 8 to 128: up to 64 tiles 7-8 / 5.5, 128 tiles 9-14 / 7.3).  The largest tile that still occupies most of the chip: 128 x 64 (192 of them 10.1 against 12.0 with
 // 64 x 64), 64 x 64 (160: 9.1, against 15.0 with 32 x 64), else 32 x 64 (80 of 64 x 64: 166, 160 of 32 x 64: 108).
 bool wavek_pays(const GemmPlan& plan, int max_m, int max_n) {
-    return 2 * tiles_of(plan, max_m, max_n, 128, 128) <= compute_units() && longest_reduction(plan) >= 512;
+    return 2 * tiles_of(plan, max_m, max_n, 128, 128) <= compute_units() && (longest_reduction(plan) >= 512 || plan.epilogue == EPI_GELU_ERF);
 }
 AnyTile wavek_tile(const GemmPlan& plan, int max_m, int max_n) {
     const int64_t cu = compute_units();
     if (plan.a_kc && max_m <= 32) return WAVEK_32;
-    if (max_m > 64 && 4 * tiles_of(plan, max_m, max_n, 128, 64) >= 3 * cu) return WAVEK_128;
+    if (max_m > 64 && 4 * tiles_of(plan, max_m, max_n, 128, 64) >= 3 * cu && plan.epilogue != EPI_GELU_ERF) return WAVEK_128;
     return !plan.a_kc || 2 * tiles_of(plan, max_m, max_n, 64, 64) >= cu ? WAVEK_64 : WAVEK_32;
 }
 // Rows at any alignment.  us, register kernel 128 x 128 / 64 x 64 / waves splitting, 32 x 64: 472 large tiles 14.7 / 16.7 /
@@ -1642,12 +1652,15 @@ AnyTile any_tile(const GemmPlan& plan, int max_m, int max_n) {
 // 128 x 128 / 64 x 64 / 32 x 32 with the waves splitting the reduction (rows x reduction x columns, devices):
 // 2000 x 750 x 1500, 4: 177 / 194 / 233; 1024 x 12500 x 512, 4 (128 large tiles): 906 / 472 / 578; 600 x 1000 x 500, 3 (240 of
 // 64 x 64): 79 / 29 / 30; 300 x 1000 x 300, 2 (50): 77 / 27 / 12; 8 x 256 x 12500, 4: 41 / 24 / 16; 256 x 8 x 12500, 4: 17 / 20 / 47.
+// Less than one stage of the 32 x 32 tile, 64 x 64 / 32 x 32: 25 to 63 long, up to 128 tiles of 64 x 64 1 / 0.75-0.95, 192 and more
+// 1 / 1.03-1.8 (1 / 0.9 up to 256 where 32 rows or columns are all there is).
 F32Tile f32_tile(const GemmPlan& plan, int max_m, int max_n) {
-    const int64_t cu = compute_units();
-    const bool deep = longest_reduction(plan) >= 64;   // the 32 x 32 tile's stage
+    const int64_t cu = compute_units(), tiles = tiles_of(plan, max_m, max_n, 64, 64);
+    const int k = longest_reduction(plan);
+    const bool narrow = max_m <= 32 || max_n <= 32;
     if (max_m > 64 && max_n > 64 && tiles_of(plan, max_m, max_n, 128, 128) >= cu) return F32_128;
-    if (deep && (max_m <= 32 || max_n <= 32)) return F32_32;
-    return !deep || 4 * tiles_of(plan, max_m, max_n, 64, 64) >= 3 * cu ? F32_64 : F32_32;
+    if (k < 64) return k > 24 && tiles <= (narrow ? cu : cu / 2) ? F32_32 : F32_64;
+    return narrow || 4 * tiles < 3 * cu ? F32_32 : F32_64;
 }
 int32_t launch_f32(const GemmPlan& plan, int max_m, int max_n, int32_t variant, hipStream_t stream) {
     const int tile = variant >= 45 ? variant - 45 : f32_tile(plan, max_m, max_n);
@@ -1674,6 +1687,31 @@ bool deep_pays(const GemmPlan& plan, int max_m, int max_n) {
     if (2 * tiles <= cu) return 8 * tiles >= 3 * cu && k <= 1536;
     return tiles <= (plan.a_kc && plan.b_kc ? 2 : 1) * cu;
 }
+// Few operations per result and few of them in all: one element per lane.  A lane's loop is then shorter than filling and draining a
+// tile, until the loads of a few lines per element tell (reduction-contiguous B: one line for each).  us, tile / one element:
+// fp32 1934 x 2 x 1, 3 devices 4.6 / 3.3; 32 x 3 x 1872 4.6 / 3.1; 873 x 22 x 412 4.9 / 6.9; bf16, aligned, 16 x 8 x 1128, 4 devices
+// 5.5 / 4.2; 104 x 16 x 1872, 2 devices 5.6 / 6.0; odd rows 10 x 6 x 3, 8 devices 4.0 / 3.3; fp32, B reduction-contiguous,
+// 69 x 24 x 1684, 8 devices 5.4 / 46.  GeLU by erfcf moves the line: 38 x 8 x 244, 4 devices 5.6 / 3.9.
+bool one_element_pays(const GemmPlan& plan, int max_m, int max_n, bool aligned_bf16) {
+    const int k = longest_reduction(plan);
+    if (k > 24 || max_m > 65535 * 16) return false;
+    const int64_t out = (int64_t)max_m * max_n * plan.groups, ops = out * k;
+    const bool odd_bf16 = plan.in_dtype == SBP_BF16 && !plan.f32_operand && !aligned_bf16;
+    if (plan.epilogue != SBP_EPI_NONE) return ops <= (plan.b_kc && k > 8 ? 1 << 21 : odd_bf16 ? 1 << 22 : 1 << 23);
+    if (odd_bf16) return k <= 10 && out <= 1 << 19 && ops <= 1 << 20;
+    if (aligned_bf16) return k <= 16 && out <= 1 << 19 && ops <= (plan.b_kc ? 1 << 21 : 1 << 22);
+    return k <= 16 && out <= 1 << 20 && ops <= (plan.b_kc && k > 4 ? 1 << 20 : 1 << 21);
+}
+
+// 128 x 128 tiles of gemm_mfma_kernel (two 64-deep stages) where those of 256 x 256 would be mostly empty: whole 64-element steps,
+// up to 128 rows or columns, and not one round of such tiles with a long reduction, which gemm_mfma_pipe16_kernel takes (two
+// workgroups of either fit a compute unit; alone there, only four stages cover the loads).  us, this / pipe16: 16 x 448 x 40 7.4 /
+// 9.2; 312 x 384 x 40 7.4 / 8.3; 8 x 12736 x 5360, 8 devices (336 tiles) 226 / 273; 120 x 11392 x 8144, 8 devices 287 / 334; 8032 x
+// 4096 x 8, 8 devices 98 / 108; but 2168 x 5952 x 8, 8 devices (136 tiles) 63 / 57, 4392 x 16320 x 24, 4 devices 236 / 172.
+bool two_stages_pay(const GemmPlan& plan, int max_m, int max_n) {
+    const int64_t cu = compute_units(), tiles = tiles_of(plan, max_m, max_n, 128, 128);
+    return (max_m <= 128 || max_n <= 128) && !(2 * tiles > cu && tiles <= cu && longest_reduction(plan) >= 1024);
+}
 int32_t launch_deep(const GemmPlan& plan, int max_m, int max_n, hipStream_t stream) {
     return launch_gemm_deep(plan, max_m, max_n, tile_order_for(tiles_along(max_m, 128), tiles_along(max_n, 128)), stream);
 }
@@ -1696,9 +1734,10 @@ int32_t launch_chosen(const GemmPlan& plan, int max_m, int max_n, int32_t varian
             return plan.f32_operand == 2 ? launch_split<true>(plan, max_m, max_n, variant, stream) : launch_split<false>(plan, max_m, max_n, variant, stream);
         }
         if (variant > 1) return SBP_ERR_UNSUPPORTED;
-        return variant == 0 ? launch_f32(plan, max_m, max_n, variant, stream) : launch_generic(plan, max_m, max_n, stream);
+        if (variant == 1 || one_element_pays(plan, max_m, max_n, false)) return launch_generic(plan, max_m, max_n, stream);
+        return launch_f32(plan, max_m, max_n, variant, stream);
     }
-    if (plan.in_dtype == SBP_F32 && (variant == 0 || (variant >= 45 && variant <= 47)))
+    if (plan.in_dtype == SBP_F32 && ((variant == 0 && !one_element_pays(plan, max_m, max_n, false)) || (variant >= 45 && variant <= 47)))
         return plan.out_dtype == SBP_F32 ? launch_f32(plan, max_m, max_n, variant, stream) : SBP_ERR_DTYPE;
     const bool fast = mfma_ok(plan);
     if (variant == 1 || !fast) {
@@ -1736,6 +1775,7 @@ int32_t launch_chosen(const GemmPlan& plan, int max_m, int max_n, int32_t varian
     }
     if (variant >= 40 && variant <= 44) return launch_any(plan, max_m, max_n, variant - 40, direct, stream);
     if (variant == 48) return direct ? launch_deep(plan, max_m, max_n, stream) : SBP_ERR_UNSUPPORTED;
+    if (variant == 0 && one_element_pays(plan, max_m, max_n, direct)) return launch_generic(plan, max_m, max_n, stream);
     if (!direct) {
         if (variant > 1) return SBP_ERR_UNSUPPORTED;
         return launch_any(plan, max_m, max_n, any_tile(plan, max_m, max_n), false, stream);
@@ -1745,9 +1785,19 @@ int32_t launch_chosen(const GemmPlan& plan, int max_m, int max_n, int32_t varian
         // unit when the reduction length allows it, on the 16x16x32 matrix instruction; 128 x 128 tiles where those
         // finish sooner, with eight waves where one such tile per compute unit is all there is; waves splitting the
         // reduction where no tile of these sizes fills the chip.
-        if (deep_pays(plan, max_m, max_n)) return launch_deep(plan, max_m, max_n, stream);
-        if (wavek_pays(plan, max_m, max_n)) return launch_any(plan, max_m, max_n, wavek_tile(plan, max_m, max_n), true, stream);
-        variant = !large_tiles_pay(plan, max_m, max_n) ? 8 : !k128 ? 9 : pingpong_pays(plan, max_m, max_n) ? 21 : 16;
+        const bool steps64 = k64 && rows_of_8(plan), two_stages = steps64 && two_stages_pay(plan, max_m, max_n);
+        // two rounds of one workgroup per compute unit against one of two: 280 tiles, 88 rows, length 704 22.4 / 18.3 us
+        const bool one_round = tiles_of(plan, max_m, max_n, 128, 128) <= compute_units() || longest_reduction(plan) >= 2048;
+        if (deep_pays(plan, max_m, max_n) && (one_round || !two_stages)) return launch_deep(plan, max_m, max_n, stream);
+        if (wavek_pays(plan, max_m, max_n)) {
+            // us, 128 x 128 tile with two stages / waves splitting: 70 tiles, 72 columns, length 768 9.9 / 11.4, 120 of 112 columns,
+            // 512 8.6 / 10.0; but 96 of 16 rows, 960 14.4 / 8.3
+            const bool few = 4 * tiles_of(plan, max_m, max_n, 128, 128) <= compute_units() || longest_reduction(plan) >= 1024;
+            if (few || max_m <= 64 || max_n <= 64 || !two_stages)
+                return launch_any(plan, max_m, max_n, wavek_tile(plan, max_m, max_n), true, stream);
+        }
+        if (two_stages) variant = 4;
+        else variant = !large_tiles_pay(plan, max_m, max_n) ? 8 : !k128 ? 9 : pingpong_pays(plan, max_m, max_n) ? 21 : 16;
     }
     if (!k64 && variant != 8 && variant != 9) return SBP_ERR_UNSUPPORTED;
     switch (variant) {
