@@ -564,7 +564,8 @@ int32_t launch_out(const GemmPlan& plan, int max_m, int max_n, int order, hipStr
     }
     if constexpr (DIRECT)
         if (plan.epilogue == SBP_EPI_GELU) return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_GELU, uint16_t>(plan, max_m, max_n, order, st);
-    if (plan.epilogue == EPI_GELU_ERF) return launch_layout<BM, BN, NW, DIRECT, EPI_GELU_ERF, uint16_t>(plan, max_m, max_n, order, st);
+    // rows of any pitch are erfcf's; a forced register kernel on others gets the more accurate form as well
+    if (plan.epilogue == EPI_GELU_ERF || plan.epilogue == SBP_EPI_GELU) return launch_layout<BM, BN, NW, DIRECT, EPI_GELU_ERF, uint16_t>(plan, max_m, max_n, order, st);
     if (plan.epilogue != SBP_EPI_NONE) return SBP_ERR_UNSUPPORTED;
     return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_NONE, uint16_t>(plan, max_m, max_n, order, st);
 }

@@ -250,3 +250,39 @@ def test_extents_near_the_largest_are_refused(rows):
         sbp.sbp_matmul(sbp.SbpTensor([x], rows, 1, sbp.F32), sbp.B, sbp.SbpTensor([w], 1, 1, sbp.F32), sbp.B, sbp.SbpTensor([y], rows, 1, sbp.F32), sbp.B, 1)
     assert e.value.status == -9
     sync()
+
+
+ROUNDED = [(v, a, tx, tw) for v in (0, 40, 41, 42, 43, 44) for a in (True, False) for tx in (0, 1) for tw in (0, 1)
+           if not (v == 40 and tx) and not (v == 42 and not a)]   # 40: reduction-contiguous left operand; 42: aligned rows
+
+
+@pytest.mark.parametrize("epilogue", [sbp.EPI_NONE, sbp.EPI_GELU])
+@pytest.mark.parametrize("variant,aligned,tx,tw", ROUNDED)
+@pytest.mark.parametrize("M,kk,N", [(1, 9, 3), (33, 65, 65), (64, 544, 72), (130, 1024, 131)])
+def test_bf16_rounded_results_any_shape_and_pitch(M, kk, N, variant, aligned, tx, tw, epilogue):
+    """results rounded to bf16, plain and under GeLU, at an odd row pitch: the additions of the waves' partial tiles, the
+    store of eight columns a lane and its ragged ends.  Bar: one rounding, half a step
+    of 8 significant bits, at most 2^-8 of the value, and the fp32 sums before it."""
+    k = 2
+    X, W = bf16(40, (M, kk)), bf16(41, (kk, k * N), 0.2)
+    Xs, Ws = orc.scatter(X, orc.B, k), orc.scatter(W, orc.S1, k)
+    ref, _ = orc.matmul_sbp([values(x) for x in Xs], orc.B, [values(w) for w in Ws], orc.S1)
+    to, extra = (8, 0) if aligned else (2, 1)
+    got, _ = run(Xs, orc.B, Ws, orc.S1, M, kk, k * N, k, tx, tw, pitch(Xs, tx, to, extra), pitch(Ws, tw, to, extra), pitch(ref, 0, 2, 1), variant=variant, epilogue=epilogue)
+    for i in range(k):
+        r = orc.gelu(ref[i]) if epilogue == sbp.EPI_GELU else ref[i]
+        assert_matmul_close(got[i], r, 2.0 ** -8 + 1e-4, f"{M}x{kk}x{N} trans=({tx},{tw}) v{variant} epilogue {epilogue} shard {i}")
+
+
+@pytest.mark.parametrize("epilogue", [sbp.EPI_NONE, sbp.EPI_GELU])
+@pytest.mark.parametrize("k,M,kk,N,extra", [(8, 500, 37, 500, 1), (3, 1000, 640, 904, 0), (2, 40, 640, 1000, 0), (8, 72, 704, 4400, 0), (4, 100, 384, 3000, 0), (2, 1304, 200, 2000, 0)])
+def test_bf16_rounded_results_default_choice(k, M, kk, N, extra, epilogue):
+    """one shape for each kernel that the default choice takes for rounded results of these sizes: 128 x 128 tiles through
+    registers, two wave groups over the reduction, the waves splitting it, two 64-deep stages (two shapes), four 32-deep ones"""
+    X, W = bf16(42, (M, kk)), bf16(43, (kk, k * N), 0.2)
+    Xs, Ws = orc.scatter(X, orc.B, k), orc.scatter(W, orc.S1, k)
+    got, _ = run(Xs, orc.B, Ws, orc.S1, M, kk, k * N, k, 0, 0, pitch(Xs, 0, 8, extra), pitch(Ws, 0, 8, extra), epilogue=epilogue)
+    for i in range(k):
+        ref = values(X) @ values(Ws[i])
+        r = orc.gelu(ref) if epilogue == sbp.EPI_GELU else ref
+        assert_matmul_close(got[i], r, 2.0 ** -8 + 1e-4, f"{M}x{kk}x{N} epilogue {epilogue} shard {i}")
