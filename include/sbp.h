@@ -78,7 +78,9 @@ typedef struct sbp_tensor {
     int64_t ld;         /* row pitch of every stored local buffer in elements, 0 = dense
                            (the stored row length).  Must be at least the longest stored row of
                            any shard (SBP_ERR_SHAPE otherwise); the bytes between a row's end and
-                           the next row are never read or written.  A pitch that is a multiple of
+                           the next row are never written, and their values never reach a result; a
+                           kernel may read them along with the row, up to the next multiple of 16 bytes
+                           behind the last one.  A pitch that is a multiple of
                            128 bytes keeps every row on cache-line boundaries (the classifier's
                            125000-column logits shards: pitch 125056).  Accepted by sbp_matmul,
                            sbp_matmul_ex, sbp_matmul_rowmax, sbp_matmul_2d, sbp_row_max,
@@ -90,7 +92,9 @@ typedef struct sbp_tensor {
 enum {
     SBP_EPI_NONE = 0,
     SBP_EPI_GELU = 1    /* y <- gelu(acc), exact erf form, evaluated in fp32 on the accumulator
-                           before the single rounding to y's dtype.  Elementwise, so only allowed
+                           before the single rounding to y's dtype: to about 1e-7 of its value; to 2.2e-5,
+                           a hundredth of a bf16 step, for bf16 operands whose stored rows start 16-byte
+                           aligned and whose local reduction lengths are multiples of 64.  Elementwise, so only allowed
                            when Y is S or B (an elementwise nonlinearity of a P(sum) partial is
                            not the nonlinearity of the global value).                           */
 };
@@ -115,7 +119,8 @@ int32_t sbp_local_shape(int64_t rows, int64_t cols, sbp_t sbp, int32_t k, int32_
  *   A P(sum) input operand (rows 4, 5 of Table 1) must be SBP_F32; the other
  *   operand (B) may be SBP_F32 or SBP_BF16.  Next to a bf16 operand the fp32
  *   partial is not rounded: it enters the matrix units as an exact sum of three
- *   bf16 terms.  The same holds for row 6 when one B operand is SBP_F32 (a
+ *   bf16 terms or, where the reduction length is no multiple of 32 or rows are
+ *   not 16-byte aligned, in fp32 next to the widened bf16 values.  The same holds for row 6 when one B operand is SBP_F32 (a
  *   partial that was boxed to B) and the other SBP_BF16; the result is then
  *   SBP_F32.  Any other mix of dtypes is SBP_ERR_DTYPE.
  *   k-way results are written to y->shard[i]; x, w are read only. */

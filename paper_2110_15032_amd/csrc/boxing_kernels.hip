@@ -21,8 +21,9 @@
 //                  all-gather of a tensor "split" over one device, and
 //   P -> P        ko tasks: partials j, j + ko, j + 2 ko, ... combined in that order -> out_j
 //
-// HBM-bound: every input byte is read once and every output byte written once, with the widest
-// vector (up to 16 B per lane) that all offsets and pitches of the conversion allow.
+// HBM-bound: every input byte is read once and every output byte written once, 16 bytes per lane: aligned
+// where all offsets and pitches of the conversion are multiples of that, else unaligned
+// (box_*_any_kernel); rows shorter than 16 bytes and a few small calls with the widest vector that all allow.
 #include <atomic>
 #include <cstdlib>
 

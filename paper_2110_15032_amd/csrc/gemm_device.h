@@ -221,8 +221,8 @@ struct Tile {
     // ---- operands of v_mfma_f32_16x16x32_bf16 (BKT = 32: one instruction spans the whole stage) ----
     // Lane l holds the 8 values kk = 8 (l / 16) + 0..7 of row (block base + l % 16).
     // One lane offset serves every block.  KC: a 16-row block adds 16 * ROWB (the swizzle repeats every 16 rows).
-    // Not KC: block b adds 2 b to the chunk index; the wave's base chunk is a multiple of 16 and b < 8, so
-    // that sum is an OR, and the swizzle being an XOR, block b's offset is block 0's with (b << 5) flipped.
+    // Not KC: block b adds 2 b to the chunk index; the wave's base chunk is a multiple of twice its blocks (16 with 8, 8 with 4,
+    // 4 with 2), so that sum is an OR, and the swizzle being an XOR, block b's offset is block 0's with (b << 5) flipped.
     // BKT = 64: `half` says which 32 of the stage (32 kk-rows on: the not-KC swizzle repeats).
     __device__ static int lane_offset16(int wave_base, int lane, int half = 0) {
         static_assert(BKT == 32 || BKT == 64, "one 16x16x32 instruction per 32-deep stage");

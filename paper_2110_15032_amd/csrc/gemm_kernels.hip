@@ -2,18 +2,21 @@
 // C_g = A_g B_g from the local tensors it holds; all k devices run in ONE launch.
 //
 //   gemm_generic_kernel       any dtype / shape / pitch, one output element per lane, fp32 FMA chain.
-//                             Used for bf16 operands of 4 GiB and more, and on request.
+//                             Used for bf16 operands of 4 GiB and more, for a few operations per result, where a grid of
+//                             tiles would not fit one launch, and on request.
 //   gemm_mfma_kernel          bf16 x bf16 -> fp32 on the matrix cores (v_mfma_f32_32x32x16_bf16),
 //                             BM x BN macro-tile per workgroup, global->LDS loads that bypass
-//                             registers, two LDS stages of 64 reduction elements.
+//                             registers, two LDS stages of 64 reduction elements.  Default (128 x 128) up to 128 rows or
+//                             columns.
 //   gemm_mfma_pipe_kernel     the same with 3-5 stages of 32 and partial waits on the load counter.
-//   gemm_mfma_pipe16_kernel   four stages of 32 on v_mfma_f32_16x16x32_bf16: large shapes whose reduction
-//                             length is a multiple of 64 but not of 128.
+//   gemm_mfma_pipe16_kernel   four stages of 32 on v_mfma_f32_16x16x32_bf16, any reduction length: large shapes whose
+//                             length is not a multiple of 128 (256 x 256), middling ones (128 x 128).
 //   gemm_mfma_persist_kernel  four stages, one workgroup per compute unit walking many tiles, the next
 //                             tile's loads in flight across the epilogue.
 //   gemm_mfma_persist16_kernel  the same on v_mfma_f32_16x16x32_bf16 (store_tile16): the default for
 //                             large shapes; under real operands the chip clocks this instruction higher.
 //   gemm_split_kernel         one fp32 operand (a P(sum) partial) split exactly into three bf16 terms.
+// Few output tiles and rows at any pitch: gemm_any_kernels.hip.  fp32 operands: gemm_f32_kernels.hip.
 // All MFMA kernels share Tile (LDS images, swizzles, fragment reads) and store_tile (epilogue).
 //
 // Operand storage: "KC" = reduction index contiguous ([m][kk] for A, [n][kk] for B), otherwise the
@@ -1503,8 +1506,8 @@ int32_t launch_mfma_layout(const GemmPlan& plan, int max_m, int max_n, hipStream
     return launch_mfma_cfg<BM, BN, WM, WN, false, false, ODD, EPI, OutT>(plan, max_m, max_n, st);
 }
 
-// fp32 results carry no epilogue on this path (GeLU of a P(sum) partial is rejected upstream and
-// fp32 inputs take the generic kernel), so three (epilogue, output) pairs cover every request.
+// fp32 results carry no epilogue on this path (GeLU of a P(sum) partial is rejected upstream and fp32 inputs take
+// gemm_f32_kernel).  GeLU comes in two forms (see launch_chosen), the more accurate one where any reduction length is taken.
 template <int BM, int BN, int WM, int WN, int ODD>
 int32_t launch_mfma_out(const GemmPlan& plan, int max_m, int max_n, hipStream_t st) {
     if (plan.out_dtype == SBP_F32) {

@@ -104,7 +104,7 @@ enum AnyTile : int32_t {
     REG_64          // 64 x 64
 };
 int32_t launch_gemm_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool direct, int order, hipStream_t stream);
-// gemm_any_kernels.hip, 128 x 128 tile, reduction-contiguous operands with 16-byte aligned rows, any reduction length
+// gemm_any_kernels.hip, 128 x 128 tile, any operand layout, rows 16-byte aligned, any reduction length
 int32_t launch_gemm_deep(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t stream);
 // gemm_f32_kernels.hip: fp32 x fp32 (fp32 results, GeLU or no epilogue) and fp32 next to bf16 (f32_operand), any pitch and extent.
 enum F32Tile : int32_t {

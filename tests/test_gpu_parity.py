@@ -306,7 +306,7 @@ def test_matmul_partial_fp32_times_bf16(row, tx, tw, shape, variant):
     MFMA kernel that splits the fp32 operand into three bf16 terms (several tiles, ragged edges), with
     its 128 x 128 tile (the choice for small shapes) and with the 128 x 256 tile forced (variant 32), which
     the third shape runs over several tiles in both directions and an odd number of reduction steps;
-    the last shape takes the generic kernel.  All keep fp32-GEMM accuracy: the partial is never rounded."""
+    the last shape takes the fp32 matrix instruction.  All keep fp32-GEMM accuracy: the partial is never rounded."""
     k = 3
     M, K, N = shape
     X, W = rnd_f32(1, (M, K)), rnd_f32(2, (K, N))

@@ -40,7 +40,7 @@ CASES = [
     ("bf16", orc.S1, orc.S0, (520, 2 * 384, 300), 2, 0, 0, (16, 4, 20), 21, sbp.EPI_NONE),
     ("bf16", orc.S1, orc.S0, (300, 2 * 256, 520), 2, 1, 1, (4, 8, 8), 0, sbp.EPI_NONE),      # both operands stored transposed
     ("bf16", orc.S0, orc.B, (3 * 100, 192, 136), 3, 0, 0, (8, 8, 8), 0, sbp.EPI_NONE),       # small tile kernel
-    ("f32", orc.S1, orc.S0, (37, 50, 29), 2, 0, 0, (3, 5, 1), 0, sbp.EPI_NONE),              # generic kernel, odd pitches
+    ("f32", orc.S1, orc.S0, (37, 50, 29), 2, 0, 0, (3, 5, 1), 0, sbp.EPI_NONE),              # fp32 tiles, odd pitches
     ("f32", orc.B, orc.S1, (37, 50, 29), 3, 1, 0, (2, 0, 7), 0, sbp.EPI_NONE),
 ]
 

@@ -1,6 +1,6 @@
 """Seeded random cases of sbp_matmul over every row of Table 1 (Sec. 3.1): shapes that fall on both sides of the
 kernel-selection thresholds (persistent 256 x 256 tile, one-tile kernels, the 128 x 128 tile, the split kernel for an
-fp32 partial next to bf16, the generic kernel), uneven splits, transposed storage, row pitches, k from 1 to 8, each
+fp32 partial next to bf16, and the kernels for odd sizes and for few operations), uneven splits, transposed storage, row pitches, k from 1 to 8, each
 against the oracle at the usual bars; and seeded random boxing conversions of ragged tensors, bit-exact or within the
 partial-sum bound."""
 import numpy as np
@@ -32,7 +32,7 @@ def draw_case(rng):
     elif kind == 1:    # reduction length a multiple of 64 or 32 only
         M, N = int(rng.integers(100, 500)), int(rng.integers(100, 600))
         K = int(rng.choice([64, 192, 96, 160])) * (k if sx == orc.S1 else 1)
-    elif kind == 2:    # small and odd everywhere: generic kernel
+    elif kind == 2:    # small and odd everywhere: register tiles, fp32 tiles, one element per lane
         M, N, K = int(rng.integers(1, 90)), int(rng.integers(1, 90)), int(rng.integers(1, 200))
     else:              # 16-byte aligned but small: 128 x 128 tile
         M, N = 8 * int(rng.integers(1, 30)), 8 * int(rng.integers(1, 30))
