@@ -304,14 +304,21 @@ __device__ inline float max3f(float a, float b, float c) {
     return r;
 }
 
+// max(x, 0), NaN for NaN (v_max3_f32 would give 0)
+__device__ inline float relu_nan(float x) {
+    float r;
+    asm("v_maximum3_f32 %0, %1, 0, 0" : "=v"(r) : "v"(x));
+    return r;
+}
+
 // gelu(x) = 0.5 x erfc(-x / sqrt 2), with erfc(z) = t 2^(-z^2 log2 e + P(t)), t = 1 / (1 + z / 2), for
 // z = |x| / sqrt 2 >= 0.  This is the form of the classic Chebyshev fit of erfc ("erfcc" in Numerical
 // Recipes), which keeps its RELATIVE accuracy in the tail, so gelu of a negative argument does too.
 // P is a degree-5 minimax fit of log2(erfc(z) e^(z^2) / t) on 0 <= z <= 14 made for this kernel (the
 // published fit has degree 9 and 1e-7; this one costs four FMAs less).  Relative error of gelu below
 // 2.2e-5 for every x whose result is a normal fp32 number, a hundredth of a bf16 rounding step.  One rcp,
-// one exp2, one max (max3f: fmaxf would add a canonicalising instruction), eight FMA/mul, no branch, no select.
-// The argument is clamped to +-14 (erfc underflows before that), so +-inf give +inf and -0.
+// one exp2, one max (relu_nan: fmaxf would add a canonicalising instruction and lose NaN), eight FMA/mul, no branch, no select.
+// The argument is clamped to +-14 (erfc underflows before that), so +-inf give +inf and -0; NaN gives NaN.
 __device__ inline float gelu_fast(float x) {
     const float xc = __builtin_amdgcn_fmed3f(x, -14.0f, 14.0f);
     const float t = __builtin_amdgcn_rcpf(fmaf(fabsf(xc), 0.35355339059327373f, 1.0f));
@@ -324,7 +331,7 @@ __device__ inline float gelu_fast(float x) {
     const float w = xc * 0.84932180028801905f;               // sqrt(log2(e) / 2): w^2 = z^2 log2 e
     const float e = t * __builtin_amdgcn_exp2f(fmaf(-w, w, p));   // 0.5 erfc(|x| / sqrt 2)
     // 0.5 x (1 + erf) = max(x, 0) - |x| 0.5 erfc(|x| / sqrt 2) for either sign; nothing cancels for x < 0
-    return fmaf(-fabsf(xc), e, max3f(x, 0.0f, 0.0f));
+    return fmaf(-fabsf(xc), e, relu_nan(x));
 }
 
 // 0.5 x (1 + erf(x / sqrt 2)) written with erfc so that the negative tail keeps its relative accuracy; NaN stays NaN

@@ -1768,7 +1768,7 @@ int32_t launch_chosen(const GemmPlan& plan, int max_m, int max_n, int32_t varian
         return launch_mfma_layout<256, 256, 2, 4, 204, EPI_ROWMAX, uint16_t>(plan, max_m, max_n, stream);
     }
     // GeLU: gelu_fast on the shapes whose steps are 64 reduction elements, with 16-byte aligned rows of 8 elements or more; on
-    // every other one the erfcf form of the one-element-per-lane kernel, accurate to fp32 and NaN for NaN.  us, gelu_fast /
+    // every other one the erfcf form of the one-element-per-lane kernel, accurate to fp32.  us, gelu_fast /
     // erfcf / no GeLU: [777, 1000] x [1000, 1000], 3 devices 16.4 / 19.4 / 14.9; [8192, 1000] x [1000, 4096], 2 devices
     // 142 / 199 / 131; [1500, 1501] x [1501, 2501], 2 devices 44.6 / 49.4 / 43.2.
     if (plan.epilogue == SBP_EPI_GELU && !(direct && k64 && rows_of_8(plan))) {

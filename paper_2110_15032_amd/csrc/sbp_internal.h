@@ -75,7 +75,7 @@ struct GemmShard {
 };
 // internal epilogue code next to the public SBP_EPI_*: store, and fold every stored row into rowmax
 constexpr int32_t EPI_ROWMAX = 2;
-// GeLU through erfcf (about 1e-7) where SBP_EPI_GELU is the fit of gelu_fast (2.2e-5, NaN to 0): see launch_gemm
+// GeLU through erfcf (about 1e-7) where SBP_EPI_GELU is the fit of gelu_fast (2.2e-5): see launch_chosen
 constexpr int32_t EPI_GELU_ERF = 3;
 struct GemmPlan {
     GemmShard s[SBP_MAX_K];

@@ -286,3 +286,21 @@ def test_bf16_rounded_results_default_choice(k, M, kk, N, extra, epilogue):
         ref = values(X) @ values(Ws[i])
         r = orc.gelu(ref) if epilogue == sbp.EPI_GELU else ref
         assert_matmul_close(got[i], r, 2.0 ** -8 + 1e-4, f"{M}x{kk}x{N} epilogue {epilogue} shard {i}")
+
+
+@pytest.mark.parametrize("variant", [0, 1, 3, 4, 6, 7, 8, 9, 12, 16, 21, 40, 41, 42, 43, 44, 48])
+def test_gelu_of_nan_and_infinity(variant):
+    """whole steps on aligned rows, every kernel: a NaN accumulator gives NaN, +inf gives +inf, and the rows beside them do not change"""
+    k, M, K, N = 2, 300, 128, 2 * 264
+    X, W = bf16(50, (M, K)), bf16(51, (K, N), 0.2)
+    W[0] = wl.to_bf16_bits(np.ones((1, N)))[0]
+    plain, (nan, inf) = X.copy(), (13, 170)
+    X[nan, 5], X[inf, 0] = 0x7FC0, 0x7F80
+    Ws = orc.scatter(W, orc.S1, k)
+    a, _ = run(orc.scatter(X, orc.B, k), orc.B, Ws, orc.S1, M, K, N, k, 0, 0, 0, 0, variant=variant, epilogue=sbp.EPI_GELU)
+    b, _ = run(orc.scatter(plain, orc.B, k), orc.B, Ws, orc.S1, M, K, N, k, 0, 0, 0, 0, variant=variant, epilogue=sbp.EPI_GELU)
+    for i in range(k):
+        assert np.isnan(a[i][nan]).all(), f"v{variant}: NaN"
+        assert (a[i][inf] == np.inf).all(), f"v{variant}: +inf"
+        rest = np.delete(np.arange(M), [nan, inf])
+        assert np.array_equal(a[i][rest], b[i][rest]), f"v{variant}: other rows"
