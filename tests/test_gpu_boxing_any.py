@@ -128,7 +128,8 @@ def test_casts_of_many_elements(k, axis):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("rows,cols,pad", [(70000, 16, 0), (60000, 18, 3), (9000, 67, 0), (9000, 67, 7), (600, 2050, 0), (300, 8191, 1)])
+@pytest.mark.parametrize("rows,cols,pad", [(70000, 16, 0), (60000, 18, 3), (9000, 67, 0), (9000, 67, 7), (600, 2050, 0), (300, 8191, 1),
+                                           (60000, 18, 7), (9000, 67, 6), (300, 8191, 8)])   # the last three: aligned rows, broken last vectors
 def test_cross_entropy_gradient_of_many_rows(rows, cols, pad, dtype):
     """against the same call on a few of the rows, which takes one element per lane: the same bits; padding untouched"""
     torch = __import__("torch")
