@@ -397,20 +397,30 @@ __global__ __launch_bounds__(256, 2) void gemm_reg_kernel(GemmPlan p, int tm, in
 // of four waves (64 x 64 each) take the two 32-deep halves of every 64-deep stage; four stages, one barrier a stage, the
 // two partial tiles added through LDS.
 //   * Two waves per SIMD cover each other's waits, which one workgroup of gemm_mfma_pipe16_kernel per compute unit does not.
-//   * A stage reads 128 consecutive bytes of a reduction-contiguous row, not 64: by the time the next 32-deep stage asks for the
-//     other half of a 128-byte line it has left the L1, so that every line came from L2 twice.
-// Bound by a compute unit's load path: 32 KB a stage take 0.56 us at 4096 x 512 results (8 devices, 1 PFLOP/s), 0.60 where rows
-// lie 250112 bytes apart and 0.95 where they lie 250000 apart and every piece straddles two lines.  Neither more stages in
-// flight (eight of 32) nor LDS reads spread over the whole stage changed these.  Feature gradient of a classifier, 8 devices,
-// [1024, 125000] x [125000, 512], us: 1523 -> 1177 and, with 250000-byte rows, 2428 -> 1885.
+//   * A stage reads one cache line of a reduction-contiguous row, whole, wherever the row starts (Tile::line_offset): pieces of
+//     128 bytes that straddle two lines cost the load path twice (all lines in L2, rows 250000 bytes apart: 0.58 us a stage
+//     against 0.35 with rows on lines).  A fragment then comes from two neighbouring stages, so that one stage less is in
+//     flight, which costs nothing: a compute unit's load path is no faster with more.
+//   * The load path returns in order.  A stage of 32 KB takes 0.21 us when all of it is in L2 and 0.58 us when any of it comes from
+//     HBM, whatever the number of stages in flight; operand tiles shared by the workgroups of an XCD are in L2 for all but the
+//     first, but all of them wait for that one.  So the lines of four stages are touched at once, three stages ahead of their
+//     loads, every workgroup the part that is its share among those that read the same tile: one wait for HBM in four stages.
+// Feature gradient of a classifier, 8 devices, [1024, 125000] x [125000, 512], us: 1477 -> 1093 (left rows on lines), with both
+// rows 250000 bytes apart 1915 -> 1073; without the touches 1168.  [1024, 16384] x [16384, 512] 160 -> 150; [777, 1000] x [1000, 1000],
+// 3 devices, 15.5 -> 14.6.  Of the 0.54 us a stage that are left the multiplication and its LDS reads take 0.36.
 template <bool A_KC, bool B_KC, int EPI, typename OutT>
 __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int tn, int order) {
     constexpr int BM = 128, BN = 128, BKT = 64, NT = 512, NST = 4, FM = 4, FN = 4;
     using TA = Tile<BM, A_KC, NT, BKT, true>;
     using TB = Tile<BN, B_KC, NT, BKT, true>;
     constexpr int NVM = TA::PER_THREAD + TB::PER_THREAD, STAGE = TA::BYTES + TB::BYTES;
+    constexpr bool LINES = A_KC || B_KC;
+    // Lines are touched this many stages ahead (5, 6 and 8 measured: within 2 % with whole lines, 2 to 12 % slower without), as long
+    // as a workgroup's share of four stages is not more: us, share, with / without: 192 lines 1073 / 1168 and 150.3 / 158.7, 256
+    // 16.9 / 16.0, 288 182.7 / 178.3; neither operand reduction-contiguous 192 148.5 / 159.9, 288 165.5 / 176.3.
+    constexpr int TOUCH_DIST = 7, TOUCH_MAX = LINES ? 224 : 320;
     static_assert(NST * STAGE == 8 * FM * FN * 1024, "the partial tiles fill the stages");
-    __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE];
+    __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE + 256];   // the last 256 bytes: what the touches bring
 
     const TileCoord tc = map_tile(blockIdx.x, gridDim.x, tm, tn, p.groups, order);
     if (!tc.valid) return;
@@ -429,29 +439,64 @@ __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int 
     const int loa = TA::lane_offset16(wm * 64, lane, half), lob = TB::lane_offset16(wn * 64, lane, half);
 
     const int steps = s.kk / BKT;
-    gbl_char* A = (gbl_char*)s.a;
-    gbl_char* B = (gbl_char*)s.b;
-    uint32_t offa[TA::PER_THREAD], offb[TB::PER_THREAD];
+    // whole lines (line_offset): stage `steps` is the last one of a reduction-contiguous operand, steps - 1 of the other kind
+    gbl_char* A = (gbl_char*)s.a - (A_KC ? 128 : 0);
+    gbl_char* B = (gbl_char*)s.b - (B_KC ? 128 : 0);
+    uint32_t offa[TA::PER_THREAD], offb[TB::PER_THREAD], enda[TA::PER_THREAD], endb[TB::PER_THREAD], begina[TA::PER_THREAD], beginb[TB::PER_THREAD];
 #pragma unroll
-    for (int it = 0; it < TA::PER_THREAD; ++it) offa[it] = TA::src_offset(s.lda, m0, s.m, it * NT + tid);
+    for (int it = 0; it < TA::PER_THREAD; ++it) {
+        if constexpr (A_KC) offa[it] = TA::line_offset(s.a, s.lda, m0, s.m, it * NT + tid, begina[it], enda[it]);
+        else offa[it] = TA::src_offset(s.lda, m0, s.m, it * NT + tid), begina[it] = enda[it] = 0;
+    }
 #pragma unroll
-    for (int it = 0; it < TB::PER_THREAD; ++it) offb[it] = TB::src_offset(s.ldb, n0, s.n, it * NT + tid);
+    for (int it = 0; it < TB::PER_THREAD; ++it) {
+        if constexpr (B_KC) offb[it] = TB::line_offset(s.b, s.ldb, n0, s.n, it * NT + tid, beginb[it], endb[it]);
+        else offb[it] = TB::src_offset(s.ldb, n0, s.n, it * NT + tid), beginb[it] = endb[it] = 0;
+    }
     const uint32_t stepa = TA::step_bytes(s.lda), stepb = TB::step_bytes(s.ldb);
     int loaded = 0;
-    auto issue = [&](char* st) {   // past the last stage the source stays: the reload is in bounds and unread
-        TA::load_direct_untracked(st, A, offa, wave);
-        TB::load_direct_untracked(st + TA::BYTES, B, offb, wave);
+    auto issue = [&](char* st, bool first) {   // past the last stage the source stays: the reload is in bounds and unread
+        const uint32_t last = !first && loaded >= steps ? ~0u : 0u;
+        uint32_t oa[TA::PER_THREAD], ob[TB::PER_THREAD];
+#pragma unroll
+        for (int it = 0; it < TA::PER_THREAD; ++it) oa[it] = !A_KC ? offa[it] : first ? offa[it] + begina[it] : offa[it] - (enda[it] & last);
+#pragma unroll
+        for (int it = 0; it < TB::PER_THREAD; ++it) ob[it] = !B_KC ? offb[it] : first ? offb[it] + beginb[it] : offb[it] - (endb[it] & last);
+        TA::load_direct_untracked(st, A, oa, wave);
+        TB::load_direct_untracked(st + TA::BYTES, B, ob, wave);
         ++loaded;
-        const bool adv = loaded < steps;
-        A += adv ? stepa : 0u;
-        B += adv ? stepb : 0u;
+        A += loaded < steps + (A_KC ? 1 : 0) ? stepa : 0u;
+        B += loaded < steps + (B_KC ? 1 : 0) ? stepb : 0u;
+    };
+    // this workgroup's share of the lines of NST stages, one per lane
+    const Sharers sh = tile_sharers(blockIdx.x, gridDim.x, tm, tn, p.groups, order);
+    constexpr int LA = TA::template touch_lines<NST>(), LB = TB::template touch_lines<NST>();
+    const int qa = (LA + sh.na - 1) / sh.na, qb = (LB + sh.nb - 1) / sh.nb;
+    const char* touch;
+    uint32_t touch_step;
+    uint64_t touch_lanes = 0;
+    {
+        const int l = lane * 8 + wave;   // dealt over the waves; l >= qa + qb: no line
+        const bool a = l < qa;
+        const int la = min(sh.a * qa + l, LA - 1), lb = min(sh.b * qb + l - qa, LB - 1);
+        touch = a ? (const char*)s.a + TA::template touch_offset<NST>(s.lda, m0, s.m, la) : (const char*)s.b + TB::template touch_offset<NST>(s.ldb, n0, s.n, max(lb, 0));
+        touch_step = a ? TA::step_bytes(s.lda) : TB::step_bytes(s.ldb);
+        static_assert(TOUCH_MAX <= NT, "one line per lane");
+        if (steps >= 4 * NST && qa + qb <= TOUCH_MAX) touch_lanes = __ballot(l < qa + qb);
+    }
+    auto touch_ahead = [&](int t) {   // the lines of stages t .. t + NST - 1
+        touch_untracked(touch + (uint64_t)touch_step * (uint32_t)min(t, steps - NST), touch_lanes, smem + NST * STAGE);
     };
     bf16x8 fa[2][FM], fb[2][FN];
-    auto read = [&](const char* st, int set) {
+    // does this lane's chunk of a step lie in the next stage?  (misalignments repeat every 16 rows)
+    const bool nexta = A_KC && 4 * half + (lane >> 4) + TA::misalignment(s.a, s.lda, m0 + (lane & 15)) >= 8;
+    const bool nextb = B_KC && 4 * half + (lane >> 4) + TB::misalignment(s.b, s.ldb, n0 + (lane & 15)) >= 8;
+    auto read = [&](int cur, int next, int set) {
+        const int oa = loa + (A_KC ? (nexta ? next : cur) * STAGE : cur * STAGE), ob = lob + (B_KC ? (nextb ? next : cur) * STAGE : cur * STAGE);
 #pragma unroll
-        for (int j = 0; j < FN; ++j) fb[set][j] = TB::frag16(st + TA::BYTES, lob, j);
+        for (int j = 0; j < FN; ++j) fb[set][j] = TB::frag16(smem + TA::BYTES, ob, j);
 #pragma unroll
-        for (int i = 0; i < FM; ++i) fa[set][i] = TA::frag16(st, loa, i);
+        for (int i = 0; i < FM; ++i) fa[set][i] = TA::frag16(smem, oa, i);
     };
     auto mfmas = [&](int set) {
 #pragma unroll
@@ -459,17 +504,21 @@ __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int 
 #pragma unroll
             for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
     };
-    // Stage t's fragments were read in the step before.  Its successor has landed for this wave, and this wave's reads have
-    // returned, before the barrier; behind it that holds for all waves: stage t is free for t + NST, and t + 1 may be read,
-    // all through the multiplication.
+    // Step t's fragments were read in the step before.  What step t + 1 reads (stage t + 1, with whole lines t + 2 as well) has
+    // landed for this wave, and this wave's reads have returned, before the barrier; behind it that holds for all waves: stage t
+    // is free for t + NST, and the next fragments may be read, all through the multiplication.
+    int t = 0;
     auto wait_keep = [](auto n) { __builtin_amdgcn_s_waitcnt((vmcnt_only(decltype(n)::value) & ~0x0F00)); };   // vmcnt(n) lgkmcnt(0)
     auto step = [&](auto cur) {
         constexpr int CUR = decltype(cur)::value;
-        wait_keep(std::integral_constant<int, (NST - 2) * NVM>{});
+        // stages t + 2, t + 3 (with whole lines only t + 3) and the touch behind the one waited for stay in flight
+        if constexpr (LINES) wait_keep(std::integral_constant<int, (NST - 3) * NVM + (CUR == 1 || CUR == 2)>{});
+        else wait_keep(std::integral_constant<int, (NST - 2) * NVM + (CUR != 0)>{});
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        issue(smem + CUR * STAGE);
-        read(smem + (CUR + 1) % NST * STAGE, (CUR + 1) & 1);
+        issue(smem + CUR * STAGE, false);
+        if constexpr (CUR == 0) touch_ahead(t + TOUCH_DIST);
+        read((CUR + 1) % NST, (CUR + 2) % NST, (CUR + 1) & 1);
         mfmas(CUR & 1);
         constexpr int NDS = (A_KC ? FM : 2 * FM) + (B_KC ? FN : 2 * FN), NM = FM * FN - 4;
         static_for<NM>([&](auto i) {   // fragment reads spread over all but the last matrix instructions
@@ -481,12 +530,11 @@ __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int 
         __builtin_amdgcn_sched_barrier(0);
     };
     if (steps > 0) {
-        static_for<NST>([&](auto i) { issue(smem + decltype(i)::value * STAGE); });
-        wait_keep(std::integral_constant<int, (NST - 1) * NVM>{});
+        static_for<NST>([&](auto i) { issue(smem + decltype(i)::value * STAGE, decltype(i)::value == 0); });
+        wait_keep(std::integral_constant<int, (NST - (LINES ? 2 : 1)) * NVM>{});
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        read(smem, 0);
-        int t = 0;
+        read(0, 1, 0);
         for (; t + NST <= steps; t += NST) static_for<NST>(step);
         const int rem = steps - t;
         static_for<NST - 1>([&](auto i) {
@@ -503,7 +551,7 @@ __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int 
         for (int it = 0; it < TB::PER_THREAD; ++it)
             *reinterpret_cast<u32x4*>(smem + TA::BYTES + (it * NT + tid) * 16) = TB::tail_chunk(static_cast<const uint16_t*>(s.b), s.ldb, n0, s.n, s.kk, k0, it * NT + tid);
         __syncthreads();
-        read(smem, 0);
+        read(0, 0, 0);
         mfmas(0);
         __syncthreads();
     }

@@ -142,6 +142,42 @@ struct Tile {
         }
         return v;
     }
+    // Whole cache lines of reduction-contiguous rows at any 16-byte pitch (BKT = 64: one line a stage).  Row g starts `mis` 16-byte
+    // chunks into a line; stage j holds line j of the row, counted from the one it starts in, so that logical chunk c of the
+    // reduction step t lies in stage t + (c + mis) / 8, at the place it has in any KC image.  line_offset: chunk position p's
+    // byte offset from 128 bytes before the operand's base, for stage 0; before: how many bytes before the row's start that is
+    // (0: none); after: how many bytes to go back in stage `steps`, whose line the reduction may end in.
+    __host__ __device__ static int misalignment(const void* base, int ld, int g) {
+        return (int)(((uint64_t)(uintptr_t)base + (uint64_t)(uint32_t)g * (uint32_t)ld * 2u) >> 4) & 7;
+    }
+    __host__ __device__ static uint32_t line_offset(const void* base, int ld, int first, int limit, int p, uint32_t& before, uint32_t& after) {
+        static_assert(!KC || BKT == 64, "a stage is a line");
+        const int row = p / CPK;
+        int g = first + row;
+        g = g < limit ? g : limit - 1;
+        const int mis = misalignment(base, ld, g), rel = ((((p % CPK) ^ ksw(row)) + mis) & 7) - mis;   // chunks from the row's start
+        before = rel < 0 ? (uint32_t)(-rel * 16) : 0u;
+        after = rel >= 0 ? (uint32_t)(rel + 1) * 16u : 0u;
+        return (uint32_t)g * (uint32_t)ld * 2u + 128u + (uint32_t)(rel * 16);
+    }
+    // Prefetching into L2: the cache lines of PF consecutive stages, one 4-byte read each (the last of every 128-byte piece: what
+    // lies before it on the line came with the piece before).  Line l of touch_lines<PF>(), first stage at reduction offset 0:
+    // byte offset from the operand's base.
+    template <int PF>
+    static constexpr int touch_lines() { return KC ? R * (PF * BKT / 64) : PF * BKT * (R / 64); }
+    template <int PF>
+    __host__ __device__ static uint32_t touch_offset(int ld, int first, int limit, int l) {
+        if constexpr (KC) {
+            constexpr int LPR = PF * BKT / 64;
+            int g = first + l / LPR;
+            g = g < limit ? g : limit - 1;
+            return ((uint32_t)g * (uint32_t)ld + (uint32_t)(l % LPR * 64)) * 2u + 124u;
+        } else {
+            int col = first + l % (R / 64) * 64;
+            if (col + 64 > limit) return ((uint32_t)(l / (R / 64)) * (uint32_t)ld + (uint32_t)first) * 2u;
+            return ((uint32_t)(l / (R / 64)) * (uint32_t)ld + (uint32_t)col) * 2u + 124u;
+        }
+    }
     // bytes to advance the source by for one BKT step
     __device__ static uint32_t step_bytes(int ld) { return KC ? BKT * 2u : (uint32_t)ld * BKT * 2u; }
 
@@ -294,6 +330,28 @@ __device__ inline TileCoord map_tile(int bid, int nblk, int tm, int tn, int grou
     return t;
 }
 
+// The workgroups of one XCD whose tiles lie in the same tile-row (a: they read the same A panel) or tile-column (b) of the same
+// shard and band at the same time: this one's place among them and their number, for one tile per workgroup and one workgroup
+// per compute unit.  Where the walk is not dealt out by XCD, nobody shares.
+struct Sharers {
+    int a, na, b, nb;
+};
+__device__ inline Sharers tile_sharers(int bid, int nblk, int tm, int tn, int groups, int order) {
+    if (order & 0x100) return {0, 1, 0, 1};
+    const int per_xcd = nblk >> 3, GM = order & 0xFF, per_group = tm * tn;
+    const int v = (bid & 7) * per_xcd + (bid >> 3), lo = v - (bid >> 3) % 32;   // 32 compute units: the workgroups at work together
+    const int hi = min(min(lo + 32, (bid & 7) * per_xcd + per_xcd), per_group * groups);
+    const int tl = v % per_group, band = tl / (GM * tn), in_band = tl - band * GM * tn;
+    const int gsz = tm - band * GM < GM ? tm - band * GM : GM;
+    const int row = in_band % gsz, col = in_band / gsz;
+    Sharers s;
+    s.a = min(col, (v - lo) / gsz);
+    s.na = s.a + 1 + min(tn - 1 - col, (hi - 1 - v) / gsz);
+    s.b = min(row, v - lo);
+    s.nb = s.b + 1 + min(gsz - 1 - row, hi - 1 - v);
+    return s;
+}
+
 // max(a, b, c) in one instruction, a NaN operand ignored next to a number (the hardware's maxNum).  Written as
 // assembly because fmaxf() on values the compiler cannot prove canonical (matrix-instruction results) costs a
 // canonicalising multiply per operand: 300 instead of 64 vector instructions per tile and wave in the fused row
@@ -357,6 +415,14 @@ __device__ inline void atomic_max_f32_untracked(float* a, float v) {
     v += 0.0f;
     if (v >= 0.0f) asm volatile("global_atomic_smax %0, %1, off" : : "v"(a), "v"(v) : "memory");
     else if (v < 0.0f) asm volatile("global_atomic_umin %0, %1, off" : : "v"(a), "v"(v) : "memory");   // a NaN is ignored
+}
+
+// One 4-byte load per lane of `lanes` (a uniform mask; all lanes active before and after) into an LDS window that nobody reads: it
+// brings the line into L2 and counts one on the memory counter whatever the mask.
+__device__ inline void touch_untracked(const char* p, uint64_t lanes, char* window) {
+    const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)window);
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 exec, %2\n\tglobal_load_lds_dword %0, off\n\ts_mov_b64 exec, -1"
+                 : : "v"(p), "s"(lds), "s"(lanes) : "memory", "m0");
 }
 
 // 16-byte streaming store the compiler does not track.  The two idle cycles cover the hardware's

@@ -95,6 +95,41 @@ def test_bf16_two_wave_groups_over_the_reduction(M, kk, N, tx, tw, out):
         assert_matmul_close(got[i], orc.gelu(ref[i]) if out == "gelu" else ref[i], 1e-5 if out == "f32" else 2.0 ** -7, f"{M}x{kk}x{N} trans=({tx},{tw}) {out} shard {i}")
 
 
+@pytest.mark.parametrize("tx,tw", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("M,kk,N,extra,start", [(130, 64, 129, 8, 0), (128, 72, 200, 24, 56), (140, 200, 136, 0, 8), (260, 256, 130, 40, 24), (129, 330, 257, 8, 120),
+                                                (300, 1100, 140, 16, 64), (256, 2113, 384, 56, 40)])
+def test_bf16_rows_anywhere_in_a_cache_line(M, kk, N, extra, start, tx, tw):
+    """variant 48, buffers that start and rows that lie 16-byte aligned anywhere in a 128-byte line: one stage to more than the
+    pipeline holds, with and without a remainder, lines touched ahead (the longer ones); NaN before, between and behind the rows"""
+    import torch
+    k = 2
+    X, W = bf16(3, (M, k * kk)), bf16(4, (k * kk, N), 0.5)
+    Xs, Ws = orc.scatter(X, orc.S1, k), orc.scatter(W, orc.S0, k)
+    ref, _ = orc.matmul_sbp([values(x) for x in Xs], orc.S1, [values(w) for w in Ws], orc.S0)
+    keep = []
+
+    def place(shards, trans):
+        ld = pitch(shards, trans, 8, extra)
+        ptrs = []
+        for a in (s.T if trans else s for s in shards):
+            buf = torch.full((start + a.shape[0] * ld,), 0x7FC1, dtype=torch.int16, device="cuda")
+            buf[start:].view(a.shape[0], ld)[:, :a.shape[1]] = torch.from_numpy(np.ascontiguousarray(a).view(np.int16)).cuda()
+            keep.append(buf)
+            ptrs.append(buf.data_ptr() + 2 * start)
+        return ptrs, ld
+
+    (px, ldx), (pw, ldw) = place(Xs, tx), place(Ws, tw)
+    dy = DevTensor.empty(M, N, np.float32, orc.P_SUM, k)
+    sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, 48)
+    try:
+        sbp.sbp_matmul(sbp.SbpTensor(px, M, k * kk, sbp.BF16, tx, ldx), sbp.S(1), sbp.SbpTensor(pw, k * kk, N, sbp.BF16, tw, ldw), sbp.S(0), dy.desc, sbp.AUTO, k)
+        sync()
+    finally:
+        sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, 0)
+    for i, y in enumerate(dy.host()):
+        assert_matmul_close(y, ref[i], 1e-5, f"{M}x{kk}x{N} trans=({tx},{tw}) shard {i}")
+
+
 @pytest.mark.parametrize("epilogue", [sbp.EPI_NONE, sbp.EPI_GELU])
 @pytest.mark.parametrize("M,K,N", [(5, 33, 7), (70, 100, 203)])
 def test_bf16_odd_rows_rounded_results(M, K, N, epilogue):
