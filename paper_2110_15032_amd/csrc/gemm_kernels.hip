@@ -283,7 +283,7 @@ __device__ __attribute__((always_inline)) inline void store_tile(const f32x16 (&
 //   bf16: a 32-row x 64-column strip (2 x 4 blocks) at a time.  Lanes round and pair their rows R, R + 1
 //         and exchange with the neighbouring column as in store_tile; one write instruction covers rows
 //         4 g + (lane & 1), 8 dwords each: the 32-byte column group j is kept at j ^ g.
-template <int BM, int BN, int TM, int TN, int EPI, typename OutT>
+template <int BM, int BN, int TM, int TN, int EPI, typename OutT, int KEEP = 0>
 __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (&acc)[TM / 16][TN / 16], const GemmShard& s, int m0, int n0, int wm, int wn, int lane, char* stage) {
     constexpr int FM = TM / 32, FN = TN / 32;       // 32 x 32 regions, as in store_tile
     OutT* C = static_cast<OutT*>(s.c);
@@ -332,7 +332,7 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
                     constexpr int q = decltype(qidx)::value;
                     const f32x4 v = *reinterpret_cast<const f32x4*>(stage + (((q & 1) ? rd1 : rd0) + q * 1024));
                     f32x4* dst = reinterpret_cast<f32x4*>(cg + (int64_t)(i * 32 + q * 8) * s.ldc + j * 32);
-                    if constexpr (decltype(idx)::value == 0 && q == 0) __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+                    if constexpr (decltype(idx)::value == 0 && q == 0) __builtin_amdgcn_s_waitcnt(vmcnt_only(KEEP));
                     store16_untracked(dst, v, stream);
                 });
                 __builtin_amdgcn_wave_barrier();
@@ -389,7 +389,7 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
                         mx = fmaxf(mx, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(mx), 0x141, 0xF, 0xF, false)));
                         rm[i][q] = fmaxf(rm[i][q], mx);
                     }
-                    if constexpr (decltype(idx)::value == 0 && q == 0) __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+                    if constexpr (decltype(idx)::value == 0 && q == 0) __builtin_amdgcn_s_waitcnt(vmcnt_only(KEEP));
                     store16_untracked(dst, v, stream);
                 });
                 __builtin_amdgcn_wave_barrier();
@@ -1063,11 +1063,19 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_persist_kernel(GemmPla
 }
 
 // ------------------------------------------------------------------------------------------------
-// The persistent kernel on v_mfma_f32_16x16x32_bf16.  Same tiles, stages, load stream, counters and
-// barriers as gemm_mfma_persist_kernel; the matrix instruction spans the whole 32-deep stage, its
+// The persistent kernel on v_mfma_f32_16x16x32_bf16.  Same tiles, stages and barriers as
+// gemm_mfma_persist_kernel; the matrix instruction spans the whole 32-deep stage, its
 // accumulator block is 16 x 16 (four registers), and a step is split by row blocks instead of by
 // reduction halves.  Under a sustained load of random operands the part's power management lets this
 // instruction run at a higher clock than the 32x32x16 form (MFMA-only loop: 2070 against 1843 TFLOP/s).
+//
+// Bound: the power limit on real operands, the load path next to it.  A reduction-contiguous operand is brought two stages at
+// a time: 64 consecutive bytes of a row a load leave the other half of the line to a later stage, by when it has left the L1
+// (with all-zero operands, i.e. at full clock, [8192, 4096] x [4096, 2048], 8 devices, took 725 us with a reduction-contiguous
+// left operand and 607 with the other layout).  us, rows x reduction x columns per device, bf16 results unless fp32, stage by
+// stage / in pairs: 8192 x 4096 x 2048, 8, left operand reduction-contiguous 824 / 790, both 889 / 823; 8192 x 2048 x 4096, 8,
+// fp32, left 892 / 858; 2048 x 2048 x 2048, 4, left 60.7 / 56.2, both 65.4 / 58.6, fp32 69.6 / 63.6; one tile of 128 or 256
+// elements 107 / 107 and 229 / 229.
 // ------------------------------------------------------------------------------------------------
 template <int BM, int BN, int WM, int WN, bool A_KC, bool B_KC, int NST, int EPI, typename OutT>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_persist16_kernel(GemmPlan p, int tm, int tn, int order, int nblk) {
@@ -1079,28 +1087,17 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_persist16_kernel(GemmP
     constexpr int HM = FM / 2;
     constexpr int NDS_A = A_KC ? HM : 2 * HM;                           // LDS reads of half the A fragments
     constexpr int NDS_B = B_KC ? FN : 2 * FN;                           // ... of all B fragments
-    using TA = Tile<BM, A_KC, NT, BKT, true>;
-    using TB = Tile<BN, B_KC, NT, BKT, true>;
-    constexpr int NVM = TA::PER_THREAD + TB::PER_THREAD;
-    constexpr int WAIT_KEEP = (NST - 2) * NVM;
+    // Reduction-contiguous operands are loaded two stages at a time, so that a load reads 128 consecutive bytes of a row.
+    constexpr int DA = A_KC ? 2 : 1, DB = B_KC ? 2 : 1;
+    using TA = Tile<BM, A_KC, NT, DA * BKT, true>;
+    using TB = Tile<BN, B_KC, NT, DB * BKT, true>;
+    constexpr int NS = (A_KC ? 0 : TA::PER_THREAD) + (B_KC ? 0 : TB::PER_THREAD);   // loads per step: single stages
+    constexpr int NP = (A_KC ? TA::PER_THREAD : 0) + (B_KC ? TB::PER_THREAD : 0);   // ... per two steps: pairs
+    constexpr int NSTORE = TM * TN * (int)sizeof(OutT) / 1024;                      // a wave's stores of a whole tile
     static_assert(NST == 4, "written for four stages");
-    __shared__ __attribute__((aligned(1024))) char sA0[TA::BYTES];
-    __shared__ __attribute__((aligned(1024))) char sA1[TA::BYTES];
-    __shared__ __attribute__((aligned(1024))) char sA2[TA::BYTES];
-    __shared__ __attribute__((aligned(1024))) char sA3[TA::BYTES];
-    __shared__ __attribute__((aligned(1024))) char sB0[TB::BYTES];
-    __shared__ __attribute__((aligned(1024))) char sB1[TB::BYTES];
-    __shared__ __attribute__((aligned(1024))) char sB2[TB::BYTES];
-    __shared__ __attribute__((aligned(1024))) char sB3[TB::BYTES];
+    __shared__ __attribute__((aligned(1024))) char sA[NST / DA * TA::BYTES];
+    __shared__ __attribute__((aligned(1024))) char sB[NST / DB * TB::BYTES];
     __shared__ __attribute__((aligned(1024))) char sOut[WM * WN * STAGE_BYTES];   // epilogue windows, one per wave
-    auto stA = [&](auto i) -> char* {
-        constexpr int I = decltype(i)::value;
-        if constexpr (I == 0) return sA0; else if constexpr (I == 1) return sA1; else if constexpr (I == 2) return sA2; else return sA3;
-    };
-    auto stB = [&](auto i) -> char* {
-        constexpr int I = decltype(i)::value;
-        if constexpr (I == 0) return sB0; else if constexpr (I == 1) return sB1; else if constexpr (I == 2) return sB2; else return sB3;
-    };
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1140,15 +1137,19 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_persist16_kernel(GemmP
         stepb = TB::step_bytes(s.ldb);
     };
     open_tile(first);
-    // Branch-free: always NVM loads (the wait counts rely on it), then one stage forward.  Because a
-    // tile has a multiple of NST stages, the cursor leaves a tile exactly after step 0 of the tile's
-    // last round; the tile loop below re-opens it there.  Past the last tile the steps are zeroed, so
-    // the last stage is simply re-read (in bounds, never used).
-    auto issue = [&](char* da, char* db) {
-        TA::load_direct_untracked(da, A, offa, wave);
-        TB::load_direct_untracked(db, B, offb, wave);
-        A += stepa;
-        B += stepb;
+    // Branch-free: always the same number of loads (the wait counts rely on it), then forward.  At step s single stages are
+    // loaded for step s + 3, at odd steps behind the barrier pairs for steps s + 3 and s + 4.  Because a tile has a multiple
+    // of NST stages, both cursors leave a tile between step 0 and step 1 of the tile's last round; the tile loop below re-opens
+    // them there.  Past the last tile the steps are zeroed, so the last stages are simply re-read (in bounds, never used).
+    auto issue_single = [&](auto dst) {
+        constexpr int D = decltype(dst)::value;
+        if constexpr (!A_KC) { TA::load_direct_untracked(sA + D * TA::BYTES, A, offa, wave); A += stepa; }
+        if constexpr (!B_KC) { TB::load_direct_untracked(sB + D * TB::BYTES, B, offb, wave); B += stepb; }
+    };
+    auto issue_pair = [&](auto dst) {
+        constexpr int D = decltype(dst)::value;
+        if constexpr (A_KC) { TA::load_direct_untracked(sA + D * TA::BYTES, A, offa, wave); A += stepa; }
+        if constexpr (B_KC) { TB::load_direct_untracked(sB + D * TB::BYTES, B, offb, wave); B += stepb; }
     };
 
     // ---- compute side --------------------------------------------------------------------------
@@ -1160,13 +1161,23 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_persist16_kernel(GemmP
     bf16x8 fa[2][HM], fb[2][FN];
     static_assert((A_KC || (TM % 128 == 0 && FM <= 8)) && (B_KC || (TN % 64 == 0 && FN <= 4)), "see Tile::lane_offset16");
     const int loa = TA::lane_offset16(wm * TM, lane), lob = TB::lane_offset16(wn * TN, lane);
-    auto read_a = [&](const char* sa, int half) {
-#pragma unroll
-        for (int i = 0; i < HM; ++i) fa[half][i] = TA::frag16(sa, loa, half * HM + i);
+    // fragments of stage ST; in the second stage of a pair chunk 4 + g lies where chunk g does in the first, with bit 2 flipped
+    auto second = [](int lo) {
+        int o;
+        asm volatile("v_xor_b32 %0, 64, %1" : "=v"(o) : "v"(lo));
+        return o;
     };
-    auto read_b = [&](const char* sb, int slot) {
+    auto read_a = [&](auto stage, int half) {
+        constexpr int ST = decltype(stage)::value;
+        const int lo = A_KC && ST % 2 ? second(loa) : loa;
 #pragma unroll
-        for (int j = 0; j < FN; ++j) fb[slot][j] = TB::frag16(sb, lob, j);
+        for (int i = 0; i < HM; ++i) fa[half][i] = TA::frag16(sA + ST / DA * TA::BYTES, lo, half * HM + i);
+    };
+    auto read_b = [&](auto stage, int slot) {
+        constexpr int ST = decltype(stage)::value;
+        const int lo = B_KC && ST % 2 ? second(lob) : lob;
+#pragma unroll
+        for (int j = 0; j < FN; ++j) fb[slot][j] = TB::frag16(sB + ST / DB * TB::BYTES, lo, j);
     };
     auto mfmas = [&](int half, int slot) {
 #pragma unroll
@@ -1175,43 +1186,53 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_persist16_kernel(GemmP
             for (int j = 0; j < FN; ++j)
                 acc[half * HM + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[half][i], fb[slot][j], acc[half * HM + i][j], 0, 0, 0);
     };
-    constexpr int WAIT_STRICT = (WAIT_KEEP & 15) | ((WAIT_KEEP >> 4) << 14) | 0x0070;   // vmcnt(WAIT_KEEP) lgkmcnt(0)
+    // What is waited for before a step's barrier is what the next step reads; the loads issued behind that stay in flight:
+    // at even steps the single stages of the two steps after it and the pair of the next two, at odd steps (whose next step
+    // opens a pair) the single stages.  With pairs only, an even step has nothing to wait for and no barrier.
     // Stores of a tile's epilogue sit in the in-order memory queue in front of the next tile's fourth
     // stage.  The first two steps of a tile need stages 1 and 2 only, which the epilogue has already
-    // waited for (see store_tile), so they run on a barrier alone (NOWAIT) and the stores drain
-    // underneath them; the third step is the first to wait on the queue again, and its "all but the
-    // two youngest stages" then covers the stores as well.
-    constexpr int WAIT_LDS_ONLY = 0xC07F;   // lgkmcnt(0), vmcnt untouched
-    auto step = [&](auto cur, auto nowait) {
+    // waited for (see store_tile16), so they run on a barrier alone and the stores drain underneath them, but for the second
+    // pair, which is younger than that: the second step counts the stores behind it (YOUNG) or, where their number is not
+    // known, waits for them.  The third step is the first to wait on the queue again, and its count covers the stores as well.
+    auto step = [&](auto cur, auto fresh, bool young) {
         constexpr int CUR = decltype(cur)::value;
-        constexpr bool NOWAIT = decltype(nowait)::value;
+        constexpr bool FRESH = decltype(fresh)::value;   // one of the first two steps of a tile
         using Nxt = std::integral_constant<int, (CUR + 1) % NST>;
         using Dst = std::integral_constant<int, (CUR + NST - 1) % NST>;
-        issue(stA(Dst{}), stB(Dst{}));
-        read_a(stA(cur), 1);
+        using Pair = std::integral_constant<int, CUR / 2>;
+        issue_single(Dst{});
+        read_a(cur, 1);
         mfmas(0, CUR & 1);
-        pace<HM * FN, NDS_A, NVM>();
-        __builtin_amdgcn_s_waitcnt(NOWAIT ? WAIT_LDS_ONLY : WAIT_STRICT);
-        __builtin_amdgcn_s_barrier();
-        read_a(stA(Nxt{}), 0);
-        read_b(stB(Nxt{}), (CUR + 1) & 1);
+        pace<HM * FN, NDS_A, NS>();
+        if constexpr (CUR % 2 == 1 || NS > 0) {
+            if constexpr (FRESH && (CUR == 0 || NP == 0)) __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+            else if constexpr (FRESH) {
+                if (young) __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * NS + NSTORE) & ~0x0F00);
+                else __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * NS) & ~0x0F00);
+            } else __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * NS + (CUR % 2 ? 0 : NP)) & ~0x0F00);   // vmcnt lgkmcnt(0)
+            __builtin_amdgcn_s_barrier();
+        }
+        if constexpr (CUR % 2 == 1) issue_pair(Pair{});
+        read_a(Nxt{}, 0);
+        read_b(Nxt{}, (CUR + 1) & 1);
         mfmas(1, CUR & 1);
-        pace<HM * FN, NDS_A + NDS_B, 0>();
+        pace<HM * FN, NDS_A + NDS_B, CUR % 2 ? NP : 0>();
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
     using I3 = std::integral_constant<int, 3>;
-    using Wait = std::false_type;
-    using NoWait = std::true_type;
-    static_assert(NST == 4, "the tile loop below is written for four stages");
+    using Old = std::false_type;
+    using Fresh = std::true_type;
 
-    static_for<NST - 1>([&](auto i) { issue(stA(i), stB(i)); });
-    __builtin_amdgcn_s_waitcnt(0x0070);   // all three stages landed: the first tile starts like every other
+    static_for<NST - 1>(issue_single);
+    static_for<2>(issue_pair);
+    __builtin_amdgcn_s_waitcnt(0x0070);   // all of it landed: the first tile starts like every other
     __builtin_amdgcn_s_barrier();
-    read_a(sA0, 0);
-    read_b(sB0, 0);
+    read_a(I0{}, 0);
+    read_b(I0{}, 0);
 
+    bool young = false;   // the stores of the tile before are behind this tile's second pair, all NSTORE of them
     for (int cv = first; cv < nblk;) {
         const TileCoord tc = map_tile(cv, nblk, tm, tn, p.groups, order);
         const GemmShard s = p.s[tc.g];
@@ -1235,19 +1256,20 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_persist16_kernel(GemmP
                 stepb = 0;
             }
         };
-        step(I0{}, NoWait{});
+        step(I0{}, Fresh{}, young);
         if (rounds == 1) switch_tile();
-        step(I1{}, NoWait{});
-        step(I2{}, Wait{});
-        step(I3{}, Wait{});
+        step(I1{}, Fresh{}, young);
+        step(I2{}, Old{}, false);
+        step(I3{}, Old{}, false);
         for (int r = 1; r < rounds; ++r) {
-            step(I0{}, Wait{});
+            step(I0{}, Old{}, false);
             if (r == rounds - 1) switch_tile();
-            step(I1{}, Wait{});
-            step(I2{}, Wait{});
-            step(I3{}, Wait{});
+            step(I1{}, Old{}, false);
+            step(I2{}, Old{}, false);
+            step(I3{}, Old{}, false);
         }
-        store_tile16<BM, BN, TM, TN, EPI, OutT>(acc, s, m0, n0, wm, wn, lane, sOut);
+        store_tile16<BM, BN, TM, TN, EPI, OutT, NP>(acc, s, m0, n0, wm, wn, lane, sOut);
+        young = EPI != EPI_ROWMAX && m0 + BM <= s.m && n0 + BN <= s.n && s.ldc % (16 / (int)sizeof(OutT)) == 0;
         cv = nv;
     }
     __builtin_amdgcn_s_waitcnt(0x0070);   // trailing (unused) loads must land before LDS is released

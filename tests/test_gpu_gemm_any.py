@@ -130,6 +130,45 @@ def test_bf16_rows_anywhere_in_a_cache_line(M, kk, N, extra, start, tx, tw):
         assert_matmul_close(y, ref[i], 1e-5, f"{M}x{kk}x{N} trans=({tx},{tw}) shard {i}")
 
 
+@pytest.mark.parametrize("out", ["f32", "bf16", "gelu", "rowmax"])
+@pytest.mark.parametrize("tx,tw", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("kk,ldy", [(128, 0), (256, 4352 + 8), (640, 4352 + 1)])
+def test_bf16_persistent_tiles(kk, ldy, tx, tw, out):
+    """variant 16, more 256 x 256 tiles than workgroups: tile after tile through one pipeline, with one round of stages, two and
+    more, whole and cut tiles, rows of the result on cache lines, 16-byte aligned and odd; against torch in fp32"""
+    import torch
+    k, M, N = 2, 2200, 4352
+    X, W = bf16(21, (M, kk)), bf16(22, (kk, k * N), 0.1)
+    Xs, Ws = orc.scatter(X, orc.B, k), orc.scatter(W, orc.S1, k)
+    if out == "f32":
+        X = bf16(21, (M, k * kk))
+        W = bf16(22, (k * kk, N), 0.1)
+        Xs, Ws = orc.scatter(X, orc.S1, k), orc.scatter(W, orc.S0, k)
+    sx, sw, K, C = (orc.S1, orc.S0, k * kk, N) if out == "f32" else (orc.B, orc.S1, kk, k * N)
+    dx = DevTensor.from_host(Xs, M, K, sx, trans=tx, ld=pitch(Xs, tx, 8))
+    dw = DevTensor.from_host(Ws, K, C, sw, trans=tw, ld=pitch(Ws, tw, 8))
+    dy = DevTensor.empty(M, C, np.float32 if out == "f32" else np.uint16, orc.P_SUM if out == "f32" else orc.S1, k, ld=ldy)
+    dm = DevTensor.empty(M, 1, np.float32, orc.P_MAX, k)
+    sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, 16)
+    try:
+        if out == "rowmax":
+            sbp.sbp_matmul_rowmax(dx.desc, TO_ABI[sx], dw.desc, TO_ABI[sw], dy.desc, sbp.AUTO, dm.desc, k)
+        else:
+            sbp.sbp_matmul_ex(dx.desc, TO_ABI[sx], dw.desc, TO_ABI[sw], dy.desc, sbp.AUTO, k, None, sbp.EPI_GELU if out == "gelu" else sbp.EPI_NONE)
+        sync()
+    finally:
+        sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, 0)
+    got, top = dy.host(), dm.host()
+    for i in range(k):
+        ref = (torch.from_numpy(values(Xs[i]).astype(np.float32)).cuda() @ torch.from_numpy(values(Ws[i]).astype(np.float32)).cuda()).cpu().numpy()
+        if out == "gelu":
+            ref = orc.gelu(ref)
+        y = got[i] if out == "f32" else values(got[i])
+        assert_matmul_close(y, ref, 1e-5 if out == "f32" else 2.0 ** -7, f"kk={kk} ldy={ldy} trans=({tx},{tw}) {out} shard {i}")
+        if out == "rowmax":
+            assert np.array_equal(top[i][:, 0], y.max(axis=1))
+
+
 @pytest.mark.parametrize("epilogue", [sbp.EPI_NONE, sbp.EPI_GELU])
 @pytest.mark.parametrize("M,K,N", [(5, 33, 7), (70, 100, 203)])
 def test_bf16_odd_rows_rounded_results(M, K, N, epilogue):
