@@ -267,7 +267,8 @@ enum {
                                    waves of a workgroup split the reduction (tile 32x64, 64x64, 128x64),
                                    43, 44 = operands through registers (tile 128x128, 64x64); fp32 operands:
                                    45-47 = tile 128x128, 64x64, 32x32 with the waves splitting the
-                                   reduction; 48 = tile 128x128, two wave groups over the reduction; a forced
+                                   reduction, 49, 50 = tile 128x128, 64x64 on bf16 terms of the fp32
+                                   operands; 48 = tile 128x128, two wave groups over the reduction; a forced
                                    kernel that cannot take the shapes gives SBP_ERR_UNSUPPORTED        */
     SBP_KNOB_TILE_ORDER = 1,    /* order in which workgroups walk output tiles: low byte = tile-rows per
                                    band (0, the default: chosen from the shape), bit 8 set = no per-XCD

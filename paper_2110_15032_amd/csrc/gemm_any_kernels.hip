@@ -32,27 +32,6 @@ namespace {
 
 constexpr int LGKM0_ONLY = 0xC07F;   // s_waitcnt lgkmcnt(0), vmcnt untouched
 
-typedef f32x4 __attribute__((aligned(4))) f32x4_any;
-typedef u32x4 __attribute__((aligned(2))) u32x4_any;
-
-// EPV consecutive columns of row m from column n on, at whatever alignment the row pitch gives
-template <typename OutT, int EPV>
-__device__ inline void store_columns(const GemmShard& s, int m, int n, const float (&v)[EPV]) {
-    if (m >= s.m) return;
-    OutT* dst = static_cast<OutT*>(s.c) + (int64_t)m * s.ldc + n;
-    if (n + EPV <= s.n) {
-        if constexpr (sizeof(OutT) == 4) *reinterpret_cast<f32x4_any*>(dst) = f32x4{v[0], v[1], v[2], v[3]};
-        else *reinterpret_cast<u32x4_any*>(dst) = u32x4{f32_to_bf16x2(v[0], v[1]), f32_to_bf16x2(v[2], v[3]), f32_to_bf16x2(v[4], v[5]), f32_to_bf16x2(v[6], v[7])};
-    } else {
-#pragma unroll
-        for (int e = 0; e < EPV; ++e)
-            if (n + e < s.n) {
-                if constexpr (sizeof(OutT) == 4) dst[e] = v[e];
-                else dst[e] = f32_to_bf16(v[e]);
-            }
-    }
-}
-
 // Whole 32-deep stages whose 16-byte chunks may be read without a look at the ends, rows of any pitch: a chunk of a
 // not-KC operand may run past the end of its row into the next one, so the stage with the last row is left to the
 // careful path, and rows shorter than a chunk leave it everything.

@@ -425,6 +425,27 @@ __device__ inline void touch_untracked(const char* p, uint64_t lanes, char* wind
                  : : "v"(p), "s"(lds), "s"(lanes) : "memory", "m0");
 }
 
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+
+// EPV consecutive columns of row m from column n on, at whatever alignment the row pitch gives
+template <typename OutT, int EPV>
+__device__ inline void store_columns(const GemmShard& s, int m, int n, const float (&v)[EPV]) {
+    if (m >= s.m) return;
+    OutT* dst = static_cast<OutT*>(s.c) + (int64_t)m * s.ldc + n;
+    if (n + EPV <= s.n) {
+        if constexpr (sizeof(OutT) == 4) *reinterpret_cast<f32x4_any*>(dst) = f32x4{v[0], v[1], v[2], v[3]};
+        else *reinterpret_cast<u32x4_any*>(dst) = u32x4{f32_to_bf16x2(v[0], v[1]), f32_to_bf16x2(v[2], v[3]), f32_to_bf16x2(v[4], v[5]), f32_to_bf16x2(v[6], v[7])};
+    } else {
+#pragma unroll
+        for (int e = 0; e < EPV; ++e)
+            if (n + e < s.n) {
+                if constexpr (sizeof(OutT) == 4) dst[e] = v[e];
+                else dst[e] = f32_to_bf16(v[e]);
+            }
+    }
+}
+
 // 16-byte streaming store the compiler does not track.  The two idle cycles cover the hardware's
 // rule that the data registers of a store wider than 8 bytes must not be rewritten right behind it
 // (the compiler inserts them for stores it knows; here it cannot).

@@ -1679,17 +1679,24 @@ AnyTile any_tile(const GemmPlan& plan, int max_m, int max_n) {
 // 64 x 64): 79 / 29 / 30; 300 x 1000 x 300, 2 (50): 77 / 27 / 12; 8 x 256 x 12500, 4: 41 / 24 / 16; 256 x 8 x 12500, 4: 17 / 20 / 47.
 // Less than one stage of the 32 x 32 tile, 64 x 64 / 32 x 32: 25 to 63 long, up to 128 tiles of 64 x 64 1 / 0.75-0.95, 192 and more
 // 1 / 1.03-1.8 (1 / 0.9 up to 256 where 32 rows or columns are all there is).
+// Three bf16 terms per fp32 operand (TERMS) in place of the 128 x 128 and 64 x 64 tiles of the fp32 instruction, and in place of those
+// only: the waves' splitting of the reduction has the smaller rounding error (see gemm_f32_kernels.hip).  us, fp32 128 / fp32 64 /
+// terms 128 / terms 64: 2000 x 750 x 1500, 4 devices (768 large tiles) 153 / 174 / 104 / 133; 720 large 183 / 207 / 112 / 141; 584 471 /
+// 454 / 289 / 334; 444 74 / 74 / 50 / 53; 352 310 / 252 / 176 / 177; 272 378 / 266 / 214 / 190.  Few tiles, fp32 64 / terms 64: 440 small ones
+// 35.0 / 26.8, 308 16.3 / 14.2, 256 18.9 / 19.0, 234 15.8 / 16.3; next to bf16 (three matrix instructions for six) 242 52 / 24, 272
+// 39 / 19.  Short reductions: length 40 65 / 77 / 54 / 66, 24 63 / 63 / 57 / 64, 15 41 / 55 / 47 / 50; next to bf16 45 18 / 16 / 16 / 13, 32
+// 11 / 9 / 13 / 11, 25 12 / 11 / 14 / 13.
 F32Tile f32_tile(const GemmPlan& plan, int max_m, int max_n) {
-    const int64_t cu = compute_units(), tiles = tiles_of(plan, max_m, max_n, 64, 64);
+    const int64_t cu = compute_units(), tiles = tiles_of(plan, max_m, max_n, 64, 64), large = tiles_of(plan, max_m, max_n, 128, 128);
     const int k = longest_reduction(plan);
-    const bool narrow = max_m <= 32 || max_n <= 32;
-    if (max_m > 64 && max_n > 64 && tiles_of(plan, max_m, max_n, 128, 128) >= cu) return F32_128;
-    if (k < 64) return k > 24 && tiles <= (narrow ? cu : cu / 2) ? F32_32 : F32_64;
-    return narrow || 4 * tiles < 3 * cu ? F32_32 : F32_64;
+    const bool narrow = max_m <= 32 || max_n <= 32, terms = plan.f32_operand ? k > 32 : k >= 24;
+    if (max_m > 64 && max_n > 64 && large >= cu) return !terms ? F32_128 : 5 * large >= 8 * cu ? TERMS_128 : TERMS_64;
+    if (k < 64 ? k > 24 && tiles <= (narrow ? cu : cu / 2) : narrow || 4 * tiles < 3 * cu) return F32_32;
+    return terms && (tiles > cu || plan.f32_operand) ? TERMS_64 : F32_64;
 }
 int32_t launch_f32(const GemmPlan& plan, int max_m, int max_n, int32_t variant, hipStream_t stream) {
-    const int tile = variant >= 45 ? variant - 45 : f32_tile(plan, max_m, max_n);
-    const int b = tile == F32_128 ? 128 : tile == F32_64 ? 64 : 32;
+    const int tile = variant >= 49 ? variant - 49 + TERMS_128 : variant >= 45 ? variant - 45 : f32_tile(plan, max_m, max_n);
+    const int b = tile == F32_128 || tile == TERMS_128 ? 128 : tile == F32_64 || tile == TERMS_64 ? 64 : 32;
     return launch_gemm_f32(plan, max_m, max_n, tile, tile_order_for(tiles_along(max_m, b), tiles_along(max_n, b)), stream);
 }
 int32_t launch_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool direct, hipStream_t stream) {
@@ -1758,7 +1765,7 @@ int32_t launch_chosen(const GemmPlan& plan, int max_m, int max_n, int32_t varian
     if (plan.f32_operand) {
         // Table 1 rows 4 / 5 with a bf16 partner: split kernel, else the fp32 matrix instruction with mixed element types
         if (plan.out_dtype != SBP_F32 || plan.epilogue != SBP_EPI_NONE) return SBP_ERR_DTYPE;
-        if (variant >= 45 && variant <= 47) return launch_f32(plan, max_m, max_n, variant, stream);
+        if ((variant >= 45 && variant <= 47) || variant == 49 || variant == 50) return launch_f32(plan, max_m, max_n, variant, stream);
         if (variant != 1 && split_ok(plan)) {
             if (variant > 1 && variant != 31 && variant != 32) return SBP_ERR_UNSUPPORTED;
             return plan.f32_operand == 2 ? launch_split<true>(plan, max_m, max_n, variant, stream) : launch_split<false>(plan, max_m, max_n, variant, stream);
@@ -1767,7 +1774,7 @@ int32_t launch_chosen(const GemmPlan& plan, int max_m, int max_n, int32_t varian
         if (variant == 1 || one_element_pays(plan, max_m, max_n, false)) return launch_generic(plan, max_m, max_n, stream);
         return launch_f32(plan, max_m, max_n, variant, stream);
     }
-    if (plan.in_dtype == SBP_F32 && ((variant == 0 && !one_element_pays(plan, max_m, max_n, false)) || (variant >= 45 && variant <= 47)))
+    if (plan.in_dtype == SBP_F32 && ((variant == 0 && !one_element_pays(plan, max_m, max_n, false)) || (variant >= 45 && variant <= 47) || variant == 49 || variant == 50))
         return plan.out_dtype == SBP_F32 ? launch_f32(plan, max_m, max_n, variant, stream) : SBP_ERR_DTYPE;
     const bool fast = mfma_ok(plan);
     if (variant == 1 || !fast) {

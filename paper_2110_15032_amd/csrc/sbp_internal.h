@@ -110,7 +110,9 @@ int32_t launch_gemm_deep(const GemmPlan& plan, int max_m, int max_n, int order, 
 enum F32Tile : int32_t {
     F32_128 = 0,   // 128 x 128
     F32_64,        // 64 x 64
-    F32_32         // 32 x 32, waves splitting the reduction
+    F32_32,        // 32 x 32, waves splitting the reduction
+    TERMS_128,     // 128 x 128 and 64 x 64 on the bf16 matrix instruction, fp32 operands as three bf16 terms
+    TERMS_64
 };
 int32_t launch_gemm_f32(const GemmPlan& plan, int max_m, int max_n, int tile, int order, hipStream_t stream);
 // Compute units of the current device, asked of the runtime once per device and kept.

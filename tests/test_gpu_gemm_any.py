@@ -210,6 +210,77 @@ def test_f32_operands_any_shape_and_pitch(M, kk, N, types, tx, tw, variant):
         assert_matmul_close(got[i], ref[i], 1e-5, f"{M}x{kk}x{N} {types} trans=({tx},{tw}) v{variant} shard {i}")
 
 
+@pytest.mark.parametrize("variant", [49, 50])
+@pytest.mark.parametrize("tx,tw", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("types", ["f32,f32", "f32,bf16", "bf16,f32"])
+@pytest.mark.parametrize("M,kk,N", [(1, 1, 1), (3, 31, 2), (33, 65, 66), (64, 32, 64), (129, 131, 67), (140, 321, 257), (128, 96, 136)])
+def test_f32_operands_as_bf16_terms(M, kk, N, types, tx, tw, variant):
+    """no whole 32-deep stage, one, several and a remainder, rows shorter than a chunk, one tile and ragged further ones.  Bar: the
+    dropped products of terms are below 2^-25 of each product, the rest is summation order"""
+    k = 2
+    if types == "f32,f32":
+        X, W, sx, sw = f32(7, (M, k * kk)), f32(8, (k * kk, N)), orc.S1, orc.S0
+        Xs, Ws = orc.scatter(X, sx, k), orc.scatter(W, sw, k)
+    elif types == "f32,bf16":
+        W, sx, sw = bf16(8, (kk, N), 0.5), orc.P_SUM, orc.B
+        Xs, Ws = [f32(10 + i, (M, kk)) for i in range(k)], orc.scatter(W, sw, k)
+    else:
+        X, sx, sw = bf16(7, (M, kk)), orc.B, orc.P_SUM
+        Xs, Ws = orc.scatter(X, sx, k), [f32(10 + i, (kk, N)) for i in range(k)]
+    wide = lambda v: values(v) if v.dtype == np.uint16 else v
+    ref, _ = orc.matmul_sbp([wide(x) for x in Xs], sx, [wide(w) for w in Ws], sw)
+    got, _ = run(Xs, sx, Ws, sw, M, k * kk if sx == orc.S1 else kk, N, k, tx, tw, pitch(Xs, tx, 2, 1), pitch(Ws, tw, 2, 1), pitch(ref, 0, 2, 1), variant=variant)
+    for i in range(k):
+        assert_matmul_close(got[i], ref[i], 1e-5, f"{M}x{kk}x{N} {types} trans=({tx},{tw}) v{variant} shard {i}")
+
+
+@pytest.mark.parametrize("variant", [49, 50])
+@pytest.mark.parametrize("types", ["f32,f32", "f32,bf16"])
+@pytest.mark.parametrize("case", ["inf", "nan", "inf times zero", "lowest", "past the largest bf16", "overflow", "small", "denormal", "zero"])
+def test_f32_values_that_terms_do_not_hold(case, types, variant):
+    """values whose bf16 terms are not finite or lose bits: infinities, NaN and overflow where the fp32 instruction gives them (one tile
+    of several), and the same accuracy; results in the range of fp32 denormals to one of their steps per product"""
+    k, M, kk, N = 1, 140, 70, 150
+    X, W = f32(31, (M, kk)), f32(32, (kk, N))
+    if types == "f32,bf16":
+        W = wl.to_bf16_bits(W)
+    tiny = np.float32(2.0) ** -140
+    if case == "inf":
+        X[3, 5], X[135, 0] = np.inf, -np.inf
+    elif case == "nan":
+        X[77, 69] = np.nan
+    elif case == "inf times zero":
+        X[3, 5] = np.inf
+        W[5, 7] = 0
+    elif case == "lowest":
+        X[9, :] = np.finfo(np.float32).min
+    elif case == "past the largest bf16":
+        X[130, 11], X[130, 12] = 3.4e38, -3.4e38
+        W[11:13, :] = wl.to_bf16_bits(np.full((2, N), 0.25)) if types == "f32,bf16" else 0.25
+    elif case == "overflow":   # in whatever order the sum is taken
+        X[0, :4] = 3e38
+        W[:4, :] = wl.to_bf16_bits(np.ones((4, N))) if types == "f32,bf16" else 1.0
+    elif case == "small":
+        X *= np.float32(1e-35)
+        if types == "f32,f32":
+            W *= np.float32(1e10)
+    elif case == "denormal":
+        X *= tiny
+    elif case == "zero":
+        X[:] = 0
+    sx, sw = (orc.S1, orc.S0) if types == "f32,f32" else (orc.P_SUM, orc.B)
+    got, _ = run([X], sx, [W], sw, M, kk, N, k, 0, 0, 0, 0, variant=variant)
+    want, _ = run([X], sx, [W], sw, M, kk, N, k, 0, 0, 0, 0, variant=45)
+    wide = (values(W) if W.dtype == np.uint16 else W).astype(np.float64)
+    got, want = got[0], want[0]
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want)) and np.array_equal(np.isneginf(got), np.isneginf(want))
+    with np.errstate(all="ignore"):
+        ref = X.astype(np.float64) @ wide
+        scale = np.abs(X.astype(np.float64)) @ np.abs(wide)
+    ok = np.isfinite(want)
+    assert np.all(np.abs(got - ref)[ok] <= 1e-5 * scale[ok] + kk * 2.0 ** -149)
+
+
 @pytest.mark.parametrize("M,K,N", [(5, 33, 7), (70, 300, 203)])
 def test_f32_gelu(M, K, N):
     k = 3
