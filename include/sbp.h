@@ -265,7 +265,9 @@ enum {
                                    12 on the 16x16x32 matrix instruction, 21 = 16 with the two waves of
                                    every SIMD taking turns at the matrix pipe (ping-pong), 40-42 = the
                                    waves of a workgroup split the reduction (tile 32x64, 64x64, 128x64),
-                                   43, 44 = operands through registers (tile 128x128, 64x64); fp32 operands:
+                                   43, 44 = operands through registers (tile 128x128, 64x64), 51, 52 = the
+                                   same, 256 reduction elements at a time (tile 32x32, 64x64; both operands
+                                   reduction-contiguous, fp32 results); fp32 operands:
                                    45-47 = tile 128x128, 64x64, 32x32 with the waves splitting the
                                    reduction, 49, 50 = tile 128x128, 64x64 on bf16 terms of the fp32
                                    operands; 48 = tile 128x128, two wave groups over the reduction; a forced

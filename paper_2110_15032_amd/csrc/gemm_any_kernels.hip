@@ -42,17 +42,60 @@ __device__ inline int plain_stages(const GemmShard& s) {
     return (s.kk - 1) / 32;
 }
 
+// Addition of the partial tiles of NW waves (FM x FN blocks of 16 x 16 each), wave order, NB blocks at a time through LDS: 1 KB per
+// block and wave.
+template <int NW, int FM, int FN>
+constexpr int partial_blocks() { return FM * FN * NW <= 128 ? FM * FN : 128 / NW; }
+template <int NW, int FM, int FN>
+constexpr int partial_bytes() { return partial_blocks<NW, FM, FN>() * NW * 1024; }
+template <int NW, int FM, int FN, int EPI, typename OutT>
+__device__ __attribute__((always_inline)) inline void add_partial_tiles(const f32x4 (&acc)[FM][FN], char* smem, const GemmShard& s, int m0, int n0, int wave, int lane) {
+    constexpr int NB = partial_blocks<NW, FM, FN>(), ROUNDS = FM * FN / NB, SIDE = sizeof(OutT) == 4 ? 2 : 4;
+    static_assert(FM * FN % NB == 0 && NB % SIDE == 0 && FN % SIDE == 0, "whole units of blocks side by side");
+    // A block is kept as it lies in the registers:
+    // row r = lane % 16, four columns from 4 q on, q = lane / 16, at (16 q + (r ^ 4 q)) * 16 (the exclusive-or spreads
+    // the reads below over the banks).  Reading, eight consecutive lanes own the 128 (bf16: 64-column) bytes of a row.
+    constexpr int EPV = 16 / (int)sizeof(OutT);           // columns per lane
+    constexpr int UNIT = sizeof(OutT) == 4 ? 2 : 4;       // blocks side by side that eight lanes cover
+    constexpr int UNITS = NB / UNIT * 2;                  // ... by eight rows: half the rows of a block
+    const int q = lane >> 4, r = lane & 15;
+    char* const dump = smem + wave * (NB * 1024) + (16 * q + (r ^ (4 * q))) * 16;
+    static_for<ROUNDS>([&](auto rix) {
+        constexpr int B0 = decltype(rix)::value * NB;
+        __syncthreads();
+        static_for<NB>([&](auto bix) {
+            constexpr int b = B0 + decltype(bix)::value;
+            *reinterpret_cast<f32x4*>(dump + decltype(bix)::value * 1024) = acc[b / FN][b % FN];
+        });
+        __syncthreads();
+        for (int u = wave; u < UNITS; u += NW) {
+            const int blk = u / 2 * UNIT, row = 8 * (u & 1) + (lane >> 3);
+            const int m = m0 + (B0 + blk) / FN * 16 + row, n = n0 + (B0 + blk) % FN * 16 + (lane & 7) * EPV;
+            float v[EPV];
+#pragma unroll
+            for (int h = 0; h < EPV / 4; ++h) {
+                const int cg = (lane & 7) * (EPV / 4) + h;   // group of four columns: block cg / 4, q = cg % 4
+                const char* at = smem + (blk + cg / 4) * 1024 + (16 * (cg & 3) + (row ^ (4 * (cg & 3)))) * 16;
+                f32x4 sum = *reinterpret_cast<const f32x4*>(at);
+#pragma unroll
+                for (int w = 1; w < NW; ++w) sum += *reinterpret_cast<const f32x4*>(at + w * (NB * 1024));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * h + e] = mfma_epilogue<EPI>(sum[e]);
+            }
+            store_columns<OutT>(s, m, n, v);
+        }
+    });
+}
+
 template <int BM, int BN, int NW, bool A_KC, bool B_KC, bool DIRECT, int EPI, typename OutT>
 __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(GemmPlan p, int tm, int tn, int order) {
-    constexpr int BKT = 32, FM = BM / 16, FN = BN / 16, BLOCKS = FM * FN;
+    constexpr int BKT = 32, FM = BM / 16, FN = BN / 16;
     using TA = Tile<BM, A_KC, 64, BKT, true>;
     using TB = Tile<BN, B_KC, 64, BKT, true>;
     constexpr int NLA = TA::PER_THREAD, NLB = TB::PER_THREAD, NVM = NLA + NLB;   // 16-byte loads per stage
     constexpr int STAGE = TA::BYTES + TB::BYTES;
-    // blocks of the partial tiles that go through LDS at a time (1 KB per block and wave)
-    constexpr int NB = BLOCKS * NW <= 128 ? BLOCKS : 128 / NW, ROUNDS = BLOCKS / NB;
-    constexpr int SMEM = NW * (2 * STAGE > NB * 1024 ? 2 * STAGE : NB * 1024);
-    static_assert(BLOCKS % NB == 0 && NB % 4 == 0 && FN % 4 == 0 && SMEM <= 160 * 1024 && NVM < 64, "tile does not fit the scheme");
+    constexpr int SMEM = NW * 2 * STAGE > partial_bytes<NW, FM, FN>() ? NW * 2 * STAGE : partial_bytes<NW, FM, FN>();
+    static_assert(SMEM <= 160 * 1024 && NVM < 64, "tile does not fit the scheme");
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
     const TileCoord tc = map_tile(blockIdx.x, gridDim.x, tm, tn, p.groups, order);
@@ -209,39 +252,112 @@ __global__ __launch_bounds__(NW * 64) void gemm_wavek_kernel(GemmPlan p, int tm,
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 
-    // Addition of the NW partial tiles, wave order, NB blocks at a time.  A block is kept as it lies in the registers:
-    // row r = lane % 16, four columns from 4 q on, q = lane / 16, at (16 q + (r ^ 4 q)) * 16 (the exclusive-or spreads
-    // the reads below over the banks).  Reading, eight consecutive lanes own the 128 (bf16: 64-column) bytes of a row.
-    constexpr int EPV = 16 / (int)sizeof(OutT);           // columns per lane
-    constexpr int UNIT = sizeof(OutT) == 4 ? 2 : 4;       // blocks side by side that eight lanes cover
-    constexpr int UNITS = NB / UNIT * 2;                  // ... by eight rows: half the rows of a block
-    const int q = lane >> 4, r = lane & 15;
-    char* const dump = smem + wave * (NB * 1024) + (16 * q + (r ^ (4 * q))) * 16;
-    static_for<ROUNDS>([&](auto rix) {
-        constexpr int B0 = decltype(rix)::value * NB;
-        __syncthreads();
-        static_for<NB>([&](auto bix) {
-            constexpr int b = B0 + decltype(bix)::value;
-            *reinterpret_cast<f32x4*>(dump + decltype(bix)::value * 1024) = acc[b / FN][b % FN];
-        });
-        __syncthreads();
-        for (int u = wave; u < UNITS; u += NW) {
-            const int blk = u / 2 * UNIT, row = 8 * (u & 1) + (lane >> 3);
-            const int m = m0 + (B0 + blk) / FN * 16 + row, n = n0 + (B0 + blk) % FN * 16 + (lane & 7) * EPV;
-            float v[EPV];
+    add_partial_tiles<NW, FM, FN, EPI, OutT>(acc, smem, s, m0, n0, wave, lane);
+}
+
+// gemm_rows_kernel: both operands reduction-contiguous, rows at any pitch, fp32 results, few output tiles: as gemm_wavek_kernel, every
+// wave multiplies the whole tile on its 32 elements of each stage, but the stage is 256 deep and loaded by all waves together, so
+// that a load instruction reads 512 consecutive bytes of two rows, not 64 of sixteen.  Bound by a compute unit's load path, which brings
+// about 500 cache lines a microsecond from HBM where an instruction touches many rows and 860 where it touches two: [200, 7503] x
+// [7503, 256], 4 devices, 40.1 us with gemm_wavek_kernel (32 x 64, 112 workgroups), 26.3 here; [512, 50000] x [50000, 64], 2
+// devices, 291 / 120; [500, 62500] x [62500, 512], 8 devices, 1274 / 619 with 64 x 64.
+template <int BM, int BN>
+__global__ __launch_bounds__(512) void gemm_rows_kernel(GemmPlan p, int tm, int tn, int order) {
+    constexpr int NW = 8, NT = 512, BKT = 256, ROWS = BM + BN, STAGE = ROWS * BKT * 2, PER = STAGE / 16 / NT, FM = BM / 16, FN = BN / 16;
+    constexpr int SMEM = 2 * STAGE > partial_bytes<NW, FM, FN>() ? 2 * STAGE : partial_bytes<NW, FM, FN>();
+    __shared__ __attribute__((aligned(1024))) char smem[SMEM];
+
+    const TileCoord tc = map_tile(blockIdx.x, gridDim.x, tm, tn, p.groups, order);
+    if (!tc.valid) return;
+    const GemmShard s = p.s[tc.g];
+    const int m0 = tc.tile_m * BM, n0 = tc.tile_n * BN;
+    if (m0 >= s.m || n0 >= s.n) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    f32x4 acc[FM][FN];
 #pragma unroll
-            for (int h = 0; h < EPV / 4; ++h) {
-                const int cg = (lane & 7) * (EPV / 4) + h;   // group of four columns: block cg / 4, q = cg % 4
-                const char* at = smem + (blk + cg / 4) * 1024 + (16 * (cg & 3) + (row ^ (4 * (cg & 3)))) * 16;
-                f32x4 sum = *reinterpret_cast<const f32x4*>(at);
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-                for (int w = 1; w < NW; ++w) sum += *reinterpret_cast<const f32x4*>(at + w * (NB * 1024));
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    // LDS: rows of A, then of B, 32 chunks of 16 bytes each; chunk c of a row lies at c ^ (row % 16), which puts the sixteen rows that
+    // a fragment read takes from a chunk column, or from two neighbouring ones, on sixteen different groups of banks
+    auto source = [&](int q) {
+        const int row = q / 32, c = (q % 32) ^ (row % 16);
+        return (row < BM ? static_cast<const uint16_t*>(s.a) + (int64_t)min(m0 + row, s.m - 1) * s.lda
+                         : static_cast<const uint16_t*>(s.b) + (int64_t)min(n0 + row - BM, s.n - 1) * s.ldb) + c * 8;
+    };
+    const uint16_t* at[PER];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[4 * h + e] = mfma_epilogue<EPI>(sum[e]);
-            }
-            store_columns<OutT>(s, m, n, v);
+    for (int it = 0; it < PER; ++it) at[it] = source(it * NT + tid);
+    u32x4 r[2][PER];
+    const int steps = s.kk / BKT;
+    int loaded = 0;
+    auto fetch = [&](int set) {   // past the last stage the source stays: the reload is in bounds and unread
+        ++loaded;
+#pragma unroll
+        for (int it = 0; it < PER; ++it) {
+            r[set][it] = *reinterpret_cast<const u32x4_any*>(at[it]);
+            at[it] += loaded < steps ? BKT : 0;
         }
-    });
+    };
+    auto stash = [&](char* st, int set) {
+#pragma unroll
+        for (int it = 0; it < PER; ++it) *reinterpret_cast<u32x4*>(st + (it * NT + tid) * 16) = r[set][it];
+    };
+    const int lo = (lane & 15) * (BKT * 2) + (((4 * wave + (lane >> 4)) ^ (lane & 15)) << 4);
+    auto multiply = [&](const char* st) {
+        bf16x8 fa[FM], fb[FN];
+#pragma unroll
+        for (int i = 0; i < FM; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(st + lo + i * 16 * BKT * 2);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(st + lo + (BM + j * 16) * BKT * 2);
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+    };
+    // LDS traffic of this wave done, then all waves: the loads into registers stay in flight
+    auto barrier = []() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    auto step = [&](auto cur) {   // stage t is in LDS (CUR), t + 1 and t + 2 are on their way in registers
+        constexpr int CUR = decltype(cur)::value;
+        stash(smem + (1 - CUR) * STAGE, 1 - CUR);
+        fetch(1 - CUR);
+        multiply(smem + CUR * STAGE);
+        barrier();
+    };
+    if (steps > 0) {
+        fetch(0);
+        fetch(1);
+        stash(smem, 0);
+        fetch(0);
+        barrier();
+        int t = 0;
+        for (; t + 2 <= steps; t += 2) {
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+        }
+        if (t < steps) step(std::integral_constant<int, 0>{});
+    }
+    if (const int k0 = steps * BKT; k0 < s.kk) {   // the rest, zeros behind it in both operands
+#pragma unroll
+        for (int it = 0; it < PER; ++it) {
+            const int q = it * NT + tid, valid = s.kk - k0 - ((q % 32) ^ (q / 32 % 16)) * 8;
+            const uint16_t* src = source(q) + k0;
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (valid >= 8) v = *reinterpret_cast<const u32x4_any*>(src);
+            else {
+#pragma unroll
+                for (int e = 0; e < 7; ++e)
+                    if (e < valid) v[e >> 1] |= (uint32_t)src[e] << (16 * (e & 1));
+            }
+            *reinterpret_cast<u32x4*>(smem + q * 16) = v;
+        }
+        __syncthreads();
+        multiply(smem);
+    }
+    add_partial_tiles<NW, FM, FN, SBP_EPI_NONE, float>(acc, smem, s, m0, n0, wave, lane);
 }
 
 // 4 waves of BM/2 x BN/2, two 32-deep LDS stages filled from registers that run two stages ahead, one barrier a
@@ -597,6 +713,16 @@ int32_t launch_out(const GemmPlan& plan, int max_m, int max_n, int order, hipStr
     return launch_layout<BM, BN, NW, DIRECT, SBP_EPI_NONE, uint16_t>(plan, max_m, max_n, order, st);
 }
 
+template <int BM, int BN>
+int32_t launch_rows(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t st) {
+    if (!plan.a_kc || !plan.b_kc || plan.out_dtype != SBP_F32 || plan.epilogue != SBP_EPI_NONE) return SBP_ERR_UNSUPPORTED;
+    const int tm = tiles_along(max_m, BM), tn = tiles_along(max_n, BN);
+    const int64_t nblk = ((int64_t)tm * tn * plan.groups + 7) / 8 * 8;
+    if (!grid_fits(nblk, 512)) return SBP_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((gemm_rows_kernel<BM, BN>), dim3((uint32_t)nblk), dim3(512), 0, st, plan, tm, tn, order);
+    return launch_status(__func__);
+}
+
 template <int EPI, typename OutT>
 int32_t launch_deep_layout(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t st) {
     const int tm = tiles_along(max_m, 128), tn = tiles_along(max_n, 128);
@@ -624,6 +750,8 @@ int32_t launch_gemm_any(const GemmPlan& plan, int max_m, int max_n, int tile, bo
         case WAVEK_128: return direct ? launch_out<128, 64, 4, true>(plan, max_m, max_n, order, stream) : SBP_ERR_UNSUPPORTED;
         case WAVEK_64: return direct ? launch_out<64, 64, 8, true>(plan, max_m, max_n, order, stream) : launch_out<64, 64, 8, false>(plan, max_m, max_n, order, stream);
         case WAVEK_32: return direct ? launch_out<32, 64, 8, true>(plan, max_m, max_n, order, stream) : launch_out<32, 64, 8, false>(plan, max_m, max_n, order, stream);
+        case ROWS_32: return launch_rows<32, 32>(plan, max_m, max_n, order, stream);
+        case ROWS_64: return launch_rows<64, 64>(plan, max_m, max_n, order, stream);
         case REG_128: return launch_out<128, 128, 0, false>(plan, max_m, max_n, order, stream);
         case REG_64: return launch_out<64, 64, 0, false>(plan, max_m, max_n, order, stream);
         default: return SBP_ERR_UNSUPPORTED;

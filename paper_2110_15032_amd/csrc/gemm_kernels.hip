@@ -1673,6 +1673,21 @@ AnyTile any_tile(const GemmPlan& plan, int max_m, int max_n) {
     if (2 * tiles_of(plan, max_m, max_n, 64, 64) <= cu && longest_reduction(plan) >= 4096) return plan.a_kc ? WAVEK_32 : WAVEK_64;
     return max_m > 64 && max_n > 64 && 2 * tiles_of(plan, max_m, max_n, 128, 128) >= cu ? REG_128 : REG_64;
 }
+// Both operands reduction-contiguous, fp32 results, few tiles: all waves of a workgroup load 512 bytes of a row at a time
+// (gemm_rows_kernel), 32 x 32 tiles where those fit one round of one per compute unit, or two if the reduction is long, else 64 x 64.
+// us, without it / 32 x 32 / 64 x 64 (rows x reduction x columns, devices; small tiles): 200 x 7503 x 256, 4 (224) 40.1 / 26.3 / 54;
+// 64 x 4096 x 128, 1 (8) 14.3 / 8.3 / 17.4; 512 x 50000 x 64, 2 (64) 291 / 120 / 251; 250 x 2000 x 250, 4 (256) 11.3 / 8.6 / 15.3;
+// 325 x 26100 x 219, 4 (308) 116 / 85 / 93; 891 x 2340 x 201, 2 (392) 14.5 / 12.8 / 16.5 but 130 x 1701 x 1062, 2 (340) 14.2 / 19.9 / 22.3;
+// 633 x 33323 x 163, 3 (360) 168 / 153 / 168.  Large: 1000 x 12501 x 128, 8 (256) 131 / 157 / 97; 500 x 62500 x 512, 8 (512) 1274 /
+// 1158 / 619; 654 x 38256 x 426, 4 (308) 506 / 369 / 329; 691 x 26688 x 726, 3 (396, rows on cache lines) 181 / 217 / 183; but
+// 594 x 4471 x 577, 2 (200) 34.0 / 54 / 41, 641 x 6567 x 1143, 8 (1584) 186 / 402 / 318.
+int rows_tile(const GemmPlan& plan, int max_m, int max_n) {   // -1: none
+    if (!plan.a_kc || !plan.b_kc || plan.out_dtype != SBP_F32 || plan.epilogue != SBP_EPI_NONE) return -1;
+    const int64_t cu = compute_units(), small = tiles_of(plan, max_m, max_n, 32, 32), large = tiles_of(plan, max_m, max_n, 64, 64);
+    const int k = longest_reduction(plan);
+    if (small <= cu ? k >= 512 : small <= 2 * cu && k >= 4096) return ROWS_32;
+    return large <= 2 * cu && k >= 8192 ? ROWS_64 : -1;
+}
 // fp32 operands on the matrix cores: the largest tile that gives the chip enough workgroups and is not mostly padding.  us,
 // 128 x 128 / 64 x 64 / 32 x 32 with the waves splitting the reduction (rows x reduction x columns, devices):
 // 2000 x 750 x 1500, 4: 177 / 194 / 233; 1024 x 12500 x 512, 4 (128 large tiles): 906 / 472 / 578; 600 x 1000 x 500, 3 (240 of
@@ -1700,7 +1715,8 @@ int32_t launch_f32(const GemmPlan& plan, int max_m, int max_n, int32_t variant, 
     return launch_gemm_f32(plan, max_m, max_n, tile, tile_order_for(tiles_along(max_m, b), tiles_along(max_n, b)), stream);
 }
 int32_t launch_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool direct, hipStream_t stream) {
-    const int bm = tile == WAVEK_32 ? 32 : tile == WAVEK_64 || tile == REG_64 ? 64 : 128, bn = tile == REG_128 ? 128 : 64;
+    const int bm = tile == WAVEK_32 || tile == ROWS_32 ? 32 : tile == WAVEK_64 || tile == REG_64 || tile == ROWS_64 ? 64 : 128;
+    const int bn = tile == REG_128 ? 128 : tile == ROWS_32 ? 32 : 64;
     return launch_gemm_any(plan, max_m, max_n, tile, direct, tile_order_for(tiles_along(max_m, bm), tiles_along(max_n, bn)), stream);
 }
 
@@ -1811,11 +1827,13 @@ int32_t launch_chosen(const GemmPlan& plan, int max_m, int max_n, int32_t varian
         return launch_chosen(erf, max_m, max_n, variant, stream);
     }
     if (variant >= 40 && variant <= 44) return launch_any(plan, max_m, max_n, variant - 40, direct, stream);
+    if (variant == 51 || variant == 52) return launch_any(plan, max_m, max_n, variant == 51 ? ROWS_32 : ROWS_64, direct, stream);
     if (variant == 48) return direct ? launch_deep(plan, max_m, max_n, stream) : SBP_ERR_UNSUPPORTED;
     if (variant == 0 && one_element_pays(plan, max_m, max_n, direct)) return launch_generic(plan, max_m, max_n, stream);
+    const int rows = variant == 0 ? rows_tile(plan, max_m, max_n) : -1;
     if (!direct) {
         if (variant > 1) return SBP_ERR_UNSUPPORTED;
-        return launch_any(plan, max_m, max_n, any_tile(plan, max_m, max_n), false, stream);
+        return launch_any(plan, max_m, max_n, rows >= 0 ? rows : any_tile(plan, max_m, max_n), false, stream);
     }
     if (variant == 0) {
         // Default: the 256 x 256 tile over 8 waves with four 32-deep LDS stages, as one persistent workgroup per compute
@@ -1825,6 +1843,7 @@ int32_t launch_chosen(const GemmPlan& plan, int max_m, int max_n, int32_t varian
         const bool steps64 = k64 && rows_of_8(plan), two_stages = steps64 && two_stages_pay(plan, max_m, max_n);
         // two rounds of one workgroup per compute unit against one of two: 280 tiles, 88 rows, length 704 22.4 / 18.3 us
         const bool one_round = tiles_of(plan, max_m, max_n, 128, 128) <= compute_units() || longest_reduction(plan) >= 2048;
+        if (rows >= 0 && 2 * tiles_of(plan, max_m, max_n, 128, 128) <= compute_units()) return launch_any(plan, max_m, max_n, rows, true, stream);
         if (deep_pays(plan, max_m, max_n) && (one_round || !two_stages)) return launch_deep(plan, max_m, max_n, stream);
         if (wavek_pays(plan, max_m, max_n)) {
             // us, 128 x 128 tile with two stages / waves splitting: 70 tiles, 72 columns, length 768 9.9 / 11.4, 120 of 112 columns,

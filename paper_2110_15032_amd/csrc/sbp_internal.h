@@ -101,7 +101,9 @@ enum AnyTile : int32_t {
     WAVEK_64,       // 64 x 64
     WAVEK_128,      // 128 x 64, direct only
     REG_128,        // 128 x 128
-    REG_64          // 64 x 64
+    REG_64,         // 64 x 64
+    ROWS_32,        // 32 x 32, both operands reduction-contiguous, fp32 results
+    ROWS_64         // 64 x 64, the same
 };
 int32_t launch_gemm_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool direct, int order, hipStream_t stream);
 // gemm_any_kernels.hip, 128 x 128 tile, any operand layout, rows 16-byte aligned, any reduction length

@@ -169,6 +169,21 @@ def test_bf16_persistent_tiles(kk, ldy, tx, tw, out):
             assert np.array_equal(top[i][:, 0], y.max(axis=1))
 
 
+@pytest.mark.parametrize("variant", [0, 51, 52])
+@pytest.mark.parametrize("odd", [0, 1])
+@pytest.mark.parametrize("M,kk,N", [(1, 1, 1), (3, 255, 2), (32, 256, 32), (33, 263, 31), (64, 511, 65), (70, 512, 40), (31, 777, 130), (130, 1025, 64), (65, 9000, 70)])
+def test_bf16_long_pieces_of_rows(M, kk, N, odd, variant):
+    """both operands reduction-contiguous, fp32 results: no whole 256-deep stage, one, two, three and more, with and without a remainder;
+    rows of any pitch; one tile and ragged further ones"""
+    k = 2
+    X, W = bf16(3, (M, k * kk)), bf16(4, (k * kk, N), 0.5)
+    Xs, Ws = orc.scatter(X, orc.S1, k), orc.scatter(W, orc.S0, k)
+    ref, _ = orc.matmul_sbp([values(x) for x in Xs], orc.S1, [values(w) for w in Ws], orc.S0)
+    got, _ = run(Xs, orc.S1, Ws, orc.S0, M, k * kk, N, k, 0, 1, pitch(Xs, 0, 8, odd), pitch(Ws, 1, 8, 8 + odd), pitch(ref, 0, 2, 1), variant=variant)
+    for i in range(k):
+        assert_matmul_close(got[i], ref[i], 1e-5, f"{M}x{kk}x{N} odd={odd} v{variant} shard {i}")
+
+
 @pytest.mark.parametrize("epilogue", [sbp.EPI_NONE, sbp.EPI_GELU])
 @pytest.mark.parametrize("M,K,N", [(5, 33, 7), (70, 100, 203)])
 def test_bf16_odd_rows_rounded_results(M, K, N, epilogue):
