@@ -492,28 +492,34 @@ __global__ __launch_bounds__(256, 2) void gemm_reg_kernel(GemmPlan p, int tm, in
 // of four waves (64 x 64 each) take the two 32-deep halves of every 64-deep stage; four stages, one barrier a stage, the
 // two partial tiles added through LDS.
 //   * Two waves per SIMD cover each other's waits, which one workgroup of gemm_mfma_pipe16_kernel per compute unit does not.
-//   * A stage reads one cache line of a reduction-contiguous row, whole, wherever the row starts (Tile::line_offset): pieces of
-//     128 bytes that straddle two lines cost the load path twice (all lines in L2, rows 250000 bytes apart: 0.58 us a stage
+//   * A stage reads one cache line of a reduction-contiguous row, whole, wherever the row starts (LINES, Tile::line_offset): pieces
+//     of 128 bytes that straddle two lines cost the load path twice (all lines in L2, rows 250000 bytes apart: 0.58 us a stage
 //     against 0.35 with rows on lines).  A fragment then comes from two neighbouring stages, so that one stage less is in
-//     flight, which costs nothing: a compute unit's load path is no faster with more.
+//     flight; with every row on a line the stages are read as they are (with lines all the same [1500, 2048] x [2048, 1500] took
+//     17.3 us, without 16.2).
 //   * The load path returns in order.  A stage of 32 KB takes 0.21 us when all of it is in L2 and 0.58 us when any of it comes from
 //     HBM, whatever the number of stages in flight; operand tiles shared by the workgroups of an XCD are in L2 for all but the
 //     first, but all of them wait for that one.  So the lines of four stages are touched at once, three stages ahead of their
 //     loads, every workgroup the part that is its share among those that read the same tile: one wait for HBM in four stages.
-// Feature gradient of a classifier, 8 devices, [1024, 125000] x [125000, 512], us: 1477 -> 1093 (left rows on lines), with both
-// rows 250000 bytes apart 1915 -> 1073; without the touches 1168.  [1024, 16384] x [16384, 512] 160 -> 150; [777, 1000] x [1000, 1000],
-// 3 devices, 15.5 -> 14.6.  Of the 0.54 us a stage that are left the multiplication and its LDS reads take 0.36.
-template <bool A_KC, bool B_KC, int EPI, typename OutT>
+// us, before / now: feature gradient of a classifier, 8 devices, [1024, 125000] x [125000, 512], left rows on lines 1475 / 1058, with both
+// rows 250000 bytes apart 1915 / 1073, neither operand reduction-contiguous 1250 / 1099; without the touches 1168.  [1024, 16384] x
+// [16384, 512] 160 / 148; [777, 1000] x [1000, 1000], 3 devices, 14.7 / 13.1.  Of the 0.54 us a stage that are left the multiplication
+// and its LDS reads take 0.36.
+// LINES: some row of a reduction-contiguous operand starts inside a cache line.
+template <bool A_KC, bool B_KC, bool LINES, int EPI, typename OutT>
 __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int tn, int order) {
     constexpr int BM = 128, BN = 128, BKT = 64, NT = 512, NST = 4, FM = 4, FN = 4;
     using TA = Tile<BM, A_KC, NT, BKT, true>;
     using TB = Tile<BN, B_KC, NT, BKT, true>;
     constexpr int NVM = TA::PER_THREAD + TB::PER_THREAD, STAGE = TA::BYTES + TB::BYTES;
-    constexpr bool LINES = A_KC || B_KC;
-    // Lines are touched this many stages ahead (5, 6 and 8 measured: within 2 % with whole lines, 2 to 12 % slower without), as long
-    // as a workgroup's share of four stages is not more: us, share, with / without: 192 lines 1073 / 1168 and 150.3 / 158.7, 256
-    // 16.9 / 16.0, 288 182.7 / 178.3; neither operand reduction-contiguous 192 148.5 / 159.9, 288 165.5 / 176.3.
-    constexpr int TOUCH_DIST = 7, TOUCH_MAX = LINES ? 224 : 320;
+    constexpr bool LA_ = LINES && A_KC, LB_ = LINES && B_KC;   // operands that are loaded by whole lines
+    static_assert(!LINES || A_KC || B_KC, "only rows along the reduction are pieced together");
+    // Lines are touched this many stages ahead (5, 6 and 8 measured: within 2 % with a reduction-contiguous operand, 2 to 12 % slower
+    // without), as long as a workgroup's share of four stages is not more than TOUCH_MAX and there are TOUCH_STEPS stages; shorter
+    // products mostly read what the memory-side cache still holds.  us, with / without: share of 192 lines 1073 / 1168 and 150.3 / 158.7,
+    // 256 16.9 / 16.0, 288 182.7 / 178.3; neither operand reduction-contiguous 192 148.5 / 159.9, 288 165.5 / 176.3; [1024, 3072] x [3072, 512],
+    // 8 devices (48 stages), 33.8 / 37.2, length 2048 26.4 / 27.0, [1767, 2048] x [2048, 1000], 2 devices, bf16 results, 20.2 / 19.0.
+    constexpr int TOUCH_DIST = 7, TOUCH_MAX = A_KC || B_KC ? 224 : 320, TOUCH_STEPS = 48;
     static_assert(NST * STAGE == 8 * FM * FN * 1024, "the partial tiles fill the stages");
     __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE + 256];   // the last 256 bytes: what the touches bring
 
@@ -535,63 +541,82 @@ __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int 
 
     const int steps = s.kk / BKT;
     // whole lines (line_offset): stage `steps` is the last one of a reduction-contiguous operand, steps - 1 of the other kind
-    gbl_char* A = (gbl_char*)s.a - (A_KC ? 128 : 0);
-    gbl_char* B = (gbl_char*)s.b - (B_KC ? 128 : 0);
+    gbl_char* A = (gbl_char*)s.a - (LA_ ? 128 : 0);
+    gbl_char* B = (gbl_char*)s.b - (LB_ ? 128 : 0);
     uint32_t offa[TA::PER_THREAD], offb[TB::PER_THREAD], enda[TA::PER_THREAD], endb[TB::PER_THREAD], begina[TA::PER_THREAD], beginb[TB::PER_THREAD];
 #pragma unroll
     for (int it = 0; it < TA::PER_THREAD; ++it) {
-        if constexpr (A_KC) offa[it] = TA::line_offset(s.a, s.lda, m0, s.m, it * NT + tid, begina[it], enda[it]);
+        if constexpr (LA_) offa[it] = TA::line_offset(s.a, s.lda, m0, s.m, it * NT + tid, begina[it], enda[it]);
         else offa[it] = TA::src_offset(s.lda, m0, s.m, it * NT + tid), begina[it] = enda[it] = 0;
     }
 #pragma unroll
     for (int it = 0; it < TB::PER_THREAD; ++it) {
-        if constexpr (B_KC) offb[it] = TB::line_offset(s.b, s.ldb, n0, s.n, it * NT + tid, beginb[it], endb[it]);
+        if constexpr (LB_) offb[it] = TB::line_offset(s.b, s.ldb, n0, s.n, it * NT + tid, beginb[it], endb[it]);
         else offb[it] = TB::src_offset(s.ldb, n0, s.n, it * NT + tid), beginb[it] = endb[it] = 0;
     }
     const uint32_t stepa = TA::step_bytes(s.lda), stepb = TB::step_bytes(s.ldb);
     int loaded = 0;
-    auto issue = [&](char* st, bool first) {   // past the last stage the source stays: the reload is in bounds and unread
+    enum Issue { FIRST, INNER, ANY };   // INNER: the stages up to the one loaded are whole, and another follows
+    auto issue = [&](char* st, auto kind) {   // past the last stage the source stays: the reload is in bounds and unread
+        constexpr Issue KIND = decltype(kind)::value;
+        if constexpr (KIND == INNER) {
+            TA::load_direct_untracked(st, A, offa, wave);
+            TB::load_direct_untracked(st + TA::BYTES, B, offb, wave);
+            ++loaded;
+            A += stepa;
+            B += stepb;
+            return;
+        }
+        constexpr bool first = KIND == FIRST;
         const uint32_t last = !first && loaded >= steps ? ~0u : 0u;
         uint32_t oa[TA::PER_THREAD], ob[TB::PER_THREAD];
 #pragma unroll
-        for (int it = 0; it < TA::PER_THREAD; ++it) oa[it] = !A_KC ? offa[it] : first ? offa[it] + begina[it] : offa[it] - (enda[it] & last);
+        for (int it = 0; it < TA::PER_THREAD; ++it) oa[it] = !LA_ ? offa[it] : first ? offa[it] + begina[it] : offa[it] - (enda[it] & last);
 #pragma unroll
-        for (int it = 0; it < TB::PER_THREAD; ++it) ob[it] = !B_KC ? offb[it] : first ? offb[it] + beginb[it] : offb[it] - (endb[it] & last);
+        for (int it = 0; it < TB::PER_THREAD; ++it) ob[it] = !LB_ ? offb[it] : first ? offb[it] + beginb[it] : offb[it] - (endb[it] & last);
         TA::load_direct_untracked(st, A, oa, wave);
         TB::load_direct_untracked(st + TA::BYTES, B, ob, wave);
         ++loaded;
-        A += loaded < steps + (A_KC ? 1 : 0) ? stepa : 0u;
-        B += loaded < steps + (B_KC ? 1 : 0) ? stepb : 0u;
+        A += loaded < steps + (LA_ ? 1 : 0) ? stepa : 0u;
+        B += loaded < steps + (LB_ ? 1 : 0) ? stepb : 0u;
     };
-    // this workgroup's share of the lines of NST stages, one per lane
-    const Sharers sh = tile_sharers(blockIdx.x, gridDim.x, tm, tn, p.groups, order);
-    constexpr int LA = TA::template touch_lines<NST>(), LB = TB::template touch_lines<NST>();
-    const int qa = (LA + sh.na - 1) / sh.na, qb = (LB + sh.nb - 1) / sh.nb;
-    const char* touch;
-    uint32_t touch_step;
+    // this workgroup's share of the lines of NST stages, one per lane; worked out while the first stages are on their way
+    const char* touch = static_cast<const char*>(s.a);
+    uint32_t touch_step = 0;
     uint64_t touch_lanes = 0;
-    {
+    auto share_touches = [&]() {
+        const Sharers sh = tile_sharers(blockIdx.x, gridDim.x, tm, tn, p.groups, order);
+        constexpr int LA = TA::template touch_lines<NST>(), LB = TB::template touch_lines<NST>();
+        const int qa = (LA + sh.na - 1) / sh.na, qb = (LB + sh.nb - 1) / sh.nb;
         const int l = lane * 8 + wave;   // dealt over the waves; l >= qa + qb: no line
         const bool a = l < qa;
         const int la = min(sh.a * qa + l, LA - 1), lb = min(sh.b * qb + l - qa, LB - 1);
         touch = a ? (const char*)s.a + TA::template touch_offset<NST>(s.lda, m0, s.m, la) : (const char*)s.b + TB::template touch_offset<NST>(s.ldb, n0, s.n, max(lb, 0));
         touch_step = a ? TA::step_bytes(s.lda) : TB::step_bytes(s.ldb);
         static_assert(TOUCH_MAX <= NT, "one line per lane");
-        if (steps >= 4 * NST && qa + qb <= TOUCH_MAX) touch_lanes = __ballot(l < qa + qb);
-    }
+        if (qa + qb <= TOUCH_MAX) touch_lanes = __ballot(l < qa + qb);
+    };
     auto touch_ahead = [&](int t) {   // the lines of stages t .. t + NST - 1
         touch_untracked(touch + (uint64_t)touch_step * (uint32_t)min(t, steps - NST), touch_lanes, smem + NST * STAGE);
     };
     bf16x8 fa[2][FM], fb[2][FN];
     // does this lane's chunk of a step lie in the next stage?  (misalignments repeat every 16 rows)
-    const bool nexta = A_KC && 4 * half + (lane >> 4) + TA::misalignment(s.a, s.lda, m0 + (lane & 15)) >= 8;
-    const bool nextb = B_KC && 4 * half + (lane >> 4) + TB::misalignment(s.b, s.ldb, n0 + (lane & 15)) >= 8;
-    auto read = [&](int cur, int next, int set) {
-        const int oa = loa + (A_KC ? (nexta ? next : cur) * STAGE : cur * STAGE), ob = lob + (B_KC ? (nextb ? next : cur) * STAGE : cur * STAGE);
+    const bool nexta = LA_ && 4 * half + (lane >> 4) + TA::misalignment(s.a, s.lda, m0 + (lane & 15)) >= 8;
+    const bool nextb = LB_ && 4 * half + (lane >> 4) + TB::misalignment(s.b, s.ldb, n0 + (lane & 15)) >= 8;
+    // what that makes of the lane offsets, for each stage that a step may start in (kept: worked out in every step they cost 60 ns)
+    int oa[NST], ob[NST];
 #pragma unroll
-        for (int j = 0; j < FN; ++j) fb[set][j] = TB::frag16(smem + TA::BYTES, ob, j);
+    for (int i = 0; i < NST; ++i) {
+        oa[i] = loa + (nexta ? (i + 1) % NST : i) * STAGE;
+        ob[i] = lob + (nextb ? (i + 1) % NST : i) * STAGE;
+        if constexpr (LA_) asm("" : "+v"(oa[i]));
+        if constexpr (LB_) asm("" : "+v"(ob[i]));
+    }
+    auto read_at = [&](int la, int lb, int set) {
 #pragma unroll
-        for (int i = 0; i < FM; ++i) fa[set][i] = TA::frag16(smem, oa, i);
+        for (int j = 0; j < FN; ++j) fb[set][j] = TB::frag16(smem + TA::BYTES, lb, j);
+#pragma unroll
+        for (int i = 0; i < FM; ++i) fa[set][i] = TA::frag16(smem, la, i);
     };
     auto mfmas = [&](int set) {
 #pragma unroll
@@ -604,16 +629,16 @@ __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int 
     // is free for t + NST, and the next fragments may be read, all through the multiplication.
     int t = 0;
     auto wait_keep = [](auto n) { __builtin_amdgcn_s_waitcnt((vmcnt_only(decltype(n)::value) & ~0x0F00)); };   // vmcnt(n) lgkmcnt(0)
-    auto step = [&](auto cur) {
+    auto step = [&](auto cur, auto kind) {
         constexpr int CUR = decltype(cur)::value;
         // stages t + 2, t + 3 (with whole lines only t + 3) and the touch behind the one waited for stay in flight
         if constexpr (LINES) wait_keep(std::integral_constant<int, (NST - 3) * NVM + (CUR == 1 || CUR == 2)>{});
         else wait_keep(std::integral_constant<int, (NST - 2) * NVM + (CUR != 0)>{});
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        issue(smem + CUR * STAGE, false);
+        issue(smem + CUR * STAGE, kind);
         if constexpr (CUR == 0) touch_ahead(t + TOUCH_DIST);
-        read((CUR + 1) % NST, (CUR + 2) % NST, (CUR + 1) & 1);
+        read_at(oa[(CUR + 1) % NST], ob[(CUR + 1) % NST], (CUR + 1) & 1);
         mfmas(CUR & 1);
         constexpr int NDS = (A_KC ? FM : 2 * FM) + (B_KC ? FN : 2 * FN), NM = FM * FN - 4;
         static_for<NM>([&](auto i) {   // fragment reads spread over all but the last matrix instructions
@@ -625,15 +650,20 @@ __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int 
         __builtin_amdgcn_sched_barrier(0);
     };
     if (steps > 0) {
-        static_for<NST>([&](auto i) { issue(smem + decltype(i)::value * STAGE, decltype(i)::value == 0); });
+        using Inner = std::integral_constant<Issue, INNER>;
+        using Any = std::integral_constant<Issue, ANY>;
+        issue(smem, std::integral_constant<Issue, FIRST>{});
+        static_for<NST - 1>([&](auto i) { issue(smem + (decltype(i)::value + 1) * STAGE, Any{}); });
+        if (steps >= TOUCH_STEPS) share_touches();
         wait_keep(std::integral_constant<int, (NST - (LINES ? 2 : 1)) * NVM>{});
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        read(0, 1, 0);
-        for (; t + NST <= steps; t += NST) static_for<NST>(step);
+        read_at(oa[0], ob[0], 0);
+        for (; t + 2 * NST < steps; t += NST) static_for<NST>([&](auto i) { step(i, Inner{}); });
+        for (; t + NST <= steps; t += NST) static_for<NST>([&](auto i) { step(i, Any{}); });
         const int rem = steps - t;
         static_for<NST - 1>([&](auto i) {
-            if (decltype(i)::value < rem) step(i);
+            if (decltype(i)::value < rem) step(i, Any{});
         });
         __builtin_amdgcn_s_waitcnt(0x0070);   // the unread trailing loads have landed before their stages are reused
     }
@@ -646,7 +676,7 @@ __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int 
         for (int it = 0; it < TB::PER_THREAD; ++it)
             *reinterpret_cast<u32x4*>(smem + TA::BYTES + (it * NT + tid) * 16) = TB::tail_chunk(static_cast<const uint16_t*>(s.b), s.ldb, n0, s.n, s.kk, k0, it * NT + tid);
         __syncthreads();
-        read(0, 0, 0);
+        read_at(loa, lob, 0);
         mfmas(0);
         __syncthreads();
     }
@@ -729,8 +759,16 @@ int32_t launch_deep_layout(const GemmPlan& plan, int max_m, int max_n, int order
     const int64_t nblk = ((int64_t)tm * tn * plan.groups + 7) / 8 * 8;
     if (!grid_fits(nblk, 512)) return SBP_ERR_UNSUPPORTED;
     void (*kern)(GemmPlan, int, int, int);
-    if (plan.a_kc) kern = plan.b_kc ? gemm_deep_kernel<true, true, EPI, OutT> : gemm_deep_kernel<true, false, EPI, OutT>;
-    else kern = plan.b_kc ? gemm_deep_kernel<false, true, EPI, OutT> : gemm_deep_kernel<false, false, EPI, OutT>;
+    bool lines = false;   // does a row along the reduction start inside a cache line?
+    for (int g = 0; g < plan.groups; ++g) {
+        const GemmShard& d = plan.s[g];
+        if (!d.m || !d.n || !d.kk) continue;
+        lines |= (plan.a_kc && ((reinterpret_cast<uintptr_t>(d.a) & 127) || d.lda % 64)) || (plan.b_kc && ((reinterpret_cast<uintptr_t>(d.b) & 127) || d.ldb % 64));
+    }
+    if (plan.a_kc && plan.b_kc) kern = lines ? gemm_deep_kernel<true, true, true, EPI, OutT> : gemm_deep_kernel<true, true, false, EPI, OutT>;
+    else if (plan.a_kc) kern = lines ? gemm_deep_kernel<true, false, true, EPI, OutT> : gemm_deep_kernel<true, false, false, EPI, OutT>;
+    else if (plan.b_kc) kern = lines ? gemm_deep_kernel<false, true, true, EPI, OutT> : gemm_deep_kernel<false, true, false, EPI, OutT>;
+    else kern = gemm_deep_kernel<false, false, false, EPI, OutT>;
     hipLaunchKernelGGL(kern, dim3((uint32_t)nblk), dim3(512), 0, st, plan, tm, tn, order);
     return launch_status(__func__);
 }

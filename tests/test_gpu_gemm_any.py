@@ -97,10 +97,10 @@ def test_bf16_two_wave_groups_over_the_reduction(M, kk, N, tx, tw, out):
 
 @pytest.mark.parametrize("tx,tw", [(0, 0), (1, 0), (0, 1), (1, 1)])
 @pytest.mark.parametrize("M,kk,N,extra,start", [(130, 64, 129, 8, 0), (128, 72, 200, 24, 56), (140, 200, 136, 0, 8), (260, 256, 130, 40, 24), (129, 330, 257, 8, 120),
-                                                (300, 1100, 140, 16, 64), (256, 2113, 384, 56, 40)])
+                                                (300, 3300, 140, 16, 64), (256, 2113, 384, 56, 40), (140, 3136, 256, 0, 0)])
 def test_bf16_rows_anywhere_in_a_cache_line(M, kk, N, extra, start, tx, tw):
-    """variant 48, buffers that start and rows that lie 16-byte aligned anywhere in a 128-byte line: one stage to more than the
-    pipeline holds, with and without a remainder, lines touched ahead (the longer ones); NaN before, between and behind the rows"""
+    """variant 48, buffers that start and rows that lie 16-byte aligned anywhere in a 128-byte line, or all on lines: one stage to more
+    than the pipeline holds, with and without a remainder, lines touched ahead (3072 and more); NaN before, between and behind the rows"""
     import torch
     k = 2
     X, W = bf16(3, (M, k * kk)), bf16(4, (k * kk, N), 0.5)
@@ -165,6 +165,39 @@ def test_bf16_persistent_tiles(kk, ldy, tx, tw, out):
             ref = orc.gelu(ref)
         y = got[i] if out == "f32" else values(got[i])
         assert_matmul_close(y, ref, 1e-5 if out == "f32" else 2.0 ** -7, f"kk={kk} ldy={ldy} trans=({tx},{tw}) {out} shard {i}")
+        if out == "rowmax":
+            assert np.array_equal(top[i][:, 0], y.max(axis=1))
+
+
+@pytest.mark.parametrize("variant", [8, 9, 16, 21])
+@pytest.mark.parametrize("out", ["f32", "bf16", "gelu", "rowmax"])
+@pytest.mark.parametrize("M,N", [(255, 264), (300, 388), (257, 392), (130, 391), (512, 520)])
+def test_bf16_tiles_cut_by_the_edge(M, N, out, variant):
+    """results stored 16 bytes at a time up to the edge: rows cut anywhere, columns at a multiple of 16 bytes or inside one; the padding
+    behind a row stays as it was (DevTensor)"""
+    k, kk = 2, 256
+    if out == "f32":
+        X, W, sx, sw, K, C = bf16(3, (M, k * kk)), bf16(4, (k * kk, N), 0.5), orc.S1, orc.S0, k * kk, N
+    else:
+        X, W, sx, sw, K, C = bf16(3, (M, kk)), bf16(4, (kk, k * N), 0.1), orc.B, orc.S1, kk, k * N
+    Xs, Ws = orc.scatter(X, sx, k), orc.scatter(W, sw, k)
+    ref, _ = orc.matmul_sbp([values(x) for x in Xs], sx, [values(w) for w in Ws], sw)
+    dx, dw = DevTensor.from_host(Xs, M, K, sx, ld=kk), DevTensor.from_host(Ws, K, C, sw, ld=-(-N // 8) * 8)
+    dy = DevTensor.empty(M, C, np.float32 if out == "f32" else np.uint16, orc.P_SUM if out == "f32" else orc.S1, k, ld=-(-N // 8) * 8 + 8)
+    dm = DevTensor.empty(M, 1, np.float32, orc.P_MAX, k)
+    sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, variant)
+    try:
+        if out == "rowmax":
+            sbp.sbp_matmul_rowmax(dx.desc, TO_ABI[sx], dw.desc, TO_ABI[sw], dy.desc, sbp.AUTO, dm.desc, k)
+        else:
+            sbp.sbp_matmul_ex(dx.desc, TO_ABI[sx], dw.desc, TO_ABI[sw], dy.desc, sbp.AUTO, k, None, sbp.EPI_GELU if out == "gelu" else sbp.EPI_NONE)
+        sync()
+    finally:
+        sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, 0)
+    got, top = dy.host(), dm.host()
+    for i in range(k):
+        y = got[i] if out == "f32" else values(got[i])
+        assert_matmul_close(y, orc.gelu(ref[i]) if out == "gelu" else ref[i], 1e-5 if out == "f32" else 2.0 ** -7, f"{M}x{N} {out} v{variant} shard {i}")
         if out == "rowmax":
             assert np.array_equal(top[i][:, 0], y.max(axis=1))
 
@@ -293,7 +326,7 @@ def test_f32_values_that_terms_do_not_hold(case, types, variant):
         ref = X.astype(np.float64) @ wide
         scale = np.abs(X.astype(np.float64)) @ np.abs(wide)
     ok = np.isfinite(want)
-    assert np.all(np.abs(got - ref)[ok] <= 1e-5 * scale[ok] + kk * 2.0 ** -149)
+    assert np.all(np.abs(got[ok] - ref[ok]) <= 1e-5 * scale[ok] + kk * 2.0 ** -149)
 
 
 @pytest.mark.parametrize("M,K,N", [(5, 33, 7), (70, 300, 203)])
