@@ -458,6 +458,12 @@ __device__ inline void store16_untracked(V* p, const V v, bool stream) {
     if (stream) asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
     else asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
+// the same store by the lanes of a uniform mask only (all lanes active before and after); counted whatever the mask
+template <typename V>
+__device__ inline void store16_untracked(V* p, const V v, bool stream, uint64_t lanes) {
+    if (stream) asm volatile("s_mov_b64 exec, %2\n\tglobal_store_dwordx4 %0, %1, off nt\n\ts_mov_b64 exec, -1\n\ts_nop 0" : : "v"(p), "v"(v), "s"(lanes) : "memory");
+    else asm volatile("s_mov_b64 exec, %2\n\tglobal_store_dwordx4 %0, %1, off\n\ts_mov_b64 exec, -1\n\ts_nop 0" : : "v"(p), "v"(v), "s"(lanes) : "memory");
+}
 // element stores of the same kind for edge tiles (a tracked store anywhere in the tile loop is enough
 // to bring the compiler's blanket waits back)
 __device__ inline void store_out_untracked(float* c, int64_t pos, float v) {

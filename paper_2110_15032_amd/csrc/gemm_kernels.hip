@@ -283,21 +283,38 @@ __device__ __attribute__((always_inline)) inline void store_tile(const f32x16 (&
 //   bf16: a 32-row x 64-column strip (2 x 4 blocks) at a time.  Lanes round and pair their rows R, R + 1
 //         and exchange with the neighbouring column as in store_tile; one write instruction covers rows
 //         4 g + (lane & 1), 8 dwords each: the 32-byte column group j is kept at j ^ g.
+// Can store_tile16 store the tiles from column n0 on 16 bytes at a time?  (The fused row maximum has no mask for columns.)  Tiles cut
+// by the edge then store what whole ones do, under a mask; element by element, half of the tiles of [445, 128] x [128, 47072], 4
+// devices, made 347 us of 56, and [144, 61] x [61, 23304], 8 devices, took 70 for 32.
+template <int EPI, int BN, typename OutT>
+__device__ inline bool stores_pieces(const GemmShard& s, int n0) {
+    constexpr int EPV = 16 / (int)sizeof(OutT);
+    return s.ldc % EPV == 0 && (n0 + BN <= s.n || (EPI != EPI_ROWMAX && s.n % EPV == 0));
+}
+
 template <int BM, int BN, int TM, int TN, int EPI, typename OutT, int KEEP = 0>
 __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (&acc)[TM / 16][TN / 16], const GemmShard& s, int m0, int n0, int wm, int wn, int lane, char* stage) {
     constexpr int FM = TM / 32, FN = TN / 32;       // 32 x 32 regions, as in store_tile
     OutT* C = static_cast<OutT*>(s.c);
     constexpr int EPV = 16 / (int)sizeof(OutT);
     const bool whole = m0 + BM <= s.m && n0 + BN <= s.n && s.ldc % EPV == 0;
+    const bool pieces = stores_pieces<EPI, BN, OutT>(s, n0);
     [[maybe_unused]] const bool stream = (s.ldc * (int)sizeof(OutT)) % 128 == 0;
     // Every lane constant of the epilogue is derived from this copy of the lane id, which the compiler cannot
     // move out of the tile loop: they are recomputed per tile (a few dozen instructions) instead of occupying
     // registers all through the reduction loop, which has none to spare.
     asm volatile("" : "+v"(lane));
     const int g = lane >> 4, c = lane & 15;
-    if (whole) {
+    // masked: a tile that the matrix edge cuts; lanes whose 16 bytes lie outside store nothing
+    auto store = [&](auto masked) __attribute__((always_inline)) {
+        constexpr bool MASKED = decltype(masked)::value;
         const int wave = (int)(threadIdx.x >> 6);
         const int h = lane >> 5;
+        [[maybe_unused]] const int rows_left = s.m - (m0 + wm * TM) - (lane >> 3), cols_left = s.n - (n0 + wn * TN) - (lane & 7) * EPV;   // this lane's
+        auto put = [&](auto* dst, const auto v, [[maybe_unused]] int row, [[maybe_unused]] int col) {
+            if constexpr (MASKED) store16_untracked(dst, v, stream, __builtin_amdgcn_ballot_w64(row < rows_left && col < cols_left));
+            else store16_untracked(dst, v, stream);
+        };
         OutT* cg = C + (int64_t)(m0 + wm * TM + (lane >> 3)) * s.ldc + (n0 + wn * TN + (lane & 7) * EPV);
         if constexpr (sizeof(OutT) == 4) {
             // read side: logical row (lane / 8) + 8 q, logical 16-byte chunk lane % 8
@@ -333,7 +350,7 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
                     const f32x4 v = *reinterpret_cast<const f32x4*>(stage + (((q & 1) ? rd1 : rd0) + q * 1024));
                     f32x4* dst = reinterpret_cast<f32x4*>(cg + (int64_t)(i * 32 + q * 8) * s.ldc + j * 32);
                     if constexpr (decltype(idx)::value == 0 && q == 0) __builtin_amdgcn_s_waitcnt(vmcnt_only(KEEP));
-                    store16_untracked(dst, v, stream);
+                    put(dst, v, i * 32 + q * 8, j * 32);
                 });
                 __builtin_amdgcn_wave_barrier();
             });
@@ -390,7 +407,7 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
                         rm[i][q] = fmaxf(rm[i][q], mx);
                     }
                     if constexpr (decltype(idx)::value == 0 && q == 0) __builtin_amdgcn_s_waitcnt(vmcnt_only(KEEP));
-                    store16_untracked(dst, v, stream);
+                    put(dst, v, i * 32 + q * 8, 0);
                 });
                 __builtin_amdgcn_wave_barrier();
             });
@@ -411,14 +428,15 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
                         float mx = win[row];
 #pragma unroll
                         for (int ww = 1; ww < WN_; ++ww) mx = fmaxf(mx, reinterpret_cast<const float*>(stage + (wave + ww) * STAGE_BYTES)[row]);
-                        atomic_max_f32_untracked(s.rowmax + (m0 + wm * TM + row), mx);
+                        if (!MASKED || m0 + wm * TM + row < s.m) atomic_max_f32_untracked(s.rowmax + (m0 + wm * TM + row), mx);
                     }
                 }
             }
         }
-        return;
-    }
-    // edge tiles: element by element, guarded
+    };
+    if (whole) return store(std::false_type{});
+    if (pieces) return store(std::true_type{});
+    // rows of the result at any alignment, or ending inside 16 bytes: element by element, guarded
     static_for<(TM / 16) * (TN / 16)>([&](auto idx) {
         constexpr int i = decltype(idx)::value / (TN / 16), j = decltype(idx)::value % (TN / 16);
         const int n = n0 + wn * TN + j * 16 + c;
@@ -1269,7 +1287,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_persist16_kernel(GemmP
             step(I3{}, Old{}, false);
         }
         store_tile16<BM, BN, TM, TN, EPI, OutT, NP>(acc, s, m0, n0, wm, wn, lane, sOut);
-        young = EPI != EPI_ROWMAX && m0 + BM <= s.m && n0 + BN <= s.n && s.ldc % (16 / (int)sizeof(OutT)) == 0;
+        young = EPI != EPI_ROWMAX && stores_pieces<EPI, BN, OutT>(s, n0);
         cv = nv;
     }
     __builtin_amdgcn_s_waitcnt(0x0070);   // trailing (unused) loads must land before LDS is released

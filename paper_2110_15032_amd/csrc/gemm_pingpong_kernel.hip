@@ -59,6 +59,13 @@ __device__ inline void store16_sbase(const char* base, uint32_t voff, const V v,
     else asm volatile("global_store_dwordx4 %0, %1, %2 offset:%3\n\ts_nop 1" : : "v"(voff), "v"(v), "s"(base), "n"(IMM) : "memory");
 }
 
+// the same store by the lanes of a uniform mask only (all lanes active before and after); counted whatever the mask
+template <int IMM, typename V>
+__device__ inline void store16_sbase(const char* base, uint32_t voff, const V v, bool stream, uint64_t lanes) {
+    if (stream) asm volatile("s_mov_b64 exec, %4\n\tglobal_store_dwordx4 %0, %1, %2 offset:%3 nt\n\ts_mov_b64 exec, -1\n\ts_nop 0" : : "v"(voff), "v"(v), "s"(base), "n"(IMM), "s"(lanes) : "memory");
+    else asm volatile("s_mov_b64 exec, %4\n\tglobal_store_dwordx4 %0, %1, %2 offset:%3\n\ts_mov_b64 exec, -1\n\ts_nop 0" : : "v"(voff), "v"(v), "s"(base), "n"(IMM), "s"(lanes) : "memory");
+}
+
 // global -> LDS without passing through registers, untracked: lane i's 16 bytes land at (base + IMM) + 16 i.  M0
 // carries that LDS address; one idle cycle separates its write from the load that reads it.
 template <int IMM>
@@ -78,6 +85,7 @@ struct OutTile {
     int32_t ldc;
     bool stream;       // row pitch a multiple of 128 bytes: whole lines, stored past the cache
     bool whole;        // not cut by the matrix edge, rows 16-byte aligned
+    bool pieces;       // rows 16-byte aligned, ending with 16 bytes (with the fused row maximum: with the tile)
     int32_t rows_left, cols_left;   // of the matrix, from the wave tile's first row / column on
     int32_t rows_key;               // (shard << 16 | tile row) + 1: names the rows this wave writes
 };
@@ -228,7 +236,7 @@ __global__ __launch_bounds__(512) void gemm_pingpong_kernel(GemmPlan p, int tm, 
         }
     };
 
-    auto store_tile = [&](const OutTile& ot) {
+    auto store_tile = [&](const OutTile& ot) __attribute__((always_inline)) {
         const int ln = lane_again();
         const int g = ln >> 4, c = ln & 15;
         if constexpr (EPI == EPI_ROWMAX) {
@@ -237,7 +245,14 @@ __global__ __launch_bounds__(512) void gemm_pingpong_kernel(GemmPlan p, int tm, 
                 run_key = ot.rows_key;
             }
         }
-        if (ot.whole) {
+        // masked: a tile that the matrix edge cuts; lanes whose 16 bytes lie outside store nothing
+        auto store = [&](auto masked) __attribute__((always_inline)) {
+            constexpr bool MASKED = decltype(masked)::value;
+            [[maybe_unused]] const int rows_left = ot.rows_left - (ln >> 3), cols_left = ot.cols_left - (ln & 7) * (16 / (int)sizeof(OutT));   // this lane's
+            auto put = [&](auto imm, const char* base, uint32_t vofs, const u32x4 v, [[maybe_unused]] int row, [[maybe_unused]] int col) __attribute__((always_inline)) {
+                if constexpr (MASKED) store16_sbase<decltype(imm)::value>(base, vofs, v, ot.stream, __builtin_amdgcn_ballot_w64(row < rows_left && col < cols_left));
+                else store16_sbase<decltype(imm)::value>(base, vofs, v, ot.stream);
+            };
             char* win = swin + wave * 4096;
             const int rr = ln >> 3, rk = ln & 7;           // read side: row (of 8), chunk (of 8)
             if constexpr (F32OUT) {
@@ -260,7 +275,7 @@ __global__ __launch_bounds__(512) void gemm_pingpong_kernel(GemmPlan p, int tm, 
                     static_for<4>([&](auto q) {
                         constexpr int T = decltype(q)::value / 2, H = decltype(q)::value % 2;
                         const u32x4 v = *reinterpret_cast<const u32x4*>(win + rd[T][H]);
-                        store16_sbase<H * 128>(rb + (T ? (ot.rowblk >> 1) : 0), vofs, v, ot.stream);
+                        put(ic<H * 128>{}, rb + (T ? (ot.rowblk >> 1) : 0), vofs, v, 16 * IA + 8 * T, 32 * H);
                     });
                     __builtin_amdgcn_wave_barrier();
                 });
@@ -297,14 +312,15 @@ __global__ __launch_bounds__(512) void gemm_pingpong_kernel(GemmPlan p, int tm, 
                     static_for<4>([&](auto q) {
                         constexpr int SUB = decltype(q)::value / 2, T = decltype(q)::value % 2, IA = 2 * IP + SUB;
                         const u32x4 v = *reinterpret_cast<const u32x4*>(win + (SUB * 2048 + rd[T]));
-                        store16_sbase<0>(ot.base + (size_t)IA * ot.rowblk + (T ? (ot.rowblk >> 1) : 0), vofs, v, ot.stream);
+                        put(ic<0>{}, ot.base + (size_t)IA * ot.rowblk + (T ? (ot.rowblk >> 1) : 0), vofs, v, 16 * IA + 8 * T, 0);
                     });
                     __builtin_amdgcn_wave_barrier();
                 });
             }
-            return;
-        }
-        // tiles cut by the matrix edge or with unaligned rows: element by element, guarded, then a full drain
+        };
+        if (ot.whole) return store(std::false_type{});
+        if (ot.pieces) return store(std::true_type{});
+        // rows of the result at any alignment, or ending inside 16 bytes: element by element, guarded, then a full drain
         OutT* C = reinterpret_cast<OutT*>(ot.base);
         [[maybe_unused]] float runmax[8];
         if constexpr (EPI == EPI_ROWMAX) {
@@ -386,6 +402,7 @@ __global__ __launch_bounds__(512) void gemm_pingpong_kernel(GemmPlan p, int tm, 
         ot.ldc = s.ldc;
         ot.stream = ((int64_t)s.ldc * (int64_t)sizeof(OutT)) % 128 == 0;
         ot.whole = m0 + BM <= s.m && n0 + BN <= s.n && s.ldc % EPV == 0;
+        ot.pieces = s.ldc % EPV == 0 && (n0 + BN <= s.n || (EPI != EPI_ROWMAX && s.n % EPV == 0));
         ot.rows_left = s.m - (m0 + wm * TM);
         ot.cols_left = s.n - (n0 + wn * TN);
         ot.rows_key = __builtin_amdgcn_readfirstlane(((tc.g << 16) | tc.tile_m) + 1);
@@ -421,7 +438,7 @@ __global__ __launch_bounds__(512) void gemm_pingpong_kernel(GemmPlan p, int tm, 
         bool young = false;
         if (pend) {
             store_tile(prev);
-            young = prev.whole;
+            young = prev.whole || prev.pieces;
         }
         step(ic<0>{}, std::true_type{}, young);
         if (rounds == 1) switch_tile();
