@@ -446,7 +446,7 @@ __device__ inline void store_columns(const GemmShard& s, int m, int n, const flo
     }
 }
 
-// 16-byte streaming store the compiler does not track.  The two idle cycles cover the hardware's
+// 16-byte streaming store the compiler does not track, at any alignment of the elements.  The two idle cycles cover the hardware's
 // rule that the data registers of a store wider than 8 bytes must not be rewritten right behind it
 // (the compiler inserts them for stores it knows; here it cannot).
 // `stream` (uniform): non-temporal.  Right when every 128-byte row segment is a whole cache line;
@@ -472,6 +472,18 @@ __device__ inline void store_out_untracked(float* c, int64_t pos, float v) {
 __device__ inline void store_out_untracked(uint16_t* c, int64_t pos, float v) {
     const uint32_t b = f32_to_bf16(v);
     asm volatile("global_store_short %0, %1, off nt" : : "v"(c + pos), "v"(b) : "memory");
+}
+
+// The first `n` elements (fewer than all) of 16 bytes of results, one store each.
+template <typename OutT, typename V>
+__device__ inline void store_first_untracked(OutT* c, const V v, int n) {
+    const u32x4 w = __builtin_bit_cast(u32x4, v);
+#pragma unroll
+    for (int e = 0; e < 16 / (int)sizeof(OutT) - 1; ++e)
+        if (e < n) {
+            if constexpr (sizeof(OutT) == 4) asm volatile("global_store_dword %0, %1, off" : : "v"(c + e), "v"(w[e]) : "memory");
+            else asm volatile("global_store_short %0, %1, off" : : "v"(c + e), "v"(w[e >> 1] >> (16 * (e & 1))) : "memory");
+        }
 }
 
 }  // namespace

@@ -283,22 +283,21 @@ __device__ __attribute__((always_inline)) inline void store_tile(const f32x16 (&
 //   bf16: a 32-row x 64-column strip (2 x 4 blocks) at a time.  Lanes round and pair their rows R, R + 1
 //         and exchange with the neighbouring column as in store_tile; one write instruction covers rows
 //         4 g + (lane & 1), 8 dwords each: the 32-byte column group j is kept at j ^ g.
-// Can store_tile16 store the tiles from column n0 on 16 bytes at a time?  (The fused row maximum has no mask for columns.)  Tiles cut
-// by the edge then store what whole ones do, under a mask; element by element, half of the tiles of [445, 128] x [128, 47072], 4
-// devices, made 347 us of 56, and [144, 61] x [61, 23304], 8 devices, took 70 for 32.
-template <int EPI, int BN, typename OutT>
-__device__ inline bool stores_pieces(const GemmShard& s, int n0) {
-    constexpr int EPV = 16 / (int)sizeof(OutT);
-    return s.ldc % EPV == 0 && (n0 + BN <= s.n || (EPI != EPI_ROWMAX && s.n % EPV == 0));
-}
+// store_tile16 stores 16 bytes at a time, rows at any pitch; tiles cut by the edge under a mask (the fused row maximum has none for
+// columns), and the elements of a piece that the edge cuts one by one (`ends_inside`).  Element by element, half of the tiles of
+// [445, 128] x [128, 47072], 4 devices, made 347 us of 56, [144, 61] x [61, 23304], 8 devices, took 70 for 32, and with rows of 23301
+// results 80 for 28; [1767, 512] x [512, 4081], 2 devices, 52 for 22.
+template <int EPI, int BN>
+__device__ inline bool stores_pieces(const GemmShard& s, int n0) { return n0 + BN <= s.n || EPI != EPI_ROWMAX; }
+template <int BN, typename OutT>
+__device__ inline bool ends_inside(const GemmShard& s, int n0) { return n0 + BN > s.n && s.n % (16 / (int)sizeof(OutT)) != 0; }
 
 template <int BM, int BN, int TM, int TN, int EPI, typename OutT, int KEEP = 0>
 __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (&acc)[TM / 16][TN / 16], const GemmShard& s, int m0, int n0, int wm, int wn, int lane, char* stage) {
     constexpr int FM = TM / 32, FN = TN / 32;       // 32 x 32 regions, as in store_tile
     OutT* C = static_cast<OutT*>(s.c);
     constexpr int EPV = 16 / (int)sizeof(OutT);
-    const bool whole = m0 + BM <= s.m && n0 + BN <= s.n && s.ldc % EPV == 0;
-    const bool pieces = stores_pieces<EPI, BN, OutT>(s, n0);
+    const bool whole = m0 + BM <= s.m && n0 + BN <= s.n, inside = ends_inside<BN, OutT>(s, n0);
     [[maybe_unused]] const bool stream = (s.ldc * (int)sizeof(OutT)) % 128 == 0;
     // Every lane constant of the epilogue is derived from this copy of the lane id, which the compiler cannot
     // move out of the tile loop: they are recomputed per tile (a few dozen instructions) instead of occupying
@@ -312,8 +311,10 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
         const int h = lane >> 5;
         [[maybe_unused]] const int rows_left = s.m - (m0 + wm * TM) - (lane >> 3), cols_left = s.n - (n0 + wn * TN) - (lane & 7) * EPV;   // this lane's
         auto put = [&](auto* dst, const auto v, [[maybe_unused]] int row, [[maybe_unused]] int col) {
-            if constexpr (MASKED) store16_untracked(dst, v, stream, __builtin_amdgcn_ballot_w64(row < rows_left && col < cols_left));
-            else store16_untracked(dst, v, stream);
+            if constexpr (MASKED) {
+                store16_untracked(dst, v, stream, __builtin_amdgcn_ballot_w64(row < rows_left && col + EPV <= cols_left));
+                if (inside && row < rows_left && col + EPV > cols_left) store_first_untracked(reinterpret_cast<OutT*>(dst), v, cols_left - col);
+            } else store16_untracked(dst, v, stream);
         };
         OutT* cg = C + (int64_t)(m0 + wm * TM + (lane >> 3)) * s.ldc + (n0 + wn * TN + (lane & 7) * EPV);
         if constexpr (sizeof(OutT) == 4) {
@@ -435,8 +436,12 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
         }
     };
     if (whole) return store(std::false_type{});
-    if (pieces) return store(std::true_type{});
-    // rows of the result at any alignment, or ending inside 16 bytes: element by element, guarded
+    if (stores_pieces<EPI, BN>(s, n0)) {
+        store(std::true_type{});
+        if (inside) __builtin_amdgcn_s_waitcnt(vmcnt_only(0));   // an unknown number of stores, and the loads
+        return;
+    }
+    // row maxima of columns that end in the tile: element by element, guarded
     static_for<(TM / 16) * (TN / 16)>([&](auto idx) {
         constexpr int i = decltype(idx)::value / (TN / 16), j = decltype(idx)::value % (TN / 16);
         const int n = n0 + wn * TN + j * 16 + c;
@@ -1287,7 +1292,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_persist16_kernel(GemmP
             step(I3{}, Old{}, false);
         }
         store_tile16<BM, BN, TM, TN, EPI, OutT, NP>(acc, s, m0, n0, wm, wn, lane, sOut);
-        young = EPI != EPI_ROWMAX && stores_pieces<EPI, BN, OutT>(s, n0);
+        young = EPI != EPI_ROWMAX && !ends_inside<BN, OutT>(s, n0);
         cv = nv;
     }
     __builtin_amdgcn_s_waitcnt(0x0070);   // trailing (unused) loads must land before LDS is released

@@ -84,8 +84,9 @@ struct OutTile {
     uint32_t rowblk;   // bytes between row blocks (16 rows)
     int32_t ldc;
     bool stream;       // row pitch a multiple of 128 bytes: whole lines, stored past the cache
-    bool whole;        // not cut by the matrix edge, rows 16-byte aligned
-    bool pieces;       // rows 16-byte aligned, ending with 16 bytes (with the fused row maximum: with the tile)
+    bool whole;        // not cut by the matrix edge
+    bool pieces;       // stored 16 bytes at a time (not with the fused row maximum where columns end in the tile)
+    bool inside;       // the columns end inside 16 bytes
     int32_t rows_left, cols_left;   // of the matrix, from the wave tile's first row / column on
     int32_t rows_key;               // (shard << 16 | tile row) + 1: names the rows this wave writes
 };
@@ -250,8 +251,11 @@ __global__ __launch_bounds__(512) void gemm_pingpong_kernel(GemmPlan p, int tm, 
             constexpr bool MASKED = decltype(masked)::value;
             [[maybe_unused]] const int rows_left = ot.rows_left - (ln >> 3), cols_left = ot.cols_left - (ln & 7) * (16 / (int)sizeof(OutT));   // this lane's
             auto put = [&](auto imm, const char* base, uint32_t vofs, const u32x4 v, [[maybe_unused]] int row, [[maybe_unused]] int col) __attribute__((always_inline)) {
-                if constexpr (MASKED) store16_sbase<decltype(imm)::value>(base, vofs, v, ot.stream, __builtin_amdgcn_ballot_w64(row < rows_left && col < cols_left));
-                else store16_sbase<decltype(imm)::value>(base, vofs, v, ot.stream);
+                if constexpr (MASKED) {
+                    constexpr int EPV = 16 / (int)sizeof(OutT);
+                    store16_sbase<decltype(imm)::value>(base, vofs, v, ot.stream, __builtin_amdgcn_ballot_w64(row < rows_left && col + EPV <= cols_left));
+                    if constexpr (EPI != EPI_ROWMAX) if (ot.inside && row < rows_left && col + EPV > cols_left) store_first_untracked(reinterpret_cast<OutT*>(const_cast<char*>(base) + vofs + decltype(imm)::value), v, cols_left - col);
+                } else store16_sbase<decltype(imm)::value>(base, vofs, v, ot.stream);
             };
             char* win = swin + wave * 4096;
             const int rr = ln >> 3, rk = ln & 7;           // read side: row (of 8), chunk (of 8)
@@ -319,8 +323,12 @@ __global__ __launch_bounds__(512) void gemm_pingpong_kernel(GemmPlan p, int tm, 
             }
         };
         if (ot.whole) return store(std::false_type{});
-        if (ot.pieces) return store(std::true_type{});
-        // rows of the result at any alignment, or ending inside 16 bytes: element by element, guarded, then a full drain
+        if (ot.pieces) {
+            store(std::true_type{});
+            if (EPI != EPI_ROWMAX && ot.inside) __builtin_amdgcn_s_waitcnt(vmcnt_only(0));   // an unknown number of stores
+            return;
+        }
+        // row maxima of columns that end in the tile: element by element, guarded, then a full drain
         OutT* C = reinterpret_cast<OutT*>(ot.base);
         [[maybe_unused]] float runmax[8];
         if constexpr (EPI == EPI_ROWMAX) {
@@ -401,8 +409,9 @@ __global__ __launch_bounds__(512) void gemm_pingpong_kernel(GemmPlan p, int tm, 
         ot.rowblk = (uint32_t)s.ldc * (16u * (uint32_t)sizeof(OutT));
         ot.ldc = s.ldc;
         ot.stream = ((int64_t)s.ldc * (int64_t)sizeof(OutT)) % 128 == 0;
-        ot.whole = m0 + BM <= s.m && n0 + BN <= s.n && s.ldc % EPV == 0;
-        ot.pieces = s.ldc % EPV == 0 && (n0 + BN <= s.n || (EPI != EPI_ROWMAX && s.n % EPV == 0));
+        ot.whole = m0 + BM <= s.m && n0 + BN <= s.n;
+        ot.pieces = n0 + BN <= s.n || EPI != EPI_ROWMAX;
+        ot.inside = n0 + BN > s.n && s.n % EPV != 0;
         ot.rows_left = s.m - (m0 + wm * TM);
         ot.cols_left = s.n - (n0 + wn * TN);
         ot.rows_key = __builtin_amdgcn_readfirstlane(((tc.g << 16) | tc.tile_m) + 1);
@@ -438,7 +447,7 @@ __global__ __launch_bounds__(512) void gemm_pingpong_kernel(GemmPlan p, int tm, 
         bool young = false;
         if (pend) {
             store_tile(prev);
-            young = prev.whole || prev.pieces;
+            young = prev.pieces && !prev.inside;
         }
         step(ic<0>{}, std::true_type{}, young);
         if (rounds == 1) switch_tile();

@@ -171,10 +171,10 @@ def test_bf16_persistent_tiles(kk, ldy, tx, tw, out):
 
 @pytest.mark.parametrize("variant", [8, 9, 16, 21])
 @pytest.mark.parametrize("out", ["f32", "bf16", "gelu", "rowmax"])
-@pytest.mark.parametrize("M,N", [(255, 264), (300, 388), (257, 392), (130, 391), (512, 520)])
-def test_bf16_tiles_cut_by_the_edge(M, N, out, variant):
-    """results stored 16 bytes at a time up to the edge: rows cut anywhere, columns at a multiple of 16 bytes or inside one; the padding
-    behind a row stays as it was (DevTensor)"""
+@pytest.mark.parametrize("M,N,odd", [(255, 264, 0), (300, 388, 1), (257, 392, 0), (130, 391, 0), (140, 389, 1), (512, 520, 3)])
+def test_bf16_tiles_cut_by_the_edge(M, N, odd, out, variant):
+    """results stored 16 bytes at a time up to the edge: rows cut anywhere, columns at a multiple of 16 bytes or inside one, rows at any
+    pitch; the padding behind a row stays as it was (DevTensor)"""
     k, kk = 2, 256
     if out == "f32":
         X, W, sx, sw, K, C = bf16(3, (M, k * kk)), bf16(4, (k * kk, N), 0.5), orc.S1, orc.S0, k * kk, N
@@ -183,7 +183,7 @@ def test_bf16_tiles_cut_by_the_edge(M, N, out, variant):
     Xs, Ws = orc.scatter(X, sx, k), orc.scatter(W, sw, k)
     ref, _ = orc.matmul_sbp([values(x) for x in Xs], sx, [values(w) for w in Ws], sw)
     dx, dw = DevTensor.from_host(Xs, M, K, sx, ld=kk), DevTensor.from_host(Ws, K, C, sw, ld=-(-N // 8) * 8)
-    dy = DevTensor.empty(M, C, np.float32 if out == "f32" else np.uint16, orc.P_SUM if out == "f32" else orc.S1, k, ld=-(-N // 8) * 8 + 8)
+    dy = DevTensor.empty(M, C, np.float32 if out == "f32" else np.uint16, orc.P_SUM if out == "f32" else orc.S1, k, ld=-(-N // 8) * 8 + 8 + odd)
     dm = DevTensor.empty(M, 1, np.float32, orc.P_MAX, k)
     sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, variant)
     try:
