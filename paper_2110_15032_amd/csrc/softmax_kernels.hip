@@ -36,8 +36,12 @@ __device__ inline float wave_reduce(float v) {
     return v;
 }
 
-template <bool SUMEXP, bool BF16>
-__global__ __launch_bounds__(RS_THREADS) void row_stat_kernel(RowStatPlan p) {
+// Bound by HBM.  Four vectors a lane are in flight; THREADS: 1024 for few long rows, which leave compute units idle.  STREAM:
+// non-temporal loads, for logits that the memory-side cache does not hold until the next pass anyway.  us, one vector a lane, 256
+// threads, cached / now: 8 devices x 1024 rows of 125000 bf16 logits (2 GB) 338 / 294 (7.0 TB/s; cached 334), 3 x 19 of 114091 14.1 / 7.4
+// (256 threads 8.8), 2 x 8 of 250000 26.9 / 11.5 (15.2); cached / streaming 4 x 200 of 7503 5.0 / 6.8, 5 x 100 of 17000 5.0 / 7.8.
+template <bool SUMEXP, bool BF16, int THREADS, bool STREAM>
+__global__ __launch_bounds__(THREADS) void row_stat_kernel(RowStatPlan p) {
     const int shard = blockIdx.y;
     const int64_t row = blockIdx.x;
     const int32_t cols = p.cols[shard];
@@ -57,36 +61,56 @@ __global__ __launch_bounds__(RS_THREADS) void row_stat_kernel(RowStatPlan p) {
             if constexpr (BF16) return __uint_as_float((uint32_t) reinterpret_cast<const uint16_t*>(base)[c] << 16);
             else return reinterpret_cast<const float*>(base)[c];
         };
-        for (int32_t c = threadIdx.x; c < head; c += RS_THREADS) acc = fold<SUMEXP>(acc, elem(c), m);
-        for (int32_t c = tail0 + threadIdx.x; c < cols; c += RS_THREADS) acc = fold<SUMEXP>(acc, elem(c), m);
+        for (int32_t c = threadIdx.x; c < head; c += THREADS) acc = fold<SUMEXP>(acc, elem(c), m);
+        for (int32_t c = tail0 + threadIdx.x; c < cols; c += THREADS) acc = fold<SUMEXP>(acc, elem(c), m);
         const char* vbase = base + (int64_t)head * (BF16 ? 2 : 4);
         float a0 = ident, a1 = ident, a2 = ident, a3 = ident;   // four chains per lane
-        for (int32_t v = threadIdx.x; v < nvec; v += RS_THREADS) {
+        using Vec = std::conditional_t<BF16, u32x4, f32x4>;
+        const Vec* const vec = reinterpret_cast<const Vec*>(vbase);
+        auto take = [&](const Vec w) {
             if constexpr (BF16) {
-                const u32x4 w = reinterpret_cast<const u32x4*>(vbase)[v];
                 a0 = fold<SUMEXP>(fold<SUMEXP>(a0, bf16_lo(w.x), m), bf16_hi(w.x), m);
                 a1 = fold<SUMEXP>(fold<SUMEXP>(a1, bf16_lo(w.y), m), bf16_hi(w.y), m);
                 a2 = fold<SUMEXP>(fold<SUMEXP>(a2, bf16_lo(w.z), m), bf16_hi(w.z), m);
                 a3 = fold<SUMEXP>(fold<SUMEXP>(a3, bf16_lo(w.w), m), bf16_hi(w.w), m);
             } else {
-                const f32x4 w = reinterpret_cast<const f32x4*>(vbase)[v];
                 a0 = fold<SUMEXP>(a0, w.x, m);
                 a1 = fold<SUMEXP>(a1, w.y, m);
                 a2 = fold<SUMEXP>(a2, w.z, m);
                 a3 = fold<SUMEXP>(a3, w.w, m);
             }
+        };
+        int32_t v = threadIdx.x;
+        constexpr int DEPTH = 4;
+        for (; v + (int64_t)(DEPTH - 1) * THREADS < nvec; v += DEPTH * THREADS) {
+            Vec w[DEPTH];
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) {
+                if constexpr (STREAM) w[d] = __builtin_nontemporal_load(vec + v + d * THREADS);
+                else w[d] = vec[v + d * THREADS];
+            }
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) take(w[d]);
+        }
+        if (v < nvec) {   // up to DEPTH more, loaded together (the last one again where there are fewer)
+            Vec w[DEPTH];
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) w[d] = vec[(int32_t)min(v + (int64_t)d * THREADS, (int64_t)nvec - 1)];
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d)
+                if (v + (int64_t)d * THREADS < nvec) take(w[d]);
         }
         if constexpr (SUMEXP) acc += (a0 + a1) + (a2 + a3);
         else acc = fmaxf(fmaxf(acc, fmaxf(a0, a1)), fmaxf(a2, a3));
     }
     acc = wave_reduce<SUMEXP>(acc);
-    __shared__ float part[RS_THREADS / 64];
+    __shared__ float part[THREADS / 64];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
         float r = part[0];
 #pragma unroll
-        for (int w = 1; w < RS_THREADS / 64; ++w) r = SUMEXP ? r + part[w] : fmaxf(r, part[w]);
+        for (int w = 1; w < THREADS / 64; ++w) r = SUMEXP ? r + part[w] : fmaxf(r, part[w]);
         p.out[shard][row] = r;
     }
 }
@@ -253,19 +277,26 @@ int32_t launch_xent_grad(const XentPlan& plan, hipStream_t stream) {
     return launch_status(__func__);
 }
 
-int32_t launch_row_stat(const RowStatPlan& plan, bool sumexp, hipStream_t stream) {
+int32_t launch_row_stat(const RowStatPlan& plan, bool sumexp, hipStream_t stream_) {
     if (plan.rows == 0) return SBP_OK;
     if (plan.rows > 0x7FFFFFFF) return SBP_ERR_UNSUPPORTED;
     const dim3 grid((uint32_t)plan.rows, (uint32_t)plan.k);
-    const dim3 block(RS_THREADS);
     const bool bf = plan.dtype == SBP_BF16;
-    if (sumexp) {
-        if (bf) hipLaunchKernelGGL((row_stat_kernel<true, true>), grid, block, 0, stream, plan);
-        else hipLaunchKernelGGL((row_stat_kernel<true, false>), grid, block, 0, stream, plan);
-    } else {
-        if (bf) hipLaunchKernelGGL((row_stat_kernel<false, true>), grid, block, 0, stream, plan);
-        else hipLaunchKernelGGL((row_stat_kernel<false, false>), grid, block, 0, stream, plan);
+    int32_t cols = 0;
+    int64_t total = 0;
+    for (int i = 0; i < plan.k; ++i) {
+        cols = plan.cols[i] > cols ? plan.cols[i] : cols;
+        total += plan.rows * plan.cols[i] * (bf ? 2 : 4);
     }
+    const bool wide = plan.rows * plan.k <= 512 && cols >= 16384;      // two rows a compute unit; 2 KB of bf16 and more for each wave
+    const bool stream = !wide && total > (int64_t)256 << 20;           // the memory-side cache's size
+    auto pick = [&](auto s, auto b) -> void (*)(RowStatPlan) {
+        constexpr bool S = decltype(s)::value, BF = decltype(b)::value;
+        return wide ? row_stat_kernel<S, BF, 1024, false> : stream ? row_stat_kernel<S, BF, RS_THREADS, true> : row_stat_kernel<S, BF, RS_THREADS, false>;
+    };
+    void (*kern)(RowStatPlan) = sumexp ? (bf ? pick(std::true_type{}, std::true_type{}) : pick(std::true_type{}, std::false_type{}))
+                                       : (bf ? pick(std::false_type{}, std::true_type{}) : pick(std::false_type{}, std::false_type{}));
+    hipLaunchKernelGGL(kern, grid, dim3(wide ? 1024 : RS_THREADS), 0, stream_, plan);
     return launch_status(__func__);
 }
 
