@@ -36,7 +36,8 @@ __device__ inline float wave_reduce(float v) {
     return v;
 }
 
-// Bound by HBM.  Four vectors a lane are in flight; THREADS: 1024 for few long rows, which leave compute units idle.  STREAM:
+// Bound by HBM.  Four vectors a lane are in flight, in cached rows of 256 threads one (8 x 153 of 32237: one 14.2, four 15.0).
+// THREADS: 1024 for few long rows, which leave compute units idle.  STREAM:
 // non-temporal loads, for logits that the memory-side cache does not hold until the next pass anyway.  us, one vector a lane, 256
 // threads, cached / now: 8 devices x 1024 rows of 125000 bf16 logits (2 GB) 338 / 294 (7.0 TB/s; cached 334), 3 x 19 of 114091 14.1 / 7.4
 // (256 threads 8.8), 2 x 8 of 250000 26.9 / 11.5 (15.2); cached / streaming 4 x 200 of 7503 5.0 / 6.8, 5 x 100 of 17000 5.0 / 7.8.
@@ -81,7 +82,7 @@ __global__ __launch_bounds__(THREADS) void row_stat_kernel(RowStatPlan p) {
             }
         };
         int32_t v = threadIdx.x;
-        constexpr int DEPTH = 4;
+        constexpr int DEPTH = THREADS > RS_THREADS || STREAM ? 4 : 1;
         for (; v + (int64_t)(DEPTH - 1) * THREADS < nvec; v += DEPTH * THREADS) {
             Vec w[DEPTH];
 #pragma unroll
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(THREADS) void row_stat_kernel(RowStatPlan p) {
 #pragma unroll
             for (int d = 0; d < DEPTH; ++d) take(w[d]);
         }
-        if (v < nvec) {   // up to DEPTH more, loaded together (the last one again where there are fewer)
+        if (DEPTH > 1 && v < nvec) {   // up to DEPTH more, loaded together (the last one again where there are fewer)
             Vec w[DEPTH];
 #pragma unroll
             for (int d = 0; d < DEPTH; ++d) w[d] = vec[(int32_t)min(v + (int64_t)d * THREADS, (int64_t)nvec - 1)];
