@@ -1703,12 +1703,14 @@ AnyTile any_tile(const GemmPlan& plan, int max_m, int max_n) {
 // 325 x 26100 x 219, 4 (308) 116 / 85 / 93; 891 x 2340 x 201, 2 (392) 14.5 / 12.8 / 16.5 but 130 x 1701 x 1062, 2 (340) 14.2 / 19.9 / 22.3;
 // 633 x 33323 x 163, 3 (360) 168 / 153 / 168.  Large: 1000 x 12501 x 128, 8 (256) 131 / 157 / 97; 500 x 62500 x 512, 8 (512) 1274 /
 // 1158 / 619; 654 x 38256 x 426, 4 (308) 506 / 369 / 329; 691 x 26688 x 726, 3 (396, rows on cache lines) 181 / 217 / 183; but
-// 594 x 4471 x 577, 2 (200) 34.0 / 54 / 41, 641 x 6567 x 1143, 8 (1584) 186 / 402 / 318.
+// 594 x 4471 x 577, 2 (200) 34.0 / 54 / 41, 641 x 6567 x 1143, 8 (1584) 186 / 402 / 318.  Short ones, with it over without, 32 x 32: length 537 and 637 1.02-1.15, 777 to
+// 1001 0.82-0.98, 896 1.00-1.13, 1024 on 0.64-0.99; whole cache lines
+// that fill the last stage in part 1088 to 1408 1.00-1.10, 1664 0.95-1.00; but 24 x 34, 4 (8) up to 1.12.
 int rows_tile(const GemmPlan& plan, int max_m, int max_n) {   // -1: none
     if (!plan.a_kc || !plan.b_kc || plan.out_dtype != SBP_F32 || plan.epilogue != SBP_EPI_NONE) return -1;
     const int64_t cu = compute_units(), small = tiles_of(plan, max_m, max_n, 32, 32), large = tiles_of(plan, max_m, max_n, 64, 64);
     const int k = longest_reduction(plan);
-    if (small <= cu ? k >= 512 : small <= 2 * cu && k >= 4096) return ROWS_32;
+    if (small <= cu ? k >= (k % 64 || k % 256 == 0 ? 1024 : 1664) : small <= 2 * cu && k >= 4096) return ROWS_32;
     return large <= 2 * cu && k >= 8192 ? ROWS_64 : -1;
 }
 // fp32 operands on the matrix cores: the largest tile that gives the chip enough workgroups and is not mostly padding.  us,
@@ -1723,11 +1725,13 @@ int rows_tile(const GemmPlan& plan, int max_m, int max_n) {   // -1: none
 // 454 / 289 / 334; 444 74 / 74 / 50 / 53; 352 310 / 252 / 176 / 177; 272 378 / 266 / 214 / 190.  Few tiles, fp32 64 / terms 64: 440 small ones
 // 35.0 / 26.8, 308 16.3 / 14.2, 256 18.9 / 19.0, 234 15.8 / 16.3; next to bf16 (three matrix instructions for six) 242 52 / 24, 272
 // 39 / 19.  Short reductions: length 40 65 / 77 / 54 / 66, 24 63 / 63 / 57 / 64, 15 41 / 55 / 47 / 50; next to bf16 45 18 / 16 / 16 / 13, 32
-// 11 / 9 / 13 / 11, 25 12 / 11 / 14 / 13.
+// 11 / 9 / 13 / 11, 25 12 / 11 / 14 / 13.  All fp32, terms over the fp32 instruction, four shapes of 378 to 2304 tiles: both operands
+// reduction-contiguous length 24 to 56 0.81-1.17, 64 0.80-1.03, 72 on 0.61-0.94; others 24 and 31 1.09-1.44, 64 1.09-1.29, 128
+// 0.89-1.10, 160 to 224 (whole stages) 0.81-1.06, 260 on 0.69-0.98.
 F32Tile f32_tile(const GemmPlan& plan, int max_m, int max_n) {
     const int64_t cu = compute_units(), tiles = tiles_of(plan, max_m, max_n, 64, 64), large = tiles_of(plan, max_m, max_n, 128, 128);
     const int k = longest_reduction(plan);
-    const bool narrow = max_m <= 32 || max_n <= 32, terms = plan.f32_operand ? k > 32 : k >= 24;
+    const bool narrow = max_m <= 32 || max_n <= 32, terms = k > (plan.f32_operand ? 32 : plan.a_kc && plan.b_kc ? 64 : 255);
     if (max_m > 64 && max_n > 64 && large >= cu) return !terms ? F32_128 : 5 * large >= 8 * cu ? TERMS_128 : TERMS_64;
     if (k < 64 ? k > 24 && tiles <= (narrow ? cu : cu / 2) : narrow || 4 * tiles < 3 * cu) return F32_32;
     return terms && (tiles > cu || plan.f32_operand) ? TERMS_64 : F32_64;
