@@ -255,9 +255,13 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmPlan p,
 // fp32 32 x 32: length 16 3.4e-8 / 7.4e-8 / 6.0e-8, 128 1.5e-7 / 2.0e-7 / 0.9e-7, 1000 4.8e-7 / 5.7e-7 / 2.1e-7, 16000 2.1e-6 / 2.3e-6 /
 // 0.8e-6; on uniform values in [0, 1] at 1000 2.9e-7 / 4.2e-7 / 0.7e-7.
 //
+// Products as sums of bf16 terms: Henry, Tang, Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
+// Higher-Precision Computations" (2019).
+//
 // What the cut cannot hold (infinities, values past the largest bf16, sums that leave the fp32 range on the way) shows as a result
-// that is not finite, and operands of nothing but values below 2^-95, whose last terms lose bits, in the bits of their hi terms;
-// such a tile is multiplied again by f32_tile.  NaN stays NaN either way.
+// that is not finite; a value other than 0 below 2^-110, whose lo term would lose bits, is seen when it is cut.  A tile with one
+// of these is multiplied again by f32_tile: one value is enough, since its partner in the reduction may be as large as they get.
+// NaN stays NaN either way.
 //
 // Bound by the power limit of the matrix cores: [4096, 4096] x [4096, 4096] 640 us, 1.29 PFLOP/s of bf16 products (1068 us on the
 // fp32 instruction); with all-zero operands 542.  [2000, 750] x [750, 1500], 4 devices, 153 -> 104.  Four waves; one LDS stage of 48 KB,
@@ -265,10 +269,8 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmPlan p,
 // register stage ahead: 110 us).  Six terms for 64 x 64 results a wave read 24 KB of fragments per 96 matrix instructions, half of
 // what LDS can deliver meanwhile; splitting a fragment after the read would read two thirds of that and split everything twice.
 // ---------------------------------------------------------------------------------------------------------------------
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-// x = hi + mid + lo, each the nearest bf16 of what is left; pairs of values.  Exact for normal values below 2^127 (2 - 2^-8) in
-// magnitude whose last bit is not below 2^-133.
+// x = hi + mid + lo, each the nearest bf16 of what is left; pairs of values.  Exact for 0 and for magnitudes below 2^127 (2 - 2^-8)
+// whose last bit is not below 2^-133, bf16's smallest: from 2^-110 on.
 struct TermPair { uint32_t hi, mid, lo; };
 __device__ inline TermPair split_pair(float x, float y) {
     TermPair t;
@@ -281,6 +283,10 @@ __device__ inline TermPair split_pair(float x, float y) {
     t.lo = f32_to_bf16x2(x, y);
     return t;
 }
+
+// Of a value's bits: grows with its magnitude, largest for 0.
+__device__ inline uint32_t magnitude_key(uint32_t bits) { return 2u * bits - 1u; }
+constexpr uint32_t CUT_EXACTLY = 2u * ((127u - 110u) << 23) - 1u;   // the key of 2^-110
 
 // One operand of gemm_terms_kernel: R rows by 32 of the reduction a stage, as one (bf16) or three (fp32) bf16 tiles.
 template <typename T, int R, bool KC, int NT>
@@ -342,8 +348,18 @@ struct TermOperand {
                 }
         }
     }
-    // into LDS; seen: the bits of every hi term, together
-    __device__ static void stash(char* st, Raw& r, int tid, uint32_t& seen) {
+    // Where columns end in the tile, chunks of plain stages bring what lies behind a row and columns of another tile, and stash looks
+    // at all they bring: there, when it has seen something, is it a value of the tile itself?
+    __device__ static bool brings_others(int first, int limit) { return F32 && !KC && first + R > limit; }
+    __device__ static bool loses_bits(const void* base, int ld, int first, int limit, int kk, int tid) {
+        const int col = first + tid % R;
+        if (col >= limit) return false;
+        uint32_t least = ~0u;
+        for (int k = tid / R; k < kk; k += NT / R) least = min(least, magnitude_key(static_cast<const uint32_t*>(base)[(int64_t)k * ld + col]));
+        return least < CUT_EXACTLY;
+    }
+    // into LDS; least: the smallest key of all values
+    __device__ static void stash(char* st, Raw& r, int tid, uint32_t& least) {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             char* const to = st + (i * NT + tid) * 16;
@@ -352,12 +368,13 @@ struct TermOperand {
                 u32x4 h, m, l;
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
-                    const TermPair t = split_pair(__uint_as_float(r.v[i][d >> 1][2 * (d & 1)]), __uint_as_float(r.v[i][d >> 1][2 * (d & 1) + 1]));
+                    const uint32_t x = r.v[i][d >> 1][2 * (d & 1)], y = r.v[i][d >> 1][2 * (d & 1) + 1];
+                    least = min(least, min(magnitude_key(x), magnitude_key(y)));
+                    const TermPair t = split_pair(__uint_as_float(x), __uint_as_float(y));
                     h[d] = t.hi;
                     m[d] = t.mid;
                     l[d] = t.lo;
                 }
-                seen |= h[0] | h[1] | h[2] | h[3];
                 *reinterpret_cast<u32x4*>(to) = h;
                 *reinterpret_cast<u32x4*>(to + Tl::BYTES) = m;
                 *reinterpret_cast<u32x4*>(to + 2 * Tl::BYTES) = l;
@@ -407,10 +424,10 @@ __global__ __launch_bounds__(256, WPS) void gemm_terms_kernel(GemmPlan p, int tm
     typename OB::Raw rb;
     // LDS traffic of this wave done, then all waves: the loads into registers stay in flight
     auto barrier = []() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-    uint32_t seena = 0, seenb = 0;
+    uint32_t leasta = ~0u, leastb = ~0u;
     auto stash = [&]() {
-        OA::stash(smem, ra, tid, seena);
-        OB::stash(smem + OA::BYTES, rb, tid, seenb);
+        OA::stash(smem, ra, tid, leasta);
+        OB::stash(smem + OA::BYTES, rb, tid, leastb);
     };
     auto multiply = [&]() {
         bf16x8 fa[2][OA::N], fb[OB::N][FN];
@@ -464,7 +481,7 @@ __global__ __launch_bounds__(256, WPS) void gemm_terms_kernel(GemmPlan p, int tm
         barrier();
     }
 
-    // Where a result is not finite, or all values of an operand are below 2^-95, whose lo terms lose bits: the tile again, in fp32.
+    // Where a value lost bits or a result is not finite: the tile again, in fp32.
     const int q = lane >> 4, r = lane & 15;
     bool odd = false;
 #pragma unroll
@@ -474,42 +491,47 @@ __global__ __launch_bounds__(256, WPS) void gemm_terms_kernel(GemmPlan p, int tm
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (m0 + wm * TM + 16 * i + r < s.m && n0 + wn * TN + 16 * j + 4 * q + e < s.n) odd |= !(__builtin_fabsf(acc[i][j][e]) <= 3.4028234663852886e38f);
-    auto any = [](bool b) { return __builtin_amdgcn_ballot_w64(b) != 0; };
-    constexpr uint32_t LARGE = 0x70007000u;   // the exponent's upper three bits, both halves
-    const uint32_t found = (any(odd) ? 1u : 0u) | (any(seena) ? 2u : 0u) | (any(seena & LARGE) ? 4u : 0u) | (any(seenb) ? 8u : 0u) | (any(seenb & LARGE) ? 16u : 0u);
-    barrier();
     uint32_t* const votes = reinterpret_cast<uint32_t*>(smem);
-    votes[wave] = found;
-    barrier();
-    const uint32_t all = votes[0] | votes[1] | votes[2] | votes[3];
-    barrier();
-    if ((all & 1) || (OA::F32 && (all & 6) == 2) || (OB::F32 && (all & 24) == 8)) {   // uniform
-        f32_tile<BM, BN, BM == 128 ? 16 : 32, 2, 2, 1, T1, T2, A_KC, B_KC, EPI>(s, m0, n0, reinterpret_cast<float*>(smem));
-        return;
-    }
+    auto vote = [&](bool b0, bool b1, bool b2) {   // of all lanes of the workgroup: bit i where any has bi
+        auto any = [](bool b) { return __builtin_amdgcn_ballot_w64(b) != 0; };
+        barrier();
+        votes[wave] = (any(b0) ? 1u : 0u) | (any(b1) ? 2u : 0u) | (any(b2) ? 4u : 0u);
+        barrier();
+        const uint32_t all = votes[0] | votes[1] | votes[2] | votes[3];
+        barrier();
+        return __builtin_amdgcn_readfirstlane(all);
+    };
+    uint32_t all = vote(odd, leasta < CUT_EXACTLY, leastb < CUT_EXACTLY);
+    const bool othera = OA::brings_others(m0, s.m), otherb = OB::brings_others(n0, s.n);
+    if (!(all & 1) && ((all & 2 && othera) || (all & 4 && otherb)))
+        all = vote(false, othera ? OA::loses_bits(s.a, s.lda, m0, s.m, s.kk, tid) : all & 2, otherb ? OB::loses_bits(s.b, s.ldb, n0, s.n, s.kk, tid) : all & 4);
 
     // Results through a private part of LDS, as in gemm_reg_kernel: eight consecutive lanes own 128 bytes of a row.
     constexpr int NB = BLOCKS < 8 ? BLOCKS : 8;   // blocks at a time
     static_assert(NB * 4096 <= (int)sizeof(smem) && BLOCKS % NB == 0 && NB % FN == 0 && FN % 2 == 0, "whole rows of blocks");
     char* const win = smem + wave * (NB * 1024);
-    static_for<BLOCKS / NB>([&](auto rix) {
-        constexpr int B0 = decltype(rix)::value * NB;
-        static_for<NB>([&](auto bix) {
-            constexpr int b = B0 + decltype(bix)::value;
-            *reinterpret_cast<f32x4*>(win + decltype(bix)::value * 1024 + (16 * q + (r ^ (4 * q))) * 16) = acc[b / FN][b % FN];
-        });
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (!all) {
+        static_for<BLOCKS / NB>([&](auto rix) {
+            constexpr int B0 = decltype(rix)::value * NB;
+            static_for<NB>([&](auto bix) {
+                constexpr int b = B0 + decltype(bix)::value;
+                *reinterpret_cast<f32x4*>(win + decltype(bix)::value * 1024 + (16 * q + (r ^ (4 * q))) * 16) = acc[b / FN][b % FN];
+            });
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll EPI == SBP_EPI_GELU ? 1 : 64
-        for (int u = 0; u < NB; ++u) {
-            const int blk = u / 2 * 2, row = u % 2 * 8 + lane / 8, cg = lane % 8;
-            const f32x4 x = *reinterpret_cast<const f32x4*>(win + (blk + cg / 4) * 1024 + (16 * (cg & 3) + (row ^ (4 * (cg & 3)))) * 16);
-            float v[4];
+            for (int u = 0; u < NB; ++u) {
+                const int blk = u / 2 * 2, row = u % 2 * 8 + lane / 8, cg = lane % 8;
+                const f32x4 x = *reinterpret_cast<const f32x4*>(win + (blk + cg / 4) * 1024 + (16 * (cg & 3) + (row ^ (4 * (cg & 3)))) * 16);
+                float v[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = EPI == SBP_EPI_GELU ? gelu_erf(x[e]) : x[e];
-            store_columns<float>(s, m0 + wm * TM + (B0 + blk) / FN * 16 + row, n0 + wn * TN + (B0 + blk) % FN * 16 + cg * 4, v);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    });
+                for (int e = 0; e < 4; ++e) v[e] = EPI == SBP_EPI_GELU ? gelu_erf(x[e]) : x[e];
+                store_columns<float>(s, m0 + wm * TM + (B0 + blk) / FN * 16 + row, n0 + wn * TN + (B0 + blk) % FN * 16 + cg * 4, v);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        });
+    }
+    asm volatile("" : "+s"(all));   // a branch of its own: as one, both ways would be laid out so that the accumulators outlive the second one's
+    if (all) f32_tile<BM, BN, BM == 128 ? 16 : 32, 2, 2, 1, T1, T2, A_KC, B_KC, EPI>(s, m0, n0, reinterpret_cast<float*>(smem));
 }
 
 // Tiles of gemm_f32_kernel, or (TERMS: waves per SIMD) of gemm_terms_kernel.

@@ -329,6 +329,68 @@ def test_f32_values_that_terms_do_not_hold(case, types, variant):
     assert np.all(np.abs(got[ok] - ref[ok]) <= 1e-5 * scale[ok] + kk * 2.0 ** -149)
 
 
+@pytest.mark.parametrize("variant,M,kk,N", [(49, 140, 70, 150), (50, 140, 70, 150), (0, 2046, 300, 2050)])
+@pytest.mark.parametrize("tx,tw", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("types", ["f32,f32", "f32,bf16", "bf16,f32"])
+@pytest.mark.parametrize("e", [-110, -111, -118, -126, -140])
+def test_f32_small_values_beside_ordinary_ones(e, types, tx, tw, variant, M, kk, N):
+    """one row of X, one column of W and one value of each that are 2^e in size among ordinary ones of 2^50, so that their results are
+    ordinary numbers: every result to the accuracy that fp32 operands give it.  From 2^-110 on down the bf16 terms cannot hold
+    fp32's bits"""
+    k = 1
+    X, W = (wl.uniform(SEED, t, shape, 1.0, 2.0).astype(np.float32) for t, shape in ((41, (M, kk)), (42, (kk, N))))
+    S, tiny = np.float32(2.0) ** 50, np.float32(2.0) ** e
+    X *= S
+    W *= S
+    if types != "bf16,f32":
+        X[5], X[99] = X[5] / S * tiny, 0
+        X[99, 33] = 1.1 * tiny
+    if types != "f32,bf16":
+        W[:, 7], W[:, 91] = W[:, 7] / S * tiny, 0
+        W[41, 91] = 1.1 * tiny
+    if types == "f32,f32":
+        sx, sw = orc.S1, orc.S0
+    else:
+        sx, sw = (orc.P_SUM, orc.B) if types == "f32,bf16" else (orc.B, orc.P_SUM)
+        X, W = (X, wl.to_bf16_bits(W)) if types == "f32,bf16" else (wl.to_bf16_bits(X), W)
+    got, _ = run([X], sx, [W], sw, M, kk, N, k, tx, tw, pitch([X], tx, 2, 1), pitch([W], tw, 2, 1), variant=variant)
+    x, w = values(X), values(W)
+    ref, scale = x @ w, np.abs(x) @ np.abs(w)
+    bad = np.abs(got[0] - ref) > 1e-5 * scale + kk * 2.0 ** -149
+    assert not bad.any(), f"{bad.sum()} results off, rows {np.unique(np.nonzero(bad)[0])[:8]}, columns {np.unique(np.nonzero(bad)[1])[:8]}"
+
+
+@pytest.mark.parametrize("variant", [49, 50])
+@pytest.mark.parametrize("small", [False, True])
+@pytest.mark.parametrize("M,kk,N", [(130, 70, 203), (5, 40, 6), (129, 65, 64)])
+def test_f32_terms_and_what_lies_behind_the_rows(M, kk, N, small, variant):
+    """both operands reduction-major, widths that are no multiple of 8: NaN, tiny and large values in the padding between rows give the
+    same bits, for ordinary and for small operands"""
+    import torch
+    X, W = f32(43, (M, kk)), f32(44, (kk, N))
+    if small:
+        X *= np.float32(2.0) ** -118
+        W *= np.float32(2.0) ** 60
+    out = []
+    for behind in (np.nan, 1e-41, 1e30, 0.0):
+        bufs = []
+        for a in (np.ascontiguousarray(X.T), W):
+            buf = torch.full((a.shape[0], a.shape[1] + 9), float(behind), device="cuda")
+            buf[:, :a.shape[1]] = torch.from_numpy(a).cuda()
+            bufs.append(buf)
+        dy = DevTensor.empty(M, N, np.float32, orc.P_SUM, 1)
+        sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, variant)
+        try:
+            sbp.sbp_matmul(sbp.SbpTensor([bufs[0]], M, kk, sbp.F32, 1, M + 9), sbp.S(1), sbp.SbpTensor([bufs[1]], kk, N, sbp.F32, 0, N + 9), sbp.S(0), dy.desc, sbp.AUTO, 1)
+            sync()
+        finally:
+            sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, 0)
+        out.append(dy.host()[0])
+    x, w = X.astype(np.float64), W.astype(np.float64)
+    assert np.all(np.abs(out[0] - x @ w) <= 1e-5 * (np.abs(x) @ np.abs(w)))
+    assert all(np.array_equal(o, out[0]) for o in out[1:])
+
+
 @pytest.mark.parametrize("M,K,N", [(5, 33, 7), (70, 300, 203)])
 def test_f32_gelu(M, K, N):
     k = 3
