@@ -312,7 +312,7 @@ struct TileCoord {
 // re-linearise so that each XCD walks a contiguous range of tiles (with k = 8 one whole shard,
 // whose W_g then lives in that XCD's L2 only), and walk the tiles of a shard in bands of GM
 // tile-rows, column by column, so that the 32 CUs of an XCD share operand tiles at any time.
-__device__ inline TileCoord map_tile(int bid, int nblk, int tm, int tn, int groups, int order) {
+__host__ __device__ inline TileCoord map_tile(int bid, int nblk, int tm, int tn, int groups, int order) {
     const int per_xcd = nblk >> 3;
     const int GM = order & 0xFF;                 // tile-rows per band
     const int v = (order & 0x100) ? bid : (bid & 7) * per_xcd + (bid >> 3);   // bit 8: no XCD re-linearisation
@@ -329,6 +329,11 @@ __device__ inline TileCoord map_tile(int bid, int nblk, int tm, int tn, int grou
     t.tile_n = in_band / gsz;
     return t;
 }
+
+// Band of gemm_deep_kernel, for shards of tm x tn tiles out of `tiles` in all: the 32 workgroups of an XCD as nearly a square of tiles as
+// the shard allows, for most sharing in its L2: all of a shard that one XCD holds, else four tile-rows.  A band is one byte of
+// the order.
+__host__ inline int deep_band(int tm, int tn, int64_t tiles) { return tm <= 255 && (int64_t)tm * tn <= (tiles + 7) / 8 ? tm : 4; }
 
 // The workgroups of one XCD whose tiles lie in the same tile-row (a: they read the same A panel) or tile-column (b) of the same
 // shard and band at the same time: this one's place among them and their number, for one tile per workgroup and one workgroup

@@ -1789,10 +1789,7 @@ bool two_stages_pay(const GemmPlan& plan, int max_m, int max_n) {
 }
 int32_t launch_deep(const GemmPlan& plan, int max_m, int max_n, hipStream_t stream) {
     const int tm = tiles_along(max_m, 128), tn = tiles_along(max_n, 128);
-    // The 32 workgroups of an XCD as nearly a square of tiles as the shard allows, for most sharing in its L2: all of a shard that
-    // one XCD holds, else bands of four tile-rows.
-    int order = tile_order_for(tm, tn);
-    if (!g_tile_order.load(std::memory_order_relaxed)) order = (int64_t)tm * tn <= (tiles_of(plan, max_m, max_n, 128, 128) + 7) / 8 ? tm : 4;
+    const int order = g_tile_order.load(std::memory_order_relaxed) ? tile_order_for(tm, tn) : deep_band(tm, tn, tiles_of(plan, max_m, max_n, 128, 128));
     return launch_gemm_deep(plan, max_m, max_n, order, stream);
 }
 

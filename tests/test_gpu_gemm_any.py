@@ -130,6 +130,17 @@ def test_bf16_rows_anywhere_in_a_cache_line(M, kk, N, extra, start, tx, tw):
         assert_matmul_close(y, ref[i], 1e-5, f"{M}x{kk}x{N} trans=({tx},{tw}) shard {i}")
 
 
+@pytest.mark.parametrize("M", [32641, 32900])
+def test_bf16_more_tile_rows_than_a_band_counts(M):
+    """variant 48, eight devices of 256 and 258 tile-rows"""
+    k, kk, N = 8, 72, 40
+    X, W = bf16(3, (M, k * kk)), bf16(4, (k * kk, N), 0.5)
+    Xs, Ws = orc.scatter(X, orc.S1, k), orc.scatter(W, orc.S0, k)
+    got, _ = run(Xs, orc.S1, Ws, orc.S0, M, k * kk, N, k, 0, 0, pitch(Xs, 0, 8), pitch(Ws, 0, 8), variant=48)
+    for i in range(k):
+        assert_matmul_close(got[i], values(Xs[i]) @ values(Ws[i]), 1e-5, f"shard {i}")
+
+
 @pytest.mark.parametrize("out", ["f32", "bf16", "gelu", "rowmax"])
 @pytest.mark.parametrize("tx,tw", [(0, 0), (1, 0), (0, 1), (1, 1)])
 @pytest.mark.parametrize("kk,ldy", [(128, 0), (256, 4352 + 8), (640, 4352 + 1)])
