@@ -258,22 +258,25 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmPlan p,
 // Products as sums of bf16 terms: Henry, Tang, Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
 // Higher-Precision Computations" (2019).
 //
-// What the cut cannot hold (infinities, values past the largest bf16, sums that leave the fp32 range on the way) shows as a result
-// that is not finite; a value other than 0 below 2^-110, whose lo term would lose bits, is seen when it is cut.  A tile with one
-// of these is multiplied again by f32_tile: one value is enough, since its partner in the reduction may be as large as they get.
-// NaN stays NaN either way.
+// A value is scaled by 2^24 before the cut, which is exact and brings the last bit of the smallest one, 2^-149, into the range of bf16; the
+// results are scaled back.  What the cut cannot hold then (infinities, values of 2^104 and more, sums that leave the fp32 range on
+// the way) shows as a result that is not finite; such a tile is multiplied again by f32_tile.  NaN stays NaN either way.
+// (A look at every value for small ones, and a second multiplication of their tiles, took 106 and 674 us where this takes 105 and 654
+// below, and twice as long where there were any.)
 //
-// Bound by the power limit of the matrix cores: [4096, 4096] x [4096, 4096] 640 us, 1.29 PFLOP/s of bf16 products (1068 us on the
-// fp32 instruction); with all-zero operands 542.  [2000, 750] x [750, 1500], 4 devices, 153 -> 104.  Four waves; one LDS stage of 48 KB,
+// Bound by the power limit of the matrix cores: [4096, 4096] x [4096, 4096] 654 us, 1.26 PFLOP/s of bf16 products (1064 us on the
+// fp32 instruction).  [2000, 750] x [750, 1500], 4 devices, 152 -> 105.  Four waves; one LDS stage of 48 KB,
 // so that three workgroups of 168 registers a wave share a compute unit: one splits while others multiply (two of them with a
 // register stage ahead: 110 us).  Six terms for 64 x 64 results a wave read 24 KB of fragments per 96 matrix instructions, half of
 // what LDS can deliver meanwhile; splitting a fragment after the read would read two thirds of that and split everything twice.
 // ---------------------------------------------------------------------------------------------------------------------
-// x = hi + mid + lo, each the nearest bf16 of what is left; pairs of values.  Exact for 0 and for magnitudes below 2^127 (2 - 2^-8)
-// whose last bit is not below 2^-133, bf16's smallest: from 2^-110 on.
+// x 2^24 = hi + mid + lo, each the nearest bf16 of what is left; pairs of values.  Exact below 2^104 in magnitude.
+constexpr int CUT_EXP = 24;
 struct TermPair { uint32_t hi, mid, lo; };
 __device__ inline TermPair split_pair(float x, float y) {
     TermPair t;
+    x *= (float)(1 << CUT_EXP);
+    y *= (float)(1 << CUT_EXP);
     t.hi = f32_to_bf16x2(x, y);
     x -= __uint_as_float(t.hi << 16);
     y -= __uint_as_float(t.hi & 0xFFFF0000u);
@@ -283,10 +286,6 @@ __device__ inline TermPair split_pair(float x, float y) {
     t.lo = f32_to_bf16x2(x, y);
     return t;
 }
-
-// Of a value's bits: grows with its magnitude, largest for 0.
-__device__ inline uint32_t magnitude_key(uint32_t bits) { return 2u * bits - 1u; }
-constexpr uint32_t CUT_EXACTLY = 2u * ((127u - 110u) << 23) - 1u;   // the key of 2^-110
 
 // One operand of gemm_terms_kernel: R rows by 32 of the reduction a stage, as one (bf16) or three (fp32) bf16 tiles.
 template <typename T, int R, bool KC, int NT>
@@ -348,18 +347,7 @@ struct TermOperand {
                 }
         }
     }
-    // Where columns end in the tile, chunks of plain stages bring what lies behind a row and columns of another tile, and stash looks
-    // at all they bring: there, when it has seen something, is it a value of the tile itself?
-    __device__ static bool brings_others(int first, int limit) { return F32 && !KC && first + R > limit; }
-    __device__ static bool loses_bits(const void* base, int ld, int first, int limit, int kk, int tid) {
-        const int col = first + tid % R;
-        if (col >= limit) return false;
-        uint32_t least = ~0u;
-        for (int k = tid / R; k < kk; k += NT / R) least = min(least, magnitude_key(static_cast<const uint32_t*>(base)[(int64_t)k * ld + col]));
-        return least < CUT_EXACTLY;
-    }
-    // into LDS; least: the smallest key of all values
-    __device__ static void stash(char* st, Raw& r, int tid, uint32_t& least) {
+    __device__ static void stash(char* st, Raw& r, int tid) {   // into LDS
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             char* const to = st + (i * NT + tid) * 16;
@@ -368,9 +356,7 @@ struct TermOperand {
                 u32x4 h, m, l;
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
-                    const uint32_t x = r.v[i][d >> 1][2 * (d & 1)], y = r.v[i][d >> 1][2 * (d & 1) + 1];
-                    least = min(least, min(magnitude_key(x), magnitude_key(y)));
-                    const TermPair t = split_pair(__uint_as_float(x), __uint_as_float(y));
+                    const TermPair t = split_pair(__uint_as_float(r.v[i][d >> 1][2 * (d & 1)]), __uint_as_float(r.v[i][d >> 1][2 * (d & 1) + 1]));
                     h[d] = t.hi;
                     m[d] = t.mid;
                     l[d] = t.lo;
@@ -424,10 +410,9 @@ __global__ __launch_bounds__(256, WPS) void gemm_terms_kernel(GemmPlan p, int tm
     typename OB::Raw rb;
     // LDS traffic of this wave done, then all waves: the loads into registers stay in flight
     auto barrier = []() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-    uint32_t leasta = ~0u, leastb = ~0u;
     auto stash = [&]() {
-        OA::stash(smem, ra, tid, leasta);
-        OB::stash(smem + OA::BYTES, rb, tid, leastb);
+        OA::stash(smem, ra, tid);
+        OB::stash(smem + OA::BYTES, rb, tid);
     };
     auto multiply = [&]() {
         bf16x8 fa[2][OA::N], fb[OB::N][FN];
@@ -481,7 +466,7 @@ __global__ __launch_bounds__(256, WPS) void gemm_terms_kernel(GemmPlan p, int tm
         barrier();
     }
 
-    // Where a value lost bits or a result is not finite: the tile again, in fp32.
+    // Where a result is not finite: the tile again, in fp32.
     const int q = lane >> 4, r = lane & 15;
     bool odd = false;
 #pragma unroll
@@ -492,25 +477,18 @@ __global__ __launch_bounds__(256, WPS) void gemm_terms_kernel(GemmPlan p, int tm
             for (int e = 0; e < 4; ++e)
                 if (m0 + wm * TM + 16 * i + r < s.m && n0 + wn * TN + 16 * j + 4 * q + e < s.n) odd |= !(__builtin_fabsf(acc[i][j][e]) <= 3.4028234663852886e38f);
     uint32_t* const votes = reinterpret_cast<uint32_t*>(smem);
-    auto vote = [&](bool b0, bool b1, bool b2) {   // of all lanes of the workgroup: bit i where any has bi
-        auto any = [](bool b) { return __builtin_amdgcn_ballot_w64(b) != 0; };
-        barrier();
-        votes[wave] = (any(b0) ? 1u : 0u) | (any(b1) ? 2u : 0u) | (any(b2) ? 4u : 0u);
-        barrier();
-        const uint32_t all = votes[0] | votes[1] | votes[2] | votes[3];
-        barrier();
-        return __builtin_amdgcn_readfirstlane(all);
-    };
-    uint32_t all = vote(odd, leasta < CUT_EXACTLY, leastb < CUT_EXACTLY);
-    const bool othera = OA::brings_others(m0, s.m), otherb = OB::brings_others(n0, s.n);
-    if (!(all & 1) && ((all & 2 && othera) || (all & 4 && otherb)))
-        all = vote(false, othera ? OA::loses_bits(s.a, s.lda, m0, s.m, s.kk, tid) : all & 2, otherb ? OB::loses_bits(s.b, s.ldb, n0, s.n, s.kk, tid) : all & 4);
+    barrier();
+    votes[wave] = __builtin_amdgcn_ballot_w64(odd) != 0;
+    barrier();
+    uint32_t again = __builtin_amdgcn_readfirstlane(votes[0] | votes[1] | votes[2] | votes[3]);
+    barrier();
 
     // Results through a private part of LDS, as in gemm_reg_kernel: eight consecutive lanes own 128 bytes of a row.
     constexpr int NB = BLOCKS < 8 ? BLOCKS : 8;   // blocks at a time
+    constexpr float BACK = 1.0f / (float)((int64_t)1 << CUT_EXP * ((OA::F32 ? 1 : 0) + (OB::F32 ? 1 : 0)));
     static_assert(NB * 4096 <= (int)sizeof(smem) && BLOCKS % NB == 0 && NB % FN == 0 && FN % 2 == 0, "whole rows of blocks");
     char* const win = smem + wave * (NB * 1024);
-    if (!all) {
+    if (!again) {
         static_for<BLOCKS / NB>([&](auto rix) {
             constexpr int B0 = decltype(rix)::value * NB;
             static_for<NB>([&](auto bix) {
@@ -524,14 +502,14 @@ __global__ __launch_bounds__(256, WPS) void gemm_terms_kernel(GemmPlan p, int tm
                 const f32x4 x = *reinterpret_cast<const f32x4*>(win + (blk + cg / 4) * 1024 + (16 * (cg & 3) + (row ^ (4 * (cg & 3)))) * 16);
                 float v[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = EPI == SBP_EPI_GELU ? gelu_erf(x[e]) : x[e];
+                for (int e = 0; e < 4; ++e) v[e] = EPI == SBP_EPI_GELU ? gelu_erf(x[e] * BACK) : x[e] * BACK;
                 store_columns<float>(s, m0 + wm * TM + (B0 + blk) / FN * 16 + row, n0 + wn * TN + (B0 + blk) % FN * 16 + cg * 4, v);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         });
     }
-    asm volatile("" : "+s"(all));   // a branch of its own: as one, both ways would be laid out so that the accumulators outlive the second one's
-    if (all) f32_tile<BM, BN, BM == 128 ? 16 : 32, 2, 2, 1, T1, T2, A_KC, B_KC, EPI>(s, m0, n0, reinterpret_cast<float*>(smem));
+    asm volatile("" : "+s"(again));   // a branch of its own: as one, both ways would be laid out so that the accumulators outlive the second one's
+    if (again) f32_tile<BM, BN, BM == 128 ? 16 : 32, 2, 2, 1, T1, T2, A_KC, B_KC, EPI>(s, m0, n0, reinterpret_cast<float*>(smem));
 }
 
 // Tiles of gemm_f32_kernel, or (TERMS: waves per SIMD) of gemm_terms_kernel.

@@ -371,6 +371,54 @@ def test_f32_small_values_beside_ordinary_ones(e, types, tx, tw, variant, M, kk,
     assert not bad.any(), f"{bad.sum()} results off, rows {np.unique(np.nonzero(bad)[0])[:8]}, columns {np.unique(np.nonzero(bad)[1])[:8]}"
 
 
+@pytest.mark.parametrize("variant", [0, 49, 50])
+@pytest.mark.parametrize("types", ["f32,bf16", "bf16,f32"])
+def test_f32_next_to_small_bf16_values(types, variant):
+    """one row or column of bf16 denormals next to fp32 values of 2^60"""
+    M, kk, N = 140, 70, 150
+    X, W = (wl.uniform(SEED, t, shape, 1.0, 2.0).astype(np.float32) for t, shape in ((45, (M, kk)), (46, (kk, N))))
+    if types == "f32,bf16":
+        X *= np.float32(2.0) ** 60
+        W[:, 7] *= np.float32(2.0) ** -130
+        W, sx, sw = wl.to_bf16_bits(W), orc.P_SUM, orc.B
+    else:
+        W *= np.float32(2.0) ** 60
+        X[5] *= np.float32(2.0) ** -130
+        X, sx, sw = wl.to_bf16_bits(X), orc.B, orc.P_SUM
+    got, _ = run([X], sx, [W], sw, M, kk, N, 1, 0, 0, pitch([X], 0, 2, 1), pitch([W], 0, 2, 1), variant=variant)
+    ref = values(X) @ values(W)
+    assert np.all(ref > 0) and np.all(np.abs(got[0] - ref) <= 1e-5 * ref)
+
+
+@pytest.mark.parametrize("variant", [49, 50])
+def test_f32_small_values_cost_no_second_multiplication(variant):
+    """the tail of a softmax (one value in fifty between 2^-149 and 2^-111) is held by the terms: as fast as ordinary values.  Multiplying
+    every tile again on the fp32 instruction takes 2.2 times as long; 1.4 leaves room for the clock"""
+    import torch
+    M = kk = N = 2048
+    g = torch.Generator(device="cuda").manual_seed(SEED)
+    x, w = (torch.empty((M, kk), device="cuda").normal_(generator=g) for _ in range(2))
+    tail = x * torch.exp2(torch.randint(-149, -111, x.shape, device="cuda", generator=g).float())
+    xs = torch.where(torch.rand(x.shape, device="cuda", generator=g) < 0.02, tail, x)
+    y = torch.empty((M, N), device="cuda")
+    ty, tw, tx = sbp.SbpTensor([y], M, N, sbp.F32), sbp.SbpTensor([w], kk, N, sbp.F32), [sbp.SbpTensor([t], M, kk, sbp.F32) for t in (x, xs)]
+    best = [float("inf"), float("inf")]
+    sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, variant)
+    try:
+        for _ in range(6):
+            for i, t in enumerate(tx):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                a.record()
+                for _ in range(5):
+                    sbp.sbp_matmul(t, sbp.S(1), tw, sbp.S(0), ty, sbp.AUTO, 1)
+                b.record()
+                sync()
+                best[i] = min(best[i], a.elapsed_time(b))
+    finally:
+        sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, 0)
+    assert best[1] <= 1.4 * best[0], best
+
+
 @pytest.mark.parametrize("variant", [49, 50])
 @pytest.mark.parametrize("small", [False, True])
 @pytest.mark.parametrize("M,kk,N", [(130, 70, 203), (5, 40, 6), (129, 65, 64)])
