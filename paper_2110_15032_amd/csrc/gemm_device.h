@@ -13,6 +13,8 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 
@@ -489,6 +491,22 @@ __device__ inline void store_first_untracked(OutT* c, const V v, int n) {
             if constexpr (sizeof(OutT) == 4) asm volatile("global_store_dword %0, %1, off" : : "v"(c + e), "v"(w[e]) : "memory");
             else asm volatile("global_store_short %0, %1, off" : : "v"(c + e), "v"(w[e >> 1] >> (16 * (e & 1))) : "memory");
         }
+}
+
+// The first `n` elements, at least one and fewer than all, of 16 bytes of results; n is uniform.
+__device__ inline void store_rest_untracked(float* c, const u32x4 v, int n) {
+    const u32x2 two = {v[0], v[1]};
+    const u32x3 three = {v[0], v[1], v[2]};
+    if (n == 1) asm volatile("global_store_dword %0, %1, off" : : "v"(c), "v"(v[0]) : "memory");
+    else if (n == 2) asm volatile("global_store_dwordx2 %0, %1, off" : : "v"(c), "v"(two) : "memory");
+    else asm volatile("global_store_dwordx3 %0, %1, off\n\ts_nop 1" : : "v"(c), "v"(three) : "memory");
+}
+__device__ inline void store_rest_untracked(uint16_t* c, const u32x4 v, int n) {
+    const u32x2 four = {v[0], v[1]};
+    const uint32_t a = n & 4 ? v[2] : v[0], b = n & 4 ? v[3] : v[1];   // behind those four
+    if (n & 4) asm volatile("global_store_dwordx2 %0, %1, off" : : "v"(c), "v"(four) : "memory");
+    if (n & 2) asm volatile("global_store_dword %0, %1, off" : : "v"(c + (n & 4)), "v"(a) : "memory");
+    if (n & 1) asm volatile("global_store_short %0, %1, off" : : "v"(c + (n & 6)), "v"(n & 2 ? b : a) : "memory");
 }
 
 }  // namespace

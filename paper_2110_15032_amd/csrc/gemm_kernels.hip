@@ -284,15 +284,19 @@ __device__ __attribute__((always_inline)) inline void store_tile(const f32x16 (&
 //         and exchange with the neighbouring column as in store_tile; one write instruction covers rows
 //         4 g + (lane & 1), 8 dwords each: the 32-byte column group j is kept at j ^ g.
 // store_tile16 stores 16 bytes at a time, rows at any pitch; tiles cut by the edge under a mask (the fused row maximum has none for
-// columns), and the elements of a piece that the edge cuts one by one (`ends_inside`).  Element by element, half of the tiles of
+// columns), and what the edge leaves of a row's last 16 bytes (`ends_inside`) with one row a lane.  Element by element, half of the tiles of
 // [445, 128] x [128, 47072], 4 devices, made 347 us of 56, [144, 61] x [61, 23304], 8 devices, took 70 for 32, and with rows of 23301
-// results 80 for 28; [1767, 512] x [512, 4081], 2 devices, 52 for 22.
+// results 80 for 28; [1767, 512] x [512, 4081], 2 devices, 52 for 22.  Where few tiles are stored, what tells is the code that has to be
+// fetched and the way through LDS: with all regions stored and the rest element by element in each piece [1797, 32] x [32, 9], 4 devices, took
+// 5.4 us and [1346, 112] x [112, 9] 6.9, element by element 4.1 and 5.6, so 4.1 and 5.6.
 template <int EPI, int BN>
 __device__ inline bool stores_pieces(const GemmShard& s, int n0) { return n0 + BN <= s.n || EPI != EPI_ROWMAX; }
 template <int BN, typename OutT>
 __device__ inline bool ends_inside(const GemmShard& s, int n0) { return n0 + BN > s.n && s.n % (16 / (int)sizeof(OutT)) != 0; }
 
-template <int BM, int BN, int TM, int TN, int EPI, typename OutT, int KEEP = 0>
+// COUNTED: the kernel counts a tile's stores, so that all of them are issued wherever the tile is cut (an empty mask counts); else 32 x 32
+// regions (bf16: 32 rows) that lie outside are left out.  KEEP: loads behind the last ones that are waited for.
+template <int BM, int BN, int TM, int TN, int EPI, typename OutT, bool COUNTED = false, int KEEP = 0>
 __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (&acc)[TM / 16][TN / 16], const GemmShard& s, int m0, int n0, int wm, int wn, int lane, char* stage) {
     constexpr int FM = TM / 32, FN = TN / 32;       // 32 x 32 regions, as in store_tile
     OutT* C = static_cast<OutT*>(s.c);
@@ -309,12 +313,19 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
         constexpr bool MASKED = decltype(masked)::value;
         const int wave = (int)(threadIdx.x >> 6);
         const int h = lane >> 5;
-        [[maybe_unused]] const int rows_left = s.m - (m0 + wm * TM) - (lane >> 3), cols_left = s.n - (n0 + wn * TN) - (lane & 7) * EPV;   // this lane's
+        [[maybe_unused]] const int wave_rows = s.m - (m0 + wm * TM), wave_cols = s.n - (n0 + wn * TN);   // inside, from the wave tile's first on
+        [[maybe_unused]] const int rows_left = wave_rows - (lane >> 3), cols_left = wave_cols - (lane & 7) * EPV;   // this lane's
         auto put = [&](auto* dst, const auto v, [[maybe_unused]] int row, [[maybe_unused]] int col) {
-            if constexpr (MASKED) {
-                store16_untracked(dst, v, stream, __builtin_amdgcn_ballot_w64(row < rows_left && col + EPV <= cols_left));
-                if (inside && row < rows_left && col + EPV > cols_left) store_first_untracked(reinterpret_cast<OutT*>(dst), v, cols_left - col);
-            } else store16_untracked(dst, v, stream);
+            if constexpr (MASKED) store16_untracked(dst, v, stream, __builtin_amdgcn_ballot_w64(row < rows_left && col + EPV <= cols_left));
+            else store16_untracked(dst, v, stream);
+        };
+        // the last columns of the rows of a region, fewer than 16 bytes: one row a lane.  `at`: where logical row and chunk lie in the window
+        [[maybe_unused]] auto put_rest = [&](int row0, int col0, int width, auto at) {
+            const int rest = s.n % EPV, col = wave_cols - rest, r = lane & 31;
+            if (inside && col >= col0 && col < col0 + width) {
+                const u32x4 v = *reinterpret_cast<const u32x4*>(stage + at(r, (col - col0) / EPV));
+                if (lane < 32 && row0 + r < wave_rows) store_rest_untracked(C + (int64_t)(m0 + wm * TM + row0 + r) * s.ldc + (s.n - rest), v, rest);
+            }
         };
         OutT* cg = C + (int64_t)(m0 + wm * TM + (lane >> 3)) * s.ldc + (n0 + wn * TN + (lane & 7) * EPV);
         if constexpr (sizeof(OutT) == 4) {
@@ -334,6 +345,8 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
                 }
             static_for<FM * FN>([&](auto idx) {
                 constexpr int i = decltype(idx)::value / FN, j = decltype(idx)::value % FN;
+                if constexpr (MASKED && !COUNTED)
+                    if (i * 32 >= wave_rows || j * 32 >= wave_cols) return;
                 static_for<2>([&](auto ibx) {
                     constexpr int ib = decltype(ibx)::value;
                     static_for<2>([&](auto jbx) {
@@ -353,6 +366,7 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
                     if constexpr (decltype(idx)::value == 0 && q == 0) __builtin_amdgcn_s_waitcnt(vmcnt_only(KEEP));
                     put(dst, v, i * 32 + q * 8, j * 32);
                 });
+                if constexpr (MASKED) put_rest(i * 32, j * 32, 32, [&](int r, int ch) { return wave * STAGE_BYTES + (r ^ (r >> 2 & 1)) * 128 + (ch ^ (r >> 1 & 4)) * 16; });
                 __builtin_amdgcn_wave_barrier();
             });
         } else {
@@ -379,6 +393,8 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
             }
             static_for<FM>([&](auto idx) {
                 constexpr int i = decltype(idx)::value;
+                if constexpr (MASKED && !COUNTED && EPI != EPI_ROWMAX)
+                    if (i * 32 >= wave_rows || wave_cols <= 0) return;
                 static_for<2>([&](auto ibx) {
                     constexpr int ib = decltype(ibx)::value;
                     static_for<4>([&](auto jidx) {
@@ -410,6 +426,7 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
                     if constexpr (decltype(idx)::value == 0 && q == 0) __builtin_amdgcn_s_waitcnt(vmcnt_only(KEEP));
                     put(dst, v, i * 32 + q * 8, 0);
                 });
+                if constexpr (MASKED && EPI != EPI_ROWMAX) put_rest(i * 32, 0, 64, [&](int r, int ch) { return wave * STAGE_BYTES + r * 128 + (ch ^ (r >> 1 & 4) ^ (r >> 1 & 2)) * 16; });
                 __builtin_amdgcn_wave_barrier();
             });
             if constexpr (EPI == EPI_ROWMAX) {
@@ -438,7 +455,7 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
     if (whole) return store(std::false_type{});
     if (stores_pieces<EPI, BN>(s, n0)) {
         store(std::true_type{});
-        if (inside) __builtin_amdgcn_s_waitcnt(vmcnt_only(0));   // an unknown number of stores, and the loads
+        if (COUNTED && inside) __builtin_amdgcn_s_waitcnt(vmcnt_only(0));   // an unknown number of stores, and the loads
         return;
     }
     // row maxima of columns that end in the tile: element by element, guarded
@@ -1291,7 +1308,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_persist16_kernel(GemmP
             step(I2{}, Old{}, false);
             step(I3{}, Old{}, false);
         }
-        store_tile16<BM, BN, TM, TN, EPI, OutT, NP>(acc, s, m0, n0, wm, wn, lane, sOut);
+        store_tile16<BM, BN, TM, TN, EPI, OutT, true, NP>(acc, s, m0, n0, wm, wn, lane, sOut);
         young = EPI != EPI_ROWMAX && !ends_inside<BN, OutT>(s, n0);
         cv = nv;
     }

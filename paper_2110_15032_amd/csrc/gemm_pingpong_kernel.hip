@@ -305,7 +305,6 @@ __global__ __launch_bounds__(512) void gemm_pingpong_kernel(GemmPlan p, int tm, 
                             const float v0 = mfma_epilogue<EPI>(acc[IA][j][0]), v1 = mfma_epilogue<EPI>(acc[IA][j][1]);
                             const float v2 = mfma_epilogue<EPI>(acc[IA][j][2]), v3 = mfma_epilogue<EPI>(acc[IA][j][3]);
                             if constexpr (EPI == EPI_ROWMAX) mx = max3f(max3f(mx, v0, v1), v2, v3);
-                            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
                             const u32x2 w = {f32_to_bf16x2(v0, v1), f32_to_bf16x2(v2, v3)};
                             *reinterpret_cast<u32x2*>(win + (decltype(sub)::value * 2048 + (wbase ^ (j << 5)))) = w;
                         }
