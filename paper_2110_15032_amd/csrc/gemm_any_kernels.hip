@@ -496,17 +496,18 @@ __global__ __launch_bounds__(256, 2) void gemm_reg_kernel(GemmPlan p, int tm, in
 //     of 128 bytes that straddle two lines cost the load path twice (all lines in L2, rows 250000 bytes apart: 0.58 us a stage
 //     against 0.35 with rows on lines).  A fragment then comes from two neighbouring stages, so that one stage less is in
 //     flight; with every row on a line the stages are read as they are (with lines all the same [1500, 2048] x [2048, 1500] took
-//     17.3 us, without 16.2).
+//     17.3 us, without 16.2).  Over the stages as they are, rows off lines: operands read from HBM 0.67-0.97, from the memory-side
+//     cache 160 tiles and more 0.71-1.03, 100 to 128 tiles 1.00-1.07 up to length 1000, 0.71-1.07 up to 3000.
 //   * The load path returns in order.  A stage of 32 KB takes 0.21 us when all of it is in L2 and 0.58 us when any of it comes from
 //     HBM, whatever the number of stages in flight; operand tiles shared by the workgroups of an XCD are in L2 for all but the
 //     first, but all of them wait for that one.  So the lines of four stages are touched at once, three stages ahead of their
-//     loads, every workgroup the part that is its share among those that read the same tile: one wait for HBM in four stages.
-// us, before / now: feature gradient of a classifier, 8 devices, [1024, 125000] x [125000, 512], left rows on lines 1475 / 1058, with both
+//     loads, every workgroup the part that is its share among those that read the same tile: one wait for HBM in four stages (TOUCH).
+// us, stages as they are / now: feature gradient of a classifier, 8 devices, [1024, 125000] x [125000, 512], left rows on lines 1475 / 1058, with both
 // rows 250000 bytes apart 1915 / 1073, neither operand reduction-contiguous 1250 / 1099; without the touches 1168.  [1024, 16384] x
 // [16384, 512] 160 / 148; [777, 1000] x [1000, 1000], 3 devices, 14.7 / 13.1.  Of the 0.54 us a stage that are left the multiplication
 // and its LDS reads take 0.36.
-// LINES: some row of a reduction-contiguous operand starts inside a cache line.
-template <bool A_KC, bool B_KC, bool LINES, int EPI, typename OutT>
+// LINES: some row of a reduction-contiguous operand starts inside a cache line.  TOUCH: see touches_pay.
+template <bool A_KC, bool B_KC, bool LINES, bool TOUCH, int EPI, typename OutT>
 __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int tn, int order) {
     constexpr int BM = 128, BN = 128, BKT = 64, NT = 512, NST = 4, FM = 4, FN = 4;
     using TA = Tile<BM, A_KC, NT, BKT, true>;
@@ -515,13 +516,11 @@ __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int 
     constexpr bool LA_ = LINES && A_KC, LB_ = LINES && B_KC;   // operands that are loaded by whole lines
     static_assert(!LINES || A_KC || B_KC, "only rows along the reduction are pieced together");
     // Lines are touched this many stages ahead (5, 6 and 8 measured: within 2 % with a reduction-contiguous operand, 2 to 12 % slower
-    // without), as long as a workgroup's share of four stages is not more than TOUCH_MAX and there are TOUCH_STEPS stages; shorter
-    // products mostly read what the memory-side cache still holds.  us, with / without: share of 192 lines 1073 / 1168 and 150.3 / 158.7,
-    // 256 16.9 / 16.0, 288 182.7 / 178.3; neither operand reduction-contiguous 192 148.5 / 159.9, 288 165.5 / 176.3; [1024, 3072] x [3072, 512],
-    // 8 devices (48 stages), 33.8 / 37.2, length 2048 26.4 / 27.0, [1767, 2048] x [2048, 1000], 2 devices, bf16 results, 20.2 / 19.0.
-    constexpr int TOUCH_DIST = 7, TOUCH_MAX = A_KC || B_KC ? 224 : 320, TOUCH_STEPS = 48;
+    // without), as long as a workgroup's share of four stages is not more than TOUCH_MAX.  us, with / without: share of 192 lines
+    // 1073 / 1168 and 150.3 / 158.7, 288 182.7 / 178.3; neither operand reduction-contiguous 192 148.5 / 159.9, 288 165.5 / 176.3.
+    constexpr int TOUCH_DIST = 7, TOUCH_MAX = A_KC || B_KC ? DEEP_TOUCH_MAX_KC : DEEP_TOUCH_MAX;
     static_assert(NST * STAGE == 8 * FM * FN * 1024, "the partial tiles fill the stages");
-    __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE + 256];   // the last 256 bytes: what the touches bring
+    __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE + (TOUCH ? 256 : 0)];   // the last 256 bytes: what the touches bring
 
     const TileCoord tc = map_tile(blockIdx.x, gridDim.x, tm, tn, p.groups, order);
     if (!tc.valid) return;
@@ -632,12 +631,12 @@ __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int 
     auto step = [&](auto cur, auto kind) {
         constexpr int CUR = decltype(cur)::value;
         // stages t + 2, t + 3 (with whole lines only t + 3) and the touch behind the one waited for stay in flight
-        if constexpr (LINES) wait_keep(std::integral_constant<int, (NST - 3) * NVM + (CUR == 1 || CUR == 2)>{});
-        else wait_keep(std::integral_constant<int, (NST - 2) * NVM + (CUR != 0)>{});
+        if constexpr (LINES) wait_keep(std::integral_constant<int, (NST - 3) * NVM + (TOUCH && (CUR == 1 || CUR == 2))>{});
+        else wait_keep(std::integral_constant<int, (NST - 2) * NVM + (TOUCH && CUR != 0)>{});
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         issue(smem + CUR * STAGE, kind);
-        if constexpr (CUR == 0) touch_ahead(t + TOUCH_DIST);
+        if constexpr (TOUCH && CUR == 0) touch_ahead(t + TOUCH_DIST);
         read_at(oa[(CUR + 1) % NST], ob[(CUR + 1) % NST], (CUR + 1) & 1);
         mfmas(CUR & 1);
         constexpr int NDS = (A_KC ? FM : 2 * FM) + (B_KC ? FN : 2 * FN), NM = FM * FN - 4;
@@ -654,7 +653,7 @@ __global__ __launch_bounds__(512) void gemm_deep_kernel(GemmPlan p, int tm, int 
         using Any = std::integral_constant<Issue, ANY>;
         issue(smem, std::integral_constant<Issue, FIRST>{});
         static_for<NST - 1>([&](auto i) { issue(smem + (decltype(i)::value + 1) * STAGE, Any{}); });
-        if (steps >= TOUCH_STEPS) share_touches();
+        if constexpr (TOUCH) if (steps >= DEEP_TOUCH_STEPS) share_touches();
         wait_keep(std::integral_constant<int, (NST - (LINES ? 2 : 1)) * NVM>{});
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
@@ -754,33 +753,34 @@ int32_t launch_rows(const GemmPlan& plan, int max_m, int max_n, int order, hipSt
 }
 
 template <int EPI, typename OutT>
-int32_t launch_deep_layout(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t st) {
+int32_t launch_deep_layout(const GemmPlan& plan, int max_m, int max_n, int order, bool touch, hipStream_t st) {
     const int tm = tiles_along(max_m, 128), tn = tiles_along(max_n, 128);
     const int64_t nblk = ((int64_t)tm * tn * plan.groups + 7) / 8 * 8;
     if (!grid_fits(nblk, 512)) return SBP_ERR_UNSUPPORTED;
-    void (*kern)(GemmPlan, int, int, int);
-    bool lines = false;   // does a row along the reduction start inside a cache line?
-    for (int g = 0; g < plan.groups; ++g) {
-        const GemmShard& d = plan.s[g];
-        if (!d.m || !d.n || !d.kk) continue;
-        lines |= (plan.a_kc && ((reinterpret_cast<uintptr_t>(d.a) & 127) || d.lda % 64)) || (plan.b_kc && ((reinterpret_cast<uintptr_t>(d.b) & 127) || d.ldb % 64));
-    }
-    if (plan.a_kc && plan.b_kc) kern = lines ? gemm_deep_kernel<true, true, true, EPI, OutT> : gemm_deep_kernel<true, true, false, EPI, OutT>;
-    else if (plan.a_kc) kern = lines ? gemm_deep_kernel<true, false, true, EPI, OutT> : gemm_deep_kernel<true, false, false, EPI, OutT>;
-    else if (plan.b_kc) kern = lines ? gemm_deep_kernel<false, true, true, EPI, OutT> : gemm_deep_kernel<false, true, false, EPI, OutT>;
-    else kern = gemm_deep_kernel<false, false, false, EPI, OutT>;
-    hipLaunchKernelGGL(kern, dim3((uint32_t)nblk), dim3(512), 0, st, plan, tm, tn, order);
+    const bool lines = !rows_on_lines(plan);
+    auto launch = [&](auto a_kc, auto b_kc, auto ln, auto tc) {
+        hipLaunchKernelGGL((gemm_deep_kernel<decltype(a_kc)::value, decltype(b_kc)::value, decltype(ln)::value, decltype(tc)::value, EPI, OutT>), dim3((uint32_t)nblk), dim3(512), 0, st, plan, tm, tn, order);
+    };
+    auto either = [](bool on, auto f) { on ? f(std::true_type{}) : f(std::false_type{}); };
+    either(plan.a_kc, [&](auto a) {
+        either(plan.b_kc, [&](auto b) {
+            either(touch, [&](auto t) {
+                if constexpr (decltype(a)::value || decltype(b)::value) either(lines, [&](auto l) { launch(a, b, l, t); });
+                else launch(a, b, std::false_type{}, t);
+            });
+        });
+    });
     return launch_status(__func__);
 }
 
 }  // namespace
 
-int32_t launch_gemm_deep(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t stream) {
-    if (plan.out_dtype == SBP_F32) return plan.epilogue == SBP_EPI_NONE ? launch_deep_layout<SBP_EPI_NONE, float>(plan, max_m, max_n, order, stream) : SBP_ERR_UNSUPPORTED;
-    if (plan.epilogue == SBP_EPI_GELU) return launch_deep_layout<SBP_EPI_GELU, uint16_t>(plan, max_m, max_n, order, stream);
-    if (plan.epilogue == EPI_GELU_ERF) return launch_deep_layout<EPI_GELU_ERF, uint16_t>(plan, max_m, max_n, order, stream);
+int32_t launch_gemm_deep(const GemmPlan& plan, int max_m, int max_n, int order, bool touch, hipStream_t stream) {
+    if (plan.out_dtype == SBP_F32) return plan.epilogue == SBP_EPI_NONE ? launch_deep_layout<SBP_EPI_NONE, float>(plan, max_m, max_n, order, touch, stream) : SBP_ERR_UNSUPPORTED;
+    if (plan.epilogue == SBP_EPI_GELU) return launch_deep_layout<SBP_EPI_GELU, uint16_t>(plan, max_m, max_n, order, touch, stream);
+    if (plan.epilogue == EPI_GELU_ERF) return launch_deep_layout<EPI_GELU_ERF, uint16_t>(plan, max_m, max_n, order, touch, stream);
     if (plan.epilogue != SBP_EPI_NONE) return SBP_ERR_UNSUPPORTED;
-    return launch_deep_layout<SBP_EPI_NONE, uint16_t>(plan, max_m, max_n, order, stream);
+    return launch_deep_layout<SBP_EPI_NONE, uint16_t>(plan, max_m, max_n, order, touch, stream);
 }
 
 int32_t launch_gemm_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool direct, int order, hipStream_t stream) {

@@ -175,9 +175,8 @@ struct Tile {
             g = g < limit ? g : limit - 1;
             return ((uint32_t)g * (uint32_t)ld + (uint32_t)(l % LPR * 64)) * 2u + 124u;
         } else {
-            int col = first + l % (R / 64) * 64;
-            if (col + 64 > limit) return ((uint32_t)(l / (R / 64)) * (uint32_t)ld + (uint32_t)first) * 2u;
-            return ((uint32_t)(l / (R / 64)) * (uint32_t)ld + (uint32_t)col) * 2u + 124u;
+            const int col = first + l % (R / 64) * 64 + 62, last = limit > first + 1 ? (limit - 2) & ~1 : first;   // 4 bytes of a cut piece: its last ones
+            return ((uint32_t)(l / (R / 64)) * (uint32_t)ld + (uint32_t)(col < last ? col : last)) * 2u;
         }
     }
     // bytes to advance the source by for one BKT step
@@ -332,10 +331,25 @@ __host__ __device__ inline TileCoord map_tile(int bid, int nblk, int tm, int tn,
     return t;
 }
 
-// Band of gemm_deep_kernel, for shards of tm x tn tiles out of `tiles` in all: the 32 workgroups of an XCD as nearly a square of tiles as
-// the shard allows, for most sharing in its L2: all of a shard that one XCD holds, else four tile-rows.  A band is one byte of
-// the order.
+// Band of gemm_deep_kernel where it touches lines ahead, for shards of tm x tn tiles out of `tiles` in all: the 32 workgroups of an XCD as
+// nearly a square of tiles as the shard allows, so that each has a small share: all of a shard that one XCD holds, else four
+// tile-rows.  A band is one byte of the order.
 __host__ inline int deep_band(int tm, int tn, int64_t tiles) { return tm <= 255 && (int64_t)tm * tn <= (tiles + 7) / 8 ? tm : 4; }
+
+// Lines touched ahead by gemm_deep_kernel: a reduction of this many stages at least, and at most this many lines of four stages for each
+// workgroup (KC: some operand reduction-contiguous).
+constexpr int DEEP_TOUCH_STEPS = 48, DEEP_TOUCH_MAX_KC = 224, DEEP_TOUCH_MAX = 320;
+
+// Does every row along the reduction start on a cache line?
+__host__ inline bool rows_on_lines(const GemmPlan& plan) {
+    for (int g = 0; g < plan.groups; ++g) {
+        const GemmShard& s = plan.s[g];
+        if (!s.m || !s.n || !s.kk) continue;
+        if (plan.a_kc && ((reinterpret_cast<uintptr_t>(s.a) & 127) || s.lda % 64)) return false;
+        if (plan.b_kc && ((reinterpret_cast<uintptr_t>(s.b) & 127) || s.ldb % 64)) return false;
+    }
+    return true;
+}
 
 // The workgroups of one XCD whose tiles lie in the same tile-row (a: they read the same A panel) or tile-column (b) of the same
 // shard and band at the same time: this one's place among them and their number, for one tile per workgroup and one workgroup

@@ -21,6 +21,7 @@
 //
 // Operand storage: "KC" = reduction index contiguous ([m][kk] for A, [n][kk] for B), otherwise the
 // reduction index is the slow one ([kk][m], [kk][n]).  Row-major X and W give A KC and B not-KC.
+#include <algorithm>
 #include <atomic>
 #include <cstdlib>
 #include <utility>
@@ -1766,12 +1767,13 @@ int32_t launch_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool di
 
 // 128 x 128 tiles with one workgroup of eight waves per compute unit (gemm_deep_kernel): where the tiles of that size fill at
 // most one round, or two if both operands are reduction-contiguous, and enough of them are not padding.  us, this / 128 x 128
-// with four waves / the choice without it (rows x reduction x columns, devices): 1024 x 125000 x 512, 8 (256 tiles), A and B
-// reduction-contiguous 1885 / 2428 / 2428, A alone 1451 / 2026 / 2033, neither 1264 / 1303 / 1326; 1024 x 4096 x 512, 8: 34-36 /
-// 39-45 / 39-44; 777 x 1000 x 1000, 3 (147): 13.3-14.2 / 15.1-16.4 / 15.1-16.6; 1024 x 512 x 512, 8: 10.6 / 10.0 / 10.6; 512
-// tiles of length 2048, A and B 39.6 / 44.0 / 44.7 (128 large tiles), A alone 40.1 / 39.4 / 38.9.  Below half a round only
-// against the waves' splitting of short reductions: 108 tiles of 1000 12.2 / 13.8 / 15.0, 96 of 600 9.3-9.8 / 10.9-11.8 /
-// 11.2-12.1; but 72 of 2000 15.7-17.9 / 19-24 / 15.6-16.4, 128 of 40000 344-358 / 383-471 / 245-329.
+// with four waves (rows x reduction x columns, devices; the same inputs again, in brackets others in every pass): 1024 x 125000 x 512, 8
+// (256 tiles), A and B reduction-contiguous 1022 / 2411 (on cache lines 1051 / 1601), A alone 1091 / 1631, neither 1113 / 1274;
+// 1024 x 4096 x 512, 8: 33-39 / 44-56 (46-55 / 54-84); 777 x 1000 x 1000, 3 (168): 13.0-13.4 / 14.8-16.3 (17.9-19.7 / 18.4-24.7);
+// 1024 x 512 x 512, 8: 10.2-10.9 / 9.2-10.9 (13.7-15.0 / 11.4-15.6); 512 tiles of length 2048, A and B 40 / 56 (on lines 40 / 41), A alone 42 / 44
+// (40 / 37).  Below half a round only against the waves' splitting of short reductions (third figure): 128 tiles of 1000 12.0 / 12.9 / 14.9,
+// 96 of 600 9.6 / 9.7 / 11.1, 128 of 1536 13.7 / 16.8 / 17.6; but 60 of 2000 17.2 / 25.8 / 15.6, 128 of 40000, neither operand
+// reduction-contiguous 313 / 379 / 263 (A and B off lines 355 / 758 / 398, 80 of 2000 so 16.4 / 21.2 / 19.0).
 bool deep_pays(const GemmPlan& plan, int max_m, int max_n) {
     const int64_t cu = compute_units(), tiles = tiles_of(plan, max_m, max_n, 128, 128);
     const int k = longest_reduction(plan);
@@ -1804,10 +1806,23 @@ bool two_stages_pay(const GemmPlan& plan, int max_m, int max_n) {
     const int64_t cu = compute_units(), tiles = tiles_of(plan, max_m, max_n, 128, 128);
     return (max_m <= 128 || max_n <= 128) && !(2 * tiles > cu && tiles <= cu && longest_reduction(plan) >= 1024);
 }
+// Lines touched ahead (gemm_deep_kernel): for operands that the memory-side cache cannot hold (256 MiB), long reductions, and a small
+// enough share for each workgroup.  us, without / with (rows x reduction x columns, devices; all layouts): 1024 x 12000 x 512, 8 (295 MB)
+// 115-131 / 108-123, 1000 x 24000 x 499, 8 225-250 / 205-217, 1001 x 24000 x 1023, 4 218-239 / 196-221.  Out of the cache the touches only
+// cost: 1024 x 6000 x 512, 8 (147 MB) 46-50 / 50-53, 2000 x 12000 x 2000, 1 82-90 / 89-97 (the same from HBM 63-71 / 60-68 and
+// 104-117 / 99-125).  With them the band that gives the smallest shares; without, bands of four tile-rows and whole shards are up to 10 %
+// slower than tile_order_for's: 1500 x 12000 x 1500, 1 70-74 / 75-82, 2433 x 10990 x 215, 4 76 / 81.
+bool touches_pay(const GemmPlan& plan, int tm, int tn, int band) {
+    int64_t bytes = 0;
+    for (int g = 0; g < plan.groups; ++g) bytes += 2 * (int64_t)plan.s[g].kk * (plan.s[g].m + plan.s[g].n);
+    const int na = std::min(tn, std::max(32 / band, 1)), nb = std::min(tm, band);
+    return bytes > (int64_t)256 << 20 && longest_reduction(plan) >= 64 * DEEP_TOUCH_STEPS && 512 / na + 512 / nb <= (plan.a_kc || plan.b_kc ? DEEP_TOUCH_MAX_KC : DEEP_TOUCH_MAX);
+}
 int32_t launch_deep(const GemmPlan& plan, int max_m, int max_n, hipStream_t stream) {
     const int tm = tiles_along(max_m, 128), tn = tiles_along(max_n, 128);
-    const int order = g_tile_order.load(std::memory_order_relaxed) ? tile_order_for(tm, tn) : deep_band(tm, tn, tiles_of(plan, max_m, max_n, 128, 128));
-    return launch_gemm_deep(plan, max_m, max_n, order, stream);
+    const int band = deep_band(tm, tn, tiles_of(plan, max_m, max_n, 128, 128));
+    const bool touch = !g_tile_order.load(std::memory_order_relaxed) && touches_pay(plan, tm, tn, band);
+    return launch_gemm_deep(plan, max_m, max_n, touch ? band : tile_order_for(tm, tn), touch, stream);
 }
 
 // The kernel of `variant` (0: the default for the shape).  max_m, max_n: largest extents of a product that is not empty.

@@ -107,7 +107,7 @@ enum AnyTile : int32_t {
 };
 int32_t launch_gemm_any(const GemmPlan& plan, int max_m, int max_n, int tile, bool direct, int order, hipStream_t stream);
 // gemm_any_kernels.hip, 128 x 128 tile, any operand layout, rows 16-byte aligned, any reduction length
-int32_t launch_gemm_deep(const GemmPlan& plan, int max_m, int max_n, int order, hipStream_t stream);
+int32_t launch_gemm_deep(const GemmPlan& plan, int max_m, int max_n, int order, bool touch, hipStream_t stream);
 // gemm_f32_kernels.hip: fp32 x fp32 (fp32 results, GeLU or no epilogue) and fp32 next to bf16 (f32_operand), any pitch and extent.
 enum F32Tile : int32_t {
     F32_128 = 0,   // 128 x 128

@@ -100,7 +100,7 @@ def test_bf16_two_wave_groups_over_the_reduction(M, kk, N, tx, tw, out):
                                                 (300, 3300, 140, 16, 64), (256, 2113, 384, 56, 40), (140, 3136, 256, 0, 0)])
 def test_bf16_rows_anywhere_in_a_cache_line(M, kk, N, extra, start, tx, tw):
     """variant 48, buffers that start and rows that lie 16-byte aligned anywhere in a 128-byte line, or all on lines: one stage to more
-    than the pipeline holds, with and without a remainder, lines touched ahead (3072 and more); NaN before, between and behind the rows"""
+    than the pipeline holds, with and without a remainder; NaN before, between and behind the rows"""
     import torch
     k = 2
     X, W = bf16(3, (M, k * kk)), bf16(4, (k * kk, N), 0.5)
@@ -128,6 +128,53 @@ def test_bf16_rows_anywhere_in_a_cache_line(M, kk, N, extra, start, tx, tw):
         sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, 0)
     for i, y in enumerate(dy.host()):
         assert_matmul_close(y, ref[i], 1e-5, f"{M}x{kk}x{N} trans=({tx},{tw}) shard {i}")
+
+
+def on_device(seed, shapes, trans, extra=0, start=0, scale=1.0):
+    """buffers of random bf16 on the device, rows of a pitch that is a multiple of 8, `start` elements into an allocation; NaN around
+    them.  The matrices, what keeps them, and pointers and pitch for a descriptor"""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    ld = -(-max(r if trans else c for r, c in shapes) // 8) * 8 + extra
+    mats, keep = [], []
+    for r, c in shapes:
+        stored = (c, r) if trans else (r, c)
+        buf = torch.full((start + stored[0] * ld,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        view = buf[start:].view(stored[0], ld)[:, :stored[1]]
+        view.normal_(0.0, scale, generator=g)
+        keep.append(buf)
+        mats.append(view.T if trans else view)
+    return mats, keep, [b.data_ptr() + 2 * start for b in keep], ld
+
+
+def close_on_device(y, x, w, gelu, bar):
+    import torch
+    ref = x.float() @ w.float()
+    if gelu:
+        ref = torch.nn.functional.gelu(ref)
+    y = y.float()
+    return bool((torch.abs(y - ref) <= bar * torch.maximum(ref.abs(), ref.square().mean().sqrt())).all())
+
+
+@pytest.mark.parametrize("tx,tw", [(0, 0), (1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("k,M,N,kk,extra,start", [(8, 1024, 512, 11008, 0, 0), (8, 1000, 499, 11200, 24, 40), (8, 1020, 450, 11463, 8, 64), (4, 1001, 1023, 16640, 0, 0)])
+def test_bf16_lines_touched_ahead(k, M, N, kk, extra, start, tx, tw):
+    """variant 48 on operands of more than 256 MiB whose shards each lie on one XCD (8 x 4 tiles: shares of 512 / 4 + 512 / 8 lines) or
+    half of one (bands of 4 x 8 tiles): every workgroup touches its share ahead; whole and cut tiles, rows on lines and anywhere"""
+    import torch
+    xs, keepx, px, ldx = on_device(SEED + 61, [(M, kk)] * k, tx, extra, start)
+    ws, keepw, pw, ldw = on_device(SEED + 62, [(kk, N)] * k, tw, extra, start, 0.5)
+    assert 2 * k * kk * (M + N) > 256 << 20
+    ys = [torch.full((M, N), float("nan"), device="cuda") for _ in range(k)]
+    sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, 48)
+    try:
+        sbp.sbp_matmul(sbp.SbpTensor(px, M, k * kk, sbp.BF16, tx, ldx), sbp.S(1), sbp.SbpTensor(pw, k * kk, N, sbp.BF16, tw, ldw), sbp.S(0), sbp.SbpTensor(ys, M, N, sbp.F32), sbp.AUTO, k)
+        sync()
+    finally:
+        sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, 0)
+    # both sums run in fp32, in different orders: sqrt(kk) 2^-24 of the scale each, below 1e-5
+    for i in range(k):
+        assert close_on_device(ys[i], xs[i], ws[i], False, 2e-5), f"shard {i}"
 
 
 @pytest.mark.parametrize("M", [32641, 32900])
@@ -178,6 +225,41 @@ def test_bf16_persistent_tiles(kk, ldy, tx, tw, out):
         assert_matmul_close(y, ref, 1e-5 if out == "f32" else 2.0 ** -7, f"kk={kk} ldy={ldy} trans=({tx},{tw}) {out} shard {i}")
         if out == "rowmax":
             assert np.array_equal(top[i][:, 0], y.max(axis=1))
+
+
+@pytest.mark.parametrize("variant", [16, 21])
+@pytest.mark.parametrize("out", ["f32", "bf16", "gelu", "rowmax"])
+@pytest.mark.parametrize("kk,tx,tw", [(128, 0, 0), (128, 1, 1), (384, 0, 1), (384, 1, 0)])
+@pytest.mark.parametrize("N", [301, 392, 515])
+def test_bf16_tiles_after_cut_ones(N, kk, tx, tw, out, variant):
+    """two devices of 130 tile-rows, every second or third tile cut by the last column (inside 16 bytes or not), more than two tiles a
+    workgroup: what is counted of a cut tile's stores when the next tile's stages are waited for"""
+    import torch
+    k, M = 2, 33100
+    sx, sw, K, C = (sbp.S(1), sbp.S(0), k * kk, N) if out == "f32" else (sbp.B, sbp.S(1), kk, k * N)
+    xs, keepx, px, ldx = on_device(SEED + 63, [(M, kk)] * k, tx)
+    if out != "f32":
+        xs, px = [xs[0]] * k, [px[0]] * k
+    ws, keepw, pw, ldw = on_device(SEED + 64, [(kk, N)] * k, tw, scale=0.1)
+    ldy = N + 3
+    bufs = [torch.full((M, ldy), 777.0, dtype=torch.float32 if out == "f32" else torch.bfloat16, device="cuda") for _ in range(k)]
+    tops = [torch.full((M,), float("nan"), device="cuda") for _ in range(k)]
+    X, W = sbp.SbpTensor(px, M, K, sbp.BF16, tx, ldx), sbp.SbpTensor(pw, K, C, sbp.BF16, tw, ldw)
+    Y = sbp.SbpTensor(bufs, M, C, sbp.F32 if out == "f32" else sbp.BF16, 0, ldy)
+    sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, variant)
+    try:
+        if out == "rowmax":
+            sbp.sbp_matmul_rowmax(X, sx, W, sw, Y, sbp.AUTO, sbp.SbpTensor(tops, M, 1, sbp.F32), k)
+        else:
+            sbp.sbp_matmul_ex(X, sx, W, sw, Y, sbp.AUTO, k, None, sbp.EPI_GELU if out == "gelu" else sbp.EPI_NONE)
+        sync()
+    finally:
+        sbp.sbp_set_knob(sbp.KNOB_GEMM_VARIANT, 0)
+    for i in range(k):
+        assert close_on_device(bufs[i][:, :N], xs[i], ws[i], out == "gelu", 1e-5 if out == "f32" else 2.0 ** -7), f"shard {i}"
+        assert bool((bufs[i][:, N:] == 777.0).all()), f"shard {i}: padding written"
+        if out == "rowmax":
+            assert bool((tops[i] == bufs[i][:, :N].float().amax(1)).all())
 
 
 @pytest.mark.parametrize("variant", [8, 9, 16, 21])
