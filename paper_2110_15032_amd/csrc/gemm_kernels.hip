@@ -1716,20 +1716,20 @@ AnyTile any_tile(const GemmPlan& plan, int max_m, int max_n) {
 }
 // Both operands reduction-contiguous, fp32 results, few tiles: all waves of a workgroup load 512 bytes of a row at a time
 // (gemm_rows_kernel), 32 x 32 tiles where those fit one round of one per compute unit, or two if the reduction is long, else 64 x 64.
-// us, without it / 32 x 32 / 64 x 64 (rows x reduction x columns, devices; small tiles): 200 x 7503 x 256, 4 (224) 40.1 / 26.3 / 54;
-// 64 x 4096 x 128, 1 (8) 14.3 / 8.3 / 17.4; 512 x 50000 x 64, 2 (64) 291 / 120 / 251; 250 x 2000 x 250, 4 (256) 11.3 / 8.6 / 15.3;
-// 325 x 26100 x 219, 4 (308) 116 / 85 / 93; 891 x 2340 x 201, 2 (392) 14.5 / 12.8 / 16.5 but 130 x 1701 x 1062, 2 (340) 14.2 / 19.9 / 22.3;
-// 633 x 33323 x 163, 3 (360) 168 / 153 / 168.  Large: 1000 x 12501 x 128, 8 (256) 131 / 157 / 97; 500 x 62500 x 512, 8 (512) 1274 /
-// 1158 / 619; 654 x 38256 x 426, 4 (308) 506 / 369 / 329; 691 x 26688 x 726, 3 (396, rows on cache lines) 181 / 217 / 183; but
-// 594 x 4471 x 577, 2 (200) 34.0 / 54 / 41, 641 x 6567 x 1143, 8 (1584) 186 / 402 / 318.  Short ones, with it over without, 32 x 32: length 537 and 637 1.02-1.15, 777 to
-// 1001 0.82-0.98, 896 1.00-1.13, 1024 on 0.64-0.99; whole cache lines
-// that fill the last stage in part 1088 to 1408 1.00-1.10, 1664 0.95-1.00; but 24 x 34, 4 (8) up to 1.12.
-int rows_tile(const GemmPlan& plan, int max_m, int max_n) {   // -1: none
+// Time over that of the choice without it, the same inputs again / others in every pass, from HBM (several shapes each).  32 x 32, one
+// round (8 to 256 tiles), rows 16-byte aligned: length 1000 0.92-0.99 / 0.80-0.97, 1280 0.93-0.98 / 0.57-0.73, 3000 0.85-0.97 / 0.55-0.72,
+// 9728 0.45-0.95 / 0.40-0.55; lengths of whole 32 but not whole 256, which gemm_wavek_kernel takes without a rest, 640 1.20 (same
+// inputs), 1504 and 1728 1.05-1.16 / 0.67-0.91, 4800 0.90-1.07 / 0.50-0.68; other rows 776 0.97-1.00 / 0.73-0.89, 1100 0.97-1.01 / 0.79-1.02,
+// 1504 0.81-0.88 / 0.63-0.67, 3000 0.66-0.71 / 0.50-0.53.  Two rounds (288 to 480), aligned 2200 0.98-1.33 / 0.91-0.97, 4096 0.87-1.40 /
+// 0.82-0.97, 8192 0.77-1.02 / 0.76-0.90; other rows 4101 1.05-1.33 / 0.97-1.21, 12501 0.92-1.25 / 0.87-1.18, 24001 0.85-1.23 / 0.84-1.17.
+// 64 x 64 from length 8200 on: aligned 200 to 512 tiles 0.54-1.03 / 0.54-1.07, but on cache lines 200 to 308 0.70-1.00 / 0.70-0.98, 396 and
+// 512 1.00-1.20 / 1.03-1.13; other rows 0.58-1.04 / 0.57-1.08.
+int rows_tile(const GemmPlan& plan, int max_m, int max_n, bool direct) {   // -1: none
     if (!plan.a_kc || !plan.b_kc || plan.out_dtype != SBP_F32 || plan.epilogue != SBP_EPI_NONE) return -1;
     const int64_t cu = compute_units(), small = tiles_of(plan, max_m, max_n, 32, 32), large = tiles_of(plan, max_m, max_n, 64, 64);
     const int k = longest_reduction(plan);
-    if (small <= cu ? k >= (k % 64 || k % 256 == 0 ? 1024 : 1664) : small <= 2 * cu && k >= 4096) return ROWS_32;
-    return large <= 2 * cu && k >= 8192 ? ROWS_64 : -1;
+    if (small <= cu ? k >= (direct && k % 64 == 0 && k % 256 ? 1664 : 1024) : small <= 2 * cu && k >= (direct ? 4096 : 16384)) return ROWS_32;
+    return small > 2 * cu && 4 * large <= (direct && rows_on_lines(plan) ? 5 : 8) * cu && k >= 8192 ? ROWS_64 : -1;
 }
 // fp32 operands on the matrix cores: the largest tile that gives the chip enough workgroups and is not mostly padding.  us,
 // 128 x 128 / 64 x 64 / 32 x 32 with the waves splitting the reduction (rows x reduction x columns, devices):
@@ -1886,7 +1886,7 @@ int32_t launch_chosen(const GemmPlan& plan, int max_m, int max_n, int32_t varian
     if (variant == 51 || variant == 52) return launch_any(plan, max_m, max_n, variant == 51 ? ROWS_32 : ROWS_64, direct, stream);
     if (variant == 48) return direct ? launch_deep(plan, max_m, max_n, stream) : SBP_ERR_UNSUPPORTED;
     if (variant == 0 && one_element_pays(plan, max_m, max_n, direct)) return launch_generic(plan, max_m, max_n, stream);
-    const int rows = variant == 0 ? rows_tile(plan, max_m, max_n) : -1;
+    const int rows = variant == 0 ? rows_tile(plan, max_m, max_n, direct) : -1;
     if (!direct) {
         if (variant > 1) return SBP_ERR_UNSUPPORTED;
         return launch_any(plan, max_m, max_n, rows >= 0 ? rows : any_tile(plan, max_m, max_n), false, stream);
