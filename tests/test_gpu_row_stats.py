@@ -35,3 +35,62 @@ def test_row_stats(rows, cols, k, ld, bf):
         want = np.exp(part - peak.cpu().numpy().astype(np.float64)).sum(axis=1)
         # a term is off by 1e-7 |v - max| < 3e-6, the sum by its order: chains of at most cols / 1024 + 16 additions
         assert np.all(np.abs(total[i].cpu().numpy()[:, 0] - want) <= 1e-5 * want)
+
+
+@pytest.mark.parametrize("bf", [True, False])
+@pytest.mark.parametrize("rows,cols,k", [(600, 125001, 2), (1100, 20011, 7)])
+def test_row_stats_streaming(rows, cols, k, bf):
+    """more than 256 MiB in rows of any alignment: loads past the cache; against torch on the device"""
+    import torch
+    dt = torch.bfloat16 if bf else torch.float32
+    pitch = cols + (5 if bf else 2)
+    g = torch.Generator(device="cuda").manual_seed(wl.SEED_BASE + 56)
+    parts = []
+    for _ in range(k):
+        buf = torch.full((rows, pitch), float("nan"), dtype=dt, device="cuda")
+        buf[:, :cols].normal_(0.0, 2.0, generator=g)
+        parts.append(buf)
+    assert k * rows * cols * (2 if bf else 4) > 256 << 20
+    logits = sbp.SbpTensor(parts, rows, cols * k, sbp.BF16 if bf else sbp.F32, 0, pitch)
+    top, total = ([torch.full((rows, 1), float("nan"), device="cuda") for _ in range(k)] for _ in range(2))
+    sbp.sbp_row_max(logits, sbp.S(1), sbp.SbpTensor(top, rows, 1, sbp.F32), k)
+    peak = torch.stack(top).amax(0)
+    sbp.sbp_row_sumexp(logits, sbp.S(1), sbp.SbpTensor([peak] * k, rows, 1, sbp.F32), sbp.SbpTensor(total, rows, 1, sbp.F32), k)
+    torch.cuda.synchronize()
+    for i in range(k):
+        part = parts[i][:, :cols].float()
+        assert torch.equal(top[i], part.amax(1, keepdim=True))
+        want = torch.exp(part.double() - peak.double()).sum(1, keepdim=True)
+        assert bool((torch.abs(total[i].double() - want) <= 1e-5 * want).all())
+
+
+@pytest.mark.parametrize("bf", [True, False])
+@pytest.mark.parametrize("rows,cols", [(4, 16391), (4, 40000), (600, 1003)])
+def test_row_stats_of_nan_and_infinity(rows, cols, bf):
+    """NaN next to numbers is ignored by the maximum, a row of NaN or -inf gives -inf, an infinity wins; -inf adds nothing to the sum,
+    NaN shows in it; few long rows (1024 threads) and others, at the first, a middle and the last element"""
+    import torch
+    host = wl.normal(wl.SEED_BASE + 57, rows, (rows, cols), 2.0).astype(np.float32)
+    nan, inf = np.float32("nan"), np.float32("inf")
+    host[0, [0, cols // 2, cols - 1]] = nan
+    host[1, :] = -inf
+    host[1, cols - 1] = 0.5
+    host[2, :] = -inf
+    host[3, :] = nan
+    plain = wl.normal(wl.SEED_BASE + 58, rows, (rows, cols), 2.0).astype(np.float32)
+    plain[0, [0, cols // 3, cols - 1]] = inf
+    for h in (host, plain):
+        dev = torch.from_numpy(h).cuda().to(torch.bfloat16 if bf else torch.float32)
+        h = dev.float().cpu().numpy()
+        logits = sbp.SbpTensor([dev], rows, cols, sbp.BF16 if bf else sbp.F32)
+        top, total = torch.full((rows, 1), 5.0, device="cuda"), torch.full((rows, 1), 5.0, device="cuda")
+        peak = torch.full((rows, 1), 4.0, device="cuda")
+        sbp.sbp_row_max(logits, sbp.S(1), sbp.SbpTensor([top], rows, 1, sbp.F32), 1)
+        sbp.sbp_row_sumexp(logits, sbp.S(1), sbp.SbpTensor([peak], rows, 1, sbp.F32), sbp.SbpTensor([total], rows, 1, sbp.F32), 1)
+        torch.cuda.synchronize()
+        assert np.array_equal(top.cpu().numpy()[:, 0], np.fmax.reduce(h, axis=1, initial=-inf))
+        want = np.exp(h.astype(np.float64) - 4.0).sum(axis=1)
+        got = total.cpu().numpy()[:, 0].astype(np.float64)
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+        ok = np.isfinite(want)
+        assert np.all(np.abs(got[ok] - want[ok]) <= 1e-5 * want[ok])
