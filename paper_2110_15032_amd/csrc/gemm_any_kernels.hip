@@ -293,6 +293,12 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(GemmPlan p, int tm, int 
     for (int it = 0; it < PER; ++it) at[it] = source(it * NT + tid);
     u32x4 r[2][PER];
     const int steps = s.kk / BKT;
+    // The rest of the reduction is a stage too, the first one.  Of its chunks (one place c for all of a lane's rows) the one that the
+    // row ends in is read so that it ends with the row, and shifted in `trim`; those behind it likewise, and cleared.  With loads of
+    // its own behind the last whole stage the rest cost 1 us of 7; trimmed as the last stage it took code that is fetched for
+    // one use, and lengths of whole stages 0.7 us.
+    static_assert(NT / 32 == 16, "rows of a lane are 16 apart");
+    const int rest = s.kk - steps * BKT, left = rest - ((tid % 32) ^ (tid / 32 % 16)) * 8;   // left: from this lane's chunk of the rest on
     int loaded = 0;
     auto fetch = [&](int set) {   // past the last stage the source stays: the reload is in bounds and unread
         ++loaded;
@@ -300,6 +306,20 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(GemmPlan p, int tm, int 
         for (int it = 0; it < PER; ++it) {
             r[set][it] = *reinterpret_cast<const u32x4_any*>(at[it]);
             at[it] += loaded < steps ? BKT : 0;
+        }
+    };
+    auto trim = [&](int set) {
+        const int e = 8 - left;
+#pragma unroll
+        for (int it = 0; it < PER; ++it) {
+            u32x4 v = r[set][it];
+            if (e > 0) {
+                if (e & 4) v = u32x4{v[2], v[3], 0u, 0u};
+                if (e & 2) v = u32x4{v[1], v[2], v[3], 0u};
+                if (e & 1) v = u32x4{v[0] >> 16 | v[1] << 16, v[1] >> 16 | v[2] << 16, v[2] >> 16 | v[3] << 16, v[3] >> 16};
+                if (e >= 8) v = u32x4{0u, 0u, 0u, 0u};
+            }
+            r[set][it] = v;
         }
     };
     auto stash = [&](char* st, int set) {
@@ -328,29 +348,33 @@ __global__ __launch_bounds__(512) void gemm_rows_kernel(GemmPlan p, int tm, int 
         barrier();
     };
     if (steps > 0) {
-        fetch(0);
+        if (rest) {
+#pragma unroll
+            for (int it = 0; it < PER; ++it) r[0][it] = *reinterpret_cast<const u32x4_any*>(at[it] + steps * BKT + min(left - 8, 0));
+        } else fetch(0);
         fetch(1);
+        if (rest) trim(0);
         stash(smem, 0);
         fetch(0);
         barrier();
+        const int stages = steps + (rest ? 1 : 0);
         int t = 0;
-        for (; t + 2 <= steps; t += 2) {
+        for (; t + 2 <= stages; t += 2) {
             step(std::integral_constant<int, 0>{});
             step(std::integral_constant<int, 1>{});
         }
-        if (t < steps) step(std::integral_constant<int, 0>{});
-    }
-    if (const int k0 = steps * BKT; k0 < s.kk) {   // the rest, zeros behind it in both operands
+        if (t < stages) step(std::integral_constant<int, 0>{});
+    } else if (s.kk > 0) {   // less than a stage, zeros behind it in both operands
 #pragma unroll
         for (int it = 0; it < PER; ++it) {
-            const int q = it * NT + tid, valid = s.kk - k0 - ((q % 32) ^ (q / 32 % 16)) * 8;
-            const uint16_t* src = source(q) + k0;
+            const int q = it * NT + tid;
+            const uint16_t* src = source(q);
             u32x4 v = {0u, 0u, 0u, 0u};
-            if (valid >= 8) v = *reinterpret_cast<const u32x4_any*>(src);
+            if (left >= 8) v = *reinterpret_cast<const u32x4_any*>(src);
             else {
 #pragma unroll
                 for (int e = 0; e < 7; ++e)
-                    if (e < valid) v[e >> 1] |= (uint32_t)src[e] << (16 * (e & 1));
+                    if (e < left) v[e >> 1] |= (uint32_t)src[e] << (16 * (e & 1));
             }
             *reinterpret_cast<u32x4*>(smem + q * 16) = v;
         }

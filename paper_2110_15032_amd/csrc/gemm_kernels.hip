@@ -1716,19 +1716,18 @@ AnyTile any_tile(const GemmPlan& plan, int max_m, int max_n) {
 }
 // Both operands reduction-contiguous, fp32 results, few tiles: all waves of a workgroup load 512 bytes of a row at a time
 // (gemm_rows_kernel), 32 x 32 tiles where those fit one round of one per compute unit, or two if the reduction is long, else 64 x 64.
-// Time over that of the choice without it, the same inputs again / others in every pass, from HBM (several shapes each).  32 x 32, one
-// round (8 to 256 tiles), rows 16-byte aligned: length 1000 0.92-0.99 / 0.80-0.97, 1280 0.93-0.98 / 0.57-0.73, 3000 0.85-0.97 / 0.55-0.72,
-// 9728 0.45-0.95 / 0.40-0.55; lengths of whole 32 but not whole 256, which gemm_wavek_kernel takes without a rest, 640 1.20 (same
-// inputs), 1504 and 1728 1.05-1.16 / 0.67-0.91, 4800 0.90-1.07 / 0.50-0.68; other rows 776 0.97-1.00 / 0.73-0.89, 1100 0.97-1.01 / 0.79-1.02,
-// 1504 0.81-0.88 / 0.63-0.67, 3000 0.66-0.71 / 0.50-0.53.  Two rounds (288 to 480), aligned 2200 0.98-1.33 / 0.91-0.97, 4096 0.87-1.40 /
-// 0.82-0.97, 8192 0.77-1.02 / 0.76-0.90; other rows 4101 1.05-1.33 / 0.97-1.21, 12501 0.92-1.25 / 0.87-1.18, 24001 0.85-1.23 / 0.84-1.17.
-// 64 x 64 from length 8200 on: aligned 200 to 512 tiles 0.54-1.03 / 0.54-1.07, but on cache lines 200 to 308 0.70-1.00 / 0.70-0.98, 396 and
-// 512 1.00-1.20 / 1.03-1.13; other rows 0.58-1.04 / 0.57-1.08.
+// Time over that of the choice without it, median (worst), the same inputs again / others in every pass, from HBM.  32 x 32, one round (8 to
+// 256 tiles), rows 16-byte aligned, lengths of whole 64: 1024 to 1600 0.95 (1.06) / 0.79-1.02 (1.08), 1664 to 5000 0.96 (1.10) / 0.75 (1.04);
+// all lengths from 600 to 40000 0.93 (1.10) / 0.67 (1.08).  Two rounds (257 to 512), rows on cache lines: length 2000 to 4096 1.07-1.36
+// (1.49) / 0.92-0.95 (1.18), to 8192 0.90-0.98 (1.46) / 0.88 (1.12), longer 0.85-0.92 (1.19) / 0.79-0.88 (1.05); other aligned rows 0.90-1.05
+// (1.49) / 0.84 (1.11), then 0.80 (1.09) / 0.81 (1.07), 0.75 (1.09) / 0.78 (1.05); rows of any pitch from 4096 on 0.74-0.87 (1.17) / 0.78-0.86 (1.16).
+// 64 x 64 from length 8192 on (513 tiles of 32 x 32 and more): aligned 0.59-0.84 (1.18) / 0.70-0.85 (1.15), but on cache lines with more than
+// 1.25 a compute unit 0.91 (1.26) / 0.90 (1.33); rows of any pitch 0.64-0.76 (1.05) / 0.63-0.73 (1.15).
 int rows_tile(const GemmPlan& plan, int max_m, int max_n, bool direct) {   // -1: none
     if (!plan.a_kc || !plan.b_kc || plan.out_dtype != SBP_F32 || plan.epilogue != SBP_EPI_NONE) return -1;
     const int64_t cu = compute_units(), small = tiles_of(plan, max_m, max_n, 32, 32), large = tiles_of(plan, max_m, max_n, 64, 64);
     const int k = longest_reduction(plan);
-    if (small <= cu ? k >= (direct && k % 64 == 0 && k % 256 ? 1664 : 1024) : small <= 2 * cu && k >= (direct ? 4096 : 16384)) return ROWS_32;
+    if (small <= cu ? k >= 1024 : small <= 2 * cu && k >= 4096) return ROWS_32;
     return small > 2 * cu && 4 * large <= (direct && rows_on_lines(plan) ? 5 : 8) * cu && k >= 8192 ? ROWS_64 : -1;
 }
 // fp32 operands on the matrix cores: the largest tile that gives the chip enough workgroups and is not mostly padding.  us,

@@ -298,7 +298,8 @@ def test_bf16_tiles_cut_by_the_edge(M, N, odd, out, variant):
 
 @pytest.mark.parametrize("variant", [0, 51, 52])
 @pytest.mark.parametrize("odd", [0, 1])
-@pytest.mark.parametrize("M,kk,N", [(1, 1, 1), (3, 255, 2), (32, 256, 32), (33, 263, 31), (64, 511, 65), (70, 512, 40), (31, 777, 130), (130, 1025, 64), (65, 9000, 70)])
+@pytest.mark.parametrize("M,kk,N", [(1, 1, 1), (3, 255, 2), (32, 256, 32), (33, 263, 31), (64, 511, 65), (70, 512, 40), (31, 777, 130), (130, 1025, 64), (65, 9000, 70),
+                                    (9, 258, 33), (40, 259, 9), (5, 260, 34), (33, 261, 5), (17, 518, 40)])
 def test_bf16_long_pieces_of_rows(M, kk, N, odd, variant):
     """both operands reduction-contiguous, fp32 results: no whole 256-deep stage, one, two, three and more, with and without a remainder;
     rows of any pitch; one tile and ragged further ones"""
