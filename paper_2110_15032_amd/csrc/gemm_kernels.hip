@@ -400,6 +400,9 @@ __device__ __attribute__((always_inline)) inline void store_tile16(const f32x4 (
                     constexpr int ib = decltype(ibx)::value;
                     static_for<4>([&](auto jidx) {
                         constexpr int j = decltype(jidx)::value;
+                        // 16 x 16 blocks outside: GeLU of all four in a row made [2173, 32] x [32, 13], 8 devices, 11.2 us (6.9 without)
+                        if constexpr (MASKED && !COUNTED && EPI != EPI_ROWMAX)
+                            if (i * 32 + ib * 16 >= wave_rows || j * 16 >= wave_cols) return;
                         static_for<2>([&](auto pidx) {
                             constexpr int r = 2 * decltype(pidx)::value;
                             const uint32_t own = f32_to_bf16x2(mfma_epilogue<EPI>(acc[2 * i + ib][j][r]), mfma_epilogue<EPI>(acc[2 * i + ib][j][r + 1]));

@@ -265,7 +265,7 @@ def test_bf16_tiles_after_cut_ones(N, kk, tx, tw, out, variant):
 @pytest.mark.parametrize("variant", [8, 9, 16, 21])
 @pytest.mark.parametrize("out", ["f32", "bf16", "gelu", "rowmax"])
 @pytest.mark.parametrize("M,N,odd", [(255, 264, 0), (300, 388, 1), (257, 392, 0), (130, 391, 0), (140, 389, 1), (512, 520, 3),
-                                     (129, 385, 0), (161, 394, 1), (225, 163, 0), (130, 190, 1), (289, 141, 3)])
+                                     (129, 385, 0), (161, 394, 1), (225, 163, 0), (130, 190, 1), (289, 141, 3), (300, 13, 0), (81, 9, 1)])
 def test_bf16_tiles_cut_by_the_edge(M, N, odd, out, variant):
     """results stored 16 bytes at a time up to the edge: rows cut anywhere, columns at a multiple of 16 bytes or inside one, rows at any
     pitch; the padding behind a row stays as it was (DevTensor)"""
