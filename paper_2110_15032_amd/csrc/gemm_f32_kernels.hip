@@ -352,12 +352,17 @@ struct TermOperand {
             }
 #pragma unroll
             for (int w = 0; w < WORDS / 4; ++w) r.v[i][w] = u32x4{0u, 0u, 0u, 0u};
+            if (valid >= 8) {   // element by element [2197, 64] x [64, 445] took 7.0 us, 5.7 on the fp32 instruction
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (e < valid) {
-                    if constexpr (F32) r.v[i][e >> 2][e & 3] = __float_as_uint(src[e]);
-                    else r.v[i][0][e >> 1] |= (uint32_t)src[e] << (16 * (e & 1));
-                }
+                for (int w = 0; w < WORDS / 4; ++w) r.v[i][w] = *reinterpret_cast<const u32x4_any*>(reinterpret_cast<const char*>(src) + 16 * w);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 7; ++e)
+                    if (e < valid) {
+                        if constexpr (F32) r.v[i][e >> 2][e & 3] = __float_as_uint(src[e]);
+                        else r.v[i][0][e >> 1] |= (uint32_t)src[e] << (16 * (e & 1));
+                    }
+            }
         }
     }
     __device__ static void stash(char* st, Raw& r, int tid) {   // into LDS
