@@ -285,23 +285,38 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmPlan p,
 // ---------------------------------------------------------------------------------------------------------------------
 // x 2^24 = hi + mid + lo, each the nearest bf16 of what is left; pairs of values.  Exact below 2^104 in magnitude.
 constexpr int CUT_EXP = 24;
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+// x minus one half of a pair of terms.  ONE_ROW: in one instruction where a shift or mask and a subtraction take two; exact as well, the
+// difference being an fp32 value.  It multiplies the other half by 0, so that an infinity or NaN there shows in x too: fit for two
+// values of one row, not for two columns, one of which may be padding.  It pays next to bf16 with 64 x 64 tiles, where cutting takes as
+// long as multiplying: [252, 3016] x [3016, 1013], both reduction-contiguous, 3 devices, 47.2 / 39.8 us, 0.85-1.02 of the time over 378 shapes; with
+// 128 x 128 tiles 0.98-1.11, two fp32 operands 0.96-1.12.
+template <bool ONE_ROW, int HALF>
+__device__ inline float minus_term(float x, uint32_t pair) {
+    if constexpr (ONE_ROW) {
+        uint32_t minus = HALF ? 0xBF800000u : 0x0000BF80u;   // -1 in that half; in a register: as a constant of the instruction both become the first
+        asm("" : "+s"(minus));
+        return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, minus), x, false);
+    } else return x - __uint_as_float(HALF ? pair & 0xFFFF0000u : pair << 16);
+}
 struct TermPair { uint32_t hi, mid, lo; };
+template <bool ONE_ROW>   // both values of one row along the reduction
 __device__ inline TermPair split_pair(float x, float y) {
     TermPair t;
     x *= (float)(1 << CUT_EXP);
     y *= (float)(1 << CUT_EXP);
     t.hi = f32_to_bf16x2(x, y);
-    x -= __uint_as_float(t.hi << 16);
-    y -= __uint_as_float(t.hi & 0xFFFF0000u);
+    x = minus_term<ONE_ROW, 0>(x, t.hi);
+    y = minus_term<ONE_ROW, 1>(y, t.hi);
     t.mid = f32_to_bf16x2(x, y);
-    x -= __uint_as_float(t.mid << 16);
-    y -= __uint_as_float(t.mid & 0xFFFF0000u);
+    x = minus_term<ONE_ROW, 0>(x, t.mid);
+    y = minus_term<ONE_ROW, 1>(y, t.mid);
     t.lo = f32_to_bf16x2(x, y);
     return t;
 }
 
 // One operand of gemm_terms_kernel: R rows by 32 of the reduction a stage, as one (bf16) or three (fp32) bf16 tiles.
-template <typename T, int R, bool KC, int NT>
+template <typename T, int R, bool KC, int NT, bool ONE_F32>   // ONE_F32: the other operand is bf16
 struct TermOperand {
     using Tl = Tile<R, KC, NT, 32, true>;
     static constexpr bool F32 = sizeof(T) == 4;
@@ -374,7 +389,7 @@ struct TermOperand {
                 u32x4 h, m, l;
 #pragma unroll
                 for (int d = 0; d < 4; ++d) {
-                    const TermPair t = split_pair(__uint_as_float(r.v[i][d >> 1][2 * (d & 1)]), __uint_as_float(r.v[i][d >> 1][2 * (d & 1) + 1]));
+                    const TermPair t = split_pair<KC && ONE_F32 && R == 64>(__uint_as_float(r.v[i][d >> 1][2 * (d & 1)]), __uint_as_float(r.v[i][d >> 1][2 * (d & 1) + 1]));
                     h[d] = t.hi;
                     m[d] = t.mid;
                     l[d] = t.lo;
@@ -392,8 +407,9 @@ struct TermOperand {
 template <int BM, int BN, int WPS, typename T1, typename T2, bool A_KC, bool B_KC, int EPI>
 __global__ __launch_bounds__(256, WPS) void gemm_terms_kernel(GemmPlan p, int tm, int tn, int order) {
     constexpr int NT = 256, TM = BM / 2, TN = BN / 2, FM = TM / 16, FN = TN / 16, BLOCKS = FM * FN;
-    using OA = TermOperand<T1, BM, A_KC, NT>;
-    using OB = TermOperand<T2, BN, B_KC, NT>;
+    constexpr bool ONE_F32 = sizeof(T1) != sizeof(T2);
+    using OA = TermOperand<T1, BM, A_KC, NT, ONE_F32>;
+    using OB = TermOperand<T2, BN, B_KC, NT, ONE_F32>;
     // The next stage is loaded ahead of the multiplication where its registers fit beside the fragments; with 128 x 128 tiles of
     // three terms each they do not, and three workgroups a compute unit cover the loads' latency instead.
     constexpr bool AHEAD = BM < 128 || !(OA::F32 && OB::F32);
