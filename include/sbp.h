@@ -118,9 +118,13 @@ int32_t sbp_local_shape(int64_t rows, int64_t cols, sbp_t sbp, int32_t k, int32_
  *   inputs accumulate in fp32 and round once, to nearest even.
  *   A P(sum) input operand (rows 4, 5 of Table 1) must be SBP_F32; the other
  *   operand (B) may be SBP_F32 or SBP_BF16.  Next to a bf16 operand the fp32
- *   partial is not rounded: it enters the matrix units as an exact sum of three
- *   bf16 terms or, where the reduction length is no multiple of 32 or rows are
- *   not 16-byte aligned, in fp32 next to the widened bf16 values.  The same holds for row 6 when one B operand is SBP_F32 (a
+ *   partial is not rounded: it enters the matrix units as a sum of three bf16
+ *   terms, exact for values of 2^-110 and more and to within 2^-134 below that
+ *   (where the reduction length is no multiple of 32 or rows are not 16-byte
+ *   aligned: exact for all values), or, for few results and for reductions of up
+ *   to 32, in fp32 next to the widened bf16 values.  Products of two fp32 operands
+ *   run on the fp32 matrix instruction or as six products of such exact terms;
+ *   their error is an fp32 sum's either way.  The same holds for row 6 when one B operand is SBP_F32 (a
  *   partial that was boxed to B) and the other SBP_BF16; the result is then
  *   SBP_F32.  Any other mix of dtypes is SBP_ERR_DTYPE.
  *   k-way results are written to y->shard[i]; x, w are read only. */
@@ -253,8 +257,10 @@ int32_t sbp_xent_grad(const sbp_tensor_t* logits, sbp_t sbp_l, const sbp_tensor_
                       const sbp_tensor_t* denom, const sbp_tensor_t* grad, const sbp_tensor_t* dlogits, int32_t k,
                       void* stream);
 
-/* Tuning knobs; they never change what is computed beyond fp32 summation order
- * inside a GEMM tile.  Unknown knob or value: SBP_ERR_UNSUPPORTED. */
+/* Tuning knobs; they never change what is computed beyond the order of fp32 sums inside a GEMM tile
+ * and, for fp32 operands, whether a product is formed by the fp32 instruction or from bf16 terms
+ * (45-47 and 49, 50 below): results stay within the error of an fp32 sum.  Unknown knob or value:
+ * SBP_ERR_UNSUPPORTED. */
 enum {
     SBP_KNOB_GEMM_VARIANT = 0,  /* 0 = default choice by shape; >0 forces a kernel: 1 generic, 3 = 256x256
                                    tile with two 64-deep stages, 4 = 128x128 tile, 6 = 256x256 with four

@@ -1817,7 +1817,7 @@ bool two_stages_pay(const GemmPlan& plan, int max_m, int max_n) {
 bool touches_pay(const GemmPlan& plan, int tm, int tn, int band) {
     int64_t bytes = 0;
     for (int g = 0; g < plan.groups; ++g) bytes += 2 * (int64_t)plan.s[g].kk * (plan.s[g].m + plan.s[g].n);
-    const int na = std::min(tn, std::max(32 / band, 1)), nb = std::min(tm, band);
+    const int na = std::min(tn, std::max(XCD_UNITS / band, 1)), nb = std::min(tm, band);
     return bytes > (int64_t)256 << 20 && longest_reduction(plan) >= 64 * DEEP_TOUCH_STEPS && 512 / na + 512 / nb <= (plan.a_kc || plan.b_kc ? DEEP_TOUCH_MAX_KC : DEEP_TOUCH_MAX);
 }
 int32_t launch_deep(const GemmPlan& plan, int max_m, int max_n, hipStream_t stream) {
@@ -1837,7 +1837,7 @@ int32_t launch_chosen(const GemmPlan& plan, int max_m, int max_n, int32_t varian
     if ((variant == 31 || variant == 32) && !(plan.f32_operand && split_ok(plan))) variant = 0;
 
     if (plan.f32_operand) {
-        // Table 1 rows 4 / 5 with a bf16 partner: split kernel, else the fp32 matrix instruction with mixed element types
+        // Table 1 rows 4 / 5 with a bf16 partner: split kernel, else bf16 terms or the fp32 matrix instruction with mixed element types
         if (plan.out_dtype != SBP_F32 || plan.epilogue != SBP_EPI_NONE) return SBP_ERR_DTYPE;
         if ((variant >= 45 && variant <= 47) || variant == 49 || variant == 50) return launch_f32(plan, max_m, max_n, variant, stream);
         if (variant != 1 && split_ok(plan)) {

@@ -289,7 +289,7 @@ int32_t launch_row_stat(const RowStatPlan& plan, bool sumexp, hipStream_t stream
         cols = plan.cols[i] > cols ? plan.cols[i] : cols;
         total += plan.rows * plan.cols[i] * (bf ? 2 : 4);
     }
-    const bool wide = plan.rows * plan.k <= 512 && cols >= 16384;      // two rows a compute unit; 2 KB of bf16 and more for each wave
+    const bool wide = plan.rows * plan.k <= 2 * compute_units() && cols >= 16384;      // two rows a compute unit; 2 KB of bf16 and more for each wave
     const bool stream = !wide && total > (int64_t)256 << 20;           // the memory-side cache's size
     auto pick = [&](auto s, auto b) -> void (*)(RowStatPlan) {
         constexpr bool S = decltype(s)::value, BF = decltype(b)::value;
